@@ -221,6 +221,12 @@ def _inputs(case, seed):
     return s
 
 
+@functools.lru_cache(maxsize=1)
+def _stream():
+    """The one stream a serving loop or a simulation runs on."""
+    return torch.cuda.Stream()
+
+
 def prepare(case, seed):
     s = _inputs(case, seed)
     x = s["x"]
@@ -244,7 +250,7 @@ def prepare(case, seed):
         if case["grad_x"]:
             x.requires_grad_(True)
     if case["graph"]:
-        s["stream"] = torch.cuda.Stream()
+        s["stream"] = _stream()
     if case["kind"] == "nnpmm":
         s["step"] = NNPMMStep(s["model"], s["coupling"], s["sp"], s["off"], s["par"], s["par_mm"])
     elif case["graph"]:
