@@ -28,13 +28,6 @@ namespace nnp {
 // bf16 storage: raw 16-bit patterns, round-to-nearest-even from float.
 typedef uint16_t bf16_t;
 
-__host__ __device__ inline bf16_t f2bf(float f) {
-    uint32_t u;
-    __builtin_memcpy(&u, &f, 4);
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (bf16_t)((u >> 16) | 0x40);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
-}
 __host__ __device__ inline float bf2f(bf16_t h) {
     uint32_t u = ((uint32_t)h) << 16;
     float f;
@@ -43,7 +36,7 @@ __host__ __device__ inline float bf2f(bf16_t h) {
 }
 
 // device conversion of two floats to packed bf16 (low half = a): the
-// hardware's round-to-nearest-even conversion, the same rounding as f2bf
+// hardware's round-to-nearest-even conversion
 typedef float nnp_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 nnp_bf16x2 __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t pack_bf16x2(float a, float b) {
@@ -200,8 +193,9 @@ struct ParamPack {
     int o1, o2;                    // widths of the packed layout's first two hidden layers
     long net, offb1, offW2, offb2, offW3, offb3, offw4, offb4;
 };
+// parameters [first, first + n) of the packed array from src[0..n)
 template <typename P, typename TSRC>
-hipError_t launch_set_params(int64_t n, const TSRC* src, const int32_t* map, const ParamPack& pk,
+hipError_t launch_set_params(int64_t first, int64_t n, const TSRC* src, const int32_t* map, const ParamPack& pk,
                              const DevWeights<P>& dw, hipStream_t st);
 
 struct Shape {

@@ -4,25 +4,26 @@
 // first optimisation: no CPU<->GPU copies per step); this kernel scatters
 // them into every device layout the evaluation kernels read (the row-major
 // and transposed matrices, the fragment-ordered copies, biases and output
-// layer) with the same rounding the host upload applies, so a handle updated
-// here computes bitwise what a handle created with the same weights does.
+// layer); nnp_create and nnp_set_weights upload host weights through it too,
+// so a handle updated here computes bitwise what a handle created with the
+// same weights does.
 #include "nnp_internal.h"
 
 namespace nnp {
 
 template <typename P, typename TSRC>
-__global__ __launch_bounds__(256) void k_set_params(int64_t n, const TSRC* __restrict__ src,
+__global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, const TSRC* __restrict__ src,
                                                     const int32_t* __restrict__ map, ParamPack pk,
                                                     DevWeights<P> dw) {
     typedef typename P::TS TS;
     typedef typename P::TA TA;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double v = (double)src[i];
+    const double v = (double)src[i];   // parameter first + i
     const TS vs = Store<TS>::st((typename P::TA)v);
     const TA va = (TA)v;
     // position in the uniform (padded) packed layout: [m][s]{W1 b1 W2 b2 W3 b3 w4 b4}
-    const int64_t pi = map ? (int64_t)map[i] : i;
+    const int64_t pi = map ? (int64_t)map[first + i] : first + i;
     const int64_t ms = pi / pk.net;
     const int64_t r = pi - ms * pk.net;
     const int m = (int)(ms / pk.S), s = (int)(ms % pk.S);
@@ -65,16 +66,16 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t n, const TSRC* __res
 }
 
 template <typename P, typename TSRC>
-hipError_t launch_set_params(int64_t n, const TSRC* src, const int32_t* map, const ParamPack& pk,
+hipError_t launch_set_params(int64_t first, int64_t n, const TSRC* src, const int32_t* map, const ParamPack& pk,
                              const DevWeights<P>& dw, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_set_params<P, TSRC>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n,
+    hipLaunchKernelGGL((k_set_params<P, TSRC>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, first, n,
                        src, map, pk, dw);
     return hipGetLastError();
 }
 
 #define NNP_SETP(P, TSRC)                                                                          \
-    template hipError_t launch_set_params<P, TSRC>(int64_t, const TSRC*, const int32_t*,            \
+    template hipError_t launch_set_params<P, TSRC>(int64_t, int64_t, const TSRC*, const int32_t*,            \
                                                    const ParamPack&, const DevWeights<P>&, hipStream_t);
 NNP_SETP(PrecF64, double)
 NNP_SETP(PrecF64, float)

@@ -69,6 +69,7 @@ struct GraphEntry {
     }
 };
 constexpr size_t kMaxGraphs = 8;
+constexpr int64_t kStageParams = (int64_t)1 << 20;   // parameters per upload piece (8 MiB)
 
 }  // namespace
 
@@ -86,11 +87,10 @@ struct nnp_handle {
     Shape shape{};
     int64_t n_params = 0;
     // element networks of their own widths: packed index -> index in the
-    // zero-padded uniform layout (host and device copies); gradients are
-    // formed in that layout (gpad) and gathered
+    // zero-padded uniform layout (on the device); gradients are formed in that
+    // layout (gpad) and gathered
     bool het = false;
     int64_t n_int = 0;
-    std::vector<int32_t> pmap;
     int32_t* dmap = nullptr;
     void* gpad = nullptr;
 
@@ -112,6 +112,7 @@ struct nnp_handle {
     hipStream_t st2 = nullptr;
     hipEvent_t pev[4] = {nullptr, nullptr, nullptr, nullptr};
     int32_t* flag = nullptr;
+    double* stage = nullptr;      // device [kStageParams]: host weights on their way to the layouts
     int8_t* zlut = nullptr;       // device [kZLut]: element of each atomic number, or null
     hipStream_t last_stream = nullptr;
 
@@ -210,113 +211,89 @@ template <typename T> void fill_const(AevConst<T>& c, const nnp_model_params* p,
     }
 }
 
-template <typename TS> TS to_store(double v);
-template <> float to_store<float>(double v) { return (float)v; }
-template <> double to_store<double>(double v) { return v; }
-template <> bf16_t to_store<bf16_t>(double v) { return f2bf((float)v); }
+// where each packed parameter goes on this handle
+ParamPack param_pack(const nnp_handle* h) {
+    const NetLayout& nl = h->nl;
+    ParamPack pk{};
+    pk.S = h->S;
+    pk.M = h->M;
+    pk.D = h->D;
+    pk.Dp = h->shape.Dp;
+    pk.H1 = h->shape.H1;
+    pk.H2 = h->shape.H2;
+    pk.H3 = h->shape.H3;
+    pk.o1 = nl.o1;
+    pk.o2 = nl.o2;
+    pk.net = nl.net;
+    pk.offb1 = nl.offb1;
+    pk.offW2 = nl.offW2;
+    pk.offb2 = nl.offb2;
+    pk.offW3 = nl.offW3;
+    pk.offb3 = nl.offb3;
+    pk.offw4 = nl.offw4;
+    pk.offb4 = nl.offb4;
+    return pk;
+}
 
-// Pack FP64 master weights [m][s][layer]{W, b} into the device layouts.
+// FP64 master weights [m][s][layer]{W, b} into the device layouts: the packed
+// array goes to the device in pieces and the kernel of nnp_set_params scatters
+// and rounds it there (8-model ANI-2x ensemble, 19 M parameters: nnp_create
+// 122 -> 7 ms in FP32, 187 -> 7 ms in FP64, against packing the layouts on the
+// host).  Padding entries are zeroed at allocation and never written.
 template <typename P> nnp_status upload_weights(nnp_handle* h, DevWeights<P>& dw,
                                                 const double* w, bool allocate) {
     typedef typename P::TS TS;
-    typedef typename P::TA TA;
-    std::vector<double> padded;
-    if (h->het) {   // into the zero-padded uniform layout
-        padded.assign((size_t)h->n_int, 0.0);
-        for (size_t i = 0; i < h->pmap.size(); ++i) padded[h->pmap[i]] = w[i];
-        w = padded.data();
-    }
     const Shape& sh = h->shape;
-    const int S = h->S, M = h->M, D = h->D, Dp = sh.Dp;
-    const int o1 = h->widths[1], o2 = h->widths[2], o3 = h->widths[3];
-    const int H1 = sh.H1, H2 = sh.H2, H3 = sh.H3;
-    std::vector<TS> W1((size_t)S * M * H1 * Dp, to_store<TS>(0.0)), W1T(W1.size(), to_store<TS>(0.0));
-    std::vector<TS> W2((size_t)S * M * H2 * H1, to_store<TS>(0.0)), W2T(W2.size(), to_store<TS>(0.0));
-    std::vector<TS> W3((size_t)S * M * H3 * H2, to_store<TS>(0.0)), W3T(W3.size(), to_store<TS>(0.0));
-    std::vector<TA> b1((size_t)S * M * H1, 0), b2((size_t)S * M * H2, 0), b3((size_t)S * M * H3, 0);
-    std::vector<TA> w4((size_t)S * M * H3, 0), b4((size_t)S * M, 0);
-    std::vector<double> sae(S, 0.0);   // summed in FP64: self-energies dwarf the network part
-    const size_t net = (size_t)o1 * D + o1 + (size_t)o2 * o1 + o2 + (size_t)o3 * o2 + o3 + o3 + 1;
-    for (int m = 0; m < M; ++m)
-        for (int s = 0; s < S; ++s) {
-            const double* p = w + ((size_t)m * S + s) * net;
-            for (int n = 0; n < o1; ++n)
-                for (int k = 0; k < D; ++k) {
-                    TS v = to_store<TS>(p[(size_t)n * D + k]);
-                    W1[((size_t)s * M * H1 + (size_t)m * H1 + n) * Dp + k] = v;
-                    W1T[((size_t)s * Dp + k) * M * H1 + (size_t)m * H1 + n] = v;
-                }
-            p += (size_t)o1 * D;
-            for (int n = 0; n < o1; ++n) b1[(size_t)s * M * H1 + (size_t)m * H1 + n] = (TA)p[n];
-            p += o1;
-            const size_t sm = (size_t)s * M + m;
-            for (int n = 0; n < o2; ++n)
-                for (int k = 0; k < o1; ++k) {
-                    TS v = to_store<TS>(p[(size_t)n * o1 + k]);
-                    W2[(sm * H2 + n) * H1 + k] = v;
-                    W2T[(sm * H1 + k) * H2 + n] = v;
-                }
-            p += (size_t)o2 * o1;
-            for (int n = 0; n < o2; ++n) b2[sm * H2 + n] = (TA)p[n];
-            p += o2;
-            for (int n = 0; n < o3; ++n)
-                for (int k = 0; k < o2; ++k) {
-                    TS v = to_store<TS>(p[(size_t)n * o2 + k]);
-                    W3[(sm * H3 + n) * H2 + k] = v;
-                    W3T[(sm * H2 + k) * H3 + n] = v;
-                }
-            p += (size_t)o3 * o2;
-            for (int n = 0; n < o3; ++n) b3[sm * H3 + n] = (TA)p[n];
-            p += o3;
-            for (int n = 0; n < o3; ++n) w4[sm * H3 + n] = (TA)p[n];
-            p += o3;
-            b4[sm] = (TA)p[0];
-        }
-    for (int s = 0; s < S; ++s) sae[s] = h->energy_scale * (h->sae.empty() ? 0.0 : h->sae[s]);
-    // fragment-order copies of the per-model matrices (the fused kernel's
-    // weight operands), one [N][K] matrix per element and model
-    auto fragments = [&](const std::vector<TS>& src, int N, int K) {
-        std::vector<TS> dst(src.size());
-        for (size_t sm = 0; sm < (size_t)S * M; ++sm)
-            for (int n = 0; n < N; ++n)
-                for (int k = 0; k < K; ++k)
-                    dst[sm * N * K + frag_index<TS>(n, k, K)] = src[(sm * N + n) * K + k];
-        return dst;
-    };
-    const std::vector<TS> W2f = fragments(W2, H2, H1), W3f = fragments(W3, H3, H2);
-    const std::vector<TS> W3Tf = fragments(W3T, H2, H3), W2Tf = fragments(W2T, H1, H2);
-    // the layer-1 weights in fragment order for the register-operand GEMMs
-    // (BF16): one [M*H1][Dp] matrix and its transpose per element
-    std::vector<TS> W1f, W1Tf;
-    if (std::is_same<TS, bf16_t>::value) {
-        const int N1 = M * H1;
-        W1f.resize(W1.size());
-        W1Tf.resize(W1T.size());
-        for (size_t e = 0; e < (size_t)S; ++e)
-            for (int n = 0; n < N1; ++n)
-                for (int k = 0; k < Dp; ++k) {
-                    W1f[e * N1 * Dp + frag_index<TS>(n, k, Dp)] = W1[(e * N1 + n) * Dp + k];
-                    W1Tf[e * N1 * Dp + frag_index<TS>(k, n, N1)] = W1[(e * N1 + n) * Dp + k];
-                }
-    }
+    const size_t S = h->S, M = h->M, Dp = sh.Dp, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3;
     hipError_t e = hipSuccess;
-    auto put = [&](auto*& dst, const auto& src) -> bool {
-        size_t bytes = src.size() * sizeof(src[0]);
-        if (allocate) {
-            dst = (std::remove_reference_t<decltype(dst)>)h->dalloc(bytes, e);
-            if (e != hipSuccess) return false;
-        }
-        e = hipMemcpy(dst, src.data(), bytes, hipMemcpyHostToDevice);
-        return e == hipSuccess;
-    };
-    if (!put(dw.W1, W1) || !put(dw.W1T, W1T) || !put(dw.b1, b1) || !put(dw.W2, W2) ||
-        !put(dw.W2T, W2T) || !put(dw.b2, b2) || !put(dw.W3, W3) || !put(dw.W3T, W3T) ||
-        !put(dw.b3, b3) || !put(dw.w4, w4) || !put(dw.b4, b4) || !put(dw.sae, sae) ||
-        !put(dw.W2f, W2f) || !put(dw.W3f, W3f) || !put(dw.W3Tf, W3Tf) || !put(dw.W2Tf, W2Tf) ||
-        (!W1f.empty() && (!put(dw.W1f, W1f) || !put(dw.W1Tf, W1Tf))))
+    const auto failed = [&]() {
         return fail(e == hipErrorOutOfMemory ? NNP_E_NOMEM : NNP_E_DEVICE,
                     std::string("weight upload: ") + hipGetErrorString(e));
-    return NNP_OK;
+    };
+    if (allocate) {
+        const auto zeros = [&](auto*& dst, size_t n) {
+            if (e != hipSuccess) return;
+            const size_t bytes = n * sizeof(*dst);
+            dst = (std::remove_reference_t<decltype(dst)>)h->dalloc(bytes, e);
+            if (e == hipSuccess) e = hipMemset(dst, 0, bytes);
+        };
+        zeros(dw.W1, S * M * H1 * Dp);
+        zeros(dw.W1T, S * M * H1 * Dp);
+        zeros(dw.b1, S * M * H1);
+        zeros(dw.W2, S * M * H2 * H1);
+        zeros(dw.W2T, S * M * H2 * H1);
+        zeros(dw.b2, S * M * H2);
+        zeros(dw.W3, S * M * H3 * H2);
+        zeros(dw.W3T, S * M * H3 * H2);
+        zeros(dw.b3, S * M * H3);
+        zeros(dw.w4, S * M * H3);
+        zeros(dw.b4, S * M);
+        zeros(dw.sae, S);
+        // fragment-order copies of the per-model matrices (the fused kernel's
+        // weight operands), one [N][K] matrix per element and model
+        zeros(dw.W2f, S * M * H2 * H1);
+        zeros(dw.W3f, S * M * H3 * H2);
+        zeros(dw.W3Tf, S * M * H3 * H2);
+        zeros(dw.W2Tf, S * M * H2 * H1);
+        // the layer-1 weights in fragment order for the register-operand
+        // GEMMs (BF16): one [M*H1][Dp] matrix and its transpose per element
+        if (std::is_same<TS, bf16_t>::value) {
+            zeros(dw.W1f, S * M * H1 * Dp);
+            zeros(dw.W1Tf, S * M * H1 * Dp);
+        }
+        if (e != hipSuccess) return failed();
+        std::vector<double> sae(S, 0.0);   // summed in FP64: self-energies dwarf the network part
+        for (size_t s = 0; s < S; ++s) sae[s] = h->energy_scale * (h->sae.empty() ? 0.0 : h->sae[s]);
+        if ((e = hipMemcpy(dw.sae, sae.data(), S * sizeof(double), hipMemcpyHostToDevice))) return failed();
+    }
+    const int32_t* map = h->het ? h->dmap : nullptr;
+    for (int64_t at = 0; at < h->n_params && e == hipSuccess; at += kStageParams) {
+        const int64_t n = std::min<int64_t>(kStageParams, h->n_params - at);
+        e = hipMemcpy(h->stage, w + at, sizeof(double) * (size_t)n, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = launch_set_params<P>(at, n, (const double*)h->stage, map, param_pack(h), dw, (hipStream_t)0);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)0);
+    return e == hipSuccess ? NNP_OK : failed();
 }
 
 // Row buffers of the pipeline's second part (sized for the whole capacity:
@@ -1053,22 +1030,23 @@ nnp_status nnp_create(const nnp_model_params* p, nnp_handle** out) {
     h->n_int = net_int * S * h->M;
     h->n_params = 0;
     for (int s = 0; s < S; ++s) h->n_params += net_of(&sw[s * 5]) * h->M;
+    std::vector<int32_t> pmap;
     if (h->het) {
         if (h->n_int >= ((int64_t)1 << 31)) {
             delete h;
             return fail(NNP_E_UNSUPPORTED, "padded parameter count above 2^31");
         }
         // packed index -> padded index, layer by layer: W row-major, then b
-        h->pmap.reserve((size_t)h->n_params);
+        pmap.reserve((size_t)h->n_params);
         for (int m = 0; m < h->M; ++m)
             for (int s = 0; s < S; ++s) {
                 const int* ws = &sw[s * 5];
                 int64_t base = ((int64_t)m * S + s) * net_int;
                 for (int l = 0; l < 4; ++l) {
                     for (int n = 0; n < ws[l + 1]; ++n)
-                        for (int k = 0; k < ws[l]; ++k) h->pmap.push_back((int32_t)(base + (int64_t)n * wi[l] + k));
+                        for (int k = 0; k < ws[l]; ++k) pmap.push_back((int32_t)(base + (int64_t)n * wi[l] + k));
                     for (int n = 0; n < ws[l + 1]; ++n)
-                        h->pmap.push_back((int32_t)(base + (int64_t)wi[l + 1] * wi[l] + n));
+                        pmap.push_back((int32_t)(base + (int64_t)wi[l + 1] * wi[l] + n));
                     base += (int64_t)wi[l + 1] * wi[l] + wi[l + 1];
                 }
             }
@@ -1126,11 +1104,15 @@ nnp_status nnp_create(const nnp_model_params* p, nnp_handle** out) {
         else if (hipMemcpy(h->zlut, lut.data(), kZLut, hipMemcpyHostToDevice) != hipSuccess)
             rc = fail(NNP_E_DEVICE, "element table upload failed");
     }
+    if (rc == NNP_OK) {
+        h->stage = (double*)h->dalloc(sizeof(double) * (size_t)std::min(kStageParams, h->n_params), e);
+        if (e != hipSuccess) rc = fail(NNP_E_NOMEM, "parameter staging allocation failed");
+    }
     if (rc == NNP_OK && h->het) {
-        h->dmap = (int32_t*)h->dalloc(sizeof(int32_t) * h->pmap.size(), e);
+        h->dmap = (int32_t*)h->dalloc(sizeof(int32_t) * pmap.size(), e);
         if (e != hipSuccess)
             rc = fail(NNP_E_NOMEM, "parameter map allocation failed");
-        else if (hipMemcpy(h->dmap, h->pmap.data(), sizeof(int32_t) * h->pmap.size(), hipMemcpyHostToDevice) != hipSuccess)
+        else if (hipMemcpy(h->dmap, pmap.data(), sizeof(int32_t) * pmap.size(), hipMemcpyHostToDevice) != hipSuccess)
             rc = fail(NNP_E_DEVICE, "parameter map upload failed");
     }
     if (rc == NNP_OK) {
@@ -1254,37 +1236,19 @@ nnp_status nnp_set_params(nnp_handle* h, const void* params, int32_t type, void*
         return fail(NNP_E_INVALID, "parameter type must be NNP_PREC_FP64 or NNP_PREC_FP32");
     DeviceGuard dg(h->device);
     if (!dg.ok) return fail(NNP_E_DEVICE, "hipSetDevice failed");
-    const NetLayout& nl = h->nl;
-    ParamPack pk{};
-    pk.S = h->S;
-    pk.M = h->M;
-    pk.D = h->D;
-    pk.Dp = h->shape.Dp;
-    pk.H1 = h->shape.H1;
-    pk.H2 = h->shape.H2;
-    pk.H3 = h->shape.H3;
-    pk.o1 = nl.o1;
-    pk.o2 = nl.o2;
-    pk.net = nl.net;
-    pk.offb1 = nl.offb1;
-    pk.offW2 = nl.offW2;
-    pk.offb2 = nl.offb2;
-    pk.offW3 = nl.offW3;
-    pk.offb3 = nl.offb3;
-    pk.offw4 = nl.offw4;
-    pk.offb4 = nl.offb4;
+    const ParamPack pk = param_pack(h);
     const int32_t* map = h->het ? h->dmap : nullptr;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     if (h->precision == NNP_PREC_FP64)
-        e = type == NNP_PREC_FP64 ? launch_set_params<PrecF64>(h->n_params, (const double*)params, map, pk, h->w64, st)
-                                  : launch_set_params<PrecF64>(h->n_params, (const float*)params, map, pk, h->w64, st);
+        e = type == NNP_PREC_FP64 ? launch_set_params<PrecF64>(0, h->n_params, (const double*)params, map, pk, h->w64, st)
+                                  : launch_set_params<PrecF64>(0, h->n_params, (const float*)params, map, pk, h->w64, st);
     else if (h->precision == NNP_PREC_FP32)
-        e = type == NNP_PREC_FP64 ? launch_set_params<PrecF32>(h->n_params, (const double*)params, map, pk, h->w32, st)
-                                  : launch_set_params<PrecF32>(h->n_params, (const float*)params, map, pk, h->w32, st);
+        e = type == NNP_PREC_FP64 ? launch_set_params<PrecF32>(0, h->n_params, (const double*)params, map, pk, h->w32, st)
+                                  : launch_set_params<PrecF32>(0, h->n_params, (const float*)params, map, pk, h->w32, st);
     else
-        e = type == NNP_PREC_FP64 ? launch_set_params<PrecBF16>(h->n_params, (const double*)params, map, pk, h->w16, st)
-                                  : launch_set_params<PrecBF16>(h->n_params, (const float*)params, map, pk, h->w16, st);
+        e = type == NNP_PREC_FP64 ? launch_set_params<PrecBF16>(0, h->n_params, (const double*)params, map, pk, h->w16, st)
+                                  : launch_set_params<PrecBF16>(0, h->n_params, (const float*)params, map, pk, h->w16, st);
     if (e != hipSuccess) return fail(NNP_E_DEVICE, std::string("parameter update: ") + hipGetErrorString(e));
     return NNP_OK;
 }
