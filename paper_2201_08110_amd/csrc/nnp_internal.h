@@ -169,6 +169,13 @@ template <typename TS> __host__ __device__ inline size_t frag_index(int n, int k
     return (((size_t)t * (K / KM) + q) * 64 + lane) * KL + kk % KL;
 }
 
+// The same order for a matrix split into three bf16 parts: the parts of a
+// fragment follow each other (part p of element (n, k) lies 512 p further on).
+__host__ __device__ inline size_t split_index(int n, int k, int K) {
+    const size_t f = frag_index<bf16_t>(n, k, K);
+    return (f / 512) * 1536 + f % 512;
+}
+
 // packed device weights (per precision)
 template <typename P> struct DevWeights {
     typedef typename P::TS TS;
@@ -183,6 +190,9 @@ template <typename P> struct DevWeights {
     // the layer-1 GEMMs' weight operands in fragment order (BF16 only, per
     // element: W1cat [M*H1][Dp] and W1cat^T [Dp][M*H1]; null otherwise)
     TS* W1f;  TS* W1Tf;
+    // every matrix split into three bf16 parts in fragment order (split_index;
+    // FP32 handles with 64-row buckets, null otherwise)
+    bf16_t *W1x, *W1Tx, *W2x, *W2Tx, *W3x, *W3Tx;
     double* sae;                   // [S] FP64 (already multiplied by energy_scale)
 };
 
@@ -216,6 +226,7 @@ struct Shape {
     int tail_tile;                     // fused kernel tile variant (1, 2 or 3)
     int chunk;                         // central atoms per featuriser / force workgroup (4, 8, 16)
     int force_fixed;                   // 1: forces summed in 64-bit fixed point (bitwise reproducible)
+    int split;                         // 1: FP32 network GEMMs on bf16 matrix cores, operands in three parts
     int force_path;                    // force kernel: 1 dE/dAEV row staged in LDS, 2 read from global
     int h3_used;                       // layer-3 width before padding (the widest element network's)
     int dev_counts;                    // 1: A and B are launch bounds; the counts are in Work::dcnt

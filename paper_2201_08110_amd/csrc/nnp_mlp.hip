@@ -27,52 +27,9 @@
 // accumulation).  Tiles are scheduled N-fastest and remapped so each XCD
 // works through a contiguous range (its L2 keeps the row block and the
 // weights it shares).
-#include <algorithm>
-#include <type_traits>
-
-#include "nnp_internal.h"
+#include "nnp_split.h"
 
 namespace nnp {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef short bf16x8 __attribute__((ext_vector_type(8)));
-
-template <typename TS> struct MF;
-template <> struct MF<float> {
-    static constexpr int KM = 4, KL = 1;   // K of one MFMA, K elements per lane
-    typedef float Frag;
-    typedef f32x4 Acc;
-    __device__ static Acc mma(Frag a, Frag b, Acc c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    // with the operands swapped (B fragment first) accumulator element r of
-    // lane l holds C[l % 16][col0(l) + r * kColStride]
-    static constexpr int kColStride = 1;
-    __device__ static int col0(int l) { return 4 * (l >> 4); }
-};
-template <> struct MF<double> {
-    static constexpr int KM = 4, KL = 1;
-    typedef double Frag;
-    typedef f64x4 Acc;
-    __device__ static Acc mma(Frag a, Frag b, Acc c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    // the FP64 16x16x4 accumulator interleaves its rows across the lane
-    // groups, so a lane's four elements are every fourth column
-    static constexpr int kColStride = 4;
-    __device__ static int col0(int l) { return l >> 4; }
-};
-template <> struct MF<bf16_t> {
-    static constexpr int KM = 32, KL = 8;
-    typedef bf16x8 Frag;
-    typedef f32x4 Acc;
-    __device__ static Acc mma(Frag a, Frag b, Acc c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
-    static constexpr int kColStride = 1;
-    __device__ static int col0(int l) { return 4 * (l >> 4); }
-};
 
 // LDS layout of one K slice of an operand: [rows][128 bytes], i.e. BK =
 // 128 / sizeof(TS) elements per row in eight 16-byte chunks; chunk c of row r
@@ -102,87 +59,6 @@ template <> struct FragGroup<double> {
     static constexpr int G = 2;
     typedef f64x2 V;
     __device__ static double at(const V& v, int j) { return v[j]; }
-};
-
-enum { EPI_CELU = 0, EPI_L3F = 1, EPI_DSIG = 2, EPI_ACC = 3, EPI_RAW = 4, EPI_REV = 5 };
-
-// CELU and its derivative, branch-free (the exponential is taken of min(z, 0)
-// and always finite); ial = 1 / alpha.  CELU'(z) is recovered from a stored
-// h = CELU(z): h >= 0 <=> z >= 0, and exp(z / alpha) = 1 + h / alpha.
-// (float: the scaled argument is clamped, min(z c, 0) = min(z, 0) c for c > 0,
-// so the minimum takes a product and needs no NaN canonicalisation of z)
-__device__ inline float celu(float z, float al, float ial) {
-    const float e = __builtin_amdgcn_exp2f(fminf(z * (ial * 1.44269504088896341f), 0.f));
-    return z >= 0.f ? z : __builtin_fmaf(al, e, -al);
-}
-__device__ inline double celu(double z, double al, double ial) {
-    const double e = expm1(fmin(z, 0.0) * ial);
-    return z >= 0.0 ? z : al * e;
-}
-__device__ inline float dcelu_z(float z, float ial) {
-    // exp2 of the clamped argument is exactly 1 for z >= 0
-    return __builtin_amdgcn_exp2f(fminf(z * (ial * 1.44269504088896341f), 0.f));
-}
-__device__ inline double dcelu_z(double z, double ial) {
-    const double e = exp(fmin(z, 0.0) * ial);
-    return z >= 0.0 ? 1.0 : e;
-}
-// (1 + h / alpha >= 1 exactly when h >= 0, so the minimum selects the branch)
-__device__ inline float dcelu_h(float h, float ial) { return fminf(__builtin_fmaf(h, ial, 1.f), 1.f); }
-__device__ inline double dcelu_h(double h, double ial) { return h >= 0.0 ? 1.0 : 1.0 + h * ial; }
-
-template <typename P> struct GemmArgs {
-    typedef typename P::TS TS;
-    typedef typename P::TA TA;
-    const TS* A; int lda; long a_z;
-    const TS* B; int ldb; long b_s, b_z;
-    const TA* bias; long bias_s, bias_z;
-    void* C; int ldc; long c_z;
-    const TS* Hr; int ldh; long h_z;        // stored activations for CELU'
-    void* C2; long c2_z;                     // second output (EPI_REV), leading dim ldc
-    const TS* X; int ldx; long x_z;          // auxiliary product (EPI_REV)
-    const TS* Tr; int ldt; long t_z;         // tangent activations (EPI_REV)
-    const TA* w4; long w4_s, w4_z;
-    TA* epart; int n_models, nt;
-    TA gscale, alpha, inv_alpha;
-    int K;
-    const int32_t* tile_species; int row_tile;
-    const BucketInfo* info;
-    int nm, nn, nz;                          // tiles along M, N and models
-};
-
-// Four output elements of one row held by one lane: columns c, c+ST, c+2ST,
-// c+3ST (ST = 1 for the f32 / bf16 MFMAs, 4 for f64).
-template <typename TS, int ST> struct Quad {
-    typedef typename std::conditional<sizeof(TS) == 8, double, float>::type TA;
-    __device__ static void ld(const TS* p, TA v[4]) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = Store<TS>::ld(p[r * ST]);
-    }
-    __device__ static void st(TS* p, const TA v[4]) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) p[r * ST] = Store<TS>::st(v[r]);
-    }
-};
-template <> struct Quad<float, 1> {
-    __device__ static void ld(const float* p, float v[4]) {
-        const float4 q = *(const float4*)p;
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    }
-    __device__ static void st(float* p, const float v[4]) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
-};
-template <> struct Quad<bf16_t, 1> {
-    __device__ static void ld(const bf16_t* p, float v[4]) {
-        const uint2 q = *(const uint2*)p;
-        v[0] = bf2f((bf16_t)(q.x & 0xffffu)); v[1] = bf2f((bf16_t)(q.x >> 16));
-        v[2] = bf2f((bf16_t)(q.y & 0xffffu)); v[3] = bf2f((bf16_t)(q.y >> 16));
-    }
-    __device__ static void st(bf16_t* p, const float v[4]) {
-        uint2 q;
-        q.x = pack_bf16x2(v[0], v[1]);
-        q.y = pack_bf16x2(v[2], v[3]);
-        *(uint2*)p = q;
-    }
 };
 
 // Store one 16-row x 64-column BF16 strip held in the MFMA accumulator
@@ -220,11 +96,6 @@ __device__ inline void st_strip_bf16(bf16_t* p, const uint32_t (&pk)[4][2], int 
         *(uint4*)(p + 32 * h) = o;
     }
 }
-
-// Row tiles are grouped kGroupM at a time: within a group the schedule runs
-// M-fastest, so the tiles an XCD has in flight share both a few row blocks
-// and a few weight column blocks in its L2.
-constexpr int kGroupM = 8;
 
 template <typename P, int BM, int BN, int WM, int WN, int S>
 struct GemmShape {
@@ -277,7 +148,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs<P> g) {
     constexpr int NQA = BM / 8, NQB = BN / 8;              // 8-row (1 KiB) loads per slice
     constexpr int QA = (NQA + NW - 1) / NW, QB = (NQB + NW - 1) / NW;   // per wave (at most)
     constexpr int QMIN = NQA / NW + NQB / NW;                            // per wave (at least)
-    constexpr int ST = mf::kColStride;
+
     extern __shared__ __align__(16) char smem_raw[];
     TS* const stage0 = (TS*)smem_raw;                      // stage s: A rows then B rows
     TA* red = (TA*)(smem_raw + (size_t)S * (BM + BN) * 128);   // [BM][WN] (L3F only)
@@ -299,7 +170,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs<P> g) {
     if (tile_m * BM >= rows) return;
     const int s = g.tile_species[(tile_m * BM) / g.row_tile];
     if (s < 0) return;
-    const int tid = threadIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN, wn = wave % WN;
 
     const TS* A = g.A + (size_t)tile_m * BM * g.lda + (size_t)z * g.a_z;
@@ -415,143 +286,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs<P> g) {
     // the workgroup ends
     vm_wait_barrier<0>();
 
-    // ---- epilogue: acc[i][j][r] of lane l is C[row_i][col_j + r * ST]
-    const int row0 = tile_m * BM + wm * WTM + (lane & 15);
-    const int col0 = tile_n * BN + wn * WTN + mf::col0(lane);
-    typedef Quad<TS, ST> Q;
-    if (EPI == EPI_CELU) {
-        TS* C = (TS*)g.C + (size_t)z * g.c_z;
-        const TA* bias = g.bias + (size_t)s * g.bias_s + (size_t)z * g.bias_z;
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            const int col = col0 + j * 16;
-            TA bb[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) bb[r] = bias[col + r * ST];
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                TA v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = celu((TA)acc[i][j][r] + bb[r], g.alpha, g.inv_alpha);
-                Q::st(C + (size_t)(row0 + i * 16) * g.ldc + col, v);
-            }
-        }
-    } else if (EPI == EPI_ACC) {
-        // dE/dAEV rows, in the precision's dE/dAEV storage type
-        typedef typename P::TG TG;
-        TG* C = (TG*)g.C + (size_t)z * g.c_z;
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                TA v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = (TA)acc[i][j][r];
-                Quad<TG, ST>::st(C + (size_t)(row0 + i * 16) * g.ldc + col0 + j * 16, v);
-            }
-    } else if (EPI == EPI_DSIG) {
-        TS* C = (TS*)g.C + (size_t)z * g.c_z;
-        const TS* Hr = g.Hr + (size_t)z * g.h_z;
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const size_t row = row0 + i * 16;
-                const int col = col0 + j * 16;
-                TA hh[4], v[4];
-                Q::ld(Hr + row * g.ldh + col, hh);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = (TA)acc[i][j][r] * dcelu_h(hh[r], g.inv_alpha);
-                Q::st(C + row * g.ldc + col, v);
-            }
-    } else if (EPI == EPI_RAW) {
-        TS* C = (TS*)g.C + (size_t)z * g.c_z;
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                TA v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = (TA)acc[i][j][r];
-                Q::st(C + (size_t)(row0 + i * 16) * g.ldc + col0 + j * 16, v);
-            }
-    } else if (EPI == EPI_REV) {
-        // reverse step through h = CELU(z) and its tangent hdot = CELU'(z) zdot:
-        //   zbar    = abar CELU'(z) + acheck (CELU''/CELU')(z) hdot
-        //   zdotbar = acheck CELU'(z)
-        // abar = this product, acheck = X (the same product of the tangent
-        // adjoint), CELU''/CELU' = 1/alpha for z < 0 and 0 otherwise.
-        TS* C = (TS*)g.C + (size_t)z * g.c_z;
-        TS* C2 = (TS*)g.C2 + (size_t)z * g.c2_z;
-        const TS* Hr = g.Hr + (size_t)z * g.h_z;
-        const TS* X = g.X + (size_t)z * g.x_z;
-        const TS* Tr = g.Tr + (size_t)z * g.t_z;
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const size_t row = row0 + i * 16;
-                const int col = col0 + j * 16;
-                TA hh[4], ac[4], hd[4], v[4], v2[4];
-                Q::ld(Hr + row * g.ldh + col, hh);
-                Q::ld(X + row * g.ldx + col, ac);
-                Q::ld(Tr + row * g.ldt + col, hd);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const TA d1 = dcelu_h(hh[r], g.inv_alpha);
-                    const TA rho = hh[r] < TA(0) ? g.inv_alpha : TA(0);
-                    v[r] = (TA)acc[i][j][r] * d1 + ac[r] * rho * hd[r];
-                    v2[r] = ac[r] * d1;
-                }
-                Q::st(C + row * g.ldc + col, v);
-                Q::st(C2 + row * g.ldc + col, v2);
-            }
-    } else {   // EPI_L3F
-        TS* C = (TS*)g.C + (size_t)z * g.c_z;
-        const TA* bias = g.bias + (size_t)s * g.bias_s + (size_t)z * g.bias_z;
-        const TA* w4 = g.w4 + (size_t)s * g.w4_s + (size_t)z * g.w4_z;
-        TA part[FM];
-#pragma unroll
-        for (int i = 0; i < FM; ++i) part[i] = 0;
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            const int col = col0 + j * 16;
-            TA bb[4], ww[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                bb[r] = bias[col + r * ST];
-                ww[r] = w4[col + r * ST];
-            }
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                TA v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const TA zz = (TA)acc[i][j][r] + bb[r];
-                    part[i] += ww[r] * celu(zz, g.alpha, g.inv_alpha);
-                    v[r] = dcelu_z(zz, g.inv_alpha) * ww[r] * g.gscale;
-                }
-                Q::st(C + (size_t)(row0 + i * 16) * g.ldc + col, v);
-            }
-        }
-        // sum over the four lane groups (same row, different columns), then
-        // over the WN waves that share the row
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            TA v = part[i];
-            v += __shfl_xor(v, 16);
-            v += __shfl_xor(v, 32);
-            if (lane < 16) red[(wm * WTM + i * 16 + lane) * WN + wn] = v;
-        }
-        __syncthreads();
-        for (int rr = tid; rr < BM; rr += 64 * NW) {
-            TA v = 0;
-#pragma unroll
-            for (int q = 0; q < WN; ++q) v += red[rr * WN + q];
-            const size_t row = (size_t)tile_m * BM + rr;
-            g.epart[(row * g.n_models + z) * g.nt + tile_n] = v;
-        }
-    }
+    // ---- epilogue
+    gemm_epilogue<P, EPI, BM, WN, FM, FN>(g, acc, lane, tile_m * BM, wm * WTM, tile_n * BN + wn * WTN + mf::col0(lane),
+                                          s, z, wn, tile_n, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -810,11 +547,26 @@ static hipError_t run_l1rb(GemmArgs<PrecBF16> a, int Rcap, int N, int stages, hi
 // GEMMs, 64-wide for the per-model layers (widths 192 / 256); S LDS stages
 template <typename P, int BM> struct Cfg;
 template <typename P> struct Cfg<P, 128> {
-    static constexpr int BNW = sizeof(typename P::TS) == 8 ? 64 : 128, BNN = 64, WM = 2, WN = 2, S = 3;
+    static constexpr int BNW = 128, BNN = 64, WM = 2, WN = 2, S = 3;
 };
 template <typename P> struct Cfg<P, 16> {
     static constexpr int BNW = 64, BNN = 64, WM = 1, WN = 4, S = 3;
 };
+// FP32 handles of more than 256 atoms split their operands instead (k_gx)
+template <typename P, int BM> constexpr bool is_split = std::is_same<P, PrecF32>::value && BM == kSplitRows;
+
+// one network GEMM over every row tile: Bx is the weight operand a.B's
+// pre-split form
+template <typename P, int BM, int EPI>
+static hipError_t net_gemm(const GemmArgs<P>& a, const bf16_t* Bx, int R, int N, int nz, hipStream_t st,
+                           const Timer& tm, const char* name) {
+    if constexpr (is_split<P, BM>) {
+        return split_gemm<EPI>(SplitArgs{a, Bx, kParts * a.b_s, kParts * a.b_z}, R, N, nz, st, tm, name);
+    } else {
+        typedef Cfg<P, BM> C;
+        return run_gemm<P, BM, C::BNN, C::WM, C::WN, C::S, EPI>(a, R, N, nz, st, tm, name);
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Fused tail of the ensemble for energies and forces: for one row tile of one
@@ -1215,10 +967,14 @@ template <typename P> struct TailBM { static constexpr int v = 128 / (int)sizeof
 // the wide layer-1 GEMMs: LDS stages and waves per workgroup from the knobs
 // (8 waves split the 128 x 128 tile 2 x 4, for 128-row buckets only)
 template <typename P, int BM, int EPI>
-static hipError_t run_l1(GemmArgs<P> a, const Shape& sh, int N, hipStream_t st, const Timer& tm,
+static hipError_t run_l1(GemmArgs<P> a, const bf16_t* Bx, const Shape& sh, int N, hipStream_t st, const Timer& tm,
                          const char* name) {
-    typedef Cfg<P, BM> C;
     const int R = sh.Rcap;
+    if constexpr (is_split<P, BM>) {
+        return net_gemm<P, BM, EPI>(a, Bx, R, N, 1, st, tm, name);
+    } else {
+    typedef Cfg<P, BM> C;
+    if (N % C::BNW != 0) return net_gemm<P, BM, EPI>(a, nullptr, R, N, 1, st, tm, name);
     // 8 waves (2 x 4 of 64 x 32) for the forward GEMM when the knob says so;
     // the backward GEMM measured better on 4
     if constexpr (BM == 128 && C::BNW == 128 && EPI == EPI_CELU) {
@@ -1235,14 +991,14 @@ static hipError_t run_l1(GemmArgs<P> a, const Shape& sh, int N, hipStream_t st, 
     }
     return sh.gemm_stages == 2 ? run_gemm<P, BM, C::BNW, C::WM, C::WN, 2, EPI>(a, R, N, 1, st, tm, name)
                                : run_gemm<P, BM, C::BNW, C::WM, C::WN, 3, EPI>(a, R, N, 1, st, tm, name);
+    }
 }
 
 // L1b: dG = DZ1cat W1cat (models summed along K)
 template <typename P, int BM>
 static hipError_t mlp_l1_bwd(const Shape& sh, const DevWeights<P>& wt, Work<P>& w,
                              const GemmArgs<P>& base, hipStream_t st, const Timer& tm) {
-    typedef Cfg<P, BM> C;
-    const int M = sh.M, H1 = sh.H1, Dp = sh.Dp, R = sh.Rcap;
+    const int M = sh.M, H1 = sh.H1, Dp = sh.Dp;
     GemmArgs<P> a = base;
     a.A = w.DZ1; a.lda = M * H1; a.a_z = 0;
     a.B = wt.W1T; a.ldb = M * H1; a.b_s = (long)Dp * M * H1; a.b_z = 0;
@@ -1251,18 +1007,16 @@ static hipError_t mlp_l1_bwd(const Shape& sh, const DevWeights<P>& wt, Work<P>& 
     if constexpr (std::is_same<P, PrecBF16>::value && BM == kRbRows) {
         if (sh.l1_path == 2) {
             a.B = wt.W1Tf;
-            return run_l1rb<EPI_ACC>(a, R, Dp, sh.gemm_stages, st, tm, "mlp_l1_bwd");
+            return run_l1rb<EPI_ACC>(a, sh.Rcap, Dp, sh.gemm_stages, st, tm, "mlp_l1_bwd");
         }
     }
-    if (Dp % C::BNW == 0) return run_l1<P, BM, EPI_ACC>(a, sh, Dp, st, tm, "mlp_l1_bwd");
-    return run_gemm<P, BM, C::BNN, C::WM, C::WN, C::S, EPI_ACC>(a, R, Dp, 1, st, tm, "mlp_l1_bwd");
+    return run_l1<P, BM, EPI_ACC>(a, wt.W1Tx, sh, Dp, st, tm, "mlp_l1_bwd");
 }
 
 template <typename P, int BM>
 static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, hipStream_t st,
                           const Timer& tm) {
     typedef typename P::TA TA;
-    typedef Cfg<P, BM> C;
     const int M = sh.M, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3, Dp = sh.Dp;
     hipError_t e = hipSuccess;
     GemmArgs<P> base{};
@@ -1291,12 +1045,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
             l1_done = true;
         }
     }
-    if (l1_done)
-        ;
-    else if ((M * H1) % C::BNW == 0)
-        e = run_l1<P, BM, EPI_CELU>(a, sh, M * H1, st, tm, "mlp_l1_fwd");
-    else
-        e = run_gemm<P, BM, C::BNN, C::WM, C::WN, C::S, EPI_CELU>(a, R, M * H1, 1, st, tm, "mlp_l1_fwd");
+    if (!l1_done) e = run_l1<P, BM, EPI_CELU>(a, wt.W1x, sh, M * H1, st, tm, "mlp_l1_fwd");
     if (e) return e;
     if (sh.mlp_fused) {
         if (!mlp_fused_supported(H1, H2, H3)) return hipErrorInvalidValue;
@@ -1324,7 +1073,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.bias = wt.b2; a.bias_s = (long)M * H2; a.bias_z = H2;
     a.C = w.H2; a.ldc = M * H2; a.c_z = H2;
     a.K = H1;
-    if ((e = run_gemm<P, BM, C::BNN, C::WM, C::WN, C::S, EPI_CELU>(a, R, H2, M, st, tm, "mlp_l2_fwd")))
+    if ((e = net_gemm<P, BM, EPI_CELU>(a, wt.W2x, R, H2, M, st, tm, "mlp_l2_fwd")))
         return e;
     // L3f (+ output layer, + dE/dz3)
     a = base;
@@ -1335,7 +1084,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.C = w.DZ3; a.ldc = M * H3; a.c_z = H3;
     a.epart = w.Epart;
     a.K = H2;
-    if ((e = run_gemm<P, BM, 64, C::WM, C::WN, C::S, EPI_L3F>(a, R, H3, M, st, tm, "mlp_l3_fwd")))
+    if ((e = net_gemm<P, BM, EPI_L3F>(a, wt.W3x, R, H3, M, st, tm, "mlp_l3_fwd")))
         return e;
     // L3b
     a = base;
@@ -1344,7 +1093,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.Hr = w.H2; a.ldh = M * H2; a.h_z = H2;
     a.C = w.DZ2; a.ldc = M * H2; a.c_z = H2;
     a.K = H3;
-    if ((e = run_gemm<P, BM, C::BNN, C::WM, C::WN, C::S, EPI_DSIG>(a, R, H2, M, st, tm, "mlp_l3_bwd")))
+    if ((e = net_gemm<P, BM, EPI_DSIG>(a, wt.W3Tx, R, H2, M, st, tm, "mlp_l3_bwd")))
         return e;
     // L2b
     a = base;
@@ -1353,11 +1102,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.Hr = w.H1; a.ldh = M * H1; a.h_z = H1;
     a.C = w.DZ1; a.ldc = M * H1; a.c_z = H1;
     a.K = H2;
-    if (H1 % C::BNW == 0)
-        e = run_gemm<P, BM, C::BNW, C::WM, C::WN, C::S, EPI_DSIG>(a, R, H1, M, st, tm, "mlp_l2_bwd");
-    else
-        e = run_gemm<P, BM, C::BNN, C::WM, C::WN, C::S, EPI_DSIG>(a, R, H1, M, st, tm, "mlp_l2_bwd");
-    if (e) return e;
+    if ((e = net_gemm<P, BM, EPI_DSIG>(a, wt.W2Tx, R, H1, M, st, tm, "mlp_l2_bwd"))) return e;
     return mlp_l1_bwd<P, BM>(sh, wt, w, base, st, tm);
 }
 
@@ -1371,8 +1116,6 @@ static hipError_t train_mlp(const Shape& sh, const DevWeights<P>& wt, Work<P>& w
                             const int32_t* mol_of_atom, const double* grad_E, bool has_gF,
                             hipStream_t st, const Timer& tm) {
     typedef typename P::TA TA;
-    typedef Cfg<P, BM> C;
-    constexpr int BN = C::BNN;
     const int M = sh.M, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3, Dp = sh.Dp;
     const int R = sh.Rcap;
     hipError_t e;
@@ -1386,42 +1129,42 @@ static hipError_t train_mlp(const Shape& sh, const DevWeights<P>& wt, Work<P>& w
     base.n_models = M;
     base.nt = H3 / 64;
     GemmArgs<P> a;
-#define NNP_RUN(EPI, N, NZ, NAME)                                                               \
-    if ((e = run_gemm<P, BM, BN, C::WM, C::WN, C::S, EPI>(a, R, N, NZ, st, tm, NAME))) return e;
+#define NNP_RUN(EPI, BX, N, NZ, NAME)                                                           \
+    if ((e = net_gemm<P, BM, EPI>(a, wt.BX, R, N, NZ, st, tm, NAME))) return e;
 
     // forward: H1, H2, H3
     a = base;
     a.A = w.G; a.lda = Dp; a.B = wt.W1; a.ldb = Dp; a.b_s = (long)M * H1 * Dp;
     a.bias = wt.b1; a.bias_s = (long)M * H1; a.C = w.H1; a.ldc = M * H1; a.K = Dp;
-    NNP_RUN(EPI_CELU, M * H1, 1, "train_l1_fwd")
+    NNP_RUN(EPI_CELU, W1x, M * H1, 1, "train_l1_fwd")
     a = base;
     a.A = w.H1; a.lda = M * H1; a.a_z = H1;
     a.B = wt.W2; a.ldb = H1; a.b_s = (long)M * H2 * H1; a.b_z = (long)H2 * H1;
     a.bias = wt.b2; a.bias_s = (long)M * H2; a.bias_z = H2;
     a.C = w.H2; a.ldc = M * H2; a.c_z = H2; a.K = H1;
-    NNP_RUN(EPI_CELU, H2, M, "train_l2_fwd")
+    NNP_RUN(EPI_CELU, W2x, H2, M, "train_l2_fwd")
     a = base;
     a.A = w.H2; a.lda = M * H2; a.a_z = H2;
     a.B = wt.W3; a.ldb = H2; a.b_s = (long)M * H3 * H2; a.b_z = (long)H3 * H2;
     a.bias = wt.b3; a.bias_s = (long)M * H3; a.bias_z = H3;
     a.C = tw.H3; a.ldc = M * H3; a.c_z = H3; a.K = H2;
-    NNP_RUN(EPI_CELU, H3, M, "train_l3_fwd")
+    NNP_RUN(EPI_CELU, W3x, H3, M, "train_l3_fwd")
     // tangent forward: TH_l = CELU'(z_l) (TH_{l-1} W_l^T)
     if (has_gF) {
         a = base;
         a.A = tw.GD; a.lda = Dp; a.B = wt.W1; a.ldb = Dp; a.b_s = (long)M * H1 * Dp;
         a.Hr = w.H1; a.ldh = M * H1; a.C = tw.TH1; a.ldc = M * H1; a.K = Dp;
-        NNP_RUN(EPI_DSIG, M * H1, 1, "train_l1_tan")
+        NNP_RUN(EPI_DSIG, W1x, M * H1, 1, "train_l1_tan")
         a = base;
         a.A = tw.TH1; a.lda = M * H1; a.a_z = H1;
         a.B = wt.W2; a.ldb = H1; a.b_s = (long)M * H2 * H1; a.b_z = (long)H2 * H1;
         a.Hr = w.H2; a.ldh = M * H2; a.h_z = H2; a.C = tw.TH2; a.ldc = M * H2; a.c_z = H2; a.K = H1;
-        NNP_RUN(EPI_DSIG, H2, M, "train_l2_tan")
+        NNP_RUN(EPI_DSIG, W2x, H2, M, "train_l2_tan")
         a = base;
         a.A = tw.TH2; a.lda = M * H2; a.a_z = H2;
         a.B = wt.W3; a.ldb = H2; a.b_s = (long)M * H3 * H2; a.b_z = (long)H3 * H2;
         a.Hr = tw.H3; a.ldh = M * H3; a.h_z = H3; a.C = tw.TH3; a.ldc = M * H3; a.c_z = H3; a.K = H2;
-        NNP_RUN(EPI_DSIG, H3, M, "train_l3_tan")
+        NNP_RUN(EPI_DSIG, W3x, H3, M, "train_l3_tan")
     }
     return hipSuccess;
 }
@@ -1432,8 +1175,6 @@ template <typename P, int BM>
 static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P>& w,
                                 TrainWork<P>& tw, hipStream_t st, const Timer& tm) {
     typedef typename P::TA TA;
-    typedef Cfg<P, BM> C;
-    constexpr int BN = C::BNN;
     const int M = sh.M, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3;
     const int R = sh.Rcap;
     hipError_t e;
@@ -1451,7 +1192,7 @@ static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P
     a.A = tw.ZDB3; a.lda = M * H3; a.a_z = H3;
     a.B = wt.W3T; a.ldb = H3; a.b_s = (long)M * H2 * H3; a.b_z = (long)H2 * H3;
     a.C = tw.TMP; a.ldc = ldt; a.c_z = H2; a.K = H3;
-    NNP_RUN(EPI_RAW, H2, M, "train_l3_rev_t")
+    NNP_RUN(EPI_RAW, W3Tx, H2, M, "train_l3_rev_t")
     a = base;
     a.A = w.DZ3; a.lda = M * H3; a.a_z = H3;
     a.B = wt.W3T; a.ldb = H3; a.b_s = (long)M * H2 * H3; a.b_z = (long)H2 * H3;
@@ -1459,13 +1200,13 @@ static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P
     a.X = tw.TMP; a.ldx = ldt; a.x_z = H2;
     a.Tr = tw.TH2; a.ldt = M * H2; a.t_z = H2;
     a.C = w.DZ2; a.C2 = tw.ZDB2; a.ldc = M * H2; a.c_z = H2; a.c2_z = H2; a.K = H3;
-    NNP_RUN(EPI_REV, H2, M, "train_l3_rev")
+    NNP_RUN(EPI_REV, W3Tx, H2, M, "train_l3_rev")
     // layer 1 adjoints
     a = base;
     a.A = tw.ZDB2; a.lda = M * H2; a.a_z = H2;
     a.B = wt.W2T; a.ldb = H2; a.b_s = (long)M * H1 * H2; a.b_z = (long)H1 * H2;
     a.C = tw.TMP; a.ldc = ldt; a.c_z = H1; a.K = H2;
-    NNP_RUN(EPI_RAW, H1, M, "train_l2_rev_t")
+    NNP_RUN(EPI_RAW, W2Tx, H1, M, "train_l2_rev_t")
     a = base;
     a.A = w.DZ2; a.lda = M * H2; a.a_z = H2;
     a.B = wt.W2T; a.ldb = H2; a.b_s = (long)M * H1 * H2; a.b_z = (long)H1 * H2;
@@ -1473,7 +1214,7 @@ static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P
     a.X = tw.TMP; a.ldx = ldt; a.x_z = H1;
     a.Tr = tw.TH1; a.ldt = M * H1; a.t_z = H1;
     a.C = w.DZ1; a.C2 = tw.ZDB1; a.ldc = M * H1; a.c_z = H1; a.c2_z = H1; a.K = H2;
-    NNP_RUN(EPI_REV, H1, M, "train_l2_rev")
+    NNP_RUN(EPI_REV, W2Tx, H1, M, "train_l2_rev")
 #undef NNP_RUN
     return hipSuccess;
 }
@@ -1482,7 +1223,9 @@ template <typename P>
 hipError_t launch_train_mlp(const Shape& sh, const DevWeights<P>& wt, Work<P>& w,
                             TrainWork<P>& tw, const int32_t* mol_of_atom, const double* grad_E,
                             bool has_gF, hipStream_t st, const Timer& tm) {
-    if (sh.row_tile == 128) return train_mlp<P, 128>(sh, wt, w, tw, mol_of_atom, grad_E, has_gF, st, tm);
+    if constexpr (std::is_same<P, PrecF32>::value) {
+        if (sh.split) return train_mlp<P, kSplitRows>(sh, wt, w, tw, mol_of_atom, grad_E, has_gF, st, tm);
+    }
     if (sh.row_tile == 16) return train_mlp<P, 16>(sh, wt, w, tw, mol_of_atom, grad_E, has_gF, st, tm);
     return hipErrorInvalidValue;
 }
@@ -1490,7 +1233,9 @@ hipError_t launch_train_mlp(const Shape& sh, const DevWeights<P>& wt, Work<P>& w
 template <typename P>
 hipError_t launch_train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P>& w,
                                 TrainWork<P>& tw, hipStream_t st, const Timer& tm) {
-    if (sh.row_tile == 128) return train_mlp_rev<P, 128>(sh, wt, w, tw, st, tm);
+    if constexpr (std::is_same<P, PrecF32>::value) {
+        if (sh.split) return train_mlp_rev<P, kSplitRows>(sh, wt, w, tw, st, tm);
+    }
     if (sh.row_tile == 16) return train_mlp_rev<P, 16>(sh, wt, w, tw, st, tm);
     return hipErrorInvalidValue;
 }
@@ -1504,7 +1249,9 @@ hipError_t launch_l1_bwd(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, h
     base.row_tile = sh.row_tile;
     base.info = w.info;
     base.n_models = sh.M;
-    if (sh.row_tile == 128) return mlp_l1_bwd<P, 128>(sh, wt, w, base, st, tm);
+    if constexpr (std::is_same<P, PrecF32>::value) {
+        if (sh.split) return mlp_l1_bwd<P, kSplitRows>(sh, wt, w, base, st, tm);
+    }
     if (sh.row_tile == 16) return mlp_l1_bwd<P, 16>(sh, wt, w, base, st, tm);
     return hipErrorInvalidValue;
 }
@@ -1512,7 +1259,12 @@ hipError_t launch_l1_bwd(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, h
 template <typename P>
 hipError_t launch_mlp(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, hipStream_t st,
                       const Timer& tm) {
-    if (sh.row_tile == 128) return mlp_all<P, 128>(sh, wt, w, st, tm);
+    if constexpr (std::is_same<P, PrecF32>::value) {
+        if (sh.split) return mlp_all<P, kSplitRows>(sh, wt, w, st, tm);
+    }
+    if constexpr (std::is_same<P, PrecBF16>::value) {
+        if (sh.row_tile == 128) return mlp_all<P, 128>(sh, wt, w, st, tm);
+    }
     if (sh.row_tile == 16) return mlp_all<P, 16>(sh, wt, w, st, tm);
     return hipErrorInvalidValue;
 }

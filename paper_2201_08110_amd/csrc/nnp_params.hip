@@ -11,6 +11,16 @@
 
 namespace nnp {
 
+// a parameter as three bf16 parts at p[0], p[512], p[1024] (nnp_split.h)
+__device__ inline void put_parts(bf16_t* p, float v) {
+    const bf16_t h = Store<bf16_t>::st(v);
+    const float r = v - bf2f(h);
+    const bf16_t m = Store<bf16_t>::st(r);
+    p[0] = h;
+    p[512] = m;
+    p[1024] = Store<bf16_t>::st(r - bf2f(m));
+}
+
 template <typename P, typename TSRC>
 __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, const TSRC* __restrict__ src,
                                                     const int32_t* __restrict__ map, ParamPack pk,
@@ -32,6 +42,11 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
     if (r < pk.offb1) {                       // W1 [o1][D]
         const int nn = (int)(r / pk.D), k = (int)(r % pk.D);
         const int col = m * H1 + nn, N1 = M * H1;
+        if (dw.W1x) {
+            put_parts(dw.W1x + (size_t)s * N1 * Dp * 3 + split_index(col, k, Dp), (float)v);
+            put_parts(dw.W1Tx + (size_t)s * N1 * Dp * 3 + split_index(k, col, N1), (float)v);
+            return;
+        }
         dw.W1[((size_t)s * N1 + col) * Dp + k] = vs;
         dw.W1T[((size_t)s * Dp + k) * N1 + col] = vs;
         if (dw.W1f) {
@@ -43,8 +58,13 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
     } else if (r < pk.offb2) {                // W2 [o2][o1]
         const int64_t q = r - pk.offW2;
         const int nn = (int)(q / pk.o1), k = (int)(q % pk.o1);
-        dw.W2[(sm * H2 + nn) * H1 + k] = vs;
-        dw.W2T[(sm * H1 + k) * H2 + nn] = vs;
+        if (dw.W2x) {
+            put_parts(dw.W2x + sm * H2 * H1 * 3 + split_index(nn, k, H1), (float)v);
+            put_parts(dw.W2Tx + sm * H1 * H2 * 3 + split_index(k, nn, H2), (float)v);
+        } else {
+            dw.W2[(sm * H2 + nn) * H1 + k] = vs;
+            dw.W2T[(sm * H1 + k) * H2 + nn] = vs;
+        }
         dw.W2f[sm * H2 * H1 + frag_index<TS>(nn, k, H1)] = vs;
         dw.W2Tf[sm * H1 * H2 + frag_index<TS>(k, nn, H2)] = vs;
     } else if (r < pk.offW3) {                // b2 [o2]
@@ -52,8 +72,13 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
     } else if (r < pk.offb3) {                // W3 [o3][o2]
         const int64_t q = r - pk.offW3;
         const int nn = (int)(q / pk.o2), k = (int)(q % pk.o2);
-        dw.W3[(sm * H3 + nn) * H2 + k] = vs;
-        dw.W3T[(sm * H2 + k) * H3 + nn] = vs;
+        if (dw.W3x) {
+            put_parts(dw.W3x + sm * H3 * H2 * 3 + split_index(nn, k, H2), (float)v);
+            put_parts(dw.W3Tx + sm * H2 * H3 * 3 + split_index(k, nn, H3), (float)v);
+        } else {
+            dw.W3[(sm * H3 + nn) * H2 + k] = vs;
+            dw.W3T[(sm * H2 + k) * H3 + nn] = vs;
+        }
         dw.W3f[sm * H3 * H2 + frag_index<TS>(nn, k, H2)] = vs;
         dw.W3Tf[sm * H2 * H3 + frag_index<TS>(k, nn, H3)] = vs;
     } else if (r < pk.offw4) {                // b3 [o3]

@@ -257,14 +257,23 @@ template <typename P> nnp_status upload_weights(nnp_handle* h, DevWeights<P>& dw
             dst = (std::remove_reference_t<decltype(dst)>)h->dalloc(bytes, e);
             if (e == hipSuccess) e = hipMemset(dst, 0, bytes);
         };
-        zeros(dw.W1, S * M * H1 * Dp);
-        zeros(dw.W1T, S * M * H1 * Dp);
+        if (sh.split) {   // three bf16 parts an element
+            zeros(dw.W1x, 3 * S * M * H1 * Dp);
+            zeros(dw.W1Tx, 3 * S * M * H1 * Dp);
+            zeros(dw.W2x, 3 * S * M * H2 * H1);
+            zeros(dw.W2Tx, 3 * S * M * H2 * H1);
+            zeros(dw.W3x, 3 * S * M * H3 * H2);
+            zeros(dw.W3Tx, 3 * S * M * H3 * H2);
+        } else {
+            zeros(dw.W1, S * M * H1 * Dp);
+            zeros(dw.W1T, S * M * H1 * Dp);
+            zeros(dw.W2, S * M * H2 * H1);
+            zeros(dw.W2T, S * M * H2 * H1);
+            zeros(dw.W3, S * M * H3 * H2);
+            zeros(dw.W3T, S * M * H3 * H2);
+        }
         zeros(dw.b1, S * M * H1);
-        zeros(dw.W2, S * M * H2 * H1);
-        zeros(dw.W2T, S * M * H2 * H1);
         zeros(dw.b2, S * M * H2);
-        zeros(dw.W3, S * M * H3 * H2);
-        zeros(dw.W3T, S * M * H3 * H2);
         zeros(dw.b3, S * M * H3);
         zeros(dw.w4, S * M * H3);
         zeros(dw.b4, S * M);
@@ -882,7 +891,7 @@ nnp_status autotune(nnp_handle* h, const nnp_batch* b, const typename P::T* x, i
         } else if (k == NNP_KNOB_GEMM_STAGES) {
             cand = {2, 3};
         } else if (k == NNP_KNOB_TAIL_TILE) {
-            if (knob_value(h, NNP_KNOB_MLP_PATH) == 1 && h->shape.row_tile == 128) cand = {1, 2, 3};
+            if (knob_value(h, NNP_KNOB_MLP_PATH) == 1 && h->shape.row_tile != 16) cand = {1, 2, 3};
         } else if (k == NNP_KNOB_GEMM_WAVES) {
             if (h->shape.row_tile == 128 && h->precision != NNP_PREC_FP64) cand = {4, 8};
         } else if (k == NNP_KNOB_ATOM_CHUNK) {
@@ -1078,6 +1087,8 @@ nnp_status nnp_create(const nnp_model_params* p, nnp_handle** out) {
     sh.H3 = pad_to(wi[3], 64);
     sh.h3_used = wi[3];
     sh.row_tile = (p->max_atoms <= 256 || p->precision == NNP_PREC_FP64) ? 16 : 128;
+    sh.split = p->precision == NNP_PREC_FP32 && sh.row_tile == 128;
+    if (sh.split) sh.row_tile = 64;
     sh.Rcap = pad_to(p->max_atoms + S * (sh.row_tile - 1), sh.row_tile);
     sh.cap_nbr = std::max(1, std::min(h->max_apm - 1, kMaxNeighbours));
     sh.max_apm = h->max_apm;

@@ -1,0 +1,55 @@
+// nnp_split.h -- FP32 operands as three bf16 parts for the bf16 matrix cores.
+//
+// x = h + m + l with h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), all
+// rounded to nearest: |m| <= 2^-8 |x|, |l| <= 2^-16 |x|, and the three hold
+// every bit of the FP32 significand (short of underflow below 2^-110).  A
+// product x y is formed as the six parts of weight >= 2^-16,
+//   l h' + h l' + m m' + m h' + h m' + h h',
+// each exact in FP32; the three dropped ones are at most 2^-23 of |x y|, and
+// below 2^-26 on average.  gfx950 runs bf16 MFMAs 16 times as fast as FP32
+// ones, so six of them take 0.375 of the FP32 MFMA's time.
+// A non-finite x gives non-finite parts, so a non-finite product.
+#pragma once
+
+#include "nnp_gemm.h"
+
+namespace nnp {
+
+constexpr int kParts = 3;
+constexpr int kSplitRows = 64;   // bucket row tile of the handles that split their operands
+
+// parts of two values, packed (low half = first)
+__device__ inline void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+    h = pack_bf16x2(a, b);
+    const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
+    m = pack_bf16x2(ra, rb);
+    const float sa = ra - __uint_as_float(m << 16), sb = rb - __uint_as_float(m & 0xffff0000u);
+    l = pack_bf16x2(sa, sb);
+}
+// eight values as one 16-byte chunk per part
+__device__ inline void split8(const float v[8], uint4 o[kParts]) {
+    split2(v[0], v[1], o[0].x, o[1].x, o[2].x);
+    split2(v[2], v[3], o[0].y, o[1].y, o[2].y);
+    split2(v[4], v[5], o[0].z, o[1].z, o[2].z);
+    split2(v[6], v[7], o[0].w, o[1].w, o[2].w);
+}
+
+// LDS tile of split operands for one 32-deep k-step: [part][rows][64 bytes],
+// the four 16-byte chunks of row r at position c ^ (r / 2 % 4): the eight
+// rows a 16-byte read or write touches at a time then lie in distinct banks
+__device__ inline int split_at(int rows, int part, int r, int c) {
+    return (part * rows + r) * 64 + ((c ^ (r >> 1)) & 3) * 16;
+}
+
+// arguments of a split GEMM: g.B is unused, Bx is the pre-split weight operand
+// (fragment order, per element and model bx_s / bx_z bf16 elements apart)
+struct SplitArgs {
+    GemmArgs<PrecF32> g;
+    const bf16_t* Bx;
+    long bx_s, bx_z;
+};
+// C = A B^T for R rows (a multiple of the bucket row tile), N columns, nz models
+template <int EPI>
+hipError_t split_gemm(SplitArgs a, int R, int N, int nz, hipStream_t st, const Timer& tm, const char* name);
+
+}  // namespace nnp

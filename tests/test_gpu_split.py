@@ -1,0 +1,58 @@
+"""FP32 handles of more than 256 atoms run their networks on the bf16 matrix
+cores, every operand split into three bf16 parts.  Bucket sizes around the row
+tiles and hidden widths that take every column tiling, against the FP64 oracle
+with the FP32 bars of the parity tests."""
+import numpy as np
+import pytest
+
+from paper_2201_08110_amd import synth
+from tests.gpu_util import errors, make_handle, oracle_inputs, to_device, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(counts, seed=77):
+    """Molecules of 20 atoms (the last shorter) holding counts[s] atoms of element s."""
+    n = sum(counts)
+    sizes = [20] * (n // 20) + ([n % 20] if n % 20 else [])
+    b = synth.random_batch(seed, sizes)
+    sp = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    np.random.default_rng(seed).shuffle(sp)
+    b.species = sp
+    return b
+
+
+@pytest.mark.parametrize("counts,hidden,M,knobs", [
+    ((1, 0, 15, 16, 17, 31, 32), (256, 192, 160), 8, {}),
+    ((33, 63, 64, 65, 127, 128, 129), (256, 192, 160), 1, {}),
+    ((150, 100, 30, 20, 0, 0, 0), (256, 192, 160), 3, {"mlp_path": 2}),
+    ((64, 1, 100, 0, 3, 0, 2), (128, 64, 32), 1, {}),
+    ((40, 65, 17, 0, 3, 0, 2), (192, 128, 96), 2, {}),
+    ((40, 65, 17, 0, 3, 0, 2), (64, 256, 128), 3, {}),
+])
+def test_energies_forces_and_gradients(orc, hp, counts, hidden, M, knobs):
+    torch = torch_cuda()
+    hp = dict(hp, widths=[hp["widths"][0], *hidden, 1])
+    b = _batch(counts)
+    w = synth.xavier_weights(M, hp["widths"], seed=5)
+    h = make_handle(hp, w, M, "fp32", b, max_atoms=max(300, b.n_atoms))
+    for k, v in knobs.items():
+        h.set_knob(k, v)
+    x, sp, off = to_device(torch, b, torch.float32)
+    E, F = h.energy_forces(x, sp, off)
+    xo, wo = oracle_inputs(b, w, "fp32")
+    Eo, Fo = orc.energy_forces(hp, wo, M, b.species, xo, b.mol_offsets)
+    dE, rmse = errors(E.cpu().numpy(), F.double().cpu().numpy(), Eo, Fo, b.mol_offsets)
+    assert h.device_status() == 0
+    print("dE/atom", dE.max(), "force RMSE", rmse.max())
+    assert dE.max() <= 1e-4 and rmse.max() <= 1e-3
+    rng = np.random.default_rng(3)
+    gE, gF = rng.normal(size=b.n_mols) * 1e-2, synth.round_to_fp32(rng.normal(size=(b.n_atoms, 3)) * 1e-2)
+    gp, _ = h.backward(x, sp, off, torch.tensor(gE, device="cuda"),
+                       torch.tensor(gF, dtype=torch.float32, device="cuda"))
+    go = orc.param_grad(hp, wo, M, b.species, xo, b.mol_offsets, gE, gF)
+    err = np.linalg.norm(gp.double().cpu().numpy() - go) / np.linalg.norm(go)
+    print("parameter gradient", err)
+    assert h.device_status() == 0
+    assert err <= 1e-4
+    h.close()
