@@ -41,6 +41,16 @@ __device__ inline int split_at(int rows, int part, int r, int c) {
     return (part * rows + r) * 64 + ((c ^ (r >> 1)) & 3) * 16;
 }
 
+// acc[j] += a b[j], smallest products first, the accumulators in turn
+template <int FN>
+__device__ inline void split_mma(f32x4 (&acc)[FN], const bf16x8 (&b)[FN][kParts], const bf16x8 (&a)[kParts]) {
+    constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[j] = MF<bf16_t>::mma(b[j][pb[q]], a[pa[q]], acc[j]);
+}
+
 // arguments of a split GEMM: g.B is unused, Bx is the pre-split weight operand
 // (fragment order, per element and model bx_s / bx_z bf16 elements apart)
 struct SplitArgs {

@@ -92,12 +92,7 @@ __global__ __launch_bounds__(64 * WN, 2) void k_gx(SplitArgs a) {
 #pragma unroll
             for (int p = 0; p < kParts; ++p)
                 af[p] = *(const Frag*)(st + split_at(BM, p, i * 16 + (lane & 15), lane >> 4));
-            // smallest products first, the FN accumulators in turn
-            constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};
-#pragma unroll
-            for (int q = 0; q < 6; ++q)
-#pragma unroll
-                for (int j = 0; j < FN; ++j) acc[i][j] = MF<bf16_t>::mma(b[j][pb[q]], af[pa[q]], acc[i][j]);
+            split_mma(acc[i], b, af);
         }
     };
 

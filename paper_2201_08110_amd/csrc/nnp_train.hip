@@ -9,7 +9,7 @@
 // beta = -u/M (tangent).  This file holds the elementwise layer-3 reverse
 // step, the weight-gradient reductions over each element bucket's rows and
 // the bias / output-layer sums; the GEMM steps live in nnp_mlp.hip.
-#include "nnp_internal.h"
+#include "nnp_split.h"
 
 namespace nnp {
 
@@ -83,19 +83,11 @@ hipError_t launch_train_rev3(const Shape& sh, const DevWeights<P>& wt, Work<P>& 
 //   Wbar[n][k] = sum over the element's bucket rows r of
 //                X1[r][xo + n] Y1[r][yo + k] + X2[r][xo + n] Y2[r][yo + k]
 // (xo = m * out width, yo = m * in width or 0 for the AEV operands),
-// written into the packed gradient array.  MFMA 16x16x4 (FP32 / FP64) takes
-// one element per lane, so the row-major tiles feed it without a transpose:
-// the reduction runs over rows, 16 per LDS slice.
-typedef float f32x4_ __attribute__((ext_vector_type(4)));
-typedef double f64x4_ __attribute__((ext_vector_type(4)));
-template <typename TS> struct MFW;
-template <> struct MFW<float> {
-    typedef f32x4_ Acc;
-    __device__ static Acc mma(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    __device__ static int row(int l, int r) { return 4 * (l >> 4) + r; }
-};
-template <> struct MFW<double> {
-    typedef f64x4_ Acc;
+// written into the packed gradient array.  FP64: MFMA 16x16x4 takes one
+// element per lane, so the row-major tiles feed it without a transpose: the
+// reduction runs over rows, 16 per LDS slice.  (FP32: k_wgx.)
+struct MFW {
+    typedef f64x4 Acc;
     __device__ static Acc mma(double a, double b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
     __device__ static int row(int l, int r) { return (l >> 4) + 4 * r; }
 };
@@ -119,12 +111,12 @@ __global__ __launch_bounds__(256) void k_wgrad(int S, int M, const BucketInfo* _
                                                typename P::TA* __restrict__ gparam) {
     typedef typename P::TS TS;
     typedef typename P::TA TA;
-    typedef MFW<TS> mf;
+    typedef MFW mf;
     constexpr int VEC = 16 / (int)sizeof(TS);            // elements per 16-byte load
     constexpr int LD = kWT + VEC;                        // padded LDS row
     constexpr int NV = kWR * kWT / VEC / 256;            // vector loads per thread and operand
     constexpr int FM = kWT / 32, FN = kWT / 32;          // 16 x 16 MFMA tiles per wave
-    typedef typename std::conditional<sizeof(TS) == 8, double2, float4>::type TV;
+    typedef double2 TV;
     __shared__ __align__(16) TS Xs[kWR][LD];
     __shared__ __align__(16) TS Ys[kWR][LD];
     const int tile = blockIdx.x, sm = blockIdx.y;
@@ -201,102 +193,269 @@ __global__ __launch_bounds__(256) void k_wgrad(int S, int M, const BucketInfo* _
             }
 }
 
-// column sums over each bucket: bias gradients (and, with coefficients, the
-// output-layer weights and bias)
-template <typename P>
-__global__ __launch_bounds__(256) void k_colsum(int S, int M, const BucketInfo* __restrict__ info,
-                                                const typename P::TS* __restrict__ X, int ldx, int xw,
-                                                int out_o, long offb, long net,
-                                                typename P::TA* __restrict__ gparam) {
-    typedef typename P::TA TA;
-    typedef typename P::TS TS;
-    __shared__ TA part[4][64];
-    const int sm = blockIdx.y, s = sm % S, m = sm / S;
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63), rg = threadIdx.x >> 6;
-    TA acc = 0;
-    if (col < out_o)
-        for (int r = info->off[s] + rg; r < info->off[s + 1]; r += 4)
-            acc += Store<TS>::ld(X[(size_t)r * ldx + m * xw + col]);
-    part[rg][threadIdx.x & 63] = acc;
-    __syncthreads();
-    if (rg == 0 && col < out_o)
-        gparam[((long)m * S + s) * net + offb + col] =
-            (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
-}
+// Column sums over each element bucket: the bias gradients (adjoints of layers
+// 1-3), the output layer's weights (rows weighted by their output adjoints)
+// and its bias.  One launch: a workgroup takes 32 columns of one (element,
+// model) with 32 row groups, so a bucket of 1,600 rows is 50 strided loads a
+// thread, eight in flight, and a fixed tree over the groups; the row weights,
+// each a chain of three dependent loads, are fetched 1,024 rows at a time
+// into LDS.  64 columns x 4 row groups in four launches were bound by that
+// chain: 855 us a training step of 3,520 atoms, now 38 us.
+constexpr int kSumCols = 32, kSumGroups = 32, kSumRows = kSumCols * kSumGroups;
+template <typename P> struct SumArgs {
+    const typename P::TS* X[3];   // adjoints of layers 1-3
+    int ld[3], xw[3], out[3], nb[3];
+    long off[3];
+    const typename P::TS *Hh, *Th;   // layer-3 activations and tangents
+    int H3, o3;
+    double scale;
+    bool has_gF;
+    const int32_t *atom_of_row, *mol_of_atom;
+    const double* grad_E;
+    long offw4, offb4, net;
+};
 
 template <typename P>
-__global__ __launch_bounds__(256) void k_w4grad(int S, int M, int H3, int o3, double scale,
-                                                bool has_gF, const BucketInfo* __restrict__ info,
-                                                const int32_t* __restrict__ atom_of_row,
-                                                const int32_t* __restrict__ mol_of_atom,
-                                                const double* __restrict__ grad_E,
-                                                const typename P::TS* __restrict__ Hh,
-                                                const typename P::TS* __restrict__ Th, long offw4,
-                                                long offb4, long net,
-                                                typename P::TA* __restrict__ gparam) {
+__global__ __launch_bounds__(kSumRows) void k_row_sums(int S, int M, const BucketInfo* __restrict__ info, SumArgs<P> g,
+                                                       typename P::TA* __restrict__ gparam) {
     typedef typename P::TA TA;
     typedef typename P::TS TS;
-    __shared__ TA part[4][64];
-    __shared__ TA pb[4][64];
-    const int sm = blockIdx.y, s = sm % S, m = sm / S;
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63), rg = threadIdx.x >> 6;
+    __shared__ TA part[kSumGroups][kSumCols + 1];
+    __shared__ TA wal[kSumRows], wbe[kSumRows];
+    const int s = blockIdx.y / M, m = blockIdx.y % M;
+    int blk = blockIdx.x, layer = 0;
+    while (layer < 3 && blk >= g.nb[layer]) blk -= g.nb[layer++];
+    const int c = threadIdx.x % kSumCols, rg = threadIdx.x / kSumCols, col = blk * kSumCols + c;
+    const int r0 = info->off[s], r1 = info->off[s + 1];
+    TA* out = gparam + ((long)m * S + s) * g.net;
     TA acc = 0, accb = 0;
-    for (int r = info->off[s] + rg; r < info->off[s + 1]; r += 4) {
-        TA al, be;
-        row_adjoints(r, atom_of_row, mol_of_atom, grad_E, has_gF, scale / M, al, be);
-        if (col < o3) {
-            const size_t e = (size_t)r * M * H3 + (size_t)m * H3 + col;
-            acc += al * Store<TS>::ld(Hh[e]) + (has_gF ? be * Store<TS>::ld(Th[e]) : TA(0));
+    if (layer < 3) {
+        if (col < g.out[layer]) {
+            const TS* X = g.X[layer] + (size_t)m * g.xw[layer] + col;
+            const size_t ld = g.ld[layer];
+#pragma unroll 8
+            for (int r = r0 + rg; r < r1; r += kSumGroups) acc += Store<TS>::ld(X[r * ld]);
         }
-        accb += al;
+    } else {
+        const size_t ld = (size_t)M * g.H3, at = (size_t)m * g.H3 + min(col, g.H3 - 1);
+        for (int rc = r0; rc < r1; rc += kSumRows) {
+            __syncthreads();
+            const int r = rc + (int)threadIdx.x;
+            TA al = 0, be = 0;
+            if (r < r1) row_adjoints(r, g.atom_of_row, g.mol_of_atom, g.grad_E, g.has_gF, g.scale / M, al, be);
+            wal[threadIdx.x] = al;
+            wbe[threadIdx.x] = be;
+            accb += al;
+            __syncthreads();
+            const int n = min(kSumRows, r1 - rc);
+#pragma unroll 4
+            for (int t = rg; t < n; t += kSumGroups) {
+                const size_t e = (size_t)(rc + t) * ld + at;
+                acc += wal[t] * Store<TS>::ld(g.Hh[e]) + (g.has_gF ? wbe[t] * Store<TS>::ld(g.Th[e]) : TA(0));
+            }
+        }
     }
-    part[rg][threadIdx.x & 63] = acc;
-    pb[rg][threadIdx.x & 63] = accb;
-    __syncthreads();
-    const int c = threadIdx.x;
-    TA* out = gparam + ((long)m * S + s) * net;
-    if (rg == 0 && col < o3) out[offw4 + col] = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
-    if (threadIdx.x == 0 && blockIdx.x == 0) out[offb4] = (pb[0][0] + pb[1][0]) + (pb[2][0] + pb[3][0]);
+    auto tree = [&](TA v) {   // column sums over the row groups, left in part[0]
+        part[rg][c] = v;
+        for (int o = kSumGroups / 2; o > 0; o >>= 1) {
+            __syncthreads();
+            if (rg < o) part[rg][c] += part[rg + o][c];
+        }
+        __syncthreads();
+    };
+    tree(acc);
+    const int o_w = layer < 3 ? g.out[layer] : g.o3;
+    const long o_at = layer < 3 ? g.off[layer] : g.offw4;
+    if (rg == 0 && col < o_w) out[o_at + col] = part[0][c];
+    if (layer == 3 && blk == 0) {   // each thread's rows' weights: the sum over every row
+        __syncthreads();
+        tree(accb);
+        if (threadIdx.x == 0) {
+            TA v = 0;
+            for (int q = 0; q < kSumCols; ++q) v += part[0][q];
+            out[g.offb4] = v;
+        }
+    }
+}
+
+// The same weight gradients in FP32 on the bf16 matrix cores, both operands
+// split into three bf16 parts (nnp_split.h) on their way into LDS, transposed:
+// the reduction runs over rows, 32 a step, so a thread takes 8 rows x 2
+// columns of each operand and writes one 16-byte chunk (8 rows) a column and
+// part.  A workgroup owns a 128 x 128 tile (2 x 2 waves of 64 x 64) of one
+// (element, model, layer); all three layers' tiles are one launch, the
+// elements in index order (the commonest first), so the short chains of the
+// rare ones fill in behind the long ones.  Bound by LDS reads (24 KiB per
+// wave and step for 96 MFMAs).  Training step of 3,520 atoms: three FP32 MFMA
+// launches of 64 x 64 tiles 701 us, this one 242 us.
+struct WgLayer {
+    const float *X1, *Y1, *X2, *Y2;   // Wbar = X1^T Y1 + X2^T Y2 over the bucket's rows
+    int ldx, ldy, xw, yw;             // leading dimensions; columns per model (yw 0: shared by all)
+    int out_o, in_o, ntn, nt;         // gradient [out_o][in_o]; tiles along n and per model
+    long offW;
+};
+struct WgArgs {
+    WgLayer l[3];
+};
+constexpr int kXT = 128;
+
+__global__ __launch_bounds__(256, 2) void k_wgx(int S, int M, const BucketInfo* __restrict__ info, WgArgs w, long net,
+                                                float* __restrict__ gparam) {
+    typedef bf16x8 Frag;
+    __shared__ __align__(16) char lds[2][kParts * kXT * 64];
+    int blk = blockIdx.x, li = 0;
+    while (blk >= w.l[li].nt * M) blk -= w.l[li++].nt * M;
+    const WgLayer& g = w.l[li];
+    const int s = blockIdx.y, m = blk / g.nt, tile = blk % g.nt;
+    const int n0 = (tile % g.ntn) * kXT, k0 = (tile / g.ntn) * kXT;
+    const int r0 = info->off[s], r1 = info->off[s + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int cp = 2 * lane;                              // this thread's two columns, rows 8 wave ..
+    // columns past an operand's width repeat its last two (their products are
+    // not stored)
+    const int xc = min(n0 + cp, g.xw - 2), yc = min(k0 + cp, (g.yw ? g.yw : g.ldy) - 2);
+    const size_t xo = (size_t)m * g.xw + xc, yo = (size_t)m * g.yw + yc;
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
+    float2 xr[8], yr[8];
+    auto load = [&](const float* X, const float* Y, int r) {
+        // buckets are whole multiples of 16 rows: past the end the last eight
+        // again, against zeros
+        const bool in = r + 8 * wave < r1;
+        const size_t row = min(r + 8 * wave, r1 - 8);
+        const float *xp = X + row * g.ldx + xo, *yp = Y + row * g.ldy + yo;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            xr[q] = *(const float2*)(xp + (size_t)q * g.ldx);
+            yr[q] = *(const float2*)(yp + (size_t)q * g.ldy);
+        }
+        if (!in)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) xr[q] = make_float2(0.f, 0.f);
+    };
+    auto store = [&](char* t, const float2(&v)[8]) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            float e[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) e[q] = c ? v[q].y : v[q].x;
+            uint4 o[kParts];
+            split8(e, o);
+#pragma unroll
+            for (int p = 0; p < kParts; ++p) *(uint4*)(t + split_at(kXT, p, cp + c, wave)) = o[p];
+        }
+    };
+    for (int pass = 0; pass < 2; ++pass) {
+        const float* X = pass ? g.X2 : g.X1;
+        const float* Y = pass ? g.Y2 : g.Y1;
+        if (!X || !Y || r0 >= r1) continue;
+        load(X, Y, r0);
+        for (int r = r0; r < r1; r += 32) {
+            store(lds[0], xr);
+            store(lds[1], yr);
+            __syncthreads();
+            if (r + 32 < r1) load(X, Y, r + 32);
+            asm volatile("" ::: "memory");                // keep those loads ahead of the products
+            Frag bf[4][kParts];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int p = 0; p < kParts; ++p)
+                    bf[j][p] = *(const Frag*)(lds[1] + split_at(kXT, p, wn * 64 + j * 16 + (lane & 15), lane >> 4));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                Frag af[kParts];
+#pragma unroll
+                for (int p = 0; p < kParts; ++p)
+                    af[p] = *(const Frag*)(lds[0] + split_at(kXT, p, wm * 64 + i * 16 + (lane & 15), lane >> 4));
+                split_mma(acc[i], bf, af);
+            }
+            __syncthreads();
+        }
+    }
+    float* out = gparam + ((long)m * S + s) * net + g.offW;
+    auto write = [&](auto whole) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int n = n0 + wm * 64 + i * 16 + (lane & 15), k = k0 + wn * 64 + j * 16 + 4 * (lane >> 4) + q;
+                    if (whole.value || (n < g.out_o && k < g.in_o)) out[(long)n * g.in_o + k] = acc[i][j][q];
+                }
+    };
+    if (n0 + kXT <= g.out_o && k0 + kXT <= g.in_o) write(std::true_type{});
+    else write(std::false_type{});
 }
 
 template <typename P>
 hipError_t launch_train_grads(const Shape& sh, const NetLayout& nl, Work<P>& w, TrainWork<P>& tw,
                               const int32_t* mol_of_atom, const double* grad_E, bool has_gF,
                               typename P::TA* gp, hipStream_t st, const Timer& tm) {
+    typedef typename P::TS TS;
     const int S = sh.S, M = sh.M, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3, Dp = sh.Dp;
     const dim3 blk(256);
     tm.b("train_wgrad", st);
-    // W3: [o3 x o2] from (ZB3, H2) + (ZDB3, TH2)
-    {
-        const int ntn = (nl.o3 + kWT - 1) / kWT, ntk = (nl.o2 + kWT - 1) / kWT;
-        hipLaunchKernelGGL(k_wgrad<P>, dim3(ntn * ntk, S * M), blk, 0, st, S, M, w.info, w.DZ3,
-                           w.H2, has_gF ? tw.ZDB3 : nullptr, tw.TH2, M * H3, M * H2, H3, H2, nl.o3,
-                           nl.o2, nl.offW3, nl.net, ntn, gp);
-    }
-    // W2: [o2 x o1] from (ZB2, H1) + (ZDB2, TH1)
-    {
-        const int ntn = (nl.o2 + kWT - 1) / kWT, ntk = (nl.o1 + kWT - 1) / kWT;
-        hipLaunchKernelGGL(k_wgrad<P>, dim3(ntn * ntk, S * M), blk, 0, st, S, M, w.info, w.DZ2,
-                           w.H1, has_gF ? tw.ZDB2 : nullptr, tw.TH1, M * H2, M * H1, H2, H1, nl.o2,
-                           nl.o1, nl.offW2, nl.net, ntn, gp);
-    }
-    // W1: [o1 x D] from (ZB1, G) + (ZDB1, GD)
-    {
-        const int ntn = (nl.o1 + kWT - 1) / kWT, ntk = (nl.D + kWT - 1) / kWT;
-        hipLaunchKernelGGL(k_wgrad<P>, dim3(ntn * ntk, S * M), blk, 0, st, S, M, w.info, w.DZ1,
-                           w.G, has_gF ? tw.ZDB1 : nullptr, tw.GD, M * H1, Dp, H1, 0, nl.o1,
-                           nl.D, nl.offW1, nl.net, ntn, gp);
+    // W1 [o1 x D] from (ZB1, G) + (ZDB1, GD), W2 [o2 x o1] from (ZB2, H1) +
+    // (ZDB2, TH1), W3 [o3 x o2] from (ZB3, H2) + (ZDB3, TH2)
+    if constexpr (std::is_same<P, PrecF32>::value) {
+        WgArgs a{};
+        auto layer = [&](int i, const float* X1, const float* Y1, const float* X2, const float* Y2, int xw, int yw,
+                         int ldy, int out_o, int in_o, long offW) {
+            const int ntn = (out_o + kXT - 1) / kXT;
+            a.l[i] = {X1, Y1, has_gF ? X2 : nullptr, Y2, M * xw, ldy, xw, yw, out_o, in_o, ntn,
+                      ntn * ((in_o + kXT - 1) / kXT), offW};
+        };
+        layer(0, w.DZ1, w.G, tw.ZDB1, tw.GD, H1, 0, Dp, nl.o1, nl.D, nl.offW1);
+        layer(1, w.DZ2, w.H1, tw.ZDB2, tw.TH1, H2, H1, M * H1, nl.o2, nl.o1, nl.offW2);
+        layer(2, w.DZ3, w.H2, tw.ZDB3, tw.TH2, H3, H2, M * H2, nl.o3, nl.o2, nl.offW3);
+        hipLaunchKernelGGL(k_wgx, dim3((a.l[0].nt + a.l[1].nt + a.l[2].nt) * M, S), blk, 0, st, S, M, w.info, a, nl.net, gp);
+    } else {
+        auto layer = [&](const TS* X1, const TS* Y1, const TS* X2, const TS* Y2, int xw, int yw, int ldy, int out_o,
+                         int in_o, long offW) {
+            const int ntn = (out_o + kWT - 1) / kWT, ntk = (in_o + kWT - 1) / kWT;
+            hipLaunchKernelGGL(k_wgrad<P>, dim3(ntn * ntk, S * M), blk, 0, st, S, M, w.info, X1, Y1,
+                               has_gF ? X2 : nullptr, Y2, M * xw, ldy, xw, yw, out_o, in_o, offW, nl.net, ntn, gp);
+        };
+        layer(w.DZ3, w.H2, tw.ZDB3, tw.TH2, H3, H2, M * H2, nl.o3, nl.o2, nl.offW3);
+        layer(w.DZ2, w.H1, tw.ZDB2, tw.TH1, H2, H1, M * H1, nl.o2, nl.o1, nl.offW2);
+        layer(w.DZ1, w.G, tw.ZDB1, tw.GD, H1, 0, Dp, nl.o1, nl.D, nl.offW1);
     }
     // biases and the output layer
-    hipLaunchKernelGGL(k_colsum<P>, dim3((nl.o1 + 63) / 64, S * M), blk, 0, st, S, M, w.info, w.DZ1,
-                       M * H1, H1, nl.o1, nl.offb1, nl.net, gp);
-    hipLaunchKernelGGL(k_colsum<P>, dim3((nl.o2 + 63) / 64, S * M), blk, 0, st, S, M, w.info, w.DZ2,
-                       M * H2, H2, nl.o2, nl.offb2, nl.net, gp);
-    hipLaunchKernelGGL(k_colsum<P>, dim3((nl.o3 + 63) / 64, S * M), blk, 0, st, S, M, w.info, w.DZ3,
-                       M * H3, H3, nl.o3, nl.offb3, nl.net, gp);
-    hipLaunchKernelGGL(k_w4grad<P>, dim3((nl.o3 + 63) / 64, S * M), blk, 0, st, S, M, H3, nl.o3,
-                       sh.energy_scale, has_gF, w.info, w.atom_of_row, mol_of_atom, grad_E, tw.H3,
-                       tw.TH3, nl.offw4, nl.offb4, nl.net, gp);
+    SumArgs<P> a{};
+    const TS* X[3] = {w.DZ1, w.DZ2, w.DZ3};
+    const int xw[3] = {H1, H2, H3}, out[3] = {nl.o1, nl.o2, nl.o3};
+    const long off[3] = {nl.offb1, nl.offb2, nl.offb3};
+    int nb = (nl.o3 + kSumCols - 1) / kSumCols;
+    for (int i = 0; i < 3; ++i) {
+        a.X[i] = X[i];
+        a.ld[i] = M * xw[i];
+        a.xw[i] = xw[i];
+        a.out[i] = out[i];
+        a.nb[i] = (out[i] + kSumCols - 1) / kSumCols;
+        a.off[i] = off[i];
+        nb += a.nb[i];
+    }
+    a.Hh = tw.H3;
+    a.Th = tw.TH3;
+    a.H3 = H3;
+    a.o3 = nl.o3;
+    a.scale = sh.energy_scale;
+    a.has_gF = has_gF;
+    a.atom_of_row = w.atom_of_row;
+    a.mol_of_atom = mol_of_atom;
+    a.grad_E = grad_E;
+    a.offw4 = nl.offw4;
+    a.offb4 = nl.offb4;
+    a.net = nl.net;
+    hipLaunchKernelGGL(k_row_sums<P>, dim3(nb, S * M), dim3(kSumRows), 0, st, S, M, w.info, a, gp);
     tm.e("train_wgrad", st);
     return hipGetLastError();
 }
