@@ -136,6 +136,10 @@ template <> struct Quad<bf16_t, 1> {
 // and a few weight column blocks in its L2.
 constexpr int kGroupM = 8;
 
+// the fused tails are compiled for the ANI-2x hidden widths (256, 192, 160
+// padded to 192); other widths take the per-layer GEMMs
+constexpr int kTailH1 = 256, kTailH2 = 192, kTailH3 = 192;
+
 // Epilogue of one wave's FM x FN MFMA tiles of the product C = A B^T: element r
 // of acc[i][j] in lane l is C[row_base + lrow0 + 16 i + l % 16][col0 + 16 j +
 // r ST], col0 = the wave's first column + col0(l).  s: element, z: model,

@@ -926,10 +926,6 @@ __global__ __launch_bounds__(256 * TW, 2 * TW) void k_tail(TailArgs<P> g) {
     }
 }
 
-// the fused tail is compiled for the ANI-2x hidden widths (256, 192, 160
-// padded to 192); other widths take the per-layer GEMMs
-constexpr int kTailH1 = 256, kTailH2 = 192, kTailH3 = 192;
-
 template <typename P, int BM, int TW, int H3L = kTailH3>
 static hipError_t run_tail(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, hipStream_t st,
                            const Timer& tm) {
@@ -1051,6 +1047,10 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
         if (!mlp_fused_supported(H1, H2, H3)) return hipErrorInvalidValue;
         // fused layers 2-3 forward and backward
         w.epart_nt = 1;
+        if constexpr (is_split<P, BM>) {
+            if ((e = split_tail(sh, wt, w, st, tm))) return e;
+            return mlp_l1_bwd<P, BM>(sh, wt, w, base, st, tm);
+        } else {
         constexpr int TB = TailBM<P>::v, TH = TB / 2 >= 16 ? TB / 2 : 16;
         // layer 3 of at most 160 outputs (ANI-2x): products over the 160 real
         // columns, not the 192 the storage is padded to
@@ -1064,6 +1064,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
         else e = n160 ? run_tail<P, TB, 1, 160>(sh, wt, w, st, tm) : run_tail<P, TB, 1>(sh, wt, w, st, tm);
         if (e) return e;
         return mlp_l1_bwd<P, BM>(sh, wt, w, base, st, tm);
+        }
     }
     w.epart_nt = H3 / 64;
     // L2f

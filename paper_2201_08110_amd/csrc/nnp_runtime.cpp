@@ -891,7 +891,7 @@ nnp_status autotune(nnp_handle* h, const nnp_batch* b, const typename P::T* x, i
         } else if (k == NNP_KNOB_GEMM_STAGES) {
             cand = {2, 3};
         } else if (k == NNP_KNOB_TAIL_TILE) {
-            if (knob_value(h, NNP_KNOB_MLP_PATH) == 1 && h->shape.row_tile != 16) cand = {1, 2, 3};
+            if (knob_value(h, NNP_KNOB_MLP_PATH) == 1 && h->shape.row_tile == 128) cand = {1, 2, 3};
         } else if (k == NNP_KNOB_GEMM_WAVES) {
             if (h->shape.row_tile == 128 && h->precision != NNP_PREC_FP64) cand = {4, 8};
         } else if (k == NNP_KNOB_ATOM_CHUNK) {

@@ -62,4 +62,7 @@ struct SplitArgs {
 template <int EPI>
 hipError_t split_gemm(SplitArgs a, int R, int N, int nz, hipStream_t st, const Timer& tm, const char* name);
 
+// layers 2-3 forward and backward (widths of mlp_fused_supported)
+hipError_t split_tail(const Shape& sh, const DevWeights<PrecF32>& wt, Work<PrecF32>& w, hipStream_t st, const Timer& tm);
+
 }  // namespace nnp
