@@ -458,13 +458,11 @@ template <typename X> inline size_t lds_bytes(size_t n) { return (sizeof(X) * n 
 // ==========================================================================
 // Neighbour lists: for every atom, the local indices of the atoms of its
 // molecule within rcr, those within rca first, each of the two runs sorted
-// by element.  A workgroup of one wave owns up to 64 central atoms of one
-// molecule, one lane per atom; the molecule's atoms are staged in LDS in
-// element order (small molecules: every atom is tested) or in (element,
-// cutoff cell) order (large molecules: only the <= 27 cells around the
-// central atom's cell are tested), so the scan emits sorted lists, which are
-// assembled in LDS and written out coalesced.  Also zeroes the forces.
-constexpr int kNbrChunk = 64;  // central atoms per neighbour-list workgroup
+// by element.  One wave per central atom: the molecule's atoms are staged in
+// LDS in element order (small molecules) or in (element, cutoff cell) order
+// (large ones), each 64-candidate slice is tested at once and its hits are
+// appended in order through ballots, so the lists come out sorted.  Also
+// zeroes the forces.
 constexpr int kChunk = 16;     // most central atoms per AEV / force workgroup (the knob picks 4..16)
 constexpr int kWaves = 4;
 constexpr size_t kMaxLds = 160 * 1024;   // LDS per workgroup on gfx950
@@ -482,175 +480,6 @@ __device__ inline T wave_max(T v) {
     return v;
 }
 
-template <typename T>
-__global__ __launch_bounds__(64) void k_neighbours(int A, int S, int max_apm, int cell_min, int cap,
-                                                   T rcr, T rca2,
-                                                   T rcr2, const int32_t* __restrict__ mol_off,
-                                                   const int32_t* __restrict__ species,
-                                                   const T* __restrict__ x, T* __restrict__ F,
-                                                   unsigned long long* __restrict__ Fq,
-                                                   uint16_t* __restrict__ nbr,
-                                                   int32_t* __restrict__ nbr_cnt,
-                                                   int32_t* __restrict__ flag) {
-    extern __shared__ __align__(16) char smem[];
-    const int b = blockIdx.x;
-    const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
-    if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
-    if (n <= cell_min) return;   // listed by k_nbr_pairs
-    const int i0 = blockIdx.y * kNbrChunk;
-    if (i0 >= n) return;
-    const int lane = lane_id();
-    LdsBump lb(smem);
-    T* sx = lb.take<T>(4 * (size_t)max_apm);            // staged atoms: x y z
-    int* sid = lb.take<int>(max_apm);                   // local index of the k-th staged atom
-    uint16_t* lst = lb.take<uint16_t>((size_t)kNbrChunk * cap);
-    T* tx = lb.take<T>(3 * (size_t)max_apm);            // the molecule's x y z, input order
-    int* tsp = lb.take<int>(max_apm);                   // and elements
-    constexpr int kKeys = kMaxSpecies * kMaxCellsPerDim * kMaxCellsPerDim * kMaxCellsPerDim;
-    int* kstart = lb.take<int>(kKeys + 1);             // bucket starts
-    int* kcur = lb.take<int>(kKeys);                   // scatter cursors
-    int* akey = lb.take<int>(max_apm);                 // key of every atom
-
-    // ---- staging: atoms in (element, cell) order over a grid of cutoff
-    // cells with edge >= rcr, so a central atom scans <= 27 cells
-    int nc0 = 1, nc1 = 1, nc2 = 1;
-    T lo0 = 0, lo1 = 0, lo2 = 0, ih0 = 0, ih1 = 0, ih2 = 0;
-    // one coalesced pass over the molecule's inputs: every later pass reads LDS
-    for (int t = lane; t < 3 * n; t += 64) tx[t] = x[3 * (size_t)a0 + t];
-    for (int j = lane; j < n; j += 64) {
-        const int s = species[a0 + j];
-        tsp[j] = (s < 0 || s >= S) ? 0 : s;
-    }
-    wave_sync();
-    {
-        T mn0 = T(1e30), mn1 = T(1e30), mn2 = T(1e30), mx0 = T(-1e30), mx1 = T(-1e30), mx2 = T(-1e30);
-        for (int j = lane; j < n; j += 64) {
-            const T* p = tx + 3 * j;
-            mn0 = fmin(mn0, p[0]); mx0 = fmax(mx0, p[0]);
-            mn1 = fmin(mn1, p[1]); mx1 = fmax(mx1, p[1]);
-            mn2 = fmin(mn2, p[2]); mx2 = fmax(mx2, p[2]);
-        }
-        lo0 = wave_min(mn0); lo1 = wave_min(mn1); lo2 = wave_min(mn2);
-        const T e0 = wave_max(mx0) - lo0, e1 = wave_max(mx1) - lo1, e2 = wave_max(mx2) - lo2;
-        nc0 = min(max((int)(e0 / rcr), 1), kMaxCellsPerDim);
-        nc1 = min(max((int)(e1 / rcr), 1), kMaxCellsPerDim);
-        nc2 = min(max((int)(e2 / rcr), 1), kMaxCellsPerDim);
-        ih0 = e0 > T(0) ? T(nc0) / e0 : T(0);
-        ih1 = e1 > T(0) ? T(nc1) / e1 : T(0);
-        ih2 = e2 > T(0) ? T(nc2) / e2 : T(0);
-        const int ncell = nc0 * nc1 * nc2, nkeys = S * ncell;
-        for (int k = lane; k <= nkeys; k += 64) kstart[k] = 0;
-        wave_sync();
-        for (int j = lane; j < n; j += 64) {
-            int s = tsp[j];
-            s = (s < 0 || s >= S) ? 0 : s;
-            const T* p = tx + 3 * j;
-            const int c0 = min((int)((p[0] - lo0) * ih0), nc0 - 1);
-            const int c1 = min((int)((p[1] - lo1) * ih1), nc1 - 1);
-            const int c2 = min((int)((p[2] - lo2) * ih2), nc2 - 1);
-            const int key = s * ncell + (c2 * nc1 + c1) * nc0 + c0;
-            akey[j] = key;
-            atomicAdd(&kstart[key + 1], 1);
-        }
-        wave_sync();
-        // inclusive scan of the counts (lane-blocked, then across lanes)
-        const int per = (nkeys + 64) / 64;
-        const int k0 = lane * per, k1 = min(k0 + per, nkeys + 1);
-        int run = 0;
-        for (int k = k0; k < k1; ++k) run += kstart[k];
-        int pre = run;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(pre, o);
-            if (lane >= o) pre += v;
-        }
-        pre -= run;
-        for (int k = k0; k < k1; ++k) {
-            pre += kstart[k];
-            kstart[k] = pre;
-        }
-        wave_sync();
-        for (int k = lane; k < nkeys; k += 64) kcur[k] = kstart[k];
-        wave_sync();
-        for (int j = lane; j < n; j += 64) {
-            const int pos = atomicAdd(&kcur[akey[j]], 1);
-            sid[pos] = j;
-            sx[4 * pos + 0] = tx[3 * j + 0];
-            sx[4 * pos + 1] = tx[3 * j + 1];
-            sx[4 * pos + 2] = tx[3 * j + 2];
-        }
-    }
-    wave_sync();
-
-    // ---- one lane per central atom: scan the staged atoms in order
-    const int il = i0 + lane;
-    const bool act = il < n;
-    T xi0 = 0, xi1 = 0, xi2 = 0;
-    if (act) {
-        xi0 = x[3 * ((size_t)a0 + il) + 0];
-        xi1 = x[3 * ((size_t)a0 + il) + 1];
-        xi2 = x[3 * ((size_t)a0 + il) + 2];
-        if (F) {
-            F[3 * ((size_t)a0 + il) + 0] = T(0);
-            F[3 * ((size_t)a0 + il) + 1] = T(0);
-            F[3 * ((size_t)a0 + il) + 2] = T(0);
-        }
-        if (Fq) {
-            Fq[3 * ((size_t)a0 + il) + 0] = 0ull;
-            Fq[3 * ((size_t)a0 + il) + 1] = 0ull;
-            Fq[3 * ((size_t)a0 + il) + 2] = 0ull;
-        }
-    }
-    uint16_t* my = lst + (size_t)lane * cap;
-    int cnt = 0, nang = 0;
-#define NNP_TEST(k)                                                                            \
-    {                                                                                          \
-        const int j_ = sid[k];                                                                 \
-        const T d0 = sx[4 * (k)] - xi0, d1 = sx[4 * (k) + 1] - xi1, d2 = sx[4 * (k) + 2] - xi2; \
-        const T r2 = d0 * d0 + d1 * d1 + d2 * d2;                                             \
-        if (act && j_ != il && (pass == 0 ? (r2 < rca2) : (r2 >= rca2 && r2 < rcr2))) {        \
-            if (cnt < cap) my[cnt] = (uint16_t)j_;                                             \
-            ++cnt;                                                                             \
-        }                                                                                      \
-    }
-    {
-        const int ncell = nc0 * nc1 * nc2;
-        const int c0 = act ? min((int)((xi0 - lo0) * ih0), nc0 - 1) : 0;
-        const int c1 = act ? min((int)((xi1 - lo1) * ih1), nc1 - 1) : 0;
-        const int c2 = act ? min((int)((xi2 - lo2) * ih2), nc2 - 1) : 0;
-        for (int pass = 0; pass < 2; ++pass) {
-            for (int q = 0; q < S; ++q)
-                for (int z = max(c2 - 1, 0); z <= min(c2 + 1, nc2 - 1); ++z)
-                    for (int y = max(c1 - 1, 0); y <= min(c1 + 1, nc1 - 1); ++y)
-                        for (int xx = max(c0 - 1, 0); xx <= min(c0 + 1, nc0 - 1); ++xx) {
-                            const int key = q * ncell + (z * nc1 + y) * nc0 + xx;
-                            for (int k = kstart[key]; k < kstart[key + 1]; ++k) NNP_TEST(k)
-                        }
-            if (pass == 0) nang = cnt;
-        }
-    }
-#undef NNP_TEST
-    if (act) {
-        int nall = cnt;
-        if (nall > cap) {
-            atomicOr(flag, FLAG_CAPACITY);
-            nall = cap;
-            nang = nang > cap ? cap : nang;
-        }
-        nbr_cnt[(size_t)a0 + il] = nang | (nall << 16);
-    }
-    wave_sync();
-    // coalesced copy of the chunk's lists
-    const int na = min(kNbrChunk, n - i0);
-    uint16_t* dst = nbr + ((size_t)a0 + i0) * cap;
-    for (int e = lane; e < na * cap; e += 64) dst[e] = lst[e];
-}
-
-// Neighbour lists of molecules of at most cell_min atoms, one wave per
-// central atom and one lane per candidate: the molecule is staged in element
-// order (as k_neighbours does), each 64-candidate slice is tested at once and
-// its hits are appended in order through a ballot, angular ones (r < rca) in
-// a first sweep and the rest (r < rcr) in a second.  The lists equal those of
-// the scanning kernel entry for entry; no lane walks the molecule serially.
 // One wave: the molecule's atoms staged in stable element order (sx4: x y z
 // and a spare word per atom, sid: input index of each staged atom).
 template <typename T>
@@ -716,9 +545,82 @@ __device__ inline int atom_neighbours(const T* sx4, const int* sid, int n, int i
     return nang | (nall << 16);
 }
 
+// All threads: a molecule's n atoms staged in (element, cell) order, input
+// order within a cell, over a grid of cutoff cells with edge >= rcr.
+// kstart / kord / akey: scratch of kCellKeys + 1, n and n integers.  The order
+// is the one a scan of the 27 cells around an atom finds its neighbours in.
+// Such a scan, one lane per central atom, was one serial chain of LDS reads:
+// 267 us for one molecule of 600 atoms (10 waves).  A wave per central atom
+// testing every staged atom is 12.7 us; at the largest molecule it makes 32
+// slices a wave.
+constexpr int kCellKeys = kMaxSpecies * kMaxCellsPerDim * kMaxCellsPerDim * kMaxCellsPerDim;
+template <typename T>
+__device__ inline void stage_cell_order(const T* tx, const int* tsp, int n, int S, T rcr, T* sx4, int* sid,
+                                        int* kstart, int* kord, int* akey) {
+    const int tid = threadIdx.x, lane = lane_id(), nt = blockDim.x;
+    T mn[3] = {T(1e30), T(1e30), T(1e30)}, mx[3] = {T(-1e30), T(-1e30), T(-1e30)}, ih[3];
+    int nc[3];
+    for (int j = lane; j < n; j += 64)
+        for (int d = 0; d < 3; ++d) {
+            mn[d] = fmin(mn[d], tx[3 * j + d]);
+            mx[d] = fmax(mx[d], tx[3 * j + d]);
+        }
+    for (int d = 0; d < 3; ++d) {
+        mn[d] = wave_min(mn[d]);
+        const T e = wave_max(mx[d]) - mn[d];
+        nc[d] = min(max((int)(e / rcr), 1), kMaxCellsPerDim);
+        ih[d] = e > T(0) ? T(nc[d]) / e : T(0);
+    }
+    const int ncell = nc[0] * nc[1] * nc[2], nkeys = S * ncell;
+    for (int k = tid; k <= nkeys; k += nt) kstart[k] = 0;
+    __syncthreads();
+    for (int j = tid; j < n; j += nt) {
+        int c[3];
+        for (int d = 0; d < 3; ++d) c[d] = min(max((int)((tx[3 * j + d] - mn[d]) * ih[d]), 0), nc[d] - 1);
+        const int key = tsp[j] * ncell + (c[2] * nc[1] + c[1]) * nc[0] + c[0];
+        akey[j] = key;
+        atomicAdd(&kstart[key + 1], 1);
+    }
+    __syncthreads();
+    if (tid < 64) {   // inclusive scan of the counts (lane-blocked, then across lanes)
+        const int per = (nkeys + 64) / 64;
+        const int k0 = lane * per, k1 = min(k0 + per, nkeys + 1);
+        int run = 0;
+        for (int k = k0; k < k1; ++k) run += kstart[k];
+        int pre = run;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(pre, o);
+            if (lane >= o) pre += v;
+        }
+        pre -= run;
+        for (int k = k0; k < k1; ++k) {
+            pre += kstart[k];
+            kstart[k] = pre;
+        }
+    }
+    __syncthreads();
+    // into the cells in any order (sid counts the places taken), then each
+    // atom to its rank among its cell's atoms
+    for (int j = tid; j < n; j += nt) sid[j] = 0;
+    __syncthreads();
+    for (int j = tid; j < n; j += nt) {
+        const int at = kstart[akey[j]];
+        kord[at + atomicAdd(&sid[at], 1)] = j;
+    }
+    __syncthreads();
+    for (int p = tid; p < n; p += nt) {
+        const int j = kord[p], key = akey[j], k0 = kstart[key], k1 = kstart[key + 1];
+        int pos = k0;
+        for (int q = k0; q < k1; ++q) pos += kord[q] < j;
+        sid[pos] = j;
+        for (int d = 0; d < 3; ++d) sx4[4 * pos + d] = tx[3 * j + d];
+    }
+    __syncthreads();
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_nbr_pairs(int A, int S, int max_apm, int cell_min, int chunk,
-                                                   int cap, T rca2, T rcr2,
+                                                   int cap, T rcr, T rca2, T rcr2,
                                                    const int32_t* __restrict__ mol_off,
                                                    const int32_t* __restrict__ species,
                                                    const T* __restrict__ x, T* __restrict__ F,
@@ -729,7 +631,7 @@ __global__ __launch_bounds__(256) void k_nbr_pairs(int A, int S, int max_apm, in
     extern __shared__ __align__(16) char smem[];
     const int b = blockIdx.x;
     const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
-    if (n <= 0 || n > max_apm || n > cell_min || a0 < 0 || a0 + n > A) return;
+    if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     const int i0 = blockIdx.y * chunk;
     if (i0 >= n) return;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
@@ -744,8 +646,15 @@ __global__ __launch_bounds__(256) void k_nbr_pairs(int A, int S, int max_apm, in
         tsp[j] = (s < 0 || s >= S) ? 0 : s;
     }
     __syncthreads();
-    if (wave == 0) stage_element_order(tx, tsp, n, S, sx, sid);
-    __syncthreads();
+    if (n > cell_min) {
+        int* kstart = lb.take<int>(kCellKeys + 1);
+        int* kord = lb.take<int>(max_apm);
+        int* akey = lb.take<int>(max_apm);
+        stage_cell_order(tx, tsp, n, S, rcr, sx, sid, kstart, kord, akey);
+    } else {
+        if (wave == 0) stage_element_order(tx, tsp, n, S, sx, sid);
+        __syncthreads();
+    }
     const int nc = min(chunk, n - i0);
     for (int ic = wave; ic < nc; ic += nw) {
         const int il = i0 + ic;
@@ -773,36 +682,17 @@ hipError_t launch_neighbours(const Shape& sh, const AevConst<typename P::T>& c,
     } else if (accumulate) {
         F = nullptr;
     }
-    // molecules up to cell_min atoms: one wave per central atom
-    {
-        const int small = std::min(sh.max_apm, sh.cell_min);
-        dim3 grid(sh.B, (small + sh.chunk - 1) / sh.chunk);
-        const size_t lds = lds_bytes<T>(4 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm) +
-                           lds_bytes<T>(3 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm);
-        if (lds > kMaxLds) return hipErrorInvalidValue;
-        hipError_t e = ensure_lds((const void*)k_nbr_pairs<T>, lds);
-        if (e != hipSuccess) return e;
-        tm.b("neighbours", st);
-        hipLaunchKernelGGL(k_nbr_pairs<T>, grid, dim3(256), lds, st, sh.A, sh.S, sh.max_apm, sh.cell_min,
-                           sh.chunk, sh.cap_nbr, c.rca2, c.rcr2, mol_off, species, x, F, Fq, w.nbr,
-                           w.nbr_cnt, w.flag);
-        tm.e("neighbours", st);
-        if ((e = hipGetLastError()) != hipSuccess || sh.max_apm <= sh.cell_min) return e;
-    }
-    // larger molecules: cutoff cells, one lane per central atom
-    dim3 grid(sh.B, (sh.max_apm + kNbrChunk - 1) / kNbrChunk);
-    const int nkeys = kMaxSpecies * kMaxCellsPerDim * kMaxCellsPerDim * kMaxCellsPerDim;
-    const size_t lds = lds_bytes<T>(4 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm) +
-                       lds_bytes<uint16_t>((size_t)kNbrChunk * sh.cap_nbr) +
-                       lds_bytes<T>(3 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm) +
-                       lds_bytes<int>(nkeys + 1) + lds_bytes<int>(nkeys) + lds_bytes<int>(sh.max_apm);
+    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk);
+    size_t lds = lds_bytes<T>(4 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm) +
+                 lds_bytes<T>(3 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm);
+    if (sh.max_apm > sh.cell_min) lds += lds_bytes<int>(kCellKeys + 1) + 2 * lds_bytes<int>(sh.max_apm);
     if (lds > kMaxLds) return hipErrorInvalidValue;
-    hipError_t e = ensure_lds((const void*)k_neighbours<T>, lds);
+    hipError_t e = ensure_lds((const void*)k_nbr_pairs<T>, lds);
     if (e != hipSuccess) return e;
     tm.b("neighbours", st);
-    hipLaunchKernelGGL(k_neighbours<T>, grid, dim3(64), lds, st, sh.A, sh.S, sh.max_apm,
-                       sh.cell_min, sh.cap_nbr, c.rcr, c.rca2, c.rcr2, mol_off, species, x, F, Fq,
-                       w.nbr, w.nbr_cnt, w.flag);
+    hipLaunchKernelGGL(k_nbr_pairs<T>, grid, dim3(256), lds, st, sh.A, sh.S, sh.max_apm, sh.cell_min,
+                       sh.chunk, sh.cap_nbr, c.rcr, c.rca2, c.rcr2, mol_off, species, x, F, Fq, w.nbr,
+                       w.nbr_cnt, w.flag);
     tm.e("neighbours", st);
     return hipGetLastError();
 }
