@@ -180,6 +180,7 @@ __host__ __device__ inline size_t split_index(int n, int k, int K) {
 template <typename P> struct DevWeights {
     typedef typename P::TS TS;
     typedef typename P::TA TA;
+    // row-major matrices (null on FP32 handles)
     TS* W1;   TS* W1T;   TA* b1;   // [S][M*H1][Dp], [S][Dp][M*H1], [S][M*H1]
     TS* W2;   TS* W2T;   TA* b2;   // [S][M][H2][H1], [S][M][H1][H2], [S][M][H2]
     TS* W3;   TS* W3T;   TA* b3;   // [S][M][H3][H2], [S][M][H2][H3], [S][M][H3]
@@ -187,7 +188,7 @@ template <typename P> struct DevWeights {
     // the fused layers 2-3 kernel's operands in fragment order (per element
     // and model: W2 [H2][H1], W3 [H3][H2], W3^T [H2][H3], W2^T [H1][H2])
     TS* W2f;  TS* W3f;  TS* W3Tf;  TS* W2Tf;
-    // the layer-1 GEMMs' weight operands in fragment order (BF16 only, per
+    // the layer-1 GEMMs' weight operands in fragment order (BF16 and FP32, per
     // element: W1cat [M*H1][Dp] and W1cat^T [Dp][M*H1]; null otherwise)
     TS* W1f;  TS* W1Tf;
     // every matrix split into three bf16 parts in fragment order (split_index;
@@ -201,12 +202,17 @@ template <typename P> struct DevWeights {
 struct ParamPack {
     int S, M, D, Dp, H1, H2, H3;   // device widths (hidden widths padded to 64)
     int o1, o2;                    // widths of the packed layout's first two hidden layers
+    int w[kMaxSpecies][4];         // every element network's own widths: D and the hidden layers
     long net, offb1, offW2, offb2, offW3, offb3, offw4, offb4;
 };
 // parameters [first, first + n) of the packed array from src[0..n)
 template <typename P, typename TSRC>
 hipError_t launch_set_params(int64_t first, int64_t n, const TSRC* src, const int32_t* map, const ParamPack& pk,
                              const DevWeights<P>& dw, hipStream_t st);
+
+// the whole packed array from the device, FP32 handles
+template <typename TSRC>
+hipError_t launch_set_nets(const TSRC* src, const ParamPack& pk, const DevWeights<PrecF32>& dw, hipStream_t st);
 
 struct Shape {
     int S, M, D, Dp, H1, H2, H3;       // H* padded to multiples of 64

@@ -552,15 +552,16 @@ template <typename P> struct Cfg<P, 128> {
 template <typename P> struct Cfg<P, 16> {
     static constexpr int BNW = 64, BNN = 64, WM = 1, WN = 4, S = 3;
 };
-// FP32 handles of more than 256 atoms split their operands instead (k_gx)
-template <typename P, int BM> constexpr bool is_split = std::is_same<P, PrecF32>::value && BM == kSplitRows;
+// FP32 handles split their operands instead (nnp_split.hip)
+template <typename P> constexpr bool is_f32 = std::is_same<P, PrecF32>::value;
 
-// one network GEMM over every row tile: Bx is the weight operand a.B's
-// pre-split form
+// one network GEMM over every row tile: a.B is the row-major weight operand;
+// FP32 takes its fragment-order form Bf or its parts Bx
 template <typename P, int BM, int EPI>
-static hipError_t net_gemm(const GemmArgs<P>& a, const bf16_t* Bx, int R, int N, int nz, hipStream_t st,
+static hipError_t net_gemm(GemmArgs<P> a, const typename P::TS* Bf, const bf16_t* Bx, int R, int N, int nz, hipStream_t st,
                            const Timer& tm, const char* name) {
-    if constexpr (is_split<P, BM>) {
+    if constexpr (is_f32<P>) {
+        a.B = Bf;
         return split_gemm<EPI>(SplitArgs{a, Bx, kParts * a.b_s, kParts * a.b_z}, R, N, nz, st, tm, name);
     } else {
         typedef Cfg<P, BM> C;
@@ -963,14 +964,14 @@ template <typename P> struct TailBM { static constexpr int v = 128 / (int)sizeof
 // the wide layer-1 GEMMs: LDS stages and waves per workgroup from the knobs
 // (8 waves split the 128 x 128 tile 2 x 4, for 128-row buckets only)
 template <typename P, int BM, int EPI>
-static hipError_t run_l1(GemmArgs<P> a, const bf16_t* Bx, const Shape& sh, int N, hipStream_t st, const Timer& tm,
+static hipError_t run_l1(GemmArgs<P> a, const typename P::TS* Bf, const bf16_t* Bx, const Shape& sh, int N, hipStream_t st, const Timer& tm,
                          const char* name) {
     const int R = sh.Rcap;
-    if constexpr (is_split<P, BM>) {
-        return net_gemm<P, BM, EPI>(a, Bx, R, N, 1, st, tm, name);
+    if constexpr (is_f32<P>) {
+        return net_gemm<P, BM, EPI>(a, Bf, Bx, R, N, 1, st, tm, name);
     } else {
     typedef Cfg<P, BM> C;
-    if (N % C::BNW != 0) return net_gemm<P, BM, EPI>(a, nullptr, R, N, 1, st, tm, name);
+    if (N % C::BNW != 0) return net_gemm<P, BM, EPI>(a, nullptr, nullptr, R, N, 1, st, tm, name);
     // 8 waves (2 x 4 of 64 x 32) for the forward GEMM when the knob says so;
     // the backward GEMM measured better on 4
     if constexpr (BM == 128 && C::BNW == 128 && EPI == EPI_CELU) {
@@ -1006,7 +1007,7 @@ static hipError_t mlp_l1_bwd(const Shape& sh, const DevWeights<P>& wt, Work<P>& 
             return run_l1rb<EPI_ACC>(a, sh.Rcap, Dp, sh.gemm_stages, st, tm, "mlp_l1_bwd");
         }
     }
-    return run_l1<P, BM, EPI_ACC>(a, wt.W1Tx, sh, Dp, st, tm, "mlp_l1_bwd");
+    return run_l1<P, BM, EPI_ACC>(a, wt.W1Tf, wt.W1Tx, sh, Dp, st, tm, "mlp_l1_bwd");
 }
 
 template <typename P, int BM>
@@ -1041,13 +1042,13 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
             l1_done = true;
         }
     }
-    if (!l1_done) e = run_l1<P, BM, EPI_CELU>(a, wt.W1x, sh, M * H1, st, tm, "mlp_l1_fwd");
+    if (!l1_done) e = run_l1<P, BM, EPI_CELU>(a, wt.W1f, wt.W1x, sh, M * H1, st, tm, "mlp_l1_fwd");
     if (e) return e;
     if (sh.mlp_fused) {
         if (!mlp_fused_supported(H1, H2, H3)) return hipErrorInvalidValue;
         // fused layers 2-3 forward and backward
         w.epart_nt = 1;
-        if constexpr (is_split<P, BM>) {
+        if constexpr (is_f32<P> && BM == kSplitRows) {
             if ((e = split_tail(sh, wt, w, st, tm))) return e;
             return mlp_l1_bwd<P, BM>(sh, wt, w, base, st, tm);
         } else {
@@ -1074,7 +1075,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.bias = wt.b2; a.bias_s = (long)M * H2; a.bias_z = H2;
     a.C = w.H2; a.ldc = M * H2; a.c_z = H2;
     a.K = H1;
-    if ((e = net_gemm<P, BM, EPI_CELU>(a, wt.W2x, R, H2, M, st, tm, "mlp_l2_fwd")))
+    if ((e = net_gemm<P, BM, EPI_CELU>(a, wt.W2f, wt.W2x, R, H2, M, st, tm, "mlp_l2_fwd")))
         return e;
     // L3f (+ output layer, + dE/dz3)
     a = base;
@@ -1085,7 +1086,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.C = w.DZ3; a.ldc = M * H3; a.c_z = H3;
     a.epart = w.Epart;
     a.K = H2;
-    if ((e = net_gemm<P, BM, EPI_L3F>(a, wt.W3x, R, H3, M, st, tm, "mlp_l3_fwd")))
+    if ((e = net_gemm<P, BM, EPI_L3F>(a, wt.W3f, wt.W3x, R, H3, M, st, tm, "mlp_l3_fwd")))
         return e;
     // L3b
     a = base;
@@ -1094,7 +1095,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.Hr = w.H2; a.ldh = M * H2; a.h_z = H2;
     a.C = w.DZ2; a.ldc = M * H2; a.c_z = H2;
     a.K = H3;
-    if ((e = net_gemm<P, BM, EPI_DSIG>(a, wt.W3Tx, R, H2, M, st, tm, "mlp_l3_bwd")))
+    if ((e = net_gemm<P, BM, EPI_DSIG>(a, wt.W3Tf, wt.W3Tx, R, H2, M, st, tm, "mlp_l3_bwd")))
         return e;
     // L2b
     a = base;
@@ -1103,7 +1104,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     a.Hr = w.H1; a.ldh = M * H1; a.h_z = H1;
     a.C = w.DZ1; a.ldc = M * H1; a.c_z = H1;
     a.K = H2;
-    if ((e = net_gemm<P, BM, EPI_DSIG>(a, wt.W2Tx, R, H1, M, st, tm, "mlp_l2_bwd"))) return e;
+    if ((e = net_gemm<P, BM, EPI_DSIG>(a, wt.W2Tf, wt.W2Tx, R, H1, M, st, tm, "mlp_l2_bwd"))) return e;
     return mlp_l1_bwd<P, BM>(sh, wt, w, base, st, tm);
 }
 
@@ -1131,41 +1132,41 @@ static hipError_t train_mlp(const Shape& sh, const DevWeights<P>& wt, Work<P>& w
     base.nt = H3 / 64;
     GemmArgs<P> a;
 #define NNP_RUN(EPI, BX, N, NZ, NAME)                                                           \
-    if ((e = net_gemm<P, BM, EPI>(a, wt.BX, R, N, NZ, st, tm, NAME))) return e;
+    if ((e = net_gemm<P, BM, EPI>(a, wt.BX##f, wt.BX##x, R, N, NZ, st, tm, NAME))) return e;
 
     // forward: H1, H2, H3
     a = base;
     a.A = w.G; a.lda = Dp; a.B = wt.W1; a.ldb = Dp; a.b_s = (long)M * H1 * Dp;
     a.bias = wt.b1; a.bias_s = (long)M * H1; a.C = w.H1; a.ldc = M * H1; a.K = Dp;
-    NNP_RUN(EPI_CELU, W1x, M * H1, 1, "train_l1_fwd")
+    NNP_RUN(EPI_CELU, W1, M * H1, 1, "train_l1_fwd")
     a = base;
     a.A = w.H1; a.lda = M * H1; a.a_z = H1;
     a.B = wt.W2; a.ldb = H1; a.b_s = (long)M * H2 * H1; a.b_z = (long)H2 * H1;
     a.bias = wt.b2; a.bias_s = (long)M * H2; a.bias_z = H2;
     a.C = w.H2; a.ldc = M * H2; a.c_z = H2; a.K = H1;
-    NNP_RUN(EPI_CELU, W2x, H2, M, "train_l2_fwd")
+    NNP_RUN(EPI_CELU, W2, H2, M, "train_l2_fwd")
     a = base;
     a.A = w.H2; a.lda = M * H2; a.a_z = H2;
     a.B = wt.W3; a.ldb = H2; a.b_s = (long)M * H3 * H2; a.b_z = (long)H3 * H2;
     a.bias = wt.b3; a.bias_s = (long)M * H3; a.bias_z = H3;
     a.C = tw.H3; a.ldc = M * H3; a.c_z = H3; a.K = H2;
-    NNP_RUN(EPI_CELU, W3x, H3, M, "train_l3_fwd")
+    NNP_RUN(EPI_CELU, W3, H3, M, "train_l3_fwd")
     // tangent forward: TH_l = CELU'(z_l) (TH_{l-1} W_l^T)
     if (has_gF) {
         a = base;
         a.A = tw.GD; a.lda = Dp; a.B = wt.W1; a.ldb = Dp; a.b_s = (long)M * H1 * Dp;
         a.Hr = w.H1; a.ldh = M * H1; a.C = tw.TH1; a.ldc = M * H1; a.K = Dp;
-        NNP_RUN(EPI_DSIG, W1x, M * H1, 1, "train_l1_tan")
+        NNP_RUN(EPI_DSIG, W1, M * H1, 1, "train_l1_tan")
         a = base;
         a.A = tw.TH1; a.lda = M * H1; a.a_z = H1;
         a.B = wt.W2; a.ldb = H1; a.b_s = (long)M * H2 * H1; a.b_z = (long)H2 * H1;
         a.Hr = w.H2; a.ldh = M * H2; a.h_z = H2; a.C = tw.TH2; a.ldc = M * H2; a.c_z = H2; a.K = H1;
-        NNP_RUN(EPI_DSIG, W2x, H2, M, "train_l2_tan")
+        NNP_RUN(EPI_DSIG, W2, H2, M, "train_l2_tan")
         a = base;
         a.A = tw.TH2; a.lda = M * H2; a.a_z = H2;
         a.B = wt.W3; a.ldb = H2; a.b_s = (long)M * H3 * H2; a.b_z = (long)H3 * H2;
         a.Hr = tw.H3; a.ldh = M * H3; a.h_z = H3; a.C = tw.TH3; a.ldc = M * H3; a.c_z = H3; a.K = H2;
-        NNP_RUN(EPI_DSIG, W3x, H3, M, "train_l3_tan")
+        NNP_RUN(EPI_DSIG, W3, H3, M, "train_l3_tan")
     }
     return hipSuccess;
 }
@@ -1193,7 +1194,7 @@ static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P
     a.A = tw.ZDB3; a.lda = M * H3; a.a_z = H3;
     a.B = wt.W3T; a.ldb = H3; a.b_s = (long)M * H2 * H3; a.b_z = (long)H2 * H3;
     a.C = tw.TMP; a.ldc = ldt; a.c_z = H2; a.K = H3;
-    NNP_RUN(EPI_RAW, W3Tx, H2, M, "train_l3_rev_t")
+    NNP_RUN(EPI_RAW, W3T, H2, M, "train_l3_rev_t")
     a = base;
     a.A = w.DZ3; a.lda = M * H3; a.a_z = H3;
     a.B = wt.W3T; a.ldb = H3; a.b_s = (long)M * H2 * H3; a.b_z = (long)H2 * H3;
@@ -1201,13 +1202,13 @@ static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P
     a.X = tw.TMP; a.ldx = ldt; a.x_z = H2;
     a.Tr = tw.TH2; a.ldt = M * H2; a.t_z = H2;
     a.C = w.DZ2; a.C2 = tw.ZDB2; a.ldc = M * H2; a.c_z = H2; a.c2_z = H2; a.K = H3;
-    NNP_RUN(EPI_REV, W3Tx, H2, M, "train_l3_rev")
+    NNP_RUN(EPI_REV, W3T, H2, M, "train_l3_rev")
     // layer 1 adjoints
     a = base;
     a.A = tw.ZDB2; a.lda = M * H2; a.a_z = H2;
     a.B = wt.W2T; a.ldb = H2; a.b_s = (long)M * H1 * H2; a.b_z = (long)H1 * H2;
     a.C = tw.TMP; a.ldc = ldt; a.c_z = H1; a.K = H2;
-    NNP_RUN(EPI_RAW, W2Tx, H1, M, "train_l2_rev_t")
+    NNP_RUN(EPI_RAW, W2T, H1, M, "train_l2_rev_t")
     a = base;
     a.A = w.DZ2; a.lda = M * H2; a.a_z = H2;
     a.B = wt.W2T; a.ldb = H2; a.b_s = (long)M * H1 * H2; a.b_z = (long)H1 * H2;
@@ -1215,7 +1216,7 @@ static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P
     a.X = tw.TMP; a.ldx = ldt; a.x_z = H1;
     a.Tr = tw.TH1; a.ldt = M * H1; a.t_z = H1;
     a.C = w.DZ1; a.C2 = tw.ZDB1; a.ldc = M * H1; a.c_z = H1; a.c2_z = H1; a.K = H2;
-    NNP_RUN(EPI_REV, W2Tx, H1, M, "train_l2_rev")
+    NNP_RUN(EPI_REV, W2T, H1, M, "train_l2_rev")
 #undef NNP_RUN
     return hipSuccess;
 }

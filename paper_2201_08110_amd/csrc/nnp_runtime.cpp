@@ -91,6 +91,7 @@ struct nnp_handle {
     // layout (gpad) and gathered
     bool het = false;
     int64_t n_int = 0;
+    std::vector<int> sw;          // [S][5] widths of every element's network
     int32_t* dmap = nullptr;
     void* gpad = nullptr;
 
@@ -225,6 +226,8 @@ ParamPack param_pack(const nnp_handle* h) {
     pk.o1 = nl.o1;
     pk.o2 = nl.o2;
     pk.net = nl.net;
+    for (int s = 0, l = 0; s < h->S; ++s)
+        for (l = 0; l < 4; ++l) pk.w[s][l] = h->sw[s * 5 + l];
     pk.offb1 = nl.offb1;
     pk.offW2 = nl.offW2;
     pk.offb2 = nl.offb2;
@@ -242,7 +245,6 @@ ParamPack param_pack(const nnp_handle* h) {
 // host).  Padding entries are zeroed at allocation and never written.
 template <typename P> nnp_status upload_weights(nnp_handle* h, DevWeights<P>& dw,
                                                 const double* w, bool allocate) {
-    typedef typename P::TS TS;
     const Shape& sh = h->shape;
     const size_t S = h->S, M = h->M, Dp = sh.Dp, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3;
     hipError_t e = hipSuccess;
@@ -264,7 +266,8 @@ template <typename P> nnp_status upload_weights(nnp_handle* h, DevWeights<P>& dw
             zeros(dw.W2Tx, 3 * S * M * H2 * H1);
             zeros(dw.W3x, 3 * S * M * H3 * H2);
             zeros(dw.W3Tx, 3 * S * M * H3 * H2);
-        } else {
+        }
+        if (!std::is_same<P, PrecF32>::value) {   // row-major
             zeros(dw.W1, S * M * H1 * Dp);
             zeros(dw.W1T, S * M * H1 * Dp);
             zeros(dw.W2, S * M * H2 * H1);
@@ -284,9 +287,10 @@ template <typename P> nnp_status upload_weights(nnp_handle* h, DevWeights<P>& dw
         zeros(dw.W3f, S * M * H3 * H2);
         zeros(dw.W3Tf, S * M * H3 * H2);
         zeros(dw.W2Tf, S * M * H2 * H1);
-        // the layer-1 weights in fragment order for the register-operand
-        // GEMMs (BF16): one [M*H1][Dp] matrix and its transpose per element
-        if (std::is_same<TS, bf16_t>::value) {
+        // the layer-1 weights in fragment order for the GEMMs that load them
+        // straight into registers (BF16, FP32): one [M*H1][Dp] matrix and its
+        // transpose per element
+        if (!std::is_same<P, PrecF64>::value) {
             zeros(dw.W1f, S * M * H1 * Dp);
             zeros(dw.W1Tf, S * M * H1 * Dp);
         }
@@ -434,6 +438,8 @@ bool l1_regs_supported(const nnp_handle* h) {
            sh.Dp % 256 == 0;
 }
 
+Shape call_shape(const nnp_handle* h, int A, int B);
+
 // value in effect of a knob (automatic choices resolved)
 int32_t knob_value(const nnp_handle* h, int k) {
     const Shape& sh = h->shape;
@@ -448,7 +454,7 @@ int32_t knob_value(const nnp_handle* h, int k) {
     case NNP_KNOB_GEMM_WAVES: return v ? v : 8;
     case NNP_KNOB_ATOM_CHUNK:
         if (v) return v;
-        return (int64_t)h->max_mols * ((h->max_apm + 15) / 16) >= 1024 ? 16 : 4;
+        return call_shape(h, h->max_atoms, h->max_mols).chunk;   // of a call that fills the handle
     case NNP_KNOB_L1_PATH:
         if (v) return v;
         return l1_regs_supported(h) ? 2 : 1;
@@ -497,6 +503,23 @@ void launch_bounds(const nnp_handle* h, const nnp_batch* b, int& A, int& B) {
         A = pow2_bound(std::max(A, 1), h->max_atoms);
         B = pow2_bound(std::max(B, 1), h->max_mols);
     }
+}
+
+// The handle's shape for a call of at most A atoms and B molecules.  Launches
+// cover the rows A atoms can fill, not the capacity's.  Central atoms per
+// featuriser / force workgroup, unless the knob fixes them: a workgroup's four
+// waves take them in turn, so calls of few atoms want 4 (1,178 atoms, both
+// kernels and the neighbour lists: 42 us at 4, 58 at 8, 88 at 16; 4,999: 62 /
+// 72 / 100; 7,966: 78 / 78 / 99), while large ones want each molecule staged
+// less often (23,990: 156 / 146 / 162; 47,999: 272 / 254 / 268; 49,152 of one
+// ligand: 268 / 225 / 219).
+Shape call_shape(const nnp_handle* h, int A, int B) {
+    Shape sh = h->shape;
+    sh.A = A;
+    sh.B = B;
+    sh.Rcap = std::min<int64_t>(sh.Rcap, pad_to(A + sh.S * (sh.row_tile - 1), sh.row_tile));
+    if (!h->knob[NNP_KNOB_ATOM_CHUNK]) sh.chunk = A < 8192 ? 4 : A < 48000 ? 8 : 16;
+    return sh;
 }
 
 // The three stages of an evaluation of molecules [moff[0], moff[B]):
@@ -558,11 +581,9 @@ nnp_status run_forward_split(nnp_handle* h, const nnp_batch* b, const typename P
     const bool acc = (b->flags & NNP_FLAG_ACCUMULATE) != 0;
     hipStream_t st = (hipStream_t)b->stream, st2 = h->st2;
     h->last_stream = st;
-    Shape s1 = h->shape, s2 = h->shape;
     const int B1 = b->n_mols / 2;
-    s1.A = s2.A = b->n_atoms;   // launch bound of each part
-    s1.B = B1;
-    s2.B = b->n_mols - B1;
+    // n_atoms is each part's launch bound
+    Shape s1 = call_shape(h, b->n_atoms, B1), s2 = call_shape(h, b->n_atoms, b->n_mols - B1);
     s1.sub = s2.sub = 1;
     const int32_t* m1 = b->mol_offsets;
     const int32_t* m2 = b->mol_offsets + B1;
@@ -594,8 +615,9 @@ nnp_status run_forward(nnp_handle* h, const nnp_batch* b, const typename P::T* x
     if (h->shape.pipeline == 2 && h->pipe_ready && !aev_out && b->n_mols >= 2 &&
         !(b->flags & NNP_FLAG_DEVICE_COUNTS))
         return run_forward_split<P>(h, b, x, E, F);
-    Shape sh = h->shape;
-    launch_bounds(h, b, sh.A, sh.B);
+    int A, B;
+    launch_bounds(h, b, A, B);
+    Shape sh = call_shape(h, A, B);
     sh.dev_counts = (b->flags & NNP_FLAG_DEVICE_COUNTS) ? 1 : 0;
     const bool acc = (b->flags & NNP_FLAG_ACCUMULATE) != 0;
     hipStream_t st = (hipStream_t)b->stream;
@@ -722,9 +744,7 @@ nnp_status run_backward(nnp_handle* h, const nnp_batch* bin, const typename P::T
     nnp_batch bb = *bin;   // the internal evaluations overwrite their outputs, eagerly
     bb.flags = 0;
     const nnp_batch* b = &bb;
-    Shape sh = h->shape;
-    sh.A = b->n_atoms;
-    sh.B = b->n_mols;
+    Shape sh = call_shape(h, b->n_atoms, b->n_mols);
     sh.force_fixed = 0;    // the force contraction below writes F directly
     hipStream_t st = (hipStream_t)b->stream;
     h->last_stream = st;
@@ -1021,6 +1041,7 @@ nnp_status nnp_create(const nnp_model_params* p, nnp_handle** out) {
     h->M = p->n_models;
     h->L = p->n_layers;
     h->widths = wi;
+    h->sw = sw;
     h->het = p->species_widths != nullptr;
     h->precision = p->precision;
     h->device = p->device;
@@ -1255,8 +1276,8 @@ nnp_status nnp_set_params(nnp_handle* h, const void* params, int32_t type, void*
         e = type == NNP_PREC_FP64 ? launch_set_params<PrecF64>(0, h->n_params, (const double*)params, map, pk, h->w64, st)
                                   : launch_set_params<PrecF64>(0, h->n_params, (const float*)params, map, pk, h->w64, st);
     else if (h->precision == NNP_PREC_FP32)
-        e = type == NNP_PREC_FP64 ? launch_set_params<PrecF32>(0, h->n_params, (const double*)params, map, pk, h->w32, st)
-                                  : launch_set_params<PrecF32>(0, h->n_params, (const float*)params, map, pk, h->w32, st);
+        e = type == NNP_PREC_FP64 ? launch_set_nets((const double*)params, pk, h->w32, st)
+                                  : launch_set_nets((const float*)params, pk, h->w32, st);
     else
         e = type == NNP_PREC_FP64 ? launch_set_params<PrecBF16>(0, h->n_params, (const double*)params, map, pk, h->w16, st)
                                   : launch_set_params<PrecBF16>(0, h->n_params, (const float*)params, map, pk, h->w16, st);

@@ -26,12 +26,19 @@ __device__ inline void split2(float a, float b, uint32_t& h, uint32_t& m, uint32
     const float sa = ra - __uint_as_float(m << 16), sb = rb - __uint_as_float(m & 0xffff0000u);
     l = pack_bf16x2(sa, sb);
 }
-// eight values as one 16-byte chunk per part
+// eight values as one 16-byte chunk (or fragment) per part
 __device__ inline void split8(const float v[8], uint4 o[kParts]) {
     split2(v[0], v[1], o[0].x, o[1].x, o[2].x);
     split2(v[2], v[3], o[0].y, o[1].y, o[2].y);
     split2(v[4], v[5], o[0].z, o[1].z, o[2].z);
     split2(v[6], v[7], o[0].w, o[1].w, o[2].w);
+}
+
+__device__ inline void split8(const float v[8], bf16x8 (&f)[kParts]) {
+    uint4 o[kParts];
+    split8(v, o);
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) f[p] = __builtin_bit_cast(bf16x8, o[p]);
 }
 
 // LDS tile of split operands for one 32-deep k-step: [part][rows][64 bytes],
@@ -51,8 +58,9 @@ __device__ inline void split_mma(f32x4 (&acc)[FN], const bf16x8 (&b)[FN][kParts]
         for (int j = 0; j < FN; ++j) acc[j] = MF<bf16_t>::mma(b[j][pb[q]], a[pa[q]], acc[j]);
 }
 
-// arguments of a split GEMM: g.B is unused, Bx is the pre-split weight operand
-// (fragment order, per element and model bx_s / bx_z bf16 elements apart)
+// arguments of a split GEMM: g.B is the FP32 weight operand in fragment order
+// (frag_index), Bx its parts (split_index; bx_s / bx_z bf16 elements apart per
+// element and model), null on handles with 16-row buckets
 struct SplitArgs {
     GemmArgs<PrecF32> g;
     const bf16_t* Bx;

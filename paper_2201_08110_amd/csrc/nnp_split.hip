@@ -11,12 +11,12 @@ namespace nnp {
 // The rows of a step are loaded as FP32 (32 bytes a thread), split in
 // registers and written to one of two LDS stages as three bf16 tiles; the
 // weight fragments go from L2 straight into registers, one step ahead.  Per
-// step and wave at FM = FN = 4: 96 MFMAs (1536 clocks), 12 LDS fragment reads
-// for the rows and 12 KiB of weight fragments; the split costs each thread
-// about 44 vector instructions, which the other wave of the SIMD hides.
+// step and wave at FM = 4, FN = 2: 48 MFMAs (768 clocks), 12 LDS fragment
+// reads for the rows and 6 KiB of weight fragments; the split costs each
+// thread about 44 vector instructions, which the other waves of the SIMD hide.
 // Bound by the matrix cores: 33,248 ragged atoms, 8 ANI-2x models, forward
-// 1146 -> 575 us and backward 1138 -> 642 us against the FP32 MFMA kernel
-// (k_gemm, both operands through LDS), 1.46 / 1.31 PFLOP/s of bf16 products.
+// 1146 -> 550 us and backward 1138 -> 600 us against the FP32 MFMA kernel
+// (k_gemm, both operands through LDS), about 1.5 / 1.4 PFLOP/s of bf16 products.
 template <int FM, int FN, int WN, int EPI>
 __global__ __launch_bounds__(64 * WN, 2) void k_gx(SplitArgs a) {
     constexpr int BM = 16 * FM, BN = 16 * FN * WN, NT = 64 * WN;
@@ -116,6 +116,131 @@ __global__ __launch_bounds__(64 * WN, 2) void k_gx(SplitArgs a) {
     }
     gemm_epilogue<PrecF32, EPI, BM, WN, FM, FN>(g, acc, lane, tile_m * BM, 0, tile_n * BN + wn * 16 * FN + 4 * (lane >> 4),
                                                 s, z, wn, tile_n, red);
+}
+
+// The same product where there are few tiles (or 16-row buckets): the eight
+// waves of a workgroup split K instead of the columns, so a 16 FM x 64 tile's
+// chain is an eighth as long and needs no barrier.  Both operands are FP32 in
+// memory (weights in fragment order, a third fewer bytes than their parts: few
+// rows are bound by reading the weights once), loaded straight into registers
+// and split there; within a step lane group g holds k = 4 g + 0..3 and
+// 16 + 4 g + 0..3 of both operands.  A wave takes U steps a round, all
+// requested before the first is used, each buffer again as soon as it is
+// split; steps past its share multiply zeros.  The waves' sums meet in LDS,
+// each wave finishing its share of the 16 x 16 pieces.
+template <int FM, int FN, int KW> struct KSplit {
+    static constexpr int TN = FM * FN;               // pieces of the tile
+    static constexpr int TW = (TN + KW - 1) / KW;    // pieces a wave finishes
+    static constexpr size_t part = (size_t)KW * TN * 64 * 16;
+    static constexpr size_t lds_bytes = part + sizeof(float) * 16 * FM * (FN / TW);
+};
+
+template <int FM, int FN, int KW, int U, int EPI>
+__global__ __launch_bounds__(64 * KW, 2) void k_gxk(SplitArgs a) {
+    typedef KSplit<FM, FN, KW> Ks;
+    constexpr int TN = Ks::TN, TW = Ks::TW, BM = 16 * FM, BN = 16 * FN;
+    extern __shared__ __align__(16) char smem[];
+    const GemmArgs<PrecF32>& g = a.g;
+    const int T = g.nm * g.nn * g.nz;
+    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
+    const int q8 = T >> 3, r8 = T & 7;
+    const int lin = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
+    const int per_z = g.nm * g.nn;
+    const int z = lin / per_z, rem = lin % per_z;
+    const int tile_n = rem / g.nm, tile_m = rem % g.nm;   // M-fastest: the weights are read once
+    if (tile_m * BM >= g.info->rows) return;
+    const int s = g.tile_species[(tile_m * BM) / g.row_tile];
+    if (s < 0) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nk = g.K / 32, rounds = (nk + KW * U - 1) / (KW * U), k0 = wave * rounds * U;
+
+    const float* Ap = g.A + (size_t)(tile_m * BM + (lane & 15)) * g.lda + (size_t)z * g.a_z + 4 * (lane >> 4);
+    const float* Bp = g.B + (size_t)s * g.b_s + (size_t)z * g.b_z + (size_t)tile_n * FN * nk * 512 + lane * 4;
+    float av[U][FM][8], bv[U][FN][8];
+    auto load = [&](int u, int step) {
+        const int st = min(step, nk - 1);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const float* p = Bp + (size_t)(j * nk + st) * 512;
+            *(float4*)&bv[u][j][0] = *(const float4*)p;
+            *(float4*)&bv[u][j][4] = *(const float4*)(p + 256);
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const float* p = Ap + (size_t)i * 16 * g.lda + st * 32;
+            *(float4*)&av[u][i][0] = *(const float4*)p;
+            *(float4*)&av[u][i][4] = *(const float4*)(p + 16);
+        }
+    };
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
+    auto round = [&](int kb, auto more) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            bf16x8 bq[FN][kParts], aq[FM][kParts];
+#pragma unroll
+            for (int j = 0; j < FN; ++j) split8(bv[u][j], bq[j]);
+            if (kb + u >= nk)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) av[u][i][e] = 0.f;
+#pragma unroll
+            for (int i = 0; i < FM; ++i) split8(av[u][i], aq[i]);
+            if constexpr (more.value) {
+                load(u, kb + u + U);
+                asm volatile("" ::: "memory");   // the loads stay ahead of the products
+            }
+#pragma unroll
+            for (int i = 0; i < FM; ++i) split_mma(acc[i], bq, aq[i]);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u, k0 + u);
+    for (int r = 0; r < rounds - 1; ++r) round(k0 + r * U, std::true_type{});
+    round(k0 + (rounds - 1) * U, std::false_type{});
+    f32x4* part = (f32x4*)smem;                        // [wave][piece][lane]
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) part[(size_t)(wave * TN + i * FN + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    // fewer pieces than waves: the others are done, or, where the epilogue has
+    // a barrier, finish a piece a second time (the same values)
+    if (EPI != EPI_L3F && wave * TW >= TN) return;
+    const int t0 = wave * TW % TN;
+    f32x4 sum[1][TW];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        sum[0][t] = part[(size_t)(t0 + t) * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < KW; ++w) sum[0][t] += part[(size_t)(w * TN + t0 + t) * 64 + lane];
+    }
+    gemm_epilogue<PrecF32, EPI, BM, FN / TW, 1, TW>(g, sum, lane, tile_m * BM, 16 * (t0 / FN),
+                                                    tile_n * BN + 16 * (t0 % FN) + 4 * (lane >> 4), s, z, t0 % FN / TW,
+                                                    tile_n, (float*)(smem + Ks::part));
+}
+
+template <int FM, int FN, int KW, int U, int EPI>
+static hipError_t run_gxk(SplitArgs a, int R, int N, hipStream_t st, const Timer& tm, const char* name) {
+    typedef KSplit<FM, FN, KW> Ks;
+    constexpr int BM = 16 * FM, BN = 16 * FN;
+    a.g.nm = R / BM;
+    a.g.nn = N / BN;
+    if (a.g.K % 32 != 0 || a.g.K < 32 || N % BN != 0 || R % BM != 0 || a.g.row_tile % BM != 0 || !a.g.B)
+        return hipErrorInvalidValue;
+    auto kern = k_gxk<FM, FN, KW, U, EPI>;
+    hipError_t e = ensure_lds((const void*)kern, Ks::lds_bytes);
+    if (e != hipSuccess) return e;
+    tm.b(name, st);
+    hipLaunchKernelGGL(kern, dim3(a.g.nm * a.g.nn * a.g.nz), dim3(64 * KW), Ks::lds_bytes, st, a);
+    tm.e(name, st);
+    return hipGetLastError();
 }
 
 template <int FM, int FN, int WN, int EPI>
@@ -417,11 +542,30 @@ hipError_t split_tail(const Shape& sh, const DevWeights<PrecF32>& wt, Work<PrecF
 template <int EPI>
 hipError_t split_gemm(SplitArgs a, int R, int N, int nz, hipStream_t st, const Timer& tm, const char* name) {
     a.g.nz = nz;
-    // layer 3's energy partials are counted per 64 columns
+    // 16-row buckets (at most 256 atoms): K split over four waves.  One 64-atom
+    // ligand, 8 models: 16.6 / 15.1 us forward / backward (k_gemm on FP32 MFMAs
+    // 17.1 / 18.4), 59 MB of weights each, near the rate a copy reaches; eight
+    // waves or 16-column tiles 17-21 us.  (Layer 3's energy partials are
+    // counted per 64 columns.)
+    if (a.g.row_tile == 16) {
+        if (EPI == EPI_L3F) return run_gxk<1, 4, 4, 1, EPI>(a, R, N, st, tm, name);
+        if (a.g.K >= 2048) return run_gxk<1, 4, 4, 2, EPI>(a, R, N, st, tm, name);
+        if (a.g.K >= 512) return run_gxk<1, 2, 4, 4, EPI>(a, R, N, st, tm, name);
+        return run_gxk<1, 2, 4, 2, EPI>(a, R, N, st, tm, name);
+    }
+    const int tiles = R / 64 * nz;
     if (EPI == EPI_L3F) return run_gx<4, 1, 4, EPI>(a, R, N, st, tm, name);
-    if (N % 256 == 0) return run_gx<4, 4, 4, EPI>(a, R, N, st, tm, name);
-    if (N % 192 == 0) return run_gx<4, 3, 4, EPI>(a, R, N, st, tm, name);
-    if (N % 128 == 0) return run_gx<4, 2, 4, EPI>(a, R, N, st, tm, name);
+    // long K and at most one workgroup per CU: K split over eight waves (the
+    // layer-1 backward of 569 atoms 34 us, 40 on the tile below, 55 on 128
+    // columns; at two rounds, 848 atoms, 58 against 51)
+    if (a.g.K >= 1024 && tiles * (N / 64) <= 256) return run_gxk<4, 4, 8, 2, EPI>(a, R, N, st, tm, name);
+    // 128 columns where they give about three workgroups per two CUs (3,445
+    // atoms, forward / backward: 93 / 97 us, 256 columns 93 / 106; 12,011:
+    // 235 / 267 against 252 / 292; 47,999: 817 / 891 against 880 / 900), 64
+    // where they don't (848 atoms: 38 / 51 us against 46 / 57; 2,403 atoms'
+    // backward 80 against 91)
+    if (N % 128 == 0 && tiles * (N / 128) >= 384) return run_gx<4, 2, 4, EPI>(a, R, N, st, tm, name);
+    if (N % 192 == 0 && tiles * (N / 192) >= 256) return run_gx<4, 3, 4, EPI>(a, R, N, st, tm, name);
     return run_gx<4, 1, 4, EPI>(a, R, N, st, tm, name);
 }
 #define NNP_SPLIT(EPI)                                                                                  \

@@ -1,7 +1,7 @@
-"""FP32 handles of more than 256 atoms run their networks on the bf16 matrix
-cores, every operand split into three bf16 parts.  Bucket sizes around the row
-tiles and hidden widths that take every column tiling, against the FP64 oracle
-with the FP32 bars of the parity tests."""
+"""FP32 handles run their networks on the bf16 matrix cores, every operand split
+into three bf16 parts: 64-row buckets above 256 atoms, 16-row buckets below.
+Bucket sizes around the row tiles and hidden widths that take every column
+tiling, against the FP64 oracle with the FP32 bars of the parity tests."""
 import numpy as np
 import pytest
 
@@ -22,6 +22,7 @@ def _batch(counts, seed=77):
     return b
 
 
+@pytest.mark.parametrize("cap", [300, 0])
 @pytest.mark.parametrize("counts,hidden,M,knobs", [
     ((1, 0, 15, 16, 17, 31, 32), (256, 192, 160), 8, {}),
     ((33, 63, 64, 65, 127, 128, 129), (256, 192, 160), 1, {}),
@@ -30,12 +31,12 @@ def _batch(counts, seed=77):
     ((40, 65, 17, 0, 3, 0, 2), (192, 128, 96), 2, {}),
     ((40, 65, 17, 0, 3, 0, 2), (64, 256, 128), 3, {}),
 ])
-def test_energies_forces_and_gradients(orc, hp, counts, hidden, M, knobs):
+def test_energies_forces_and_gradients(orc, hp, counts, hidden, M, knobs, cap):
     torch = torch_cuda()
     hp = dict(hp, widths=[hp["widths"][0], *hidden, 1])
     b = _batch(counts)
     w = synth.xavier_weights(M, hp["widths"], seed=5)
-    h = make_handle(hp, w, M, "fp32", b, max_atoms=max(300, b.n_atoms))
+    h = make_handle(hp, w, M, "fp32", b, max_atoms=max(cap, b.n_atoms))
     for k, v in knobs.items():
         h.set_knob(k, v)
     x, sp, off = to_device(torch, b, torch.float32)
