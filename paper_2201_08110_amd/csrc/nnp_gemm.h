@@ -94,7 +94,7 @@ template <typename P> struct GemmArgs {
     int K;
     const int32_t* tile_species; int row_tile;
     const BucketInfo* info;
-    int nm, nn, nz;                          // tiles along M, N and models
+    int nm, nn, nz;                          // tiles along M (launch bound), N and models
 };
 
 // Four output elements of one row held by one lane: columns c, c+ST, c+2ST,
@@ -130,6 +130,25 @@ template <> struct Quad<bf16_t, 1> {
         *(uint2*)p = q;
     }
 };
+
+// This workgroup's tile among the T in use (at most the grid), or -1.  Block
+// ids are dealt round-robin to the 8 XCDs; XCD x gets the contiguous range of
+// tiles it would own in order.
+__device__ inline int xcd_tile(int T) {
+    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
+    const int q8 = T >> 3, r8 = T & 7;
+    if (slot >= q8 + (xcd < r8 ? 1 : 0)) return -1;
+    return xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
+}
+// Row tiles the schedule deals out: those the buckets hold, known on the
+// device only, so that every XCD's range is as long (48 molecules in a
+// 128-molecule handle: layer 1 56 -> 33 us); for 16-row tiles the launch's
+// bound, which is at most 7 tiles more and spares small calls the wait for
+// that count before the index arithmetic (about 0.6 us a kernel).
+template <int BM> __device__ inline int row_tiles(const BucketInfo* info, int bound) {
+    if constexpr (BM == 16) return bound;
+    else return info->rows / BM;
+}
 
 // Row tiles are grouped kGroupM at a time: within a group the schedule runs
 // M-fastest, so the tiles an XCD has in flight share both a few row blocks

@@ -153,21 +153,17 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs<P> g) {
     TS* const stage0 = (TS*)smem_raw;                      // stage s: A rows then B rows
     TA* red = (TA*)(smem_raw + (size_t)S * (BM + BN) * 128);   // [BM][WN] (L3F only)
 
-    // ---- tile schedule.  Block ids are dealt round-robin to the 8 XCDs;
-    // XCD x gets the contiguous logical range it would own in order, and
-    // that range is walked group by group (kGroupM row tiles, M-fastest).
-    const int T = g.nm * g.nn * g.nz;
-    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-    const int q8 = T >> 3, r8 = T & 7;
-    const int lin = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
-    const int per_z = g.nm * g.nn;
+    // ---- tile schedule: this XCD's range (xcd_tile) is walked group by group
+    // (kGroupM row tiles, M-fastest)
+    const int nm = row_tiles<BM>(g.info, g.nm), per_z = nm * g.nn;
+    const int lin = xcd_tile(per_z * g.nz);
+    if (lin < 0) return;
     const int z = lin / per_z, rem = lin % per_z;
     const int grp = rem / (kGroupM * g.nn), inside = rem % (kGroupM * g.nn);
-    const int gsz = min(kGroupM, g.nm - grp * kGroupM);
+    const int gsz = min(kGroupM, nm - grp * kGroupM);
     const int tile_n = inside / gsz, tile_m = grp * kGroupM + inside % gsz;
 
-    const int rows = g.info->rows;
-    if (tile_m * BM >= rows) return;
+    if (tile_m * BM >= g.info->rows) return;
     const int s = g.tile_species[(tile_m * BM) / g.row_tile];
     if (s < 0) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -330,36 +326,32 @@ static hipError_t run_gemm(GemmArgs<P> a, int Rcap, int N, int nz, hipStream_t s
 // the end the last slice and the last fragments are loaded again (L2 hits).
 // The LDS fragment reads of the next k-step are interleaved with the MFMAs
 // of the current one.
-constexpr int kRbBM = 128, kRbBN = 256, kRbWN = 4;
 constexpr int kRbRows = 128;   // bucket row tile the register-weight path runs on
 
-template <int S, int EPI>
-__global__ __launch_bounds__(256, 2) void k_l1rb(GemmArgs<PrecBF16> g) {
+template <int S, int BM, int WN, int EPI>
+__global__ __launch_bounds__(64 * WN, BM == 128 ? 2 : 3) void k_l1rb(GemmArgs<PrecBF16> g) {
     typedef bf16_t TS;
     typedef float TA;
     typedef MF<TS> mf;
     typedef typename mf::Acc Acc;
     typedef typename mf::Frag Frag;
     typedef Slice<TS> L;
-    constexpr int BM = kRbBM, BN = kRbBN, BK = L::BK;   // BK = 64 (two 32-deep k-steps)
-    constexpr int WTN = BN / kRbWN, FM = BM / 16, FN = WTN / 16;
-    constexpr int NQ = BM / 8 / kRbWN;                   // direct row loads per wave per slice
+    constexpr int WTN = 64, BN = WTN * WN, BK = L::BK;   // BK = 64 (two 32-deep k-steps)
+    constexpr int FM = BM / 16, FN = WTN / 16;
+    constexpr int NQ = BM / 8 / WN;                      // direct row loads per wave per slice
     static_assert(BK == 2 * mf::KM && NQ >= 1 && FN == 4, "tile");
     static_assert(S == 2 || S == 3, "stages");
     extern __shared__ __align__(16) char smem_raw[];
     TS* const stage0 = (TS*)smem_raw;                    // S stages of BM rows
 
     // tile schedule as in k_gemm (XCD-contiguous ranges, kGroupM row tiles)
-    const int T = g.nm * g.nn;
-    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-    const int q8 = T >> 3, r8 = T & 7;
-    const int lin = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
+    const int nm = g.info->rows / BM;
+    const int lin = xcd_tile(nm * g.nn);
+    if (lin < 0) return;
     const int grp = lin / (kGroupM * g.nn), inside = lin % (kGroupM * g.nn);
-    const int gsz = min(kGroupM, g.nm - grp * kGroupM);
+    const int gsz = min(kGroupM, nm - grp * kGroupM);
     const int tile_n = inside / gsz, tile_m = grp * kGroupM + inside % gsz;
 
-    const int rows = g.info->rows;
-    if (tile_m * BM >= rows) return;
     const int s = g.tile_species[(tile_m * BM) / g.row_tile];
     if (s < 0) return;
     const int lane = threadIdx.x & 63, wn = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -376,7 +368,7 @@ __global__ __launch_bounds__(256, 2) void k_l1rb(GemmArgs<PrecBF16> g) {
         const int k0 = src * BK + ld_chunk * L::VE;
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
-            const int q = wn + kRbWN * u;
+            const int q = wn + WN * u;
             __builtin_amdgcn_global_load_lds(NNP_GPTR(A + (size_t)(q * 8 + ld_row) * g.lda + k0),
                                              NNP_LPTR(d + q * 8 * BK), 16, 0, 0);
         }
@@ -523,24 +515,36 @@ __global__ __launch_bounds__(256, 2) void k_l1rb(GemmArgs<PrecBF16> g) {
 }
 
 static bool l1rb_fits(int Rcap, int N, int K) {
-    return Rcap % kRbBM == 0 && N % kRbBN == 0 && K % Slice<bf16_t>::BK == 0 && K > 0;
+    return Rcap % kRbRows == 0 && N % 256 == 0 && K % Slice<bf16_t>::BK == 0 && K > 0;
 }
 
-template <int EPI>
-static hipError_t run_l1rb(GemmArgs<PrecBF16> a, int Rcap, int N, int stages, hipStream_t st,
-                           const Timer& tm, const char* name) {
-    if (!l1rb_fits(Rcap, N, a.K) || a.B == nullptr || (stages != 2 && stages != 3)) return hipErrorInvalidValue;
-    a.nm = Rcap / kRbBM;
-    a.nn = N / kRbBN;
+template <int S, int BM, int WN, int EPI>
+static hipError_t launch_l1rb(GemmArgs<PrecBF16> a, int Rcap, int N, hipStream_t st, const Timer& tm,
+                              const char* name) {
+    a.nn = N / (64 * WN);
     a.nz = 1;
-    const size_t lds = (size_t)stages * kRbBM * 128;
-    auto kern = stages == 2 ? k_l1rb<2, EPI> : k_l1rb<3, EPI>;
+    const size_t lds = (size_t)S * BM * 128;
+    auto kern = k_l1rb<S, BM, WN, EPI>;
     hipError_t e = ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     tm.b(name, st);
-    hipLaunchKernelGGL(kern, dim3(a.nm * a.nn), dim3(64 * kRbWN), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(Rcap / BM * a.nn), dim3(64 * WN), lds, st, a);
     tm.e(name, st);
     return hipGetLastError();
+}
+
+template <int EPI>
+static hipError_t run_l1rb(const GemmArgs<PrecBF16>& a, int Rcap, int N, int stages, hipStream_t st,
+                           const Timer& tm, const char* name) {
+    if (!l1rb_fits(Rcap, N, a.K) || a.B == nullptr || (stages != 2 && stages != 3)) return hipErrorInvalidValue;
+    // half the rows a tile while 128 x 256 tiles give less than three quarters
+    // of the CUs one each (forward / backward of 569 atoms 17 / 22 us against
+    // 21 / 29, of 2,403 24 / 25 against 24 / 32; at 4,999 the same, at 47,999
+    // 215 / 217 against 176 / 168: each weight fragment then feeds half as
+    // many MFMAs).  The sums are the same bit for bit.
+    if (stages == 3) return launch_l1rb<3, 128, 4, EPI>(a, Rcap, N, st, tm, name);
+    if (Rcap / 128 * (N / 256) <= 192) return launch_l1rb<2, 64, 4, EPI>(a, Rcap, N, st, tm, name);
+    return launch_l1rb<2, 128, 4, EPI>(a, Rcap, N, st, tm, name);
 }
 
 // tile shapes per row tile: BM = row tile; wide N tiles for the layer-1
@@ -692,7 +696,7 @@ template <typename P> struct TailArgs {
     int M;
     const int32_t* tile_species; int row_tile;
     const BucketInfo* info;
-    int nm;                                   // row tiles
+    int nm;                                   // row tiles (launch bound)
 };
 
 // LDS of the fused tail: H2 / DZ2 [BM][H2] at 0, DZ3 [BM][H3] after it, then
@@ -736,12 +740,9 @@ __global__ __launch_bounds__(256 * TW, 2 * TW) void k_tail(TailArgs<P> g) {
 
     // XCD-contiguous ranges over (model, row tile): an XCD works through
     // consecutive tiles of one model and keeps that model's weights in L2
-    const int T = g.nm * g.M;
-    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-    const int q8 = T >> 3, r8 = T & 7;
-    const int lin = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
-    const int z = lin / g.nm, tile_m = lin % g.nm;
-    const int row0 = tile_m * BM;
+    const int nm = row_tiles<BM>(g.info, g.nm), lin = xcd_tile(nm * g.M);
+    if (lin < 0) return;
+    const int z = lin / nm, row0 = lin % nm * BM;
     if (row0 >= g.info->rows) return;
     const int s = g.tile_species[row0 / g.row_tile];
     if (s < 0) return;

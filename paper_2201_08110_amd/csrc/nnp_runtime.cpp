@@ -238,75 +238,75 @@ ParamPack param_pack(const nnp_handle* h) {
     return pk;
 }
 
+// the device layouts of the weights, zeroed: padding entries are never written
+template <typename P> nnp_status alloc_weights(nnp_handle* h, DevWeights<P>& dw) {
+    const Shape& sh = h->shape;
+    const size_t S = h->S, M = h->M, Dp = sh.Dp, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3;
+    const size_t n1 = S * M * H1, n2 = S * M * H2, n3 = S * M * H3;
+    const bool rowmajor = !std::is_same<P, PrecF32>::value;
+    hipError_t e = hipSuccess;
+    const auto zeros = [&](auto*& dst, size_t n) {
+        if (e != hipSuccess) return;
+        const size_t bytes = n * sizeof(*dst);
+        dst = (std::remove_reference_t<decltype(dst)>)h->dalloc(bytes, e);
+        if (e == hipSuccess) e = hipMemset(dst, 0, bytes);
+    };
+    if (rowmajor) zeros(dw.W1, n1 * Dp), zeros(dw.W1T, n1 * Dp);
+    zeros(dw.b1, n1);
+    if (rowmajor) zeros(dw.W2, n2 * H1), zeros(dw.W2T, n2 * H1);
+    zeros(dw.b2, n2);
+    if (rowmajor) zeros(dw.W3, n3 * H2), zeros(dw.W3T, n3 * H2);
+    zeros(dw.b3, n3);
+    zeros(dw.w4, n3);
+    zeros(dw.b4, S * M);
+    zeros(dw.sae, S);
+    // fragment order: the per-model matrices, one [N][K] matrix per element and
+    // model; the layer-1 weights for the GEMMs that load them straight into
+    // registers (BF16, FP32), one [M*H1][Dp] matrix and its transpose per element
+    zeros(dw.W2f, n2 * H1), zeros(dw.W3f, n3 * H2), zeros(dw.W3Tf, n3 * H2), zeros(dw.W2Tf, n2 * H1);
+    if (!std::is_same<P, PrecF64>::value) zeros(dw.W1f, n1 * Dp), zeros(dw.W1Tf, n1 * Dp);
+    if (sh.split) {   // three bf16 parts an element
+        zeros(dw.W1x, 3 * n1 * Dp), zeros(dw.W1Tx, 3 * n1 * Dp);
+        zeros(dw.W2x, 3 * n2 * H1), zeros(dw.W2Tx, 3 * n2 * H1);
+        zeros(dw.W3x, 3 * n3 * H2), zeros(dw.W3Tx, 3 * n3 * H2);
+    }
+    std::vector<double> sae(S, 0.0);   // summed in FP64: self-energies dwarf the network part
+    for (size_t s = 0; s < S; ++s) sae[s] = h->energy_scale * (h->sae.empty() ? 0.0 : h->sae[s]);
+    if (e == hipSuccess) e = hipMemcpy(dw.sae, sae.data(), S * sizeof(double), hipMemcpyHostToDevice);
+    if (e != hipSuccess)
+        return fail(e == hipErrorOutOfMemory ? NNP_E_NOMEM : NNP_E_DEVICE, std::string("weight allocation: ") + hipGetErrorString(e));
+    return NNP_OK;
+}
+
 // FP64 master weights [m][s][layer]{W, b} into the device layouts: the packed
 // array goes to the device in pieces and the kernel of nnp_set_params scatters
 // and rounds it there (8-model ANI-2x ensemble, 19 M parameters: nnp_create
 // 122 -> 7 ms in FP32, 187 -> 7 ms in FP64, against packing the layouts on the
-// host).  Padding entries are zeroed at allocation and never written.
-template <typename P> nnp_status upload_weights(nnp_handle* h, DevWeights<P>& dw,
-                                                const double* w, bool allocate) {
-    const Shape& sh = h->shape;
-    const size_t S = h->S, M = h->M, Dp = sh.Dp, H1 = sh.H1, H2 = sh.H2, H3 = sh.H3;
-    hipError_t e = hipSuccess;
-    const auto failed = [&]() {
-        return fail(e == hipErrorOutOfMemory ? NNP_E_NOMEM : NNP_E_DEVICE,
-                    std::string("weight upload: ") + hipGetErrorString(e));
-    };
-    if (allocate) {
-        const auto zeros = [&](auto*& dst, size_t n) {
-            if (e != hipSuccess) return;
-            const size_t bytes = n * sizeof(*dst);
-            dst = (std::remove_reference_t<decltype(dst)>)h->dalloc(bytes, e);
-            if (e == hipSuccess) e = hipMemset(dst, 0, bytes);
-        };
-        if (sh.split) {   // three bf16 parts an element
-            zeros(dw.W1x, 3 * S * M * H1 * Dp);
-            zeros(dw.W1Tx, 3 * S * M * H1 * Dp);
-            zeros(dw.W2x, 3 * S * M * H2 * H1);
-            zeros(dw.W2Tx, 3 * S * M * H2 * H1);
-            zeros(dw.W3x, 3 * S * M * H3 * H2);
-            zeros(dw.W3Tx, 3 * S * M * H3 * H2);
-        }
-        if (!std::is_same<P, PrecF32>::value) {   // row-major
-            zeros(dw.W1, S * M * H1 * Dp);
-            zeros(dw.W1T, S * M * H1 * Dp);
-            zeros(dw.W2, S * M * H2 * H1);
-            zeros(dw.W2T, S * M * H2 * H1);
-            zeros(dw.W3, S * M * H3 * H2);
-            zeros(dw.W3T, S * M * H3 * H2);
-        }
-        zeros(dw.b1, S * M * H1);
-        zeros(dw.b2, S * M * H2);
-        zeros(dw.b3, S * M * H3);
-        zeros(dw.w4, S * M * H3);
-        zeros(dw.b4, S * M);
-        zeros(dw.sae, S);
-        // fragment-order copies of the per-model matrices (the fused kernel's
-        // weight operands), one [N][K] matrix per element and model
-        zeros(dw.W2f, S * M * H2 * H1);
-        zeros(dw.W3f, S * M * H3 * H2);
-        zeros(dw.W3Tf, S * M * H3 * H2);
-        zeros(dw.W2Tf, S * M * H2 * H1);
-        // the layer-1 weights in fragment order for the GEMMs that load them
-        // straight into registers (BF16, FP32): one [M*H1][Dp] matrix and its
-        // transpose per element
-        if (!std::is_same<P, PrecF64>::value) {
-            zeros(dw.W1f, S * M * H1 * Dp);
-            zeros(dw.W1Tf, S * M * H1 * Dp);
-        }
-        if (e != hipSuccess) return failed();
-        std::vector<double> sae(S, 0.0);   // summed in FP64: self-energies dwarf the network part
-        for (size_t s = 0; s < S; ++s) sae[s] = h->energy_scale * (h->sae.empty() ? 0.0 : h->sae[s]);
-        if ((e = hipMemcpy(dw.sae, sae.data(), S * sizeof(double), hipMemcpyHostToDevice))) return failed();
-    }
+// host).
+template <typename P> nnp_status upload_weights(nnp_handle* h, DevWeights<P>& dw, const double* w) {
     const int32_t* map = h->het ? h->dmap : nullptr;
+    hipError_t e = hipSuccess;
     for (int64_t at = 0; at < h->n_params && e == hipSuccess; at += kStageParams) {
         const int64_t n = std::min<int64_t>(kStageParams, h->n_params - at);
         e = hipMemcpy(h->stage, w + at, sizeof(double) * (size_t)n, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = launch_set_params<P>(at, n, (const double*)h->stage, map, param_pack(h), dw, (hipStream_t)0);
     }
     if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)0);
-    return e == hipSuccess ? NNP_OK : failed();
+    if (e != hipSuccess) return fail(NNP_E_DEVICE, std::string("weight upload: ") + hipGetErrorString(e));
+    return NNP_OK;
+}
+
+template <typename P> nnp_status alloc_work(nnp_handle* h, Work<P>& w);
+
+template <typename P>
+nnp_status make_device_state(nnp_handle* h, DevWeights<P>& dw, Work<P>& w, const double* weights) {
+    nnp_status rc = alloc_weights<P>(h, dw);
+    if (rc == NNP_OK) rc = alloc_work<P>(h, w);
+    if (rc) return rc;
+    hipError_t e = hipSuccess;
+    h->stage = (double*)h->dalloc(sizeof(double) * (size_t)std::min(kStageParams, h->n_params), e);
+    if (e != hipSuccess) return fail(NNP_E_NOMEM, "parameter staging allocation failed");
+    return upload_weights<P>(h, dw, weights);
 }
 
 // Row buffers of the pipeline's second part (sized for the whole capacity:
@@ -510,7 +510,7 @@ void launch_bounds(const nnp_handle* h, const nnp_batch* b, int& A, int& B) {
 // featuriser / force workgroup, unless the knob fixes them: a workgroup's four
 // waves take them in turn, so calls of few atoms want 4 (1,178 atoms, both
 // kernels and the neighbour lists: 42 us at 4, 58 at 8, 88 at 16; 4,999: 62 /
-// 72 / 100; 7,966: 78 / 78 / 99), while large ones want each molecule staged
+// 72 / 100; 12,011: 96 / 101 / 121), while large ones want each molecule staged
 // less often (23,990: 156 / 146 / 162; 47,999: 272 / 254 / 268; 49,152 of one
 // ligand: 268 / 225 / 219).
 Shape call_shape(const nnp_handle* h, int A, int B) {
@@ -518,7 +518,7 @@ Shape call_shape(const nnp_handle* h, int A, int B) {
     sh.A = A;
     sh.B = B;
     sh.Rcap = std::min<int64_t>(sh.Rcap, pad_to(A + sh.S * (sh.row_tile - 1), sh.row_tile));
-    if (!h->knob[NNP_KNOB_ATOM_CHUNK]) sh.chunk = A < 8192 ? 4 : A < 48000 ? 8 : 16;
+    if (!h->knob[NNP_KNOB_ATOM_CHUNK]) sh.chunk = A < 16384 ? 4 : A < 48000 ? 8 : 16;
     return sh;
 }
 
@@ -1136,10 +1136,6 @@ nnp_status nnp_create(const nnp_model_params* p, nnp_handle** out) {
         else if (hipMemcpy(h->zlut, lut.data(), kZLut, hipMemcpyHostToDevice) != hipSuccess)
             rc = fail(NNP_E_DEVICE, "element table upload failed");
     }
-    if (rc == NNP_OK) {
-        h->stage = (double*)h->dalloc(sizeof(double) * (size_t)std::min(kStageParams, h->n_params), e);
-        if (e != hipSuccess) rc = fail(NNP_E_NOMEM, "parameter staging allocation failed");
-    }
     if (rc == NNP_OK && h->het) {
         h->dmap = (int32_t*)h->dalloc(sizeof(int32_t) * pmap.size(), e);
         if (e != hipSuccess)
@@ -1148,16 +1144,9 @@ nnp_status nnp_create(const nnp_model_params* p, nnp_handle** out) {
             rc = fail(NNP_E_DEVICE, "parameter map upload failed");
     }
     if (rc == NNP_OK) {
-        if (p->precision == NNP_PREC_FP64) {
-            rc = upload_weights<PrecF64>(h, h->w64, p->weights, true);
-            if (rc == NNP_OK) rc = alloc_work<PrecF64>(h, h->k64);
-        } else if (p->precision == NNP_PREC_FP32) {
-            rc = upload_weights<PrecF32>(h, h->w32, p->weights, true);
-            if (rc == NNP_OK) rc = alloc_work<PrecF32>(h, h->k32);
-        } else {
-            rc = upload_weights<PrecBF16>(h, h->w16, p->weights, true);
-            if (rc == NNP_OK) rc = alloc_work<PrecBF16>(h, h->k16);
-        }
+        rc = p->precision == NNP_PREC_FP64   ? make_device_state<PrecF64>(h, h->w64, h->k64, p->weights)
+             : p->precision == NNP_PREC_FP32 ? make_device_state<PrecF32>(h, h->w32, h->k32, p->weights)
+                                             : make_device_state<PrecBF16>(h, h->w16, h->k16, p->weights);
     }
     if (rc == NNP_OK) rc = ensure_pipeline(h);
     if (rc == NNP_OK && (p->create_flags & NNP_CREATE_TRAINING))
@@ -1257,9 +1246,9 @@ nnp_status nnp_set_weights(nnp_handle* h, const double* weights) {
     DeviceGuard dg(h->device);
     if (!dg.ok) return fail(NNP_E_DEVICE, "hipSetDevice failed");
     HIP_TRY(hipDeviceSynchronize());
-    if (h->precision == NNP_PREC_FP64) return upload_weights<PrecF64>(h, h->w64, weights, false);
-    if (h->precision == NNP_PREC_FP32) return upload_weights<PrecF32>(h, h->w32, weights, false);
-    return upload_weights<PrecBF16>(h, h->w16, weights, false);
+    if (h->precision == NNP_PREC_FP64) return upload_weights<PrecF64>(h, h->w64, weights);
+    if (h->precision == NNP_PREC_FP32) return upload_weights<PrecF32>(h, h->w32, weights);
+    return upload_weights<PrecBF16>(h, h->w16, weights);
 }
 
 nnp_status nnp_set_params(nnp_handle* h, const void* params, int32_t type, void* stream) {

@@ -27,18 +27,14 @@ __global__ __launch_bounds__(64 * WN, 2) void k_gx(SplitArgs a) {
     const GemmArgs<PrecF32>& g = a.g;
 
     // tile schedule as in k_gemm (XCD-contiguous ranges, kGroupM row tiles)
-    const int T = g.nm * g.nn * g.nz;
-    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-    const int q8 = T >> 3, r8 = T & 7;
-    const int lin = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
-    const int per_z = g.nm * g.nn;
+    const int nm = g.info->rows / BM, per_z = nm * g.nn;
+    const int lin = xcd_tile(per_z * g.nz);
+    if (lin < 0) return;
     const int z = lin / per_z, rem = lin % per_z;
     const int grp = rem / (kGroupM * g.nn), inside = rem % (kGroupM * g.nn);
-    const int gsz = min(kGroupM, g.nm - grp * kGroupM);
+    const int gsz = min(kGroupM, nm - grp * kGroupM);
     const int tile_n = inside / gsz, tile_m = grp * kGroupM + inside % gsz;
 
-    const int rows = g.info->rows;
-    if (tile_m * BM >= rows) return;
     const int s = g.tile_species[(tile_m * BM) / g.row_tile];
     if (s < 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wn = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -141,13 +137,11 @@ __global__ __launch_bounds__(64 * KW, 2) void k_gxk(SplitArgs a) {
     constexpr int TN = Ks::TN, TW = Ks::TW, BM = 16 * FM, BN = 16 * FN;
     extern __shared__ __align__(16) char smem[];
     const GemmArgs<PrecF32>& g = a.g;
-    const int T = g.nm * g.nn * g.nz;
-    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-    const int q8 = T >> 3, r8 = T & 7;
-    const int lin = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
-    const int per_z = g.nm * g.nn;
+    const int nm = row_tiles<BM>(g.info, g.nm), per_z = nm * g.nn;
+    const int lin = xcd_tile(per_z * g.nz);
+    if (lin < 0) return;
     const int z = lin / per_z, rem = lin % per_z;
-    const int tile_n = rem / g.nm, tile_m = rem % g.nm;   // M-fastest: the weights are read once
+    const int tile_n = rem / nm, tile_m = rem % nm;   // M-fastest: the weights are read once
     if (tile_m * BM >= g.info->rows) return;
     const int s = g.tile_species[(tile_m * BM) / g.row_tile];
     if (s < 0) return;
@@ -246,12 +240,11 @@ static hipError_t run_gxk(SplitArgs a, int R, int N, hipStream_t st, const Timer
 template <int FM, int FN, int WN, int EPI>
 static hipError_t run_gx(SplitArgs a, int R, int N, hipStream_t st, const Timer& tm, const char* name) {
     constexpr int BM = 16 * FM, BN = 16 * FN * WN;
-    a.g.nm = R / BM;
     a.g.nn = N / BN;
     if (a.g.K % 64 != 0 || a.g.K < 64 || N % BN != 0 || R % BM != 0 || a.g.row_tile % BM != 0 || !a.Bx)
         return hipErrorInvalidValue;
     tm.b(name, st);
-    hipLaunchKernelGGL((k_gx<FM, FN, WN, EPI>), dim3(a.g.nm * a.g.nn * a.g.nz), dim3(64 * WN), 0, st, a);
+    hipLaunchKernelGGL((k_gx<FM, FN, WN, EPI>), dim3(R / BM * a.g.nn * a.g.nz), dim3(64 * WN), 0, st, a);
     tm.e(name, st);
     return hipGetLastError();
 }
@@ -288,7 +281,6 @@ struct SplitTailArgs {
     const int32_t* tile_species;
     int row_tile;
     const BucketInfo* info;
-    int nm;                                     // row tiles
 };
 
 // acc = A rows [0, 16 FM) (LDS step tiles of BM rows) x B^T over K, B
@@ -367,12 +359,9 @@ __global__ __launch_bounds__(256, 2) void k_tailx(SplitTailArgs g) {
     float *sb3 = sb2 + H2, *sw4 = sb3 + H3, *red = sw4 + H3;   // red [BM][4]
 
     // XCD-contiguous ranges over (model, row tile), as in k_tail
-    const int T = g.nm * g.M;
-    const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-    const int q8 = T >> 3, r8 = T & 7;
-    const int lin = xcd * q8 + (xcd < r8 ? xcd : r8) + slot;
-    const int z = lin / g.nm, row0 = lin % g.nm * BM;
-    if (row0 >= g.info->rows) return;
+    const int nm = g.info->rows / BM, lin = xcd_tile(nm * g.M);
+    if (lin < 0) return;
+    const int z = lin / nm, row0 = lin % nm * BM;
     const int s = g.tile_species[row0 / g.row_tile];
     if (s < 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -511,13 +500,12 @@ static hipError_t run_tailx(const Shape& sh, const SplitTailArgs& a0, hipStream_
     constexpr size_t lds = SplitTail<H1, H2, H3, BM>::lds_bytes;
     static_assert(lds <= 160 * 1024, "LDS of the split tail");
     SplitTailArgs a = a0;
-    a.nm = sh.Rcap / BM;
     if (sh.Rcap % BM || sh.row_tile % BM) return hipErrorInvalidValue;
     auto kern = k_tailx<BM, H1, H2, H3>;
     hipError_t e = ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     tm.b("mlp_tail", st);
-    hipLaunchKernelGGL(kern, dim3(a.nm * sh.M), dim3(256), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(sh.Rcap / BM * sh.M), dim3(256), lds, st, a);
     tm.e("mlp_tail", st);
     return hipGetLastError();
 }
