@@ -429,13 +429,11 @@ nnp_status nnp_coupling_eval(nnp_coupling* c, int32_t n_nnp, const void* x_nnp, 
  * cutoff; runs on the current HIP device.
  *
  * Its partial sums live in a static device array of 8 MiB that the library
- * holds on every GPU it runs on until the process ends: ceil(n_mm / 64)
- * doubles plus 3 n_nnp ceil(n_mm / chunk) values of the operand type, where
- * chunk is the handle's MM-atoms-per-wave rule widened (up to 512) until they
- * fit.  The 64-atom ligand in 47,648 MM atoms needs 2.3 MB (FP32) or 4.6 MB
- * (FP64).  Larger systems, or n_nnp > 1024 or n_mm > 2^22, return
- * NNP_E_CAPACITY before anything is launched.  The first call on a device
- * looks up that device's copy of the array (no allocation).
+ * holds on every GPU it runs on until the process ends.  Systems above the
+ * size where ceil(n_mm / 64) doubles (rounded up to 256 bytes) plus 3 n_nnp
+ * ceil(n_mm / 512) values of the operand type fit it, or n_nnp > 1024 or
+ * n_mm > 2^22, return NNP_E_CAPACITY before anything is launched.  The first
+ * call on a device looks up that device's copy of the array (no allocation).
  *
  * Every call on one GPU shares that array: calls that overlap in time on one
  * GPU (two streams, two host threads) race and give wrong results; serialise

@@ -7,15 +7,19 @@
 // eps_ij = sqrt(eps_i eps_j) and an optional plain cutoff.  Forces act on both
 // sides.  Both force sums are formed without atomics and in a fixed order:
 //
-//   MM side       four lanes per MM atom, the NNP atoms staged in LDS:
-//                 F_j and a per-block energy partial;
-//   NNP side      one thread per NNP atom for one chunk of MM atoms staged
-//                 in LDS: per-chunk partial F_i;
-//                 (both sides run as the two halves of one launch)
-//   k_couple_sum  fixed-shape sums of the partials into F_i and E.
+// k_couple_pairs evaluates every pair once.  A wave takes 16 MM atoms at a
+// time against 64 NNP atoms (staged in LDS): row r of 16 lanes holds the same
+// 16 MM atoms and NNP atoms 16 r .. 16 r + 15, lane c meeting atom (c + t) mod
+// 16 in step t.  The MM force stays in its lane; the NNP force sums move one
+// lane along the row a step (a DPP rotation), so after 16 steps each is back in
+// its atom's lane.  Each workgroup writes partial F_i and E; k_couple_sum adds
+// them in a fixed order.
 //
-// Each pair is therefore evaluated twice (once per side), which costs
-// ~30 flops per pair and saves every cross-thread reduction of the scatter.
+// 64 x 47,648 pairs, FP32: evaluating each pair once per side took 12.1 + 5.4 us,
+// this 8.6 + 2.5.  Bound by vector ALU issue (about 45 instructions a pair) and
+// the latency of one trip through memory.  Summing in the same launch (the last
+// workgroup of 16 sums theirs, the last of those the rest) took 18.2: each of
+// the two hand-overs waits for memory three times.
 #include <hip/hip_runtime.h>
 
 #include "nnp_internal.h"
@@ -24,7 +28,7 @@ namespace nnp {
 
 // per-atom operands staged in LDS: x, y, z, q, sigma/2, sqrt(eps)
 constexpr int kCoupleVals = 6;
-constexpr int kMmBlock = 256;
+constexpr int kCoupleThreads = 1024, kCoupleWaves = kCoupleThreads / 64;
 
 template <typename T> __device__ inline T c_rsqrt(T x);
 template <> __device__ inline float c_rsqrt<float>(float x) { return __builtin_amdgcn_rsqf(x); }
@@ -53,174 +57,149 @@ __device__ inline void load_atom(const T* __restrict__ x, const T* __restrict__ 
     out[5] = sqrt(par[3 * (size_t)i + 2]);
 }
 
-// MM side: four lanes per MM atom j, each over every fourth NNP atom (staged
-// in LDS, s = [6][n_nnp]), combined by a fixed two-step shuffle tree; F_j and
-// the block's energy partial.
-constexpr int kMmLanes = 4;
-constexpr int kMmPerBlock = kMmBlock / kMmLanes;   // MM atoms per workgroup
-static_assert(kMmPerBlock == kCoupleMmPerBlock, "energy partials sized by the handle");
-
-template <typename T>
-__device__ inline void couple_mm_side(int blk, int n_nnp, const T* __restrict__ x_nnp,
-                                      const T* __restrict__ par_nnp, int n_mm, const T* __restrict__ x_mm,
-                                      const T* __restrict__ par_mm, T k, T rc2, T* __restrict__ F_mm,
-                                      int accumulate, double* __restrict__ e_part, T* s, double* red) {
-    for (int i = threadIdx.x; i < n_nnp; i += blockDim.x) {
-        T a[kCoupleVals];
-        load_atom(x_nnp, par_nnp, i, a);
-#pragma unroll
-        for (int v = 0; v < kCoupleVals; ++v) s[v * n_nnp + i] = a[v];
-    }
-    __syncthreads();
-    const int j = blk * kMmPerBlock + (int)(threadIdx.x / kMmLanes), sub = threadIdx.x % kMmLanes;
-    const bool act = j < n_mm;
-    T f0 = 0, f1 = 0, f2 = 0;
-    double e = 0.0;
-    if (act) {
-        T b[kCoupleVals];
-        load_atom(x_mm, par_mm, j, b);
-        for (int i = sub; i < n_nnp; i += kMmLanes) {
-            const T d0 = b[0] - s[i], d1 = b[1] - s[n_nnp + i], d2 = b[2] - s[2 * n_nnp + i];
-            const T r2 = d0 * d0 + d1 * d1 + d2 * d2;
-            if (rc2 > T(0) && r2 >= rc2) continue;
-            T v, dvr;
-            couple_pair(k, r2, s[3 * n_nnp + i] * b[3], s[4 * n_nnp + i] + b[4], s[5 * n_nnp + i] * b[5], v,
-                        dvr);
-            e += (double)v;
-            f0 -= dvr * d0;
-            f1 -= dvr * d1;
-            f2 -= dvr * d2;
-        }
-    }
-    // the four lanes of one MM atom are adjacent
-#pragma unroll
-    for (int o = 1; o < kMmLanes; o <<= 1) {
-        f0 += __shfl_xor(f0, o);
-        f1 += __shfl_xor(f1, o);
-        f2 += __shfl_xor(f2, o);
-        e += __shfl_xor(e, o);
-    }
-    if (act && sub == 0) {
-        T* F = F_mm + 3 * (size_t)j;
-        F[0] = (accumulate ? F[0] : T(0)) + f0;
-        F[1] = (accumulate ? F[1] : T(0)) + f1;
-        F[2] = (accumulate ? F[2] : T(0)) + f2;
-    }
-    if (sub != 0) e = 0.0;
-    for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
-    __syncthreads();
-    if (threadIdx.x == 0) e_part[blk] = (red[0] + red[1]) + (red[2] + red[3]);
+// v from the next lane of its row of 16 (the last from the first)
+__device__ inline float row_next(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x12f, 0xf, 0xf, false));   // row_ror:15
+}
+__device__ inline double row_next(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x12f, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x12f, 0xf, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// NNP side: each wave takes one chunk of MM atoms (staged in its own LDS
-// slice) and one group of 64 NNP atoms, a thread per NNP atom; partial F_i of
-// the chunk, stored component-major ([3 n_nnp][n_chunks]).
-template <typename T>
-__device__ inline void couple_nnp_side(int blk, int n_cg, int n_chunks, int n_nnp, const T* __restrict__ x_nnp,
-                                       const T* __restrict__ par_nnp, int n_mm, const T* __restrict__ x_mm,
-                                       const T* __restrict__ par_mm, T k, T rc2, int chunk,
-                                       T* __restrict__ f_part, T* s_all) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int g = blk / n_cg, c = (blk % n_cg) * 4 + wave;
-    if (c >= n_chunks) return;
-    T* s = s_all + (size_t)wave * kCoupleVals * chunk;
-    const int j0 = c * chunk, nj = min(chunk, n_mm - j0);
-    for (int t = lane; t < nj; t += 64) {
-        T b[kCoupleVals];
-        load_atom(x_mm, par_mm, j0 + t, b);
-#pragma unroll
-        for (int v = 0; v < kCoupleVals; ++v) s[v * chunk + t] = b[v];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int i = g * 64 + lane;
-    if (i >= n_nnp) return;
-    T a[kCoupleVals];
-    load_atom(x_nnp, par_nnp, i, a);
-    T f[2][3] = {{0, 0, 0}, {0, 0, 0}};
-    int t = 0;
-    for (; t < nj; ++t) {
-        const int u = t & 1;
-        const T d0 = s[t] - a[0], d1 = s[chunk + t] - a[1], d2 = s[2 * chunk + t] - a[2];
-        const T r2 = d0 * d0 + d1 * d1 + d2 * d2;
-        if (rc2 > T(0) && r2 >= rc2) continue;
-        T v, dvr;
-        couple_pair(k, r2, a[3] * s[3 * chunk + t], a[4] + s[4 * chunk + t], a[5] * s[5 * chunk + t], v, dvr);
-        // F_i = -dV/dx_i = +(dV/dr)(d/r)
-        f[u][0] += dvr * d0;
-        f[u][1] += dvr * d1;
-        f[u][2] += dvr * d2;
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) f_part[(size_t)(3 * i + q) * n_chunks + c] = f[0][q] + f[1][q];
-}
-
-// both sides in one launch: blocks [0, n_eblk) take the MM side, the rest
-// the NNP side (n_groups x n_cg blocks of four chunks)
-template <typename T>
-__global__ __launch_bounds__(kMmBlock) void k_couple_pairs(int n_eblk, int n_cg, int n_chunks, int n_nnp,
-                                                           const T* __restrict__ x_nnp,
-                                                           const T* __restrict__ par_nnp, int n_mm,
-                                                           const T* __restrict__ x_mm,
-                                                           const T* __restrict__ par_mm, T k, T rc2,
-                                                           int chunk, T* __restrict__ F_mm, int accumulate,
-                                                           double* __restrict__ e_part,
-                                                           T* __restrict__ f_part) {
+// Sums: an MM atom's force in T over 64 NNP atoms (four partial sums of 16), an
+// NNP atom's in T over 16 MM atoms and in FP64 beyond, the energy in FP64.
+template <typename T, bool CUT>
+__global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, const T* __restrict__ x_nnp,
+                                                                 const T* __restrict__ par_nnp, int n_mm,
+                                                                 const T* __restrict__ x_mm,
+                                                                 const T* __restrict__ par_mm, T k, T rc2,
+                                                                 T* __restrict__ F_mm, int accumulate,
+                                                                 double* __restrict__ e_part,
+                                                                 T* __restrict__ f_part) {
     extern __shared__ __align__(16) char smem[];
-    __shared__ double red[kMmBlock / 64];
-    if ((int)blockIdx.x < n_eblk)
-        couple_mm_side(blockIdx.x, n_nnp, x_nnp, par_nnp, n_mm, x_mm, par_mm, k, rc2, F_mm, accumulate,
-                       e_part, (T*)smem, red);
-    else
-        couple_nnp_side(blockIdx.x - n_eblk, n_cg, n_chunks, n_nnp, x_nnp, par_nnp, n_mm, x_mm, par_mm, k,
-                        rc2, chunk, f_part, (T*)smem);
+    __shared__ double red[kCoupleWaves][3][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15;
+    const int ngroups = (n_mm + 15) / 16, nw = gridDim.x * kCoupleWaves;
+    const int g0 = wave * gridDim.x + blockIdx.x;      // consecutive groups go to different workgroups
+    T b[kCoupleVals] = {0, 0, 0, 0, 0, 0};
+    if (g0 < ngroups) load_atom(x_mm, par_mm, min(g0 * 16 + c, n_mm - 1), b);   // in flight while the NNP atoms are staged
+    const int nblk = n_nnp > 0 ? (n_nnp + 63) / 64 : 1, np = nblk * 64;
+    T* s = (T*)smem;                                   // [6][np], past n_nnp far away and inert
+    for (int i = tid; i < np; i += kCoupleThreads) {
+        T a[kCoupleVals] = {T(1e15), T(1e15), T(1e15), T(0), T(0), T(0)};
+        if (i < n_nnp) load_atom(x_nnp, par_nnp, i, a);
+#pragma unroll
+        for (int v = 0; v < kCoupleVals; ++v) s[v * np + i] = a[v];
+    }
+    __syncthreads();
+    double e = 0.0;
+    for (int blk = 0; blk < nblk; ++blk) {
+        const T* sb = s + blk * 64 + (lane & 48);
+        double fi[3] = {0.0, 0.0, 0.0};
+        for (int g = g0; g < ngroups; g += nw) {
+            const int j = g * 16 + c;
+            const bool act = j < n_mm;
+            if (g != g0 || blk > 0) load_atom(x_mm, par_mm, act ? j : n_mm - 1, b);
+            if (!act) b[3] = b[5] = T(0);              // no charge, no well depth: no force, no energy
+            T fj[3] = {0, 0, 0}, fr[3] = {0, 0, 0};
+#pragma unroll 4
+            for (int t = 0; t < 16; ++t) {
+                const T* q = sb + ((c + t) & 15);
+                const T d0 = b[0] - q[0], d1 = b[1] - q[np], d2 = b[2] - q[2 * np];
+                const T r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                T v, dvr;
+                couple_pair(k, r2, q[3 * np] * b[3], q[4 * np] + b[4], q[5 * np] * b[5], v, dvr);
+                if (CUT && r2 >= rc2) v = dvr = T(0);
+                e += (double)v;
+                // F_i = -dV/dx_i = (dV/dr) d / r, F_j = -F_i
+                fj[0] -= dvr * d0;
+                fj[1] -= dvr * d1;
+                fj[2] -= dvr * d2;
+                fr[0] = row_next(fr[0] + dvr * d0);
+                fr[1] = row_next(fr[1] + dvr * d1);
+                fr[2] = row_next(fr[2] + dvr * d2);
+            }
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                fi[d] += (double)fr[d];
+                fj[d] += __shfl_xor(fj[d], 16);
+                fj[d] += __shfl_xor(fj[d], 32);
+            }
+            if (act && lane < 16) {
+                T* F = F_mm + 3 * (size_t)j;
+                const bool add = accumulate || blk > 0;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) F[d] = (add ? F[d] : T(0)) + fj[d];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) red[wave][d][lane] = fi[d];
+        __syncthreads();
+        if (tid < 192) {
+            const int d = tid >> 6, i = blk * 64 + lane;
+            double v = 0.0;
+            for (int w = 0; w < kCoupleWaves; ++w) v += red[w][d][lane];
+            if (i < n_nnp) f_part[(size_t)(3 * i + d) * gridDim.x + blockIdx.x] = (T)v;
+        }
+        __syncthreads();
+    }
+    for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
+    if (lane == 0) red[wave][0][0] = e;
+    __syncthreads();
+    if (tid == 0) {
+        double v = 0.0;
+        for (int w = 0; w < kCoupleWaves; ++w) v += red[w][0][0];
+        e_part[blockIdx.x] = v;
+    }
 }
 
-// One workgroup per NNP force component (and one for the energy): the
-// threads stride over the partials, then a fixed-shape tree combines them,
-// so the sum is the same on every run.
+// One workgroup per NNP force component (and one for the energy), one partial
+// a thread, then a fixed tree, so the sum is the same on every run.
 template <typename T>
-__global__ __launch_bounds__(256) void k_couple_sum(int n_nnp, int n_chunks, const T* __restrict__ f_part,
-                                                    int n_eblk, const double* __restrict__ e_part,
-                                                    T* __restrict__ F_nnp, double* __restrict__ E,
-                                                    int accumulate) {
-    __shared__ double red[4];
-    const int t = blockIdx.x;                 // component (t < 3 n_nnp) or the energy
+__global__ __launch_bounds__(kCoupleMaxWg) void k_couple_sum(int n_nnp, int n, const T* __restrict__ f_part,
+                                                             const double* __restrict__ e_part,
+                                                             T* __restrict__ F_nnp, double* __restrict__ E,
+                                                             int accumulate) {
+    __shared__ double red[kCoupleMaxWg / 64];
+    const int t = blockIdx.x, w = threadIdx.x;   // component (t < 3 n_nnp) or the energy
     const bool energy = t == 3 * n_nnp;
-    const int n = energy ? n_eblk : n_chunks;
-    double v = 0.0;
-    for (int c = threadIdx.x; c < n; c += blockDim.x)
-        v += energy ? e_part[c] : (double)f_part[(size_t)t * n_chunks + c];
+    double v = w >= n ? 0.0 : energy ? e_part[w] : (double)f_part[(size_t)t * n + w];
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    if ((w & 63) == 0) red[w >> 6] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        v = (red[0] + red[1]) + (red[2] + red[3]);
-        if (energy) *E = accumulate ? *E + v : v;
-        else F_nnp[t] = accumulate ? F_nnp[t] + (T)v : (T)v;
-    }
+    if (w > 0) return;
+    v = (red[0] + red[1]) + (red[2] + red[3]);
+    if (energy) *E = accumulate ? *E + v : v;
+    else F_nnp[t] = accumulate ? F_nnp[t] + (T)v : (T)v;
+}
+
+// bytes of the partials of a call with n_nnp NNP atoms
+size_t coupling_scratch_bytes(int n_nnp, size_t tsz) {
+    return kCoupleMaxWg * (sizeof(double) + tsz * 3 * (size_t)n_nnp);
 }
 
 template <typename T>
 hipError_t launch_coupling(const CouplingShape& cs, int n_nnp, const T* x_nnp, const T* par_nnp,
                            int n_mm, const T* x_mm, const T* par_mm, double* E, T* F_nnp, T* F_mm,
-                           double* e_part, T* f_part, bool accumulate, hipStream_t st) {
+                           void* scratch, bool accumulate, hipStream_t st) {
     const T k = (T)cs.coulomb_k, rc2 = (T)(cs.cutoff > 0 ? cs.cutoff * cs.cutoff : 0.0);
-    const int n_eblk = n_mm > 0 ? (n_mm + kMmPerBlock - 1) / kMmPerBlock : 0;
-    const int n_chunks = n_mm > 0 ? (n_mm + cs.chunk - 1) / cs.chunk : 0;
-    if (n_eblk > 0) {
-        const int n_groups = n_nnp > 0 ? (n_nnp + 63) / 64 : 0, n_cg = (n_chunks + 3) / 4;
-        const size_t lds = sizeof(T) * kCoupleVals * std::max((size_t)std::max(n_nnp, 1), (size_t)4 * cs.chunk);
-        hipError_t e = ensure_lds((const void*)k_couple_pairs<T>, lds);
+    double* e_part = (double*)scratch;
+    T* f_part = (T*)(e_part + kCoupleMaxWg);
+    // one workgroup per CU at most, and four groups of 16 MM atoms a workgroup
+    // at least: few groups spread over many CUs
+    const int ng = (n_mm + 15) / 16, nwg = std::min(kCoupleMaxWg, (ng + 3) / 4);
+    if (nwg > 0) {
+        const size_t lds = sizeof(T) * kCoupleVals * ((size_t)(std::max(n_nnp, 1) + 63) / 64 * 64);
+        auto kern = rc2 > T(0) ? k_couple_pairs<T, true> : k_couple_pairs<T, false>;
+        hipError_t e = ensure_lds((const void*)kern, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_couple_pairs<T>, dim3(n_eblk + n_groups * n_cg), dim3(kMmBlock), lds, st,
-                           n_eblk, n_cg, n_chunks, n_nnp, x_nnp, par_nnp, n_mm, x_mm, par_mm, k, rc2,
-                           cs.chunk, F_mm, accumulate ? 1 : 0, e_part, f_part);
+        hipLaunchKernelGGL(kern, dim3(nwg), dim3(kCoupleThreads), lds, st, n_nnp, x_nnp, par_nnp, n_mm, x_mm, par_mm,
+                           k, rc2, F_mm, accumulate ? 1 : 0, e_part, f_part);
     }
-    hipLaunchKernelGGL(k_couple_sum<T>, dim3(3 * n_nnp + 1), dim3(256), 0, st, n_nnp,
-                       n_nnp > 0 ? n_chunks : 0, f_part, n_eblk, e_part, F_nnp, E, accumulate ? 1 : 0);
+    hipLaunchKernelGGL(k_couple_sum<T>, dim3(3 * n_nnp + 1), dim3(kCoupleMaxWg), 0, st, n_nnp, nwg, f_part,
+                       e_part, F_nnp, E, accumulate ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -248,9 +227,11 @@ hipError_t coupling_scratch(void** ptr) {
         if (!p) return hipErrorInvalidSymbol;
         // raise the pair kernel's dynamic-LDS limit now (its largest size),
         // so later calls do no host-side set-up
-        e = ensure_lds((const void*)k_couple_pairs<float>, sizeof(float) * kCoupleVals * 4 * 512);
-        if (e == hipSuccess)
-            e = ensure_lds((const void*)k_couple_pairs<double>, sizeof(double) * kCoupleVals * 4 * 512);
+        const size_t lds = kCoupleVals * 1024;
+        for (const void* kern : {(const void*)k_couple_pairs<float, false>, (const void*)k_couple_pairs<float, true>})
+            if (e == hipSuccess) e = ensure_lds(kern, sizeof(float) * lds);
+        for (const void* kern : {(const void*)k_couple_pairs<double, false>, (const void*)k_couple_pairs<double, true>})
+            if (e == hipSuccess) e = ensure_lds(kern, sizeof(double) * lds);
         if (e != hipSuccess) return e;
         addr[dev] = p;
     }
@@ -259,10 +240,10 @@ hipError_t coupling_scratch(void** ptr) {
 }
 
 template hipError_t launch_coupling<float>(const CouplingShape&, int, const float*, const float*, int,
-                                           const float*, const float*, double*, float*, float*,
-                                           double*, float*, bool, hipStream_t);
+                                           const float*, const float*, double*, float*, float*, void*, bool,
+                                           hipStream_t);
 template hipError_t launch_coupling<double>(const CouplingShape&, int, const double*, const double*,
-                                            int, const double*, const double*, double*, double*,
-                                            double*, double*, double*, bool, hipStream_t);
+                                            int, const double*, const double*, double*, double*, double*, void*,
+                                            bool, hipStream_t);
 
 }  // namespace nnp

@@ -268,16 +268,14 @@ inline hipError_t ensure_lds(const void* kern, size_t bytes) {
 }
 
 // NNP-MM coupling (fixed at creation of a coupling handle)
-// MM atoms per MM-side coupling workgroup (four lanes each): the size of the
-// per-workgroup energy partials the handle allocates
-constexpr int kCoupleMmPerBlock = 64;
-
+constexpr int kCoupleMaxWg = 256;   // workgroups of the pair kernel: one partial of each component each
 struct CouplingShape {
     double coulomb_k;   // 1 / (4 pi eps0) in the caller's units
     double cutoff;      // 0: every pair
     int max_nnp, max_mm;
-    int chunk;          // MM atoms per workgroup of the NNP-side force kernel
 };
+// scratch of a call
+size_t coupling_scratch_bytes(int n_nnp, size_t tsz);
 // Bytes of the per-device static scratch behind nnp_coupling_eval_noalloc
 // and its device address on the current device (looked up once per device).
 constexpr size_t kCoupleScratchBytes = (size_t)8 << 20;
@@ -286,7 +284,7 @@ hipError_t coupling_scratch(void** ptr);
 template <typename T>
 hipError_t launch_coupling(const CouplingShape& cs, int n_nnp, const T* x_nnp, const T* par_nnp,
                            int n_mm, const T* x_mm, const T* par_mm, double* E, T* F_nnp, T* F_mm,
-                           double* e_part, T* f_part, bool accumulate, hipStream_t st);
+                           void* scratch, bool accumulate, hipStream_t st);
 
 // launchers (explicitly instantiated for PrecF64 / PrecF32 / PrecBF16)
 template <typename P>

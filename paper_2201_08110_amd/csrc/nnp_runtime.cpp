@@ -1446,12 +1446,6 @@ nnp_status nnp_autotune(nnp_handle* h, const nnp_batch* b, const void* coords, i
 }  // extern "C"
 
 namespace {
-// MM atoms per NNP-side wave: 16, widened (up to 512, the LDS limit of four
-// FP64 chunks) by 16 per 64k MM atoms so the partials stay bounded
-int coupling_chunk(int max_mm) {
-    return 16 * std::min(32, std::max(1, (max_mm + 64 * 1024 - 1) / (64 * 1024)));
-}
-
 nnp_status check_coupling_args(int32_t n_nnp, const void* x_nnp, const void* par_nnp, int32_t n_mm,
                                const void* x_mm, const void* par_mm, const double* out_E,
                                const void* F_nnp, const void* F_mm, uint32_t flags) {
@@ -1468,8 +1462,7 @@ struct nnp_coupling {
     nnp::CouplingShape cs{};
     int precision = NNP_PREC_FP32;
     int device = 0;
-    double* e_part = nullptr;   // [ceil(max_mm / 256)]
-    void* f_part = nullptr;     // [ceil(max_mm / chunk)][max_nnp][3]
+    void* scratch = nullptr;    // partials (coupling_scratch_bytes)
 };
 
 extern "C" {
@@ -1496,12 +1489,8 @@ nnp_status nnp_coupling_create(int32_t precision, int32_t max_nnp, int32_t max_m
     c->cs.cutoff = cutoff;
     c->cs.max_nnp = max_nnp;
     c->cs.max_mm = max_mm;
-    c->cs.chunk = coupling_chunk(max_mm);
     const size_t tsz = precision == NNP_PREC_FP64 ? sizeof(double) : sizeof(float);
-    const size_t n_eblk = (size_t)(max_mm + kCoupleMmPerBlock - 1) / kCoupleMmPerBlock;
-    const size_t n_chunks = (size_t)(max_mm + c->cs.chunk - 1) / c->cs.chunk;
-    hipError_t e = hipMalloc(&c->e_part, sizeof(double) * n_eblk);
-    if (e == hipSuccess) e = hipMalloc(&c->f_part, tsz * 3 * n_chunks * (size_t)max_nnp);
+    hipError_t e = hipMalloc(&c->scratch, coupling_scratch_bytes(max_nnp, tsz));
     if (e != hipSuccess) {
         nnp_coupling_destroy(c);
         return fail(NNP_E_NOMEM, "coupling workspace allocation failed");
@@ -1514,8 +1503,7 @@ void nnp_coupling_destroy(nnp_coupling* c) {
     if (!c) return;
     DeviceGuard dg(c->device);
     (void)hipDeviceSynchronize();
-    if (c->e_part) (void)hipFree(c->e_part);
-    if (c->f_part) (void)hipFree(c->f_part);
+    if (c->scratch) (void)hipFree(c->scratch);
     delete c;
 }
 
@@ -1535,11 +1523,11 @@ nnp_status nnp_coupling_eval(nnp_coupling* c, int32_t n_nnp, const void* x_nnp, 
     if (c->precision == NNP_PREC_FP64)
         e = launch_coupling<double>(c->cs, n_nnp, (const double*)x_nnp, (const double*)par_nnp, n_mm,
                                     (const double*)x_mm, (const double*)par_mm, out_E, (double*)F_nnp,
-                                    (double*)F_mm, c->e_part, (double*)c->f_part, acc, st);
+                                    (double*)F_mm, c->scratch, acc, st);
     else
         e = launch_coupling<float>(c->cs, n_nnp, (const float*)x_nnp, (const float*)par_nnp, n_mm,
                                    (const float*)x_mm, (const float*)par_mm, out_E, (float*)F_nnp,
-                                   (float*)F_mm, c->e_part, (float*)c->f_part, acc, st);
+                                   (float*)F_mm, c->scratch, acc, st);
     if (e != hipSuccess) return fail(NNP_E_DEVICE, std::string("coupling launch: ") + hipGetErrorString(e));
     return NNP_OK;
 }
@@ -1559,34 +1547,28 @@ nnp_status nnp_coupling_eval_noalloc(int32_t precision, double coulomb_k, double
     void* scratch = nullptr;
     hipError_t e = coupling_scratch(&scratch);
     if (e != hipSuccess) return fail(NNP_E_DEVICE, std::string("coupling scratch: ") + hipGetErrorString(e));
-    // the partials: [ceil(n_mm / 64)] doubles, then [3 n_nnp][ceil(n_mm / chunk)]
-    // of the operand type; a chunk wider than the handle's rule (up to 512 MM
-    // atoms) is taken when that makes them fit
+    // the partials of any accepted size fit; the limit is the entry point's
+    // stated one, in chunks of 512 MM atoms
     const size_t tsz = precision == NNP_PREC_FP64 ? sizeof(double) : sizeof(float);
-    const size_t e_bytes = (((size_t)(n_mm + kCoupleMmPerBlock - 1) / kCoupleMmPerBlock) * sizeof(double) + 255) &
-                           ~(size_t)255;
+    const size_t limit = ((((size_t)n_mm + 63) / 64 * sizeof(double) + 255) & ~(size_t)255) +
+                         tsz * 3 * (size_t)n_nnp * (((size_t)n_mm + 511) / 512);
+    if (limit > kCoupleScratchBytes || coupling_scratch_bytes(n_nnp, tsz) > kCoupleScratchBytes)
+        return fail(NNP_E_CAPACITY, "coupling partials exceed the static scratch (8 MiB)");
     CouplingShape cs{};
     cs.coulomb_k = coulomb_k;
     cs.cutoff = cutoff;
     cs.max_nnp = std::max(n_nnp, 1);
     cs.max_mm = std::max(n_mm, 1);
-    cs.chunk = coupling_chunk(cs.max_mm);
-    auto f_bytes = [&](int chunk) { return tsz * 3 * (size_t)n_nnp * (size_t)((n_mm + chunk - 1) / chunk); };
-    while (e_bytes + f_bytes(cs.chunk) > kCoupleScratchBytes && cs.chunk < 512) cs.chunk += 16;
-    if (e_bytes + f_bytes(cs.chunk) > kCoupleScratchBytes)
-        return fail(NNP_E_CAPACITY, "coupling partials exceed the static scratch (8 MiB)");
-    double* e_part = (double*)scratch;
-    void* f_part = (char*)scratch + e_bytes;
     const bool acc = (flags & NNP_FLAG_ACCUMULATE) != 0;
     hipStream_t st = (hipStream_t)stream;
     if (precision == NNP_PREC_FP64)
         e = launch_coupling<double>(cs, n_nnp, (const double*)x_nnp, (const double*)par_nnp, n_mm,
                                     (const double*)x_mm, (const double*)par_mm, out_E, (double*)F_nnp,
-                                    (double*)F_mm, e_part, (double*)f_part, acc, st);
+                                    (double*)F_mm, scratch, acc, st);
     else
         e = launch_coupling<float>(cs, n_nnp, (const float*)x_nnp, (const float*)par_nnp, n_mm,
                                    (const float*)x_mm, (const float*)par_mm, out_E, (float*)F_nnp,
-                                   (float*)F_mm, e_part, (float*)f_part, acc, st);
+                                   (float*)F_mm, scratch, acc, st);
     if (e != hipSuccess) return fail(NNP_E_DEVICE, std::string("coupling launch: ") + hipGetErrorString(e));
     return NNP_OK;
 }
