@@ -62,6 +62,70 @@ __device__ inline void gbl_add(double* p, double v) { unsafeAtomicAdd(p, v); }
 
 __device__ inline int lane_id() { return __lane_id(); }
 
+// Lane scans through DPP (a few clocks a step; a shuffle through the LDS is
+// over a hundred, and these chains are what a few-atom call waits for).
+// v of the lane CTRL names, 0 where it names none or the row is masked off.
+template <int CTRL, int ROWS = 0xf> __device__ inline int dpp(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+constexpr int kRowShl1 = 0x101, kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+__device__ inline int next_lane(int v) { return dpp<kRowShl1>(v); }   // lane i + 1 of its row of 16
+// inclusive prefix sums over each row of 16, and over the wave
+__device__ inline int row_scan(int v) {
+    v += dpp<kRowShr + 1>(v);
+    v += dpp<kRowShr + 2>(v);
+    v += dpp<kRowShr + 4>(v);
+    return v + dpp<kRowShr + 8>(v);
+}
+__device__ inline int wave_scan(int v) {
+    v = row_scan(v);
+    v += dpp<kRowBcast15, 0xa>(v);
+    return v + dpp<kRowBcast31, 0xc>(v);
+}
+// inclusive prefix maximum over the wave (v >= 0)
+__device__ inline int wave_scan_max(int v) {
+    v = max(v, dpp<kRowShr + 1>(v));
+    v = max(v, dpp<kRowShr + 2>(v));
+    v = max(v, dpp<kRowShr + 4>(v));
+    v = max(v, dpp<kRowShr + 8>(v));
+    v = max(v, dpp<kRowBcast15, 0xa>(v));
+    return max(v, dpp<kRowBcast31, 0xc>(v));
+}
+// v of another lane of the row (every lane named exists)
+template <int CTRL> __device__ inline float dpp_of(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL> __device__ inline double dpp_of(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kHalfMirror = 0x141, kRowMirror = 0x140;
+template <typename T> __device__ inline T quad_sum(T v) {
+    v += dpp_of<kXor1>(v);
+    return v + dpp_of<kXor2>(v);
+}
+template <typename T> __device__ inline T row_sum(T v) {
+    v = quad_sum(v);
+    v += dpp_of<kHalfMirror>(v);
+    return v + dpp_of<kRowMirror>(v);
+}
+__device__ inline unsigned long long below(int lane) { return lane == 0 ? 0ull : ~0ull >> (64 - lane); }
+
+// Starts the load of every line of the kernel's arguments at once: the
+// compiler loads an argument where it is first used, and each line that is
+// not yet in the scalar cache costs about a thousand clocks there (2,300 of
+// the featuriser's 33,600 on 64 atoms, net of 840 for this).
+template <int BYTES> __device__ inline void touch_kernargs() {
+    typedef const volatile int __attribute__((address_space(4))) * Args;
+    Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    int v[BYTES / 64 + 1], all = 0;
+#pragma unroll
+    for (int i = 0; i <= BYTES / 64; ++i) v[i] = p[i * 16 < BYTES / 4 ? i * 16 : BYTES / 4 - 1];
+#pragma unroll
+    for (int i = 0; i <= BYTES / 64; ++i) all |= v[i];
+    asm volatile("" ::"s"(all));
+}
+
 // upper-triangle index of the unordered element pair (b, c)
 __device__ inline int pair_index(int b, int c, int S) {
     int lo = b < c ? b : c, hi = b < c ? c : b;
@@ -485,22 +549,33 @@ __device__ inline T wave_max(T v) {
 template <typename T>
 __device__ inline void stage_element_order(const T* tx, const int* tsp, int n, int S, T* sx4, int* sid) {
     const int lane = lane_id();
-    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int base = 0;
-    for (int q = 0; q < S; ++q)
-        for (int j0 = 0; j0 < n; j0 += 64) {
-            const int j = j0 + lane;
-            const int s = j < n ? tsp[j] : -1;
-            const unsigned long long m = __ballot(s == q);
-            if (s == q) {
-                const int pos = base + __popcll(m & lt);
-                sid[pos] = j;
-                sx4[4 * pos + 0] = tx[3 * j + 0];
-                sx4[4 * pos + 1] = tx[3 * j + 1];
-                sx4[4 * pos + 2] = tx[3 * j + 2];
-            }
-            base += __popcll(m);
+    const unsigned long long lt = below(lane);
+    int cnt = 0;   // lane q: atoms of element q
+    for (int j0 = 0; j0 < n; j0 += 64) {
+        const int s = j0 + lane < n ? tsp[j0 + lane] : -1;
+        for (int q = 0; q < S; ++q) {
+            const int m = __popcll(__ballot(s == q));
+            cnt += lane == q ? m : 0;
         }
+    }
+    int base = row_scan(cnt) - cnt;   // lane q: place of its next atom
+    for (int j0 = 0; j0 < n; j0 += 64) {
+        const int j = j0 + lane;
+        const int s = j < n ? tsp[j] : -1;
+        int pos = 0;
+        for (int q = 0; q < S; ++q) {
+            const unsigned long long m = __ballot(s == q);
+            const int at = __builtin_amdgcn_readlane(base, q);
+            pos = s == q ? at + __popcll(m & lt) : pos;
+            base += lane == q ? __popcll(m) : 0;
+        }
+        if (j < n) {
+            sid[pos] = j;
+            sx4[4 * pos + 0] = tx[3 * j + 0];
+            sx4[4 * pos + 1] = tx[3 * j + 1];
+            sx4[4 * pos + 2] = tx[3 * j + 2];
+        }
+    }
 }
 
 // One wave: the neighbours of atom il within Rcr, those within Rca first,
@@ -513,7 +588,7 @@ __device__ inline int atom_neighbours(const T* sx4, const int* sid, int n, int i
                                       T rca2, T rcr2, int cap, uint16_t* out, uint16_t* out2,
                                       int32_t* __restrict__ flag) {
     const int lane = lane_id();
-    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const unsigned long long lt = below(lane);
     int cnt = 0, nang = 0;
     for (int pass = 0; pass < 2; ++pass) {
         for (int k0 = 0; k0 < n; k0 += 64) {
@@ -790,6 +865,21 @@ __device__ inline int tag_of(const float* e) { return __float_as_int(e[8]); }
 __device__ inline int tag_of(const double* e) { return (int)e[8]; }
 static_assert(kNbStride >= 9, "record tag slot");
 
+// one neighbour's record from its displacement
+template <typename T>
+__device__ inline void put_record(const AevConst<T>& c, T* __restrict__ e, T d0, T d1, T d2, bool ang, int j, int sp) {
+    const T r = m_sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+    e[0] = d0;
+    e[1] = d1;
+    e[2] = d2;
+    e[3] = r;
+    e[4] = T(0.5) * m_cos(c.pi_rcr * r) + T(0.5);
+    e[5] = -T(0.5) * c.pi_rcr * m_sin(c.pi_rcr * r);
+    e[6] = ang ? T(0.5) * m_cos(c.pi_rca * r) + T(0.5) : T(0);
+    e[7] = ang ? -T(0.5) * c.pi_rca * m_sin(c.pi_rca * r) : T(0);
+    put_tag(e, (j << 8) | sp);
+}
+
 // load_neighbours with the tag in the record instead of nsp / nid
 template <typename T>
 __device__ inline void load_records(const AevConst<T>& c, const T* __restrict__ sx,
@@ -799,24 +889,54 @@ __device__ inline void load_records(const AevConst<T>& c, const T* __restrict__ 
     const T xi0 = sx[3 * il], xi1 = sx[3 * il + 1], xi2 = sx[3 * il + 2];
     for (int t = lane_id(); t < nall; t += 64) {
         const int j = nb_list[t];
-        const T d0 = sx[3 * j] - xi0, d1 = sx[3 * j + 1] - xi1, d2 = sx[3 * j + 2] - xi2;
-        const T r = m_sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-        T* e = nb + kNbStride * t;
-        e[0] = d0;
-        e[1] = d1;
-        e[2] = d2;
-        e[3] = r;
-        e[4] = T(0.5) * m_cos(c.pi_rcr * r) + T(0.5);
-        e[5] = -T(0.5) * c.pi_rcr * m_sin(c.pi_rcr * r);
-        if (t < nang) {
-            e[6] = T(0.5) * m_cos(c.pi_rca * r) + T(0.5);
-            e[7] = -T(0.5) * c.pi_rca * m_sin(c.pi_rca * r);
-        } else {
-            e[6] = T(0);
-            e[7] = T(0);
-        }
-        put_tag(e, (j << 8) | ssp[j]);
+        put_record(c, nb + kNbStride * t, sx[3 * j] - xi0, sx[3 * j + 1] - xi1, sx[3 * j + 2] - xi2, t < nang, j, ssp[j]);
     }
+}
+
+// atom_neighbours and load_records in one step for molecules of at most 128
+// atoms: each lane holds two candidates of the staged order, and a hit writes
+// its record itself.  The list goes to out.
+constexpr int kDirectAtoms = 128;
+template <typename T>
+__device__ inline int find_records(const AevConst<T>& c, const T* sx4, const int* sid, const int* ssp, int n, int il,
+                                   T xi0, T xi1, T xi2, T rca2, T rcr2, int cap, T* __restrict__ nb,
+                                   uint16_t* out, int32_t* __restrict__ flag) {
+    const int lane = lane_id();
+    const unsigned long long lt = below(lane);
+    T d[2][3];
+    int j[2] = {0, 0};
+    bool ha[2] = {false, false}, hb[2] = {false, false};
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int k = 64 * u + lane;
+        if (64 * u < n && k < n) {
+            j[u] = sid[k];
+            d[u][0] = sx4[4 * k] - xi0;
+            d[u][1] = sx4[4 * k + 1] - xi1;
+            d[u][2] = sx4[4 * k + 2] - xi2;
+            const T r2 = d[u][0] * d[u][0] + d[u][1] * d[u][1] + d[u][2] * d[u][2];
+            ha[u] = j[u] != il && r2 < rca2;
+            hb[u] = j[u] != il && r2 >= rca2 && r2 < rcr2;
+        }
+    }
+    const unsigned long long a0 = __ballot(ha[0]), a1 = __ballot(ha[1]), b0 = __ballot(hb[0]), b1 = __ballot(hb[1]);
+    int nang = __popcll(a0) + __popcll(a1), nall = nang + __popcll(b0) + __popcll(b1);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        if (ha[u] || hb[u]) {
+            const int t = ha[u] ? (u ? __popcll(a0) : 0) + __popcll((u ? a1 : a0) & lt)
+                                : nang + (u ? __popcll(b0) : 0) + __popcll((u ? b1 : b0) & lt);
+            if (t < cap) {
+                put_record(c, nb + kNbStride * t, d[u][0], d[u][1], d[u][2], ha[u], j[u], ssp[j[u]]);
+                out[t] = (uint16_t)j[u];
+            }
+        }
+    if (nall > cap) {
+        if (lane == 0) atomicOr(flag, FLAG_CAPACITY);
+        nall = cap;
+        nang = nang > cap ? cap : nang;
+    }
+    return nang | (nall << 16);
 }
 
 // --------------------------------------------------------------------------
@@ -827,22 +947,17 @@ __device__ inline void load_records(const AevConst<T>& c, const T* __restrict__ 
 // rectangle (a < b) or a triangle (a == b) of index space.  Pairs are
 // numbered block by block (blocks in AEV order, i.e. by pair_index(a, b)), so
 // every 32-slot angular block of the AEV is a contiguous pair range and can
-// be summed by the lanes that own its slots, with no atomics.
-template <typename T> struct AtomLists {
-    int* aoff;   // [kMaxSpecies + 1]  angular-run start of each element
-    int* roff;   // [kMaxSpecies + 1]  radial-only-run start of each element
-    int* bst;    // [kMaxBlocks + 1]   first pair of each angular block
-    static constexpr int kMaxBlocks = kMaxSpecies * (kMaxSpecies + 1) / 2;
-    __device__ void take(LdsBump& lb) {
-        aoff = lb.take<int>(kMaxSpecies + 1);
-        roff = lb.take<int>(kMaxSpecies + 1);
-        bst = lb.take<int>(kMaxBlocks + 1);
-    }
-    static constexpr size_t bytes() {
-        return 2 * (((kMaxSpecies + 1) * sizeof(int) + 15) & ~size_t(15)) +
-               (((kMaxBlocks + 1) * sizeof(int) + 15) & ~size_t(15));
-    }
+// be summed by the lanes that own its slots, with no atomics.  The tables are
+// one entry a lane, in registers.
+struct AtomLists {
+    int range;   // lane s: first angular neighbour of element s, one past its
+                 // last, and the same of the radial-only run, 8 bits each
+    int blo, bhi;   // lane b: angular block b's pairs
+    int desc;    // lane b: its elements' first neighbours a | b << 8, the count
+                 // of b << 16, and a == b << 24
+    int npair;
 };
+static_assert(kMaxNeighbours < 256, "list positions in 8 bits");
 
 // elements (a, b), a <= b, of the angular block with triangular index L
 __device__ inline void block_elements(int L, int S, int& a, int& b) {
@@ -855,194 +970,174 @@ __device__ inline void block_elements(int L, int S, int& a, int& b) {
     b = aa + (L - base);
 }
 
-// Fill aoff / roff / bst for one atom (wave-wide); sp_of(t) = element of
-// neighbour t.  Returns the number of angular pairs.
-template <typename T, typename SpOf>
-__device__ inline int atom_lists(const AtomLists<T>& al, SpOf sp_of, int nang, int nall, int S) {
+// The lists of one atom (wave-wide); sp_of(t) = element of neighbour t, (ba,
+// bb) = this lane's block's elements.  Both runs (angular [0, nang),
+// radial-only [nang, nall)) are sorted by element, so an element starts after
+// the neighbours of smaller ones.
+template <typename SpOf>
+__device__ inline AtomLists atom_lists(SpOf sp_of, int nang, int nall, int S, int ba, int bb) {
     const int lane = lane_id();
-    // Both runs (angular [0, nang), radial-only [nang, nall)) are sorted by
-    // element: the first neighbour of each element in a run marks where that
-    // element starts; an element absent from a run starts where the next
-    // present one does (or at the run's end).
-    if (lane <= S) {
-        al.aoff[lane] = nang;
-        al.roff[lane] = nall;
-    }
-    wave_sync();
-    for (int t = lane; t < nall; t += 64) {
-        const int sp = sp_of(t);
-        if (t == 0 || t == nang || sp_of(t - 1) != sp) {
-            if (t < nang) al.aoff[sp] = t;
-            else al.roff[sp] = t;
+    int ao = 0, ro = nang;   // lane s <= S
+    for (int t0 = 0; t0 < nall; t0 += 64) {
+        const int sp = t0 + lane < nall ? sp_of(t0 + lane) : kMaxSpecies;
+        const int na = min(max(nang - t0, 0), 64);
+        const unsigned long long ang = na == 64 ? ~0ull : (1ull << na) - 1;
+        for (int s = 1; s <= S; ++s) {
+            const unsigned long long m = __ballot(sp < s);
+            const int ca = __popcll(m & ang), cr = __popcll(m & ~ang);
+            ao += lane == s ? ca : 0;
+            ro += lane == s ? cr : 0;
         }
     }
-    wave_sync();
-    int ao = lane <= S ? al.aoff[lane] : nang, ro = lane <= S ? al.roff[lane] : nall;
-    for (int o = 1; o <= 8; o <<= 1) {   // suffix minimum over lanes 0..S
-        const int va = __shfl_down(ao, o), vr = __shfl_down(ro, o);
-        if (lane + o <= S) {
-            ao = min(ao, va);
-            ro = min(ro, vr);
-        }
-    }
-    if (lane <= S) {
-        al.aoff[lane] = ao;
-        al.roff[lane] = ro;
-    }
-    // lane s: angular neighbours of element s (the shuffle runs on every
-    // lane: a lane outside the condition would not supply its value)
-    const int ao_next = __shfl_down(ao, 1);
-    const int ca = lane < S ? ao_next - ao : 0;
+    AtomLists al;
+    const int ae = next_lane(ao);
+    al.range = ao | (ae << 8) | (ro << 16) | (next_lane(ro) << 24);
     // angular block sizes and their prefix
-    const int NB = S * (S + 1) / 2;
-    int a = 0, b = 0;
-    if (lane < NB) block_elements(lane, S, a, b);
-    const int na = __shfl(ca, a), nb = __shfl(ca, b);
-    const int cnt = lane < NB ? (a < b ? na * nb : na * (na - 1) / 2) : 0;
-    int inc = cnt;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(inc, o);
-        if (lane >= o) inc += v;
-    }
-    if (lane < NB) al.bst[lane + 1] = inc;
-    if (lane == 0) al.bst[0] = 0;
-    return __shfl(inc, NB - 1);
+    const int NB = S * (S + 1) / 2, run = ao | ((ae - ao) << 8);
+    const int ra = __shfl(run, ba), rb = __shfl(run, bb), na = ra >> 8, nb = rb >> 8;
+    const int cnt = lane < NB ? (ba < bb ? na * nb : na * (na - 1) / 2) : 0;
+    al.bhi = wave_scan(cnt);
+    al.blo = al.bhi - cnt;
+    al.desc = (ra & 0xff) | ((rb & 0xff) << 8) | (nb << 16) | (ba == bb ? 1 << 24 : 0);
+    al.npair = __builtin_amdgcn_readlane(al.bhi, 63);
+    return al;
 }
 
-// neighbour indices (j, k) of angular pair p (block-ordered numbering)
-template <typename T>
-__device__ inline void pair_of(const AtomLists<T>& al, int NB, int S, int p, int& j, int& k) {
-    int lo = 0;   // last block with bst[lo] <= p
-    for (int step = 32; step > 0; step >>= 1)
-        if (lo + step < NB && al.bst[lo + step] <= p) lo += step;
-    int a, b;
-    block_elements(lo, S, a, b);
-    const int u = p - al.bst[lo];
-    if (a < b) {
-        const int nb = al.aoff[b + 1] - al.aoff[b];
+// Neighbour indices (j, k) of this lane's pair p0 + lane (block-ordered
+// numbering; lanes past the last pair get some block's).  mark: 64 integers of
+// this wave's LDS.  Each block that starts in the batch marks its first pair,
+// and a running maximum over the lanes finds every pair's block.
+__device__ inline void batch_pairs(const AtomLists& al, int p0, int* mark, int& j, int& k) {
+    const int lane = lane_id();
+    const bool some = al.blo < al.bhi;
+    mark[lane] = 0;
+    if (some && al.blo >= p0 && al.blo < p0 + 64) mark[al.blo - p0] = lane + 1;
+    const unsigned long long before = __ballot(some && al.blo <= p0);   // the batch's first pair's block is the last of these
+    wave_sync();
+    int blk = mark[lane];
+    if (lane == 0) blk = 64 - __builtin_clzll(before);
+    blk = wave_scan_max(blk) - 1;
+    const int lo = __shfl(al.blo, blk), desc = __shfl(al.desc, blk);
+    const int u = p0 + lane - lo, fa = desc & 0xff, fb = (desc >> 8) & 0xff, nb = (desc >> 16) & 0xff;
+    if (desc >> 24) {
+        // row-major triangle of nb atoms: start(j) = j (2 nb - j - 1) / 2; the
+        // estimate from the hardware square root is off by one at most
+        const float t = (float)(2 * nb - 1);
+        int jj = (int)((t - __builtin_amdgcn_sqrtf(fmaxf(t * t - 8.0f * (float)u, 0.0f))) * 0.5f);
+        jj = min(max(jj, 0), nb - 2);
+        if (jj > 0 && (jj * (2 * nb - jj - 1)) / 2 > u) --jj;
+        if (jj + 1 <= nb - 2 && ((jj + 1) * (2 * nb - jj - 2)) / 2 <= u) ++jj;
+        j = fa + jj;
+        k = fa + u - (jj * (2 * nb - jj - 1)) / 2 + jj + 1;
+    } else {
         // u / nb through the float reciprocal, corrected (u < 2^16)
         int q = (int)((float)u * __builtin_amdgcn_rcpf((float)nb));
         if (q * nb > u) --q;
         if ((q + 1) * nb <= u) ++q;
-        j = al.aoff[a] + q;
-        k = al.aoff[b] + (u - q * nb);
-    } else {
-        int jj, kk;
-        decode_pair(u, al.aoff[a + 1] - al.aoff[a], jj, kk);
-        j = al.aoff[a] + jj;
-        k = al.aoff[a] + kk;
+        j = fa + q;
+        k = fb + (u - q * nb);
     }
 }
 
 // Bucketing inside the featuriser, for batches of at most kPrepBlock atoms and
 // molecules: the steps and results of k_bucket_one without its launch.  Every
-// workgroup counts the elements of the batch's atoms per 64-atom segment
-// (ballots) and forms the padded bucket offsets (prefix over the lanes of
-// wave 0); it then places its own central atoms [c0, c0 + nc) (row = bucket
-// start + atoms of the element in earlier segments + rank in its segment),
-// keeps their rows in crow and writes their per-atom outputs.  The lead
-// workgroup also writes the bucket table, the row tiles' elements, the
-// padding rows and the capacity flags.  Returns false when the rows exceed
-// the capacity (the rows are then not written, as the kernel leaves them).
-constexpr int kBucketScratch = (kPrepBlock / 64) * kMaxSpecies + 2 * kMaxSpecies + 1 + 2 * kChunk;
-__device__ inline bool bucket_in_features(const BucketFuse& bk, int S, int A, int max_apm,
-                                          const int32_t* __restrict__ mol_off,
-                                          const int32_t* __restrict__ species, int b, int c0, int nc,
-                                          bool mine, bool lead, int* scr, int* crow,
-                                          int32_t* __restrict__ flag) {
-    int* segcnt = scr;                                   // [segment][element]
-    int* base = segcnt + (kPrepBlock / 64) * kMaxSpecies;   // [S + 1] padded starts
-    int* tot = base + kMaxSpecies + 1;                   // [S] atoms per element
-    int* crank = tot + kMaxSpecies;                      // [nc] rank in its segment
-    int* csp = crank + kChunk;                           // [nc] element (| 0x100: invalid)
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
+// wave counts the elements of the batch's atoms for itself (ballots; no LDS
+// and no barrier) and places the central atoms it takes; one workgroup beside
+// the molecules' writes the bucket table, the row tiles' elements, the padding
+// rows and the capacity flags (in a molecule's own workgroup those were 3,600
+// of its 33,600 clocks).
+struct WaveBuckets {
     int A0, A1;
-    const bool rng = atom_range(A, bk.B, bk.dA, mol_off, bk.sub, A0, A1);
-    if (lead) {
-        if (!rng && tid == 0) atomicOr(flag, FLAG_CAPACITY);
-        for (int m = tid; m < bk.B; m += blockDim.x) {
-            const int m0 = mol_off[m], m1 = mol_off[m + 1];
-            if (m0 < A0 || m1 < m0 || m1 > A1 || m1 - m0 > max_apm) atomicOr(flag, FLAG_CAPACITY);
-        }
-    }
-    // central atoms outside the call's range have no row (the lead has flagged them)
-    mine = mine && c0 >= A0 && c0 + nc <= A1;
-    const int nseg = (A1 - A0 + 63) >> 6;
-    const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (int g = wave; g < nseg; g += nw) {
-        const int a = A0 + 64 * g + lane;
-        int sv = -1;
-        if (a < A1) {
-            sv = species[a];
-            if (bk.zlut) sv = (sv >= 0 && sv < kZLut) ? (int)bk.zlut[sv] : -1;
-            if (sv >= S) sv = -1;
-        }
-        const int s = sv < 0 ? 0 : sv;   // as the bucketing kernel counts them
-        for (int q = 0; q < S; ++q) {
-            const unsigned long long m = __ballot(a < A1 && s == q);
-            if (lane == 0) segcnt[g * kMaxSpecies + q] = __popcll(m);
-            if (a < A1 && s == q && a >= c0 && a < c0 + nc) {
-                crank[a - c0] = __popcll(m & lt);
-                csp[a - c0] = q | (sv < 0 ? 0x100 : 0);
+    bool ok;          // the call's atom range is valid
+    int tot, base;    // lane q: atoms of element q and its padded start (lane S: all rows)
+    int pre;          // lane q: atoms of element q before atom a
+    bool bad;         // atom a's label names no element
+};
+// (a label that names no element counts as element 0, as in the bucketing kernel)
+__device__ inline WaveBuckets wave_buckets(const BucketFuse& bk, int S, int A, const int32_t* __restrict__ mol_off,
+                                           const int32_t* __restrict__ species, int a) {
+    const int lane = lane_id();
+    WaveBuckets w;
+    w.ok = atom_range(A, bk.B, bk.dA, mol_off, bk.sub, w.A0, w.A1);
+    w.tot = w.pre = 0;
+    w.bad = false;
+    constexpr int U = 4;   // segments of 64 atoms whose labels load together
+    for (int a4 = w.A0; a4 < w.A1; a4 += 64 * U) {
+        int sv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) sv[u] = species[min(a4 + 64 * u + lane, w.A1 - 1)];
+        if (bk.zlut)
+#pragma unroll
+            for (int u = 0; u < U; ++u) sv[u] = (sv[u] >= 0 && sv[u] < kZLut) ? (int)bk.zlut[sv[u]] : -1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int a1 = a4 + 64 * u;
+            if (a1 >= w.A1) break;
+            const bool bad = sv[u] < 0 || sv[u] >= S;
+            const int s = a1 + lane < w.A1 ? (bad ? 0 : sv[u]) : -1;
+            const int before = min(max(a - a1, 0), 64);
+            const unsigned long long lt = before == 64 ? ~0ull : (1ull << before) - 1;
+            w.bad |= __ballot(bad && a1 + lane == a && s >= 0) != 0;
+            for (int q = 0; q < S; ++q) {
+                const unsigned long long m = __ballot(s == q);
+                const int ct = __popcll(m), cb = __popcll(m & lt);
+                w.tot += lane == q ? ct : 0;
+                w.pre += lane == q ? cb : 0;
             }
         }
     }
-    __syncthreads();
-    if (wave == 0) {
-        int c = 0;
-        if (lane < S)
-            for (int g = 0; g < nseg; ++g) c += segcnt[g * kMaxSpecies + lane];
-        const int pc = ((c + bk.row_tile - 1) / bk.row_tile) * bk.row_tile;
-        int incl = pc;
-        for (int d = 1; d < 2 * kMaxSpecies; d <<= 1) {
-            const int v = __shfl_up(incl, d);
-            if (lane >= d) incl += v;
-        }
-        if (lane < S) tot[lane] = c;
-        if (lane <= S) base[lane] = incl - pc;
-        if (lead) {
-            if (lane < S) bk.info->count[lane] = c;
-            if (lane <= S) bk.info->off[lane] = incl - pc;
-            if (lane == S) {
-                int rows = incl;
-                if (rows > bk.Rcap) {
-                    atomicOr(flag, FLAG_CAPACITY);
-                    rows = 0;
-                }
-                bk.info->rows = rows;
-            }
-        }
-    }
-    __syncthreads();
-    const bool fits = base[S] <= bk.Rcap;
-    const int rows = fits ? base[S] : 0;
-    if (lead) {
-        for (int t = tid; t < bk.Rcap / bk.row_tile; t += blockDim.x) {
-            const int r = t * bk.row_tile;
-            int sp = -1;
-            if (r < rows)
-                for (int q = 0; q < S; ++q)
-                    if (base[q] <= r && r < base[q + 1]) sp = q;
-            bk.tile_species[t] = sp;
-        }
-        for (int q = 0; q < S; ++q)
-            for (int r = base[q] + tot[q] + tid; r < base[q + 1] && r < rows; r += blockDim.x)
-                bk.atom_of_row[r] = -1;
-    }
-    if (!fits || !mine) return false;
-    for (int ic = tid; ic < nc; ic += blockDim.x) {
-        const int a = c0 + ic, s = csp[ic] & 0xff, g = (a - A0) >> 6;
-        int row = base[s] + crank[ic];
-        for (int g2 = 0; g2 < g; ++g2) row += segcnt[g2 * kMaxSpecies + s];
-        crow[ic] = row;
+    const int pc = (w.tot + bk.row_tile - 1) / bk.row_tile * bk.row_tile;
+    w.base = row_scan(pc) - pc;
+    return w;
+}
+// row of the atom a of element s that w was formed for, or -1 when the rows
+// exceed the capacity or the atom lies outside the call's range; writes the
+// atom's outputs
+__device__ inline int bucket_atom(const BucketFuse& bk, const WaveBuckets& w, int S, int s, int a, int b,
+                                  int32_t* __restrict__ flag) {
+    if (__builtin_amdgcn_readlane(w.base, S) > bk.Rcap || a < w.A0 || a >= w.A1) return -1;
+    s = __builtin_amdgcn_readfirstlane(s);
+    const int row = __builtin_amdgcn_readlane(w.base, s) + __builtin_amdgcn_readlane(w.pre, s);
+    if (lane_id() == 0) {
         bk.row_of_atom[a] = row;
         bk.atom_of_row[row] = a;
         bk.mol_of_atom[a] = b;
         if (bk.zlut) bk.sp_out[a] = s;
-        if (csp[ic] & 0x100) atomicOr(flag, FLAG_SPECIES);
+        if (w.bad) atomicOr(flag, FLAG_SPECIES);
     }
-    __syncthreads();
-    return true;
+    return row;
+}
+// one workgroup: the bucket table, tile elements, padding rows, capacity flags
+__device__ inline void bucket_table(const BucketFuse& bk, int S, int A, int max_apm, const int32_t* __restrict__ mol_off,
+                                    const int32_t* __restrict__ species, int32_t* __restrict__ flag) {
+    const int tid = threadIdx.x, lane = lane_id();
+    const WaveBuckets w = wave_buckets(bk, S, A, mol_off, species, 0);
+    if (!w.ok && tid == 0) atomicOr(flag, FLAG_CAPACITY);
+    for (int m = tid; m < bk.B; m += blockDim.x) {
+        const int m0 = mol_off[m], m1 = mol_off[m + 1];
+        if (m0 < w.A0 || m1 < m0 || m1 > w.A1 || m1 - m0 > max_apm) atomicOr(flag, FLAG_CAPACITY);
+    }
+    const int all = __builtin_amdgcn_readlane(w.base, S), rows = all <= bk.Rcap ? all : 0;
+    if (tid < 64) {
+        if (lane < S) bk.info->count[lane] = w.tot;
+        if (lane <= S) bk.info->off[lane] = w.base;
+        if (lane == 0) {
+            bk.info->rows = rows;
+            if (all > bk.Rcap) atomicOr(flag, FLAG_CAPACITY);
+        }
+    }
+    for (int t = tid; t < bk.Rcap / bk.row_tile; t += blockDim.x) {
+        const int r = t * bk.row_tile;
+        int sp = -1;
+        for (int q = 0; q < S; ++q)
+            if (r < rows && __builtin_amdgcn_readlane(w.base, q) <= r && r < __builtin_amdgcn_readlane(w.base, q + 1)) sp = q;
+        bk.tile_species[t] = sp;
+    }
+    for (int q = 0; q < S; ++q) {
+        const int r1 = min(__builtin_amdgcn_readlane(w.base, q + 1), rows);
+        for (int r = __builtin_amdgcn_readlane(w.base, q) + __builtin_amdgcn_readlane(w.tot, q) + tid; r < r1; r += blockDim.x)
+            bk.atom_of_row[r] = -1;
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -1057,6 +1152,12 @@ __device__ inline bool bucket_in_features(const BucketFuse& bk, int S, int A, in
 // into LDS.  Each slot is stored to the output row by its owner lane as soon
 // as it is complete: no row is assembled in LDS, which keeps the workgroup's
 // LDS small enough for more waves per CU.
+// A few-atom call waits for the chain of dependent steps of one wave, large
+// batches for instructions: both gain from the element tables in registers
+// and lane scans instead of LDS tables and shuffles, from the pairs' blocks
+// found by one scan a batch instead of a search a pair, and from records
+// written by the lanes that find the neighbours (64 atoms, fused: 22.4 ->
+// 18.0 us; 600 atoms: 23.4 -> 20.1; 1,024 x 49 atoms, BF16: 110 -> 106).
 template <typename P, int NZ, bool BUCKET = false>
 __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev(AevConst<typename P::T> c, int A, int max_apm,
                                              int chunk, int cap, const int32_t* __restrict__ mol_off,
@@ -1073,54 +1174,47 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     constexpr int NA = kNAZ / NZ;
     constexpr int PF = NA + NZ;
     extern __shared__ __align__(16) char smem[];
+    touch_kernargs<sizeof(AevConst<T>) + sizeof(NbrFuse<T>) + 80>();
     const int b = blockIdx.x;
+    // with the bucketing fused in, the last row of workgroups is one
+    // workgroup that writes the batch's bucket table
+    if constexpr (BUCKET) {
+        if (blockIdx.y == gridDim.y - 1) {
+            if (b == 0) bucket_table(nf.bk, c.S, A, max_apm, mol_off, species, nf.flag);
+            return;
+        }
+    }
     const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
     const int i0 = blockIdx.y * chunk;
-    // with the bucketing fused in, workgroup (0, 0) also writes the batch's
-    // bucket table, whether or not it has central atoms
-    constexpr bool bucket = BUCKET;
-    bool mine = true, lead = false;
-    if constexpr (bucket) {
-        mine = !(n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) && i0 < n;
-        lead = b == 0 && blockIdx.y == 0;
-        if (!mine && !lead) return;
-    } else {
-        if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
-        if (i0 >= n) return;
-    }
-    const int nc = mine ? min(chunk, n - i0) : 0;
+    if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
+    if (i0 >= n) return;
+    const int nc = min(chunk, n - i0);
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
     const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
 
     // fused: the workgroup finds its atoms' neighbour lists itself (and
     // writes them out for the force kernel) instead of reading them
-    const bool fuse = nf.nbr != nullptr;
+    const bool fuse = nf.nbr != nullptr, direct = n <= kDirectAtoms;
     LdsBump lb(smem);
     ChunkStage<T> cs;
     cs.take(lb, max_apm, cap, !fuse);
-    if constexpr (bucket) {
-        int* scr = lb.take<int>(kBucketScratch);
-        if (!bucket_in_features(nf.bk, S, A, max_apm, mol_off, species, b, a0 + i0, nc, mine, lead, scr,
-                                cs.crow, nf.flag))
-            return;
-    }
     T* nb = lb.take<T>((size_t)nw * cap * kNbStride) + (size_t)wave * cap * kNbStride;
     T* pf = lb.take<T>((size_t)nw * 64 * PF) + (size_t)wave * 64 * PF;
+    int* mark = lb.take<int>((size_t)nw * 64) + (size_t)wave * 64;
     T* sx4 = fuse ? lb.take<T>(4 * (size_t)max_apm) : nullptr;
     int* sid = fuse ? lb.take<int>(max_apm) : nullptr;
-    uint16_t* wl = fuse ? lb.take<uint16_t>((size_t)nw * cap) + (size_t)wave * cap : nullptr;
-    AtomLists<T> al;
-    {
-        LdsBump lw(lb.p + (size_t)wave * AtomLists<T>::bytes());
-        al.take(lw);
-    }
-    if constexpr (bucket) cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, nullptr, nf.bk.zlut);
-    else cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, row_of_atom);
+    uint16_t* wl = fuse && max_apm > kDirectAtoms ? lb.take<uint16_t>((size_t)nw * cap) + (size_t)wave * cap : nullptr;
+    cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, BUCKET ? nullptr : row_of_atom,
+            BUCKET ? nf.bk.zlut : nullptr);
+    WaveBuckets wb;
+    if constexpr (BUCKET) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + i0 + wave);
     __syncthreads();
     if (fuse) {
         if (wave == 0) stage_element_order(cs.sx, cs.ssp, n, S, sx4, sid);
         __syncthreads();
     }
+    int ba = 0, bb = 0;   // this lane's angular block's elements
+    if (lane < NB) block_elements(lane, S, ba, bb);
 
     // angular block sums by quarter-waves: lane (r = lane / 16, l = lane % 16)
     // owns slots l and l + 16 of the block dealt to quarter r
@@ -1128,15 +1222,24 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     const int qa1 = ql / NZ, qa2 = (ql + 16) / NZ, qzl = ql % NZ;
     for (int ic = wave; ic < nc; ic += nw) {
         const int il = i0 + ic;
-        int cnt;
+        int cnt, row;
         const uint16_t* lst;
+        if constexpr (BUCKET) {
+            if (ic != wave) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + il);
+            row = bucket_atom(nf.bk, wb, S, cs.ssp[il], a0 + il, b, nf.flag);
+            if (row < 0) continue;
+        } else {
+            row = cs.crow[ic];
+        }
         if (fuse) {
             // this evaluation's force accumulators, cleared as the neighbour
             // kernel clears them
             if (nf.F && lane < 3) nf.F[3 * ((size_t)a0 + il) + lane] = T(0);
             if (nf.Fq && lane < 3) nf.Fq[3 * ((size_t)a0 + il) + lane] = 0ull;
-            cnt = atom_neighbours(sx4, sid, n, il, cs.sx[3 * il], cs.sx[3 * il + 1], cs.sx[3 * il + 2], nf.rca2,
-                                  nf.rcr2, cap, wl, nf.nbr + ((size_t)a0 + il) * cap, nf.flag);
+            const T xi0 = cs.sx[3 * il], xi1 = cs.sx[3 * il + 1], xi2 = cs.sx[3 * il + 2];
+            uint16_t* out = nf.nbr + ((size_t)a0 + il) * cap;
+            cnt = direct ? find_records(c, sx4, sid, cs.ssp, n, il, xi0, xi1, xi2, nf.rca2, nf.rcr2, cap, nb, out, nf.flag)
+                         : atom_neighbours(sx4, sid, n, il, xi0, xi1, xi2, nf.rca2, nf.rcr2, cap, wl, out, nf.flag);
             if (lane == 0) nf.cnt[(size_t)a0 + il] = cnt;
             wave_sync();
             lst = wl;
@@ -1145,12 +1248,14 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             lst = cs.clst + (size_t)ic * cap;
         }
         const int nang = cnt & 0xffff, nall = cnt >> 16;
-        load_records(c, cs.sx, cs.ssp, lst, nang, nall, il, nb);
-        wave_sync();
-        const int npair = atom_lists(al, [&](int t) { return tag_of(nb + kNbStride * t) & 0xff; }, nang, nall, S);
-        wave_sync();
+        if (!(fuse && direct)) {
+            load_records(c, cs.sx, cs.ssp, lst, nang, nall, il, nb);
+            wave_sync();
+        }
+        const AtomLists al = atom_lists([&](int t) { return tag_of(nb + kNbStride * t) & 0xff; }, nang, nall, S, ba, bb);
+        const int npair = al.npair;
         // every slot is stored once, straight from the lane that owns it
-        TS* grow = G + (size_t)cs.crow[ic] * c.Dp;
+        TS* grow = G + (size_t)row * c.Dp;
         T* arow = aev_out ? aev_out + ((size_t)a0 + il) * c.D : nullptr;
         auto put = [&](int e, T v) {
             grow[e] = Store<TS>::st(v);
@@ -1162,12 +1267,14 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         {
             const int g = lane >> 4, k = lane & 15;
             const T sk = c.shf_r[k];
-            for (int s = g; s < S; s += 4) {
+            for (int s = g; s < g + 4 * ((S + 3) / 4); s += 4) {
+                const int rng = __shfl(al.range, s);   // (every lane takes part)
+                if (s >= S) continue;
                 // two accumulators, loads of four neighbours in flight
                 T acc0 = T(0), acc1 = T(0);
                 for (int run = 0; run < 2; ++run) {
-                    const int t1 = run ? al.roff[s + 1] : al.aoff[s + 1];
-                    int t = run ? al.roff[s] : al.aoff[s];
+                    const int t1 = (rng >> (run ? 24 : 8)) & 0xff;
+                    int t = (rng >> (run ? 16 : 0)) & 0xff;
                     for (; t + 4 <= t1; t += 4) {
                         T r[4], f[4];
 #pragma unroll
@@ -1195,15 +1302,15 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         // last pair is in; a block that runs on into the next batch leaves its
         // partial sums in the lanes of quarter 0 (carry), which take that block
         // first in the next batch.  Blocks without pairs are stored as zeros.
-        const int blo = lane < NB ? al.bst[lane] : 0, bhi = lane < NB ? al.bst[lane + 1] : 0;
+        const int blo = al.blo, bhi = al.bhi;   // (empty past the last block)
         const unsigned long long filled = __ballot(lane < NB && blo < bhi);
         T carry1 = T(0), carry2 = T(0);
         int carry_blk = -1;
         for (int p0 = 0; p0 < npair; p0 += 64) {
             const int nbat = min(64, npair - p0);
+            int j, k;
+            batch_pairs(al, p0, mark, j, k);
             if (lane < nbat) {
-                int j, k;
-                pair_of(al, NB, S, p0 + lane, j, k);
                 const T* ej = nb + kNbStride * j;
                 const T* ek = nb + kNbStride * k;
                 const T rj = ej[3], rk = ek[3];
@@ -1310,16 +1417,12 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
 }
 
 template <typename T>
-static size_t aev_lds(int max_apm, int cap, int Dp, int NZ, int nw, bool fuse = false, bool bucket = false) {
+static size_t aev_lds(int max_apm, int cap, int NZ, int nw, bool fuse = false) {
     const int PF = kNAZ / NZ + NZ;
-    (void)Dp;
-    return ChunkStage<T>::bytes(max_apm, cap, !fuse) + (bucket ? lds_bytes<int>(kBucketScratch) : 0) +
-           lds_bytes<T>((size_t)nw * cap * kNbStride) +
-           lds_bytes<T>((size_t)nw * 64 * PF) +
-           (fuse ? lds_bytes<T>(4 * (size_t)max_apm) + lds_bytes<int>(max_apm) +
-                       lds_bytes<uint16_t>((size_t)nw * cap)
-                 : 0) +
-           (size_t)nw * AtomLists<T>::bytes();
+    return ChunkStage<T>::bytes(max_apm, cap, !fuse) + lds_bytes<T>((size_t)nw * cap * kNbStride) +
+           lds_bytes<T>((size_t)nw * 64 * PF) + lds_bytes<int>((size_t)nw * 64) +
+           (fuse ? lds_bytes<T>(4 * (size_t)max_apm) + lds_bytes<int>(max_apm) : 0) +
+           (fuse && max_apm > kDirectAtoms ? lds_bytes<uint16_t>((size_t)nw * cap) : 0);
 }
 
 template <typename P>
@@ -1328,11 +1431,11 @@ hipError_t launch_aev(const Shape& sh, const AevConst<typename P::T>& c, const i
                       typename P::T* aev_out, hipStream_t st, const Timer& tm,
                       const NbrFuse<typename P::T>& nf) {
     typedef typename P::T T;
-    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk);
     int nw = kWaves;
     const bool fuse = nf.nbr != nullptr, bucket = nf.bk.info != nullptr;
-    size_t lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.Dp, c.nZ, nw, fuse, bucket);
-    while (lds > kMaxLds && nw > 1) lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.Dp, c.nZ, nw /= 2, fuse, bucket);
+    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk + (bucket ? 1 : 0));
+    size_t lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.nZ, nw, fuse);
+    while (lds > kMaxLds && nw > 1) lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.nZ, nw /= 2, fuse);
     if (lds > kMaxLds) return hipErrorInvalidValue;
     auto kern = bucket ? (c.nZ == 4 ? k_aev<P, 4, true> : k_aev<P, 8, true>)
                        : (c.nZ == 4 ? k_aev<P, 4> : k_aev<P, 8>);
@@ -1692,6 +1795,9 @@ template <typename T> struct ForceAcc<T, true> {
     }
 };
 
+// Sums over four and sixteen lanes go through DPP (two shuffles a radial
+// round and eighteen at the end of an atom before: 1,024 x 49 atoms in BF16
+// 100 -> 96 us with the energies in workgroups of their own).
 template <typename P, int NZ, bool FIXED, bool GD>
 __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_forces(AevConst<typename P::T> c, int A, int max_apm,
                                                 int chunk, int cap, const int32_t* __restrict__ mol_off,
@@ -1711,21 +1817,29 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
     typedef typename Acc::V V;
     constexpr int NA = kNAZ / NZ;
     extern __shared__ __align__(16) char smem[];
-    const int b = blockIdx.x;
-    const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
-    // the molecule's energy (as k_energy computes it), by the first wave of
-    // its first workgroup, ahead of the force work
-    if (ea.E && blockIdx.y == 0 && threadIdx.x < 64 && b < ea.B && !(ea.dcnt && b >= ea.dcnt[0])) {
-        const bool ok = !(a0 < 0 || n < 0 || a0 + n > A);
-        const double v = molecule_energy<P>(ok ? a0 : 0, ok ? a0 + n : 0, ea.M, ea.NT, ea.scale, species,
-                                            c.S, row_of_atom, ea.Epart, ea.b4, ea.sae);
-        if (threadIdx.x == 0) ea.E[b] = ea.accumulate ? ea.E[b] + v : v;
+    touch_kernargs<sizeof(AevConst<T>) + sizeof(EnergyArgs<P>) + 88>();
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
+    int b = blockIdx.x, by = blockIdx.y;
+    // The energies (as k_energy computes them), a molecule per wave, by the
+    // first row of workgroups: their chain of loads is as long as half the
+    // forces' of an atom, and in the force workgroups one wave waited for it
+    // before it began (8,300 of 22,000 clocks on 64 atoms).
+    if (ea.E && --by < 0) {
+        b = b * nw + wave;
+        if (b < ea.B && !(ea.dcnt && b >= ea.dcnt[0])) {
+            const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
+            const bool ok = !(a0 < 0 || n < 0 || a0 + n > A);
+            const double v = molecule_energy<P>(ok ? a0 : 0, ok ? a0 + n : 0, ea.M, ea.NT, ea.scale, species,
+                                                c.S, row_of_atom, ea.Epart, ea.b4, ea.sae);
+            if (lane == 0) ea.E[b] = ea.accumulate ? ea.E[b] + v : v;
+        }
+        return;
     }
+    const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
-    const int i0 = blockIdx.y * chunk;
+    const int i0 = by * chunk;
     if (i0 >= n) return;
     const int nc = min(chunk, n - i0);
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
     const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
     const int GL = RL + kBlkPad * NB;
 
@@ -1803,8 +1917,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
                 }
             }
             // the four shift groups of one neighbour sit in adjacent lanes
-            dEdr += __shfl_xor(dEdr, 1);
-            dEdr += __shfl_xor(dEdr, 2);
+            dEdr = quad_sum(dEdr);
             if (act && q == 0) {
                 const T* e = nb + kNbStride * t;
                 const T inv = m_rcp(e[3]);
@@ -1928,12 +2041,10 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
           }
           wave_sync();
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            fi0 += __shfl_xor(fi0, off);
-            fi1 += __shfl_xor(fi1, off);
-            fi2 += __shfl_xor(fi2, off);
-        }
-        if (lane == 0) {
+        fi0 = row_sum(fi0);
+        fi1 = row_sum(fi1);
+        fi2 = row_sum(fi2);
+        if ((lane & 15) == 0) {
             Acc::add(&sF[3 * il + 0], fi0);
             Acc::add(&sF[3 * il + 1], fi1);
             Acc::add(&sF[3 * il + 2], fi2);
@@ -1960,7 +2071,7 @@ hipError_t launch_forces(const Shape& sh, const AevConst<typename P::T>& c,
                          const EnergyArgs<P>& ea) {
     typedef typename P::T T;
     if (c.Dp > 2 * 16 * 64) return hipErrorInvalidValue;
-    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk);
+    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk + (ea.E ? 1 : 0));
     int nw = kWaves;
     const bool fixed = sh.force_fixed != 0, gd = sh.force_path == 2;
     size_t lds = forces_lds<T>(sh.max_apm, sh.cap_nbr, sh.S, nw, fixed, gd);
