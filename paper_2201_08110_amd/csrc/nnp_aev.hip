@@ -35,6 +35,11 @@ namespace nnp {
 // library functions.
 __device__ inline float m_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 __device__ inline double m_exp(double x) { return exp(x); }
+// e^x of x = u / log2_scale(): where a constant factor of x is known it takes
+// the scale, and the exponential is the bare instruction
+__device__ inline float m_exps(float u) { return __builtin_amdgcn_exp2f(u); }
+__device__ inline double m_exps(double u) { return exp(u); }
+template <typename T> constexpr T log2_scale() { return sizeof(T) == 4 ? T(1.44269504088896341) : T(1); }
 __device__ inline float m_cos(float x) { return __builtin_amdgcn_cosf(x * 0.159154943091895336f); }
 __device__ inline double m_cos(double x) { return cos(x); }
 __device__ inline float m_sin(float x) { return __builtin_amdgcn_sinf(x * 0.159154943091895336f); }
@@ -61,6 +66,9 @@ __device__ inline void gbl_add(float* p, float v) { unsafeAtomicAdd(p, v); }
 __device__ inline void gbl_add(double* p, double v) { unsafeAtomicAdd(p, v); }
 
 __device__ inline int lane_id() { return __lane_id(); }
+// a value that every lane of the wave holds, as the scalar it is: the loops
+// and addresses that it bounds are then scalar work, beside the lanes'
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Lane scans through DPP (a few clocks a step; a shuffle through the LDS is
 // over a hundred, and these chains are what a few-atom call waits for).
@@ -128,8 +136,8 @@ template <int BYTES> __device__ inline void touch_kernargs() {
 
 // upper-triangle index of the unordered element pair (b, c)
 __device__ inline int pair_index(int b, int c, int S) {
-    int lo = b < c ? b : c, hi = b < c ? c : b;
-    return lo * S - (lo * (lo - 1)) / 2 + (hi - lo);
+    const int lo = b < c ? b : c, hi = b < c ? c : b;
+    return (__mul24(lo, 2 * S - 1 - lo) >> 1) + hi;
 }
 
 // pair number p of the n(n-1)/2 pairs {j<k} of 0..n-1, row-major in j
@@ -709,7 +717,7 @@ __global__ __launch_bounds__(256) void k_nbr_pairs(int A, int S, int max_apm, in
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     const int i0 = blockIdx.y * chunk;
     if (i0 >= n) return;
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     LdsBump lb(smem);
     T* sx = lb.take<T>(4 * (size_t)max_apm);   // staged atoms x y z (element order)
     int* sid = lb.take<int>(max_apm);          // input index of the k-th staged atom
@@ -1189,7 +1197,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     if (i0 >= n) return;
     const int nc = min(chunk, n - i0);
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
 
     // fused: the workgroup finds its atoms' neighbour lists itself (and
@@ -1229,7 +1237,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             row = bucket_atom(nf.bk, wb, S, cs.ssp[il], a0 + il, b, nf.flag);
             if (row < 0) continue;
         } else {
-            row = cs.crow[ic];
+            row = uniform(cs.crow[ic]);
         }
         if (fuse) {
             // this evaluation's force accumulators, cleared as the neighbour
@@ -1244,7 +1252,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             wave_sync();
             lst = wl;
         } else {
-            cnt = cs.ccnt[ic];
+            cnt = uniform(cs.ccnt[ic]);
             lst = cs.clst + (size_t)ic * cap;
         }
         const int nang = cnt & 0xffff, nall = cnt >> 16;
@@ -1549,7 +1557,7 @@ __global__ __launch_bounds__(256) void k_aev_jvp(AevConst<typename P::T> c, int 
     const int i0 = blockIdx.y * chunk;
     if (i0 >= n) return;
     const int nc = min(chunk, n - i0);
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     const int S = c.S, RL = kNR * S;
 
     LdsBump lb(smem);
@@ -1569,7 +1577,7 @@ __global__ __launch_bounds__(256) void k_aev_jvp(AevConst<typename P::T> c, int 
 
     for (int ic = wave; ic < nc; ic += nw) {
         const int il = i0 + ic;
-        const int cnt = cs.ccnt[ic];
+        const int cnt = uniform(cs.ccnt[ic]);
         const int nang = cnt & 0xffff, nall = cnt >> 16;
         load_neighbours(c, cs.sx, cs.ssp, cs.clst + (size_t)ic * cap, nang, nall, il, nb, nsp, nid);
         wave_sync();
@@ -1673,7 +1681,7 @@ __global__ __launch_bounds__(256) void k_aev_jvp(AevConst<typename P::T> c, int 
         }
         if (cur >= 0) lds_add(row + cur + q, acc);
         wave_sync();
-        const size_t grow = (size_t)cs.crow[ic];
+        const size_t grow = (size_t)uniform(cs.crow[ic]);
         for (int e = lane; e < c.Dp; e += 64) Gd[grow * c.Dp + e] = Store<TS>::st(row[e]);
         wave_sync();
     }
@@ -1798,6 +1806,10 @@ template <typename T> struct ForceAcc<T, true> {
 // Sums over four and sixteen lanes go through DPP (two shuffles a radial
 // round and eighteen at the end of an atom before: 1,024 x 49 atoms in BF16
 // 100 -> 96 us with the energies in workgroups of their own).
+// A pair's contraction with its dE/dAEV block runs over the distance shifts
+// first, the cutoff values and the geometry once at the end: 332 -> 246 lane
+// instructions a pair besides its 20 transcendentals (64 atoms 15.7 -> 13.8
+// us, 1,024 x 49 atoms in BF16 96 -> 93).
 template <typename P, int NZ, bool FIXED, bool GD>
 __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_forces(AevConst<typename P::T> c, int A, int max_apm,
                                                 int chunk, int cap, const int32_t* __restrict__ mol_off,
@@ -1818,7 +1830,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
     constexpr int NA = kNAZ / NZ;
     extern __shared__ __align__(16) char smem[];
     touch_kernargs<sizeof(AevConst<T>) + sizeof(EnergyArgs<P>) + 88>();
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     int b = blockIdx.x, by = blockIdx.y;
     // The energies (as k_energy computes them), a molecule per wave, by the
     // first row of workgroups: their chain of loads is as long as half the
@@ -1858,15 +1870,16 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
     cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, row_of_atom);
     for (int t = tid; t < 3 * n; t += blockDim.x) sF[t] = V(0);
     __syncthreads();
+    const T nr = -c.eta_r * log2_scale<T>(), na = -c.eta_a * log2_scale<T>();
     for (int ic = wave; ic < nc; ic += nw) {
         const int il = i0 + ic;
-        const int cnt = cs.ccnt[ic];
+        const int cnt = uniform(cs.ccnt[ic]);
         const int nang = cnt & 0xffff, nall = cnt >> 16;
-        const TG* gsrc = dG + (size_t)cs.crow[ic] * c.Dp;
+        const TG* gsrc = dG + (size_t)uniform(cs.crow[ic]) * c.Dp;
         // the atom's dE/dAEV row: 16 values per lane and load, all in flight
         // before the first use; groups of 16 never straddle a block
         if constexpr (!GD) {
-            const TG* src = dG + (size_t)cs.crow[ic] * c.Dp;
+            const TG* src = dG + (size_t)uniform(cs.crow[ic]) * c.Dp;
             TA v[2][16];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -1909,12 +1922,16 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
                 } else {
                     ld4(g + kNR * st + 4 * q, gg);
                 }
+                // dG/dr = e (dfc - 2 eta d fc), the sums of g e and g e d apart
+                T s0 = T(0), s1 = T(0);
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {
                     const T d = r - c.shf_r[4 * q + kk];
-                    const T ex = c.radial_pref * m_exp(-c.eta_r * d * d);
-                    dEdr += gg[kk] * ex * (T(-2) * c.eta_r * d * fc + dfc);
+                    const T ge = gg[kk] * m_exps(nr * (d * d));
+                    s0 += ge;
+                    s1 += ge * d;
                 }
+                dEdr = c.radial_pref * (dfc * s0 + T(-2) * c.eta_r * fc * s1);
             }
             // the four shift groups of one neighbour sit in adjacent lanes
             dEdr = quad_sum(dEdr);
@@ -1939,6 +1956,13 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
         // (LDS atomic adds cost far more than stores and reads on gfx950).
         const int npair = nang * (nang - 1) / 2;
         const int full = nang * ((nang - 1) >> 1), D = (nang - 1) >> 1, half = nang >> 1;
+        const float inv_nang = __builtin_amdgcn_rcpf((float)nang);
+        auto diagonal = [&](int q) {   // 1 + q / nang
+            int d = (int)((float)q * inv_nang);
+            if (d * nang > q) --d;
+            if ((d + 1) * nang <= q) ++d;
+            return uniform(d + 1);
+        };
         for (int P0 = 0; P0 < npair; P0 += 64) {
           const int p = P0 + lane, nbat = min(64, npair - P0);
           if (p < npair) {
@@ -1948,9 +1972,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
             const T* ek = nb + kNbStride * k;
             const T rj = ej[3], rk = ek[3];
             const T ij = m_rcp(rj), ik = m_rcp(rk);
-            const T uj0 = ej[0] * ij, uj1 = ej[1] * ij, uj2 = ej[2] * ij;
-            const T uk0 = ek[0] * ik, uk1 = ek[1] * ik, uk2 = ek[2] * ik;
-            T cs_ = uj0 * uk0 + uj1 * uk1 + uj2 * uk2;
+            const T xj0 = ej[0], xj1 = ej[1], xj2 = ej[2], xk0 = ek[0], xk1 = ek[1], xk2 = ek[2];
+            T cs_ = (xj0 * xk0 + xj1 * xk1 + xj2 * xk2) * (ij * ik);
             cs_ = cs_ > T(1) ? T(1) : (cs_ < T(-1) ? T(-1) : cs_);
             const T cp = c.angle_scale * cs_;
             const T sn = m_sqrt(T(1) - cp * cp);
@@ -1961,23 +1984,26 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
             const int pb = RL + BS * pair_index(tj & 0xff, tk & 0xff, S);
             const T* gb = GD ? nullptr : g + pb;
             T fz[NZ], dfz[NZ];
+            // d cos(theta'-t)/dc = s (cos t - c' sin t / sqrt(1 - c'^2))
+            const T cot = cp * m_rcp(sn), zs = c.zeta * c.angle_scale;
 #pragma unroll
             for (int z = 0; z < NZ; ++z) {
                 const T cz = cp * c.cos_z[z] + sn * c.sin_z[z];
-                const T hh = T(0.5) * (T(1) + cz);
+                const T hh = T(0.5) * cz + T(0.5);
                 const T hp = m_powu(hh, c.zeta - T(1));
-                fz[z] = T(2) * hp * hh;
-                // d cos(theta'-t)/dc = s (cos t - c' sin t / sqrt(1 - c'^2))
-                const T dcz = c.angle_scale * (c.cos_z[z] - cp * c.sin_z[z] * m_rcp(sn));
-                dfz[z] = c.zeta * hp * dcz;
+                fz[z] = hp * hh;   // (the factor 2 below)
+                dfz[z] = hp * (c.cos_z[z] - cot * c.sin_z[z]);
             }
-            T Dc = 0, Drj = 0, Drk = 0;
+            // dE/d(angle, distance) = sum of g[a][z] e_a f_z and its two
+            // derivatives: contracted over the shifts a first (P with e_a, Q
+            // with d e_a), the cutoff values at the end
+            T P_[NZ], Q_[NZ];
+#pragma unroll
+            for (int z = 0; z < NZ; ++z) P_[z] = Q_[z] = T(0);
 #pragma unroll
             for (int a = 0; a < NA; ++a) {
                 const T d = rm - c.shf_a[a];
-                const T fa = m_exp(-c.eta_a * d * d);
-                const T dfa_half = -c.eta_a * d * fa;   // d fa / d r_ij (= d/d r_ik)
-                T sg = 0, sgd = 0;
+                const T fa = m_exps(na * (d * d)), da = d * fa;
 #pragma unroll
                 for (int z4 = 0; z4 < NZ; z4 += 4) {
                     T gg[4];
@@ -1991,21 +2017,32 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
                     }
 #pragma unroll
                     for (int z = 0; z < 4; ++z) {
-                        sg += gg[z] * fz[z4 + z];
-                        sgd += gg[z] * dfz[z4 + z];
+                        P_[z4 + z] += gg[z] * fa;
+                        Q_[z4 + z] += gg[z] * da;
                     }
                 }
-                Dc += sgd * fa * fcc;
-                Drj += sg * (dfa_half * fcc + fa * dfcj * fck);
-                Drk += sg * (dfa_half * fcc + fa * fcj * dfck);
             }
-            // dc/dx_j = (u_k - c u_j)/r_j ; dc/dx_k = (u_j - c u_k)/r_k
-            const T gj0 = Drj * uj0 + Dc * (uk0 - cs_ * uj0) * ij;
-            const T gj1 = Drj * uj1 + Dc * (uk1 - cs_ * uj1) * ij;
-            const T gj2 = Drj * uj2 + Dc * (uk2 - cs_ * uj2) * ij;
-            const T gk0 = Drk * uk0 + Dc * (uj0 - cs_ * uk0) * ik;
-            const T gk1 = Drk * uk1 + Dc * (uj1 - cs_ * uk1) * ik;
-            const T gk2 = Drk * uk2 + Dc * (uj2 - cs_ * uk2) * ik;
+            T Sf = T(0), Sa = T(0), Sd = T(0);
+#pragma unroll
+            for (int z = 0; z < NZ; ++z) {
+                Sf += P_[z] * fz[z];
+                Sa += Q_[z] * fz[z];
+                Sd += P_[z] * dfz[z];
+            }
+            Sf *= T(2);
+            Sa *= T(-2) * c.eta_a * fcc;   // d e_a / d r_ij = -eta d e_a (= d / d r_ik)
+            const T Dc = zs * fcc * Sd;
+            const T Drj = Sa + Sf * (dfcj * fck), Drk = Sa + Sf * (fcj * dfck);
+            // dc/dx_j = (u_k - c u_j)/r_j ; dc/dx_k = (u_j - c u_k)/r_k, with
+            // u = x / r
+            const T dcc = Dc * ij * ik;
+            const T fj = (Drj - Dc * cs_ * ij) * ij, fk = (Drk - Dc * cs_ * ik) * ik;
+            const T gj0 = fj * xj0 + dcc * xk0;
+            const T gj1 = fj * xj1 + dcc * xk1;
+            const T gj2 = fj * xj2 + dcc * xk2;
+            const T gk0 = fk * xk0 + dcc * xj0;
+            const T gk1 = fk * xk1 + dcc * xj1;
+            const T gk2 = fk * xk2 + dcc * xj2;
             T* o = pg + 6 * lane;
             o[0] = gj0; o[1] = gj1; o[2] = gj2;
             o[3] = gk0; o[4] = gk1; o[5] = gk2;
@@ -2016,10 +2053,9 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
           wave_sync();
           // diagonals of this batch: pair q = (d-1) n + a on diagonal d <= D,
           // q = full + a on the half diagonal d = n/2 of an even n
-          const int d0 = P0 < full ? P0 / nang + 1 : half;
-          const int d1 = P0 + nbat - 1 < full ? (P0 + nbat - 1) / nang + 1 : half;
+          const int d0 = P0 < full ? diagonal(P0) : half, d1 = P0 + nbat - 1 < full ? diagonal(P0 + nbat - 1) : half;
           for (int u = lane; u < 3 * nang; u += 64) {
-            const int t = u / 3, cc = u - 3 * t;
+            const int t = (u * 21846) >> 16, cc = u - 3 * t;   // u / 3
             T sum = T(0);
             for (int d = d0; d <= d1; ++d) {
               int qj, qk;   // the pairs (t, t+d) and (t-d, t)
@@ -2157,7 +2193,7 @@ __global__ __launch_bounds__(256) void k_forces_tan(AevConst<typename P::T> c, i
     const int i0 = blockIdx.y * chunk;
     if (i0 >= n) return;
     const int nc = min(chunk, n - i0);
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
     const int GL = RL + kBlkPad * NB;
 
@@ -2179,11 +2215,11 @@ __global__ __launch_bounds__(256) void k_forces_tan(AevConst<typename P::T> c, i
     __syncthreads();
     for (int ic = wave; ic < nc; ic += nw) {
         const int il = i0 + ic;
-        const int cnt = cs.ccnt[ic];
+        const int cnt = uniform(cs.ccnt[ic]);
         const int nang = cnt & 0xffff, nall = cnt >> 16;
         // the atom's dE/dAEV row, laid out as in k_forces
         {
-            const TA* src = dG + (size_t)cs.crow[ic] * c.Dp;
+            const TA* src = dG + (size_t)uniform(cs.crow[ic]) * c.Dp;
             for (int e = lane; e < c.D; e += 64) {
                 const int le = e < RL ? e : RL + kBlkPad * ((e - RL) / kNAZ) + (e - RL) % kNAZ;
                 g[le] = (T)src[e];
