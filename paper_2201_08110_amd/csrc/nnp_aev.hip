@@ -107,7 +107,7 @@ template <int CTRL> __device__ inline double dpp_of(double v) {
     return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
                             __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
 }
-constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kHalfMirror = 0x141, kRowMirror = 0x140;
+constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kHalfMirror = 0x141, kRowMirror = 0x140, kRowRor8 = 0x128;
 template <typename T> __device__ inline T quad_sum(T v) {
     v += dpp_of<kXor1>(v);
     return v + dpp_of<kXor2>(v);
@@ -969,13 +969,16 @@ static_assert(kMaxNeighbours < 256, "list positions in 8 bits");
 
 // elements (a, b), a <= b, of the angular block with triangular index L
 __device__ inline void block_elements(int L, int S, int& a, int& b) {
-    int base = 0, aa = 0;
-    while (aa < S - 1 && L >= base + (S - aa)) {
-        base += S - aa;
-        ++aa;
+    int start = 0, base = 0;
+    a = 0;
+    for (int r = 1; r < S; ++r) {   // row r's first block
+        start += S - r + 1;
+        if (L >= start) {
+            a = r;
+            base = start;
+        }
     }
-    a = aa;
-    b = aa + (L - base);
+    b = a + (L - base);
 }
 
 // The lists of one atom (wave-wide); sp_of(t) = element of neighbour t, (ba,
@@ -985,19 +988,19 @@ __device__ inline void block_elements(int L, int S, int& a, int& b) {
 template <typename SpOf>
 __device__ inline AtomLists atom_lists(SpOf sp_of, int nang, int nall, int S, int ba, int bb) {
     const int lane = lane_id();
-    int ao = 0, ro = nang;   // lane s <= S
+    int before = 0;   // lane s <= S: smaller elements' neighbours, angular | radial-only << 16
     for (int t0 = 0; t0 < nall; t0 += 64) {
         const int sp = t0 + lane < nall ? sp_of(t0 + lane) : kMaxSpecies;
         const int na = min(max(nang - t0, 0), 64);
         const unsigned long long ang = na == 64 ? ~0ull : (1ull << na) - 1;
         for (int s = 1; s <= S; ++s) {
             const unsigned long long m = __ballot(sp < s);
-            const int ca = __popcll(m & ang), cr = __popcll(m & ~ang);
-            ao += lane == s ? ca : 0;
-            ro += lane == s ? cr : 0;
+            const int both = __popcll(m & ang) | __popcll(m & ~ang) << 16;
+            before += lane == s ? both : 0;
         }
     }
     AtomLists al;
+    const int ao = before & 0xffff, ro = nang + (before >> 16);
     const int ae = next_lane(ao);
     al.range = ao | (ae << 8) | (ro << 16) | (next_lane(ro) << 24);
     // angular block sizes and their prefix
@@ -1033,18 +1036,177 @@ __device__ inline void batch_pairs(const AtomLists& al, int p0, int* mark, int& 
         const float t = (float)(2 * nb - 1);
         int jj = (int)((t - __builtin_amdgcn_sqrtf(fmaxf(t * t - 8.0f * (float)u, 0.0f))) * 0.5f);
         jj = min(max(jj, 0), nb - 2);
-        if (jj > 0 && (jj * (2 * nb - jj - 1)) / 2 > u) --jj;
-        if (jj + 1 <= nb - 2 && ((jj + 1) * (2 * nb - jj - 2)) / 2 <= u) ++jj;
+        if (jj > 0 && __mul24(jj, 2 * nb - jj - 1) >> 1 > u) --jj;
+        if (jj + 1 <= nb - 2 && __mul24(jj + 1, 2 * nb - jj - 2) >> 1 <= u) ++jj;
         j = fa + jj;
-        k = fa + u - (jj * (2 * nb - jj - 1)) / 2 + jj + 1;
+        k = fa + u - (__mul24(jj, 2 * nb - jj - 1) >> 1) + jj + 1;
     } else {
         // u / nb through the float reciprocal, corrected (u < 2^16)
         int q = (int)((float)u * __builtin_amdgcn_rcpf((float)nb));
-        if (q * nb > u) --q;
-        if ((q + 1) * nb <= u) ++q;
+        if (__mul24(q, nb) > u) --q;
+        if (__mul24(q + 1, nb) <= u) ++q;
         j = fa + q;
-        k = fb + (u - q * nb);
+        k = fb + (u - __mul24(q, nb));
     }
+}
+
+__device__ inline void st4(float* p, const float v[4]) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ inline void st4(double* p, const double v[4]) {
+    *(double2*)p = make_double2(v[0], v[1]);
+    *(double2*)(p + 2) = make_double2(v[2], v[3]);
+}
+
+// AEV slots on the matrix cores (FP32 arithmetic).  v_mfma_f32_4x4x1 adds, to
+// each of sixteen 4 x 4 blocks, the product of a column and a row: every
+// element is one fused multiply-add, bit for bit the vector instruction's, so
+// a slot's terms are summed in the order and in the two alternating sums of
+// the plain loops.  Block q sits in lanes 4 q ... 4 q + 3: lane 4 q + i brings
+// row i's factor and column i's, and holds column i of the result.
+constexpr int kRadU = 2, kAngU = 2;        // neighbours, and pairs of a sum, loaded together
+constexpr int kPairRoom = 2 * (kAngU - 1);
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ inline f32x4 mfma_4x4(float row, float col, f32x4 acc) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(row, col, acc, 0, 0, 0);
+}
+__device__ inline void put2(float* p, float a, float b) { *(float2*)p = make_float2(a, b); }
+__device__ inline void put2(bf16_t* p, float a, float b) { *(uint32_t*)p = pack_bf16x2(a, b); }
+__device__ inline void put4(float* p, f32x4 v) { *(f32x4*)p = v; }
+__device__ inline void put4(bf16_t* p, f32x4 v) {
+    *(uint2*)p = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+}
+
+// Radial slots of one atom.  A slot (s, k) has two sums: of a run of element
+// s's neighbours, whole groups of four alternate between them and the rest go
+// to the first.  Every row of sixteen lanes takes the neighbours of one of the
+// sums and of the even or the odd elements in order, a lane per shift: four
+// blocks of 4 shifts x 4 elements, the column factor being the cutoff for the
+// neighbour's element and zero for the others.  lst: 4 x kRadSlice entries of
+// this wave's LDS.
+constexpr int kRadSlice = 48;   // neighbours listed at once
+template <typename TS>
+__device__ inline void radial_rows(const AevConst<float>& c, const AtomLists& al, const float* nb, int nang, int nall,
+                                   f32x4* lst, TS* grow, float* arow) {
+    const int lane = lane_id();
+    const unsigned long long lt = below(lane);
+    const int k = lane & 15, j = lane & 3, s = 2 * j + (lane >> 4 & 1);
+    const float sk = c.shf_r[k];
+    f32x4* mine = lst + (lane >> 4) * kRadSlice;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int t0 = 0; t0 < nall; t0 += kRadSlice) {
+        const int t = t0 + lane;
+        const bool act = lane < kRadSlice && t < nall;
+        const float* e = nb + kNbStride * (act ? t : 0);
+        const int sp = tag_of(e) & 0xff, rng = __shfl(al.range, sp) >> (t < nang ? 0 : 16);
+        const int p = t - (rng & 0xff), n = (rng >> 8 & 0xff) - (rng & 0xff);
+        const bool second = p < (n & ~3) && (p & 1);
+        const unsigned long long ma = __ballot(act), ms = __ballot(second), mo = __ballot(sp & 1);
+        const unsigned long long m0 = ma & ~ms & ~mo, m1 = ma & ~ms & mo, m2 = ma & ms & ~mo, m3 = ma & ms & mo;
+        const int most = max(max(__popcll(m0), __popcll(m1)), max(__popcll(m2), __popcll(m3)));
+        const int nmax = (most + kRadU - 1) / kRadU * kRadU;
+        const f32x4 none = {0.f, 0.f, __int_as_float(-1), 0.f};
+        for (int i = 0; i < nmax; i += 16) mine[min(i + k, kRadSlice - 1)] = none;
+        const unsigned long long md = (second ? ms : ~ms) & (sp & 1 ? mo : ~mo) & ma & lt;
+        if (act) lst[((second ? 2 : 0) + (sp & 1)) * kRadSlice + __popcll(md)] = f32x4{e[3], e[4], __int_as_float(sp >> 1), 0.f};
+        wave_sync();
+        for (int i = 0; i < nmax; i += kRadU) {
+            f32x4 v[kRadU];
+            float ex[kRadU], f[kRadU];
+#pragma unroll
+            for (int u = 0; u < kRadU; ++u) v[u] = mine[i + u];
+#pragma unroll
+            for (int u = 0; u < kRadU; ++u) {
+                const float d = v[u][0] - sk;
+                ex[u] = m_exp(-c.eta_r * d * d);
+                f[u] = __float_as_int(v[u][2]) == j ? v[u][1] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < kRadU; ++u) acc = mfma_4x4(ex[u], f[u], acc);
+        }
+        wave_sync();
+    }
+    // first + second sums: rows 0, 1 in the lower half, 2, 3 in the upper
+    auto both = [&](float lo, float hi) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+        return c.radial_pref * (__uint_as_float(r[0]) + __uint_as_float(r[1]));
+    };
+    const float v0 = both(acc[0], acc[2]), v1 = both(acc[1], acc[3]);
+    const int slot = kNR * s + (k & 12) + (lane >> 5) * 2;
+    if (s < c.S) {
+        put2(grow + slot, v0, v1);
+        if (arow) {
+            arow[slot] = v0;
+            arow[slot + 1] = v1;
+        }
+    }
+}
+
+// Angular slots from a batch of pairs [p0, p0 + nbat) whose factors are in pf
+// (PF a pair: NA distance, NZ angle).  The element blocks that meet the batch
+// are taken four at a time, sixteen lanes each: two sums of the alternate
+// pairs, each of two 4 x 4 blocks.  A block's slots are stored when its last
+// pair is in; one that runs on leaves its sums in carry (every row of sixteen
+// lanes), and is the first of the next batch.  lst: 64 integers of this
+// wave's LDS.
+template <int NA, int NZ, typename TS>
+__device__ inline void angular_rows(const AtomLists& al, int p0, int nbat, const float* pf, int* lst, f32x4& carry,
+                                    TS* gang, float* aang) {
+    constexpr int PF = NA + NZ;
+    const int lane = lane_id(), pe = p0 + nbat;
+    const bool live = al.blo < al.bhi && al.blo < pe && al.bhi > p0;
+    const unsigned long long lm = __ballot(live);
+    const int nlive = __popcll(lm);
+    lst[lane] = 0;
+    if (live)
+        lst[__popcll(lm & below(lane))] = lane | (max(al.blo, p0) - p0) << 8 | (min(al.bhi, pe) - p0) << 16 |
+                                          (al.bhi > pe ? 1 << 24 : 0) | (al.blo < p0 ? 1 << 25 : 0);
+    wave_sync();
+    const int par = lane >> 3 & 1, half = lane >> 2 & 1, i4 = lane & 3;
+    const int zi = (NZ == 8 ? 4 * half : 0) + i4, ai = (NA == 8 ? 4 * half : 0) + i4;
+    f32x4 onward = {0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < nlive; q += 4) {
+        const int w = lst[q + (lane >> 4)], s0 = w >> 8 & 0xff, e0 = w >> 16 & 0xff, len = e0 - s0;
+        const int most = max(max(__builtin_amdgcn_readlane(len, 0), __builtin_amdgcn_readlane(len, 16)),
+                             max(__builtin_amdgcn_readlane(len, 32), __builtin_amdgcn_readlane(len, 48)));
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        // past a sum's last pair both factors are zero; the addresses end in
+        // the kPairRoom pairs that pf has beyond the batch's
+        int at = PF * min(s0 + par, 63);
+        const int left = len - par;
+        for (int o = 0; o < most; o += 2 * kAngU) {
+            const float* f = pf + at;
+            float r[kAngU], k[kAngU];
+#pragma unroll
+            for (int u = 0; u < kAngU; ++u) {
+                r[u] = f[2 * PF * u + NA + zi];
+                k[u] = f[2 * PF * u + ai];
+            }
+#pragma unroll
+            for (int u = 0; u < kAngU; ++u) {
+                const bool in = o + 2 * u < left;
+                acc = mfma_4x4(in ? r[u] : 0.f, in ? k[u] : 0.f, acc);
+            }
+            at = min(at + 2 * PF * kAngU, PF * 63);
+        }
+        f32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = acc[i] + dpp_of<kRowRor8>(acc[i]);
+        if (w & 1 << 25) v += carry;
+        if (w & 1 << 24) onward = v;
+        else if (len > 0 && par == 0) {
+            const int slot = kNAZ * (w & 0xff) + NZ * ai + (NZ == 8 ? 4 * half : 0);
+            put4(gang + slot, v);
+            if (aang)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) aang[slot + i] = v[i];
+        }
+    }
+    // the block that runs on is the batch's last: its rank mod 4 is its row
+    const int from = 16 * ((nlive - 1) & 3) + (lane & 15);
+    if (__ballot(live && al.bhi > pe)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) carry[i] = __shfl(onward[i], from);
+    }
+    wave_sync();
 }
 
 // Bucketing inside the featuriser, for batches of at most kPrepBlock atoms and
@@ -1151,22 +1313,26 @@ __device__ inline void bucket_table(const BucketFuse& bk, int S, int A, int max_
 // --------------------------------------------------------------------------
 // AEV forward.  One wave per central atom; the output row of atom a goes to
 // G[row_of_atom[a]] in the GEMM operand type, optionally also to aev_out[a]
-// (atom order, unpadded).  Every AEV slot is owned by one lane: radial slot
-// (s, k) by lane (group s % 4, shift k) summing over the neighbours of
-// element s; angular slots l and l + 16 of a block by lane l of one
-// quarter-wave (the blocks meeting a 64-pair batch are dealt to the four
-// quarters in turn, and a block's pairs are contiguous).  Pair factors (NA distance
-// terms, NZ angle terms) are computed once per pair, 64 pairs at a time,
-// into LDS.  Each slot is stored to the output row by its owner lane as soon
-// as it is complete: no row is assembled in LDS, which keeps the workgroup's
-// LDS small enough for more waves per CU.
+// (atom order, unpadded).  Pair factors (NA distance terms, NZ angle terms)
+// are computed once per pair, 64 pairs at a time, into LDS.  FP32 arithmetic
+// sums the slots on the matrix cores (radial_rows, angular_rows); in FP64,
+// whose smallest matrix product already adds four terms, every slot has an
+// owner lane that runs the plain loops.  A slot is stored to the output row as
+// soon as it is complete: no row is assembled in LDS, which keeps the
+// workgroup's LDS small enough for more waves per CU.
 // A few-atom call waits for the chain of dependent steps of one wave, large
 // batches for instructions: both gain from the element tables in registers
 // and lane scans instead of LDS tables and shuffles, from the pairs' blocks
 // found by one scan a batch instead of a search a pair, and from records
 // written by the lanes that find the neighbours (64 atoms, fused: 22.4 ->
-// 18.0 us; 600 atoms: 23.4 -> 20.1; 1,024 x 49 atoms, BF16: 110 -> 106).
-template <typename P, int NZ, bool BUCKET = false>
+// 18.0 us; 600 atoms: 23.4 -> 20.1; 1,024 x 48 atoms, BF16: 110 -> 106), and
+// from the sums on the matrix cores, where a term costs one instruction and
+// two LDS reads for all its slots (18.0 -> 15.2 us; 106 -> 100; 512 molecules
+// of 10 to 120 atoms 111 -> 97).  Large batches are bound by the lanes'
+// instructions, 900 an atom.
+// neighbour lists given, found here, or found here with the bucketing too
+constexpr int kLists = 0, kSearch = 1, kBuckets = 2;
+template <typename P, int NZ, int MODE>
 __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev(AevConst<typename P::T> c, int A, int max_apm,
                                              int chunk, int cap, const int32_t* __restrict__ mol_off,
                                              const int32_t* __restrict__ species,
@@ -1186,7 +1352,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     const int b = blockIdx.x;
     // with the bucketing fused in, the last row of workgroups is one
     // workgroup that writes the batch's bucket table
-    if constexpr (BUCKET) {
+    if constexpr (MODE == kBuckets) {
         if (blockIdx.y == gridDim.y - 1) {
             if (b == 0) bucket_table(nf.bk, c.S, A, max_apm, mol_off, species, nf.flag);
             return;
@@ -1202,22 +1368,23 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
 
     // fused: the workgroup finds its atoms' neighbour lists itself (and
     // writes them out for the force kernel) instead of reading them
-    const bool fuse = nf.nbr != nullptr, direct = n <= kDirectAtoms;
+    constexpr bool fuse = MODE != kLists;
+    const bool direct = n <= kDirectAtoms;
     LdsBump lb(smem);
     ChunkStage<T> cs;
     cs.take(lb, max_apm, cap, !fuse);
     T* nb = lb.take<T>((size_t)nw * cap * kNbStride) + (size_t)wave * cap * kNbStride;
-    T* pf = lb.take<T>((size_t)nw * 64 * PF) + (size_t)wave * 64 * PF;
+    T* pf = lb.take<T>((size_t)nw * (64 + kPairRoom) * PF) + (size_t)wave * (64 + kPairRoom) * PF;
     int* mark = lb.take<int>((size_t)nw * 64) + (size_t)wave * 64;
     T* sx4 = fuse ? lb.take<T>(4 * (size_t)max_apm) : nullptr;
     int* sid = fuse ? lb.take<int>(max_apm) : nullptr;
     uint16_t* wl = fuse && max_apm > kDirectAtoms ? lb.take<uint16_t>((size_t)nw * cap) + (size_t)wave * cap : nullptr;
-    cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, BUCKET ? nullptr : row_of_atom,
-            BUCKET ? nf.bk.zlut : nullptr);
+    cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, MODE == kBuckets ? nullptr : row_of_atom,
+            MODE == kBuckets ? nf.bk.zlut : nullptr);
     WaveBuckets wb;
-    if constexpr (BUCKET) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + i0 + wave);
+    if constexpr (MODE == kBuckets) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + i0 + wave);
     __syncthreads();
-    if (fuse) {
+    if constexpr (fuse) {
         if (wave == 0) stage_element_order(cs.sx, cs.ssp, n, S, sx4, sid);
         __syncthreads();
     }
@@ -1232,14 +1399,14 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         const int il = i0 + ic;
         int cnt, row;
         const uint16_t* lst;
-        if constexpr (BUCKET) {
+        if constexpr (MODE == kBuckets) {
             if (ic != wave) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + il);
             row = bucket_atom(nf.bk, wb, S, cs.ssp[il], a0 + il, b, nf.flag);
             if (row < 0) continue;
         } else {
             row = uniform(cs.crow[ic]);
         }
-        if (fuse) {
+        if constexpr (fuse) {
             // this evaluation's force accumulators, cleared as the neighbour
             // kernel clears them
             if (nf.F && lane < 3) nf.F[3 * ((size_t)a0 + il) + lane] = T(0);
@@ -1271,8 +1438,11 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         };
         for (int e = c.D + lane; e < c.Dp; e += 64) grow[e] = Store<TS>::st(T(0));
 
-        // ---- radial: lane (group g, shift k) owns slots (s, k), s = g mod 4
-        {
+        // ---- radial
+        if constexpr (sizeof(T) == 4) {
+            radial_rows(c, al, nb, nang, nall, (f32x4*)pf, grow, arow);
+        } else {
+            // lane (group g, shift k) owns slots (s, k), s = g mod 4
             const int g = lane >> 4, k = lane & 15;
             const T sk = c.shf_r[k];
             for (int s = g; s < g + 4 * ((S + 3) / 4); s += 4) {
@@ -1314,6 +1484,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         const unsigned long long filled = __ballot(lane < NB && blo < bhi);
         T carry1 = T(0), carry2 = T(0);
         int carry_blk = -1;
+        f32x4 carry = {0.f, 0.f, 0.f, 0.f};
         for (int p0 = 0; p0 < npair; p0 += 64) {
             const int nbat = min(64, npair - p0);
             int j, k;
@@ -1328,7 +1499,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
                 const T sn = m_sqrt(T(1) - cp * cp);
                 const T fcc = ej[6] * ek[6];
                 const T rm = T(0.5) * (rj + rk);
-                T* f = pf + PF * lane;
+                T f[PF];
 #pragma unroll
                 for (int a = 0; a < NA; ++a) {
                     const T d = rm - c.shf_a[a];
@@ -1339,74 +1510,80 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
                     const T cz = cp * c.cos_z[z] + sn * c.sin_z[z];
                     f[NA + z] = T(2) * m_powu(T(0.5) * (T(1) + cz), c.zeta);
                 }
+#pragma unroll
+                for (int u = 0; u < PF; u += 4) st4(pf + PF * lane + u, f + u);
             }
             wave_sync();
-            // blocks meeting this batch, taken four at a time, one per
-            // quarter-wave, each quarter summing its block's pairs in order
-            // (two pairs' factors in flight)
-            const int pe_ = p0 + nbat;
-            const unsigned long long live = __ballot(lane < NB && blo < bhi && blo < pe_ && bhi > p0);
-            const unsigned long long goes_on = __ballot(lane < NB && blo < bhi && blo < pe_ && bhi > pe_);
-            T nc1 = T(0), nc2 = T(0);
-            for (unsigned long long mset = live; mset;) {
-                int bq[4], lq[4], hq[4];
+            if constexpr (sizeof(T) == 4) {
+                angular_rows<NA, NZ>(al, p0, nbat, pf, mark, carry, grow + RL, arow ? arow + RL : nullptr);
+            } else {
+                // blocks meeting this batch, taken four at a time, one per
+                // quarter-wave, each quarter summing its block's pairs in order
+                // (two pairs' factors in flight)
+                const int pe_ = p0 + nbat;
+                const unsigned long long live = __ballot(lane < NB && blo < bhi && blo < pe_ && bhi > p0);
+                const unsigned long long goes_on = __ballot(lane < NB && blo < bhi && blo < pe_ && bhi > pe_);
+                T nc1 = T(0), nc2 = T(0);
+                for (unsigned long long mset = live; mset;) {
+                    int bq[4], lq[4], hq[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    bq[r] = mset ? __builtin_ctzll(mset) : -1;
-                    lq[r] = bq[r] >= 0 ? __builtin_amdgcn_readlane(blo, bq[r]) : 0;
-                    hq[r] = bq[r] >= 0 ? __builtin_amdgcn_readlane(bhi, bq[r]) : 0;
-                    mset &= mset - 1;
-                }
-                const int bl = qr == 0 ? bq[0] : (qr == 1 ? bq[1] : (qr == 2 ? bq[2] : bq[3]));
-                const int lo = qr == 0 ? lq[0] : (qr == 1 ? lq[1] : (qr == 2 ? lq[2] : lq[3]));
-                const int hi = qr == 0 ? hq[0] : (qr == 1 ? hq[1] : (qr == 2 ? hq[2] : hq[3]));
-                const int s0 = bl < 0 ? 0 : max(lo, p0) - p0;
-                const int e0 = bl < 0 ? 0 : min(hi, pe_) - p0;
-                T a1 = T(0), a2 = T(0), b1 = T(0), b2 = T(0);
-                int p = s0;
-                for (; p + 2 <= e0; p += 2) {
-                    const T* f0 = pf + PF * p;
-                    const T* f1 = f0 + PF;
-                    const T z0 = f0[NA + qzl], z1 = f1[NA + qzl];
-                    const T x1 = f0[qa1], x2 = f0[qa2], y1 = f1[qa1], y2 = f1[qa2];
-                    a1 += x1 * z0;
-                    a2 += x2 * z0;
-                    b1 += y1 * z1;
-                    b2 += y2 * z1;
-                }
-                if (p < e0) {
-                    const T* f0 = pf + PF * p;
-                    const T z0 = f0[NA + qzl];
-                    a1 += f0[qa1] * z0;
-                    a2 += f0[qa2] * z0;
-                }
-                T v1 = a1 + b1, v2 = a2 + b2;
-                if (bl == carry_blk) {
-                    v1 += carry1;
-                    v2 += carry2;
-                }
-                if (s0 < e0) {
-                    if (hi > pe_) {
-                        nc1 = v1;
-                        nc2 = v2;
-                    } else {
-                        put(RL + kNAZ * bl + ql, v1);
-                        put(RL + kNAZ * bl + ql + 16, v2);
+                    for (int r = 0; r < 4; ++r) {
+                        bq[r] = mset ? __builtin_ctzll(mset) : -1;
+                        lq[r] = bq[r] >= 0 ? __builtin_amdgcn_readlane(blo, bq[r]) : 0;
+                        hq[r] = bq[r] >= 0 ? __builtin_amdgcn_readlane(bhi, bq[r]) : 0;
+                        mset &= mset - 1;
+                    }
+                    const int bl = qr == 0 ? bq[0] : (qr == 1 ? bq[1] : (qr == 2 ? bq[2] : bq[3]));
+                    const int lo = qr == 0 ? lq[0] : (qr == 1 ? lq[1] : (qr == 2 ? lq[2] : lq[3]));
+                    const int hi = qr == 0 ? hq[0] : (qr == 1 ? hq[1] : (qr == 2 ? hq[2] : hq[3]));
+                    const int s0 = bl < 0 ? 0 : max(lo, p0) - p0;
+                    const int e0 = bl < 0 ? 0 : min(hi, pe_) - p0;
+                    T a1 = T(0), a2 = T(0), b1 = T(0), b2 = T(0);
+                    int p = s0;
+                    for (; p + 2 <= e0; p += 2) {
+                        const T* f0 = pf + PF * p;
+                        const T* f1 = f0 + PF;
+                        const T z0 = f0[NA + qzl], z1 = f1[NA + qzl];
+                        const T x1 = f0[qa1], x2 = f0[qa2], y1 = f1[qa1], y2 = f1[qa2];
+                        a1 += x1 * z0;
+                        a2 += x2 * z0;
+                        b1 += y1 * z1;
+                        b2 += y2 * z1;
+                    }
+                    if (p < e0) {
+                        const T* f0 = pf + PF * p;
+                        const T z0 = f0[NA + qzl];
+                        a1 += f0[qa1] * z0;
+                        a2 += f0[qa2] * z0;
+                    }
+                    T v1 = a1 + b1, v2 = a2 + b2;
+                    if (bl == carry_blk) {
+                        v1 += carry1;
+                        v2 += carry2;
+                    }
+                    if (s0 < e0) {
+                        if (hi > pe_) {
+                            nc1 = v1;
+                            nc2 = v2;
+                        } else {
+                            put(RL + kNAZ * bl + ql, v1);
+                            put(RL + kNAZ * bl + ql + 16, v2);
+                        }
                     }
                 }
+                if (goes_on) {
+                    // the continuing block is the batch's last; its quarter is its
+                    // rank among the batch's blocks, mod 4
+                    const int cb = __builtin_ctzll(goes_on);
+                    const int qc = __popcll(live & ((1ull << cb) - 1)) & 3;
+                    carry1 = __shfl(nc1, ql + 16 * qc);
+                    carry2 = __shfl(nc2, ql + 16 * qc);
+                    carry_blk = cb;
+                } else {
+                    carry_blk = -1;
+                }
+                wave_sync();
             }
-            if (goes_on) {
-                // the continuing block is the batch's last; its quarter is its
-                // rank among the batch's blocks, mod 4
-                const int cb = __builtin_ctzll(goes_on);
-                const int qc = __popcll(live & ((1ull << cb) - 1)) & 3;
-                carry1 = __shfl(nc1, ql + 16 * qc);
-                carry2 = __shfl(nc2, ql + 16 * qc);
-                carry_blk = cb;
-            } else {
-                carry_blk = -1;
-            }
-            wave_sync();
         }
         // blocks without pairs: zeros in 16-byte pieces, a few lanes per block
         {
@@ -1428,7 +1605,7 @@ template <typename T>
 static size_t aev_lds(int max_apm, int cap, int NZ, int nw, bool fuse = false) {
     const int PF = kNAZ / NZ + NZ;
     return ChunkStage<T>::bytes(max_apm, cap, !fuse) + lds_bytes<T>((size_t)nw * cap * kNbStride) +
-           lds_bytes<T>((size_t)nw * 64 * PF) + lds_bytes<int>((size_t)nw * 64) +
+           lds_bytes<T>((size_t)nw * (64 + kPairRoom) * PF) + lds_bytes<int>((size_t)nw * 64) +
            (fuse ? lds_bytes<T>(4 * (size_t)max_apm) + lds_bytes<int>(max_apm) : 0) +
            (fuse && max_apm > kDirectAtoms ? lds_bytes<uint16_t>((size_t)nw * cap) : 0);
 }
@@ -1445,8 +1622,9 @@ hipError_t launch_aev(const Shape& sh, const AevConst<typename P::T>& c, const i
     size_t lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.nZ, nw, fuse);
     while (lds > kMaxLds && nw > 1) lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.nZ, nw /= 2, fuse);
     if (lds > kMaxLds) return hipErrorInvalidValue;
-    auto kern = bucket ? (c.nZ == 4 ? k_aev<P, 4, true> : k_aev<P, 8, true>)
-                       : (c.nZ == 4 ? k_aev<P, 4> : k_aev<P, 8>);
+    auto kern = bucket ? (c.nZ == 4 ? k_aev<P, 4, kBuckets> : k_aev<P, 8, kBuckets>)
+              : fuse   ? (c.nZ == 4 ? k_aev<P, 4, kSearch> : k_aev<P, 8, kSearch>)
+                       : (c.nZ == 4 ? k_aev<P, 4, kLists> : k_aev<P, 8, kLists>);
     hipError_t e = ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     tm.b("aev", st);
@@ -1743,12 +1921,6 @@ __device__ inline void ldg4(const bf16_t* p, float v[4]) {
     v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xffff0000u);
     v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
 }
-__device__ inline void st4(float* p, const float v[4]) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
-__device__ inline void st4(double* p, const double v[4]) {
-    *(double2*)p = make_double2(v[0], v[1]);
-    *(double2*)(p + 2) = make_double2(v[2], v[3]);
-}
-
 // Force accumulators.  Floating point: LDS and global atomic adds, whose
 // order (and so the last bits of F) varies from run to run.  Fixed point:
 // every contribution is scaled by 2^32 and rounded to a 64-bit integer
@@ -1804,12 +1976,12 @@ template <typename T> struct ForceAcc<T, true> {
 };
 
 // Sums over four and sixteen lanes go through DPP (two shuffles a radial
-// round and eighteen at the end of an atom before: 1,024 x 49 atoms in BF16
+// round and eighteen at the end of an atom before: 1,024 x 48 atoms in BF16
 // 100 -> 96 us with the energies in workgroups of their own).
 // A pair's contraction with its dE/dAEV block runs over the distance shifts
 // first, the cutoff values and the geometry once at the end: 332 -> 246 lane
 // instructions a pair besides its 20 transcendentals (64 atoms 15.7 -> 13.8
-// us, 1,024 x 49 atoms in BF16 96 -> 93).
+// us, 1,024 x 48 atoms in BF16 96 -> 93).
 template <typename P, int NZ, bool FIXED, bool GD>
 __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_forces(AevConst<typename P::T> c, int A, int max_apm,
                                                 int chunk, int cap, const int32_t* __restrict__ mol_off,

@@ -39,3 +39,42 @@ def test_records_and_rows_match_oracle(orc, hp, sizes, prec, chunk):
     np.testing.assert_allclose(E.cpu().numpy(), Eo, rtol=1e-10 if prec == "fp64" else 1e-5, atol=tol_e)
     np.testing.assert_allclose(F.cpu().numpy(), Fo, rtol=0, atol=tol_f * fmax)
     h.close()
+
+
+def _packed(n, edge, seed, elements):
+    """n atoms, 1 A lattice sites of a cube taken at random (each atom has many
+    neighbours), the given elements in turn."""
+    rng = np.random.default_rng(seed)
+    g = np.arange(int(edge) + 1) * 1.0
+    sites = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    pos = sites[rng.permutation(len(sites))[:n]] + rng.uniform(-0.05, 0.05, (n, 3))
+    return pos, np.array([elements[i % len(elements)] for i in range(n)], dtype=np.int32)
+
+
+@pytest.mark.parametrize("model,elements", [
+    ("ani2x", [0]),                    # one block over many batches of pairs
+    ("ani2x", [6, 0, 5]),              # the last elements, runs longer than one list
+    ("ani2x", [0, 1, 2, 3, 4, 5, 6]),  # every block, short runs
+    ("ani1x", [3, 1]),                 # four distance shifts x eight angles
+])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_slot_sums_of_many_neighbours(orc, hp, model, elements, prec):
+    """AEV rows where a slot's sum runs over several lists and batches; FP32
+    within 1e-5 of a row's largest slot (some hundred terms of 1e-7 each)."""
+    torch = torch_cuda()
+    from paper_2201_08110_amd import synth
+    hp = synth.ani1x_hparams() if model == "ani1x" else hp
+    sizes = [3, 64, 5]
+    b = synth.random_batch(11, sizes, ratio=[1.0] * hp["n_species"])
+    pos, sp = _packed(64, 4, 5, elements)
+    b.coords[3:67], b.species[3:67] = pos, sp
+    w = synth.xavier_weights(1, hp.get("species_widths") or hp["widths"], hp["n_species"], seed=9)
+    h = make_handle(hp, w, 1, prec, b)
+    x, s, off = to_device(torch, b, torch.float64 if prec == "fp64" else torch.float32)
+    G = h.aev(x, s, off).double().cpu().numpy()
+    xo = x.double().cpu().numpy()
+    o = b.mol_offsets
+    Go = np.concatenate([orc.aev(hp, b.species[p:q], xo[p:q]) for p, q in zip(o[:-1], o[1:])])
+    tol = 1e-11 if prec == "fp64" else 1e-5
+    assert (np.abs(G - Go).max(1) <= tol * np.maximum(np.abs(Go).max(1), 1.0)).all()
+    h.close()
