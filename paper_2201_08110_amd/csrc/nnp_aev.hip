@@ -1081,11 +1081,14 @@ __device__ inline void put4(bf16_t* p, f32x4 v) {
 // sums and of the even or the odd elements in order, a lane per shift: four
 // blocks of 4 shifts x 4 elements, the column factor being the cutoff for the
 // neighbour's element and zero for the others.  lst: 4 x kRadSlice entries of
-// this wave's LDS.
+// this wave's LDS.  TANGENT: the rows' derivative along a coordinate tangent,
+// nt the neighbours' rates (kTanStride apart, dr/dt the fourth), with
+// d(e fc)/dt = e (fc' - 2 eta d fc) dr/dt as two products.
 constexpr int kRadSlice = 48;   // neighbours listed at once
-template <typename TS>
-__device__ inline void radial_rows(const AevConst<float>& c, const AtomLists& al, const float* nb, int nang, int nall,
-                                   f32x4* lst, TS* grow, float* arow) {
+constexpr int kTanStride = 5;   // (odd, as the records')
+template <bool TANGENT, typename TS>
+__device__ inline void radial_rows(const AevConst<float>& c, const AtomLists& al, const float* nb, const float* nt,
+                                   int nang, int nall, f32x4* lst, TS* grow, float* arow) {
     const int lane = lane_id();
     const unsigned long long lt = below(lane);
     const int k = lane & 15, j = lane & 3, s = 2 * j + (lane >> 4 & 1);
@@ -1106,21 +1109,30 @@ __device__ inline void radial_rows(const AevConst<float>& c, const AtomLists& al
         const f32x4 none = {0.f, 0.f, __int_as_float(-1), 0.f};
         for (int i = 0; i < nmax; i += 16) mine[min(i + k, kRadSlice - 1)] = none;
         const unsigned long long md = (second ? ms : ~ms) & (sp & 1 ? mo : ~mo) & ma & lt;
-        if (act) lst[((second ? 2 : 0) + (sp & 1)) * kRadSlice + __popcll(md)] = f32x4{e[3], e[4], __int_as_float(sp >> 1), 0.f};
+        f32x4 v = {e[3], e[4], __int_as_float(sp >> 1), 0.f};
+        if constexpr (TANGENT) {
+            const float rate = nt[kTanStride * (act ? t : 0) + 3];
+            v[1] = -2.f * c.eta_r * e[4] * rate;
+            v[3] = e[5] * rate;
+        }
+        if (act) lst[((second ? 2 : 0) + (sp & 1)) * kRadSlice + __popcll(md)] = v;
         wave_sync();
         for (int i = 0; i < nmax; i += kRadU) {
             f32x4 v[kRadU];
-            float ex[kRadU], f[kRadU];
+            float ex[kRadU], d[kRadU];
 #pragma unroll
             for (int u = 0; u < kRadU; ++u) v[u] = mine[i + u];
 #pragma unroll
             for (int u = 0; u < kRadU; ++u) {
-                const float d = v[u][0] - sk;
-                ex[u] = m_exp(-c.eta_r * d * d);
-                f[u] = __float_as_int(v[u][2]) == j ? v[u][1] : 0.f;
+                d[u] = v[u][0] - sk;
+                ex[u] = m_exp(-c.eta_r * d[u] * d[u]);
             }
 #pragma unroll
-            for (int u = 0; u < kRadU; ++u) acc = mfma_4x4(ex[u], f[u], acc);
+            for (int u = 0; u < kRadU; ++u) {
+                const bool own = __float_as_int(v[u][2]) == j;
+                acc = mfma_4x4(TANGENT ? ex[u] * d[u] : ex[u], own ? v[u][1] : 0.f, acc);
+                if (TANGENT) acc = mfma_4x4(ex[u], own ? v[u][3] : 0.f, acc);
+            }
         }
         wave_sync();
     }
@@ -1141,16 +1153,16 @@ __device__ inline void radial_rows(const AevConst<float>& c, const AtomLists& al
 }
 
 // Angular slots from a batch of pairs [p0, p0 + nbat) whose factors are in pf
-// (PF a pair: NA distance, NZ angle).  The element blocks that meet the batch
+// (TERMS products a pair, each NA distance and NZ angle factors).  The element blocks that meet the batch
 // are taken four at a time, sixteen lanes each: two sums of the alternate
 // pairs, each of two 4 x 4 blocks.  A block's slots are stored when its last
 // pair is in; one that runs on leaves its sums in carry (every row of sixteen
 // lanes), and is the first of the next batch.  lst: 64 integers of this
 // wave's LDS.
-template <int NA, int NZ, typename TS>
+template <int NA, int NZ, int TERMS, typename TS>
 __device__ inline void angular_rows(const AtomLists& al, int p0, int nbat, const float* pf, int* lst, f32x4& carry,
                                     TS* gang, float* aang) {
-    constexpr int PF = NA + NZ;
+    constexpr int PT = NA + NZ, PF = TERMS * PT;
     const int lane = lane_id(), pe = p0 + nbat;
     const bool live = al.blo < al.bhi && al.blo < pe && al.bhi > p0;
     const unsigned long long lm = __ballot(live);
@@ -1174,16 +1186,19 @@ __device__ inline void angular_rows(const AtomLists& al, int p0, int nbat, const
         const int left = len - par;
         for (int o = 0; o < most; o += 2 * kAngU) {
             const float* f = pf + at;
-            float r[kAngU], k[kAngU];
+            float r[kAngU][TERMS], k[kAngU][TERMS];
 #pragma unroll
-            for (int u = 0; u < kAngU; ++u) {
-                r[u] = f[2 * PF * u + NA + zi];
-                k[u] = f[2 * PF * u + ai];
-            }
+            for (int u = 0; u < kAngU; ++u)
+#pragma unroll
+                for (int m = 0; m < TERMS; ++m) {
+                    r[u][m] = f[2 * PF * u + PT * m + NA + zi];
+                    k[u][m] = f[2 * PF * u + PT * m + ai];
+                }
 #pragma unroll
             for (int u = 0; u < kAngU; ++u) {
                 const bool in = o + 2 * u < left;
-                acc = mfma_4x4(in ? r[u] : 0.f, in ? k[u] : 0.f, acc);
+#pragma unroll
+                for (int m = 0; m < TERMS; ++m) acc = mfma_4x4(in ? r[u][m] : 0.f, in ? k[u][m] : 0.f, acc);
             }
             at = min(at + 2 * PF * kAngU, PF * 63);
         }
@@ -1330,6 +1345,20 @@ __device__ inline void bucket_table(const BucketFuse& bk, int S, int A, int max_
 // two LDS reads for all its slots (18.0 -> 15.2 us; 106 -> 100; 512 molecules
 // of 10 to 120 atoms 111 -> 97).  Large batches are bound by the lanes'
 // instructions, 900 an atom.
+// blocks without pairs: zeros in 16-byte pieces, a few lanes per block
+template <typename TS, typename T>
+__device__ inline void zero_blocks(TS* gang, T* aang, int NB, unsigned long long filled) {
+    constexpr int VP = 16 / (int)sizeof(TS), PPB = kNAZ / VP, BPP = 64 / PPB;
+    const int lane = lane_id(), pc = lane % PPB;
+    for (int b0 = 0; b0 < NB; b0 += BPP) {
+        const int zb = b0 + lane / PPB;
+        if (zb < NB && !((filled >> zb) & 1ull)) *(uint4*)(gang + kNAZ * zb + VP * pc) = make_uint4(0u, 0u, 0u, 0u);
+    }
+    if (aang)
+        for (int e = lane; e < NB * kNAZ; e += 64)
+            if (!((filled >> (e / kNAZ)) & 1ull)) aang[e] = T(0);
+}
+
 // neighbour lists given, found here, or found here with the bucketing too
 constexpr int kLists = 0, kSearch = 1, kBuckets = 2;
 template <typename P, int NZ, int MODE>
@@ -1440,7 +1469,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
 
         // ---- radial
         if constexpr (sizeof(T) == 4) {
-            radial_rows(c, al, nb, nang, nall, (f32x4*)pf, grow, arow);
+            radial_rows<false>(c, al, nb, nullptr, nang, nall, (f32x4*)pf, grow, arow);
         } else {
             // lane (group g, shift k) owns slots (s, k), s = g mod 4
             const int g = lane >> 4, k = lane & 15;
@@ -1515,7 +1544,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             }
             wave_sync();
             if constexpr (sizeof(T) == 4) {
-                angular_rows<NA, NZ>(al, p0, nbat, pf, mark, carry, grow + RL, arow ? arow + RL : nullptr);
+                angular_rows<NA, NZ, 1>(al, p0, nbat, pf, mark, carry, grow + RL, arow ? arow + RL : nullptr);
             } else {
                 // blocks meeting this batch, taken four at a time, one per
                 // quarter-wave, each quarter summing its block's pairs in order
@@ -1585,19 +1614,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
                 wave_sync();
             }
         }
-        // blocks without pairs: zeros in 16-byte pieces, a few lanes per block
-        {
-            constexpr int VP = 16 / (int)sizeof(TS), PPB = kNAZ / VP, BPP = 64 / PPB;
-            const int pc = lane % PPB;
-            for (int b0 = 0; b0 < NB; b0 += BPP) {
-                const int zb = b0 + lane / PPB;
-                if (zb < NB && !((filled >> zb) & 1ull))
-                    *(uint4*)(grow + RL + kNAZ * zb + VP * pc) = make_uint4(0u, 0u, 0u, 0u);
-            }
-            if (arow)
-                for (int e = lane; e < NB * kNAZ; e += 64)
-                    if (!((filled >> (e / kNAZ)) & 1ull)) arow[RL + e] = T(0);
-        }
+        zero_blocks(grow + RL, arow ? arow + RL : nullptr, NB, filled);
     }
 }
 
@@ -1865,6 +1882,122 @@ __global__ __launch_bounds__(256) void k_aev_jvp(AevConst<typename P::T> c, int 
     }
 }
 
+// The same in FP32 arithmetic, on the forward kernel's lists, pair order and
+// matrix-core sums, with two products a neighbour and a pair.  The kernel above
+// (which FP64 keeps) adds to a row in LDS whenever the element changes, which
+// in its pair order is every few pairs (64 molecules of 30 to 80 atoms: 75 -> 29 us).
+template <typename P, int NZ>
+__global__ __launch_bounds__(256) void k_aev_tangent(AevConst<float> c, int A, int max_apm, int chunk, int cap,
+                                                     const int32_t* __restrict__ mol_off,
+                                                     const int32_t* __restrict__ species,
+                                                     const float* __restrict__ x, const float* __restrict__ v,
+                                                     const uint16_t* __restrict__ nbr,
+                                                     const int32_t* __restrict__ nbr_cnt,
+                                                     const int32_t* __restrict__ row_of_atom,
+                                                     typename P::TS* __restrict__ Gd) {
+    typedef typename P::TS TS;
+    constexpr int NA = kNAZ / NZ, PT = NA + NZ, PF = 2 * PT;
+    extern __shared__ __align__(16) char smem[];
+    const int b = blockIdx.x;
+    const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
+    if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
+    const int i0 = blockIdx.y * chunk;
+    if (i0 >= n) return;
+    const int nc = min(chunk, n - i0);
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
+    const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
+
+    LdsBump lb(smem);
+    ChunkStage<float> cs;
+    cs.take(lb, max_apm, cap);
+    float* sv = lb.take<float>(3 * (size_t)max_apm);
+    float* nb = lb.take<float>((size_t)nw * cap * kNbStride) + (size_t)wave * cap * kNbStride;
+    float* nt = lb.take<float>((size_t)nw * cap * kTanStride) + (size_t)wave * cap * kTanStride;
+    float* pf = lb.take<float>((size_t)nw * (64 + kPairRoom) * PF) + (size_t)wave * (64 + kPairRoom) * PF;
+    int* mark = lb.take<int>((size_t)nw * 64) + (size_t)wave * 64;
+    cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, row_of_atom);
+    for (int t = tid; t < 3 * n; t += blockDim.x) sv[t] = v[3 * (size_t)a0 + t];
+    __syncthreads();
+    int ba = 0, bb = 0;   // this lane's angular block's elements
+    if (lane < NB) block_elements(lane, S, ba, bb);
+
+    for (int ic = wave; ic < nc; ic += nw) {
+        const int il = i0 + ic;
+        const int cnt = uniform(cs.ccnt[ic]), nang = cnt & 0xffff, nall = cnt >> 16;
+        TS* grow = Gd + (size_t)uniform(cs.crow[ic]) * c.Dp;
+        load_records(c, cs.sx, cs.ssp, cs.clst + (size_t)ic * cap, nang, nall, il, nb);
+        wave_sync();
+        const float v0 = sv[3 * il], v1 = sv[3 * il + 1], v2 = sv[3 * il + 2];
+        for (int t = lane; t < nall; t += 64) {
+            const float* e = nb + kNbStride * t;
+            const int j = tag_of(e) >> 8;
+            const float w0 = sv[3 * j] - v0, w1 = sv[3 * j + 1] - v1, w2 = sv[3 * j + 2] - v2;
+            float* o = nt + kTanStride * t;
+            o[0] = w0;
+            o[1] = w1;
+            o[2] = w2;
+            o[3] = (e[0] * w0 + e[1] * w1 + e[2] * w2) * m_rcp(e[3]);   // dr/dt
+        }
+        wave_sync();
+        const AtomLists al = atom_lists([&](int t) { return tag_of(nb + kNbStride * t) & 0xff; }, nang, nall, S, ba, bb);
+        for (int e = c.D + lane; e < c.Dp; e += 64) grow[e] = Store<TS>::st(0.f);
+        radial_rows<true>(c, al, nb, nt, nang, nall, (f32x4*)pf, grow, nullptr);
+        f32x4 carry = {0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < al.npair; p0 += 64) {
+            const int nbat = min(64, al.npair - p0);
+            int j, k;
+            batch_pairs(al, p0, mark, j, k);
+            if (lane < nbat) {
+                const float* ej = nb + kNbStride * j;
+                const float* ek = nb + kNbStride * k;
+                const float* tj = nt + kTanStride * j;
+                const float* tk = nt + kTanStride * k;
+                const float rj = ej[3], rk = ek[3], rjd = tj[3], rkd = tk[3];
+                const float ijk = m_rcp(rj * rk);
+                float cs_ = (ej[0] * ek[0] + ej[1] * ek[1] + ej[2] * ek[2]) * ijk;
+                cs_ = cs_ > 1.f ? 1.f : (cs_ < -1.f ? -1.f : cs_);
+                // d(x_j . x_k)/dt / (r_j r_k) - c (dr_j/dt / r_j + dr_k/dt / r_k)
+                const float cdot = (tj[0] * ek[0] + tj[1] * ek[1] + tj[2] * ek[2] + tk[0] * ej[0] + tk[1] * ej[1] +
+                                    tk[2] * ej[2] - cs_ * (rjd * rk + rkd * rj)) * ijk;
+                const float cp = c.angle_scale * cs_;
+                const float sn = m_sqrt(1.f - cp * cp), cot = cp * m_rcp(sn);
+                const float F = ej[6] * ek[6];
+                const float Fd = ej[7] * ek[6] * rjd + ej[6] * ek[7] * rkd;
+                const float rm = 0.5f * (rj + rk), Fr = -c.eta_a * (rjd + rkd) * F, Fc = F * cdot;
+                float f[PF];   // P_a, fz, Q_a, dfz
+#pragma unroll
+                for (int a = 0; a < NA; ++a) {
+                    const float d = rm - c.shf_a[a];
+                    const float Aa = m_exp(-c.eta_a * d * d);
+                    f[a] = d * Aa * Fr + Aa * Fd;
+                    f[PT + a] = Aa * Fc;
+                }
+#pragma unroll
+                for (int z = 0; z < NZ; ++z) {
+                    const float cz = cp * c.cos_z[z] + sn * c.sin_z[z];
+                    const float hh = 0.5f * (1.f + cz);
+                    const float hp = m_powu(hh, c.zeta - 1.f);
+                    f[NA + z] = 2.f * hp * hh;
+                    f[PT + NA + z] = c.zeta * c.angle_scale * hp * (c.cos_z[z] - cot * c.sin_z[z]);
+                }
+#pragma unroll
+                for (int u = 0; u < PF; u += 4) st4(pf + PF * lane + u, f + u);
+            }
+            wave_sync();
+            angular_rows<NA, NZ, 2>(al, p0, nbat, pf, mark, carry, grow + RL, (float*)nullptr);
+        }
+        zero_blocks(grow + RL, (float*)nullptr, NB, __ballot(al.blo < al.bhi));
+        wave_sync();
+    }
+}
+
+static size_t tangent_lds(int max_apm, int cap, int NZ, int nw) {
+    const int PF = 2 * (kNAZ / NZ + NZ);
+    return ChunkStage<float>::bytes(max_apm, cap) + lds_bytes<float>(3 * (size_t)max_apm) +
+           lds_bytes<float>((size_t)nw * cap * kNbStride) + lds_bytes<float>((size_t)nw * cap * kTanStride) +
+           lds_bytes<float>((size_t)nw * (64 + kPairRoom) * PF) + lds_bytes<int>((size_t)nw * 64);
+}
+
 template <typename T>
 static size_t jvp_lds(int max_apm, int cap, int Dp, int NZ, int nw) {
     const int PF = 2 * (kNAZ / NZ) + 2 * NZ;
@@ -1882,10 +2015,17 @@ hipError_t launch_aev_jvp(const Shape& sh, const AevConst<typename P::T>& c,
     typedef typename P::T T;
     dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk);
     int nw = kWaves;
-    size_t lds = jvp_lds<T>(sh.max_apm, sh.cap_nbr, c.Dp, c.nZ, nw);
-    while (lds > kMaxLds && nw > 1) lds = jvp_lds<T>(sh.max_apm, sh.cap_nbr, c.Dp, c.nZ, nw /= 2);
+    auto lds_of = [&](int waves) {
+        if constexpr (sizeof(T) == 4) return tangent_lds(sh.max_apm, sh.cap_nbr, c.nZ, waves);
+        else return jvp_lds<T>(sh.max_apm, sh.cap_nbr, c.Dp, c.nZ, waves);
+    };
+    size_t lds = lds_of(nw);
+    while (lds > kMaxLds && nw > 1) lds = lds_of(nw /= 2);
     if (lds > kMaxLds) return hipErrorInvalidValue;
-    auto kern = c.nZ == 4 ? k_aev_jvp<P, 4> : k_aev_jvp<P, 8>;
+    auto kern = [&] {
+        if constexpr (sizeof(T) == 4) return c.nZ == 4 ? k_aev_tangent<P, 4> : k_aev_tangent<P, 8>;
+        else return c.nZ == 4 ? k_aev_jvp<P, 4> : k_aev_jvp<P, 8>;
+    }();
     hipError_t e = ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     tm.b("aev_jvp", st);

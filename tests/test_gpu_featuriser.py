@@ -78,3 +78,32 @@ def test_slot_sums_of_many_neighbours(orc, hp, model, elements, prec):
     tol = 1e-11 if prec == "fp64" else 1e-5
     assert (np.abs(G - Go).max(1) <= tol * np.maximum(np.abs(Go).max(1), 1.0)).all()
     h.close()
+
+
+@pytest.mark.parametrize("model,elements,chunk", [
+    ("ani2x", [0], 4),                 # one block over many batches of pairs
+    ("ani2x", [6, 0, 5, 1], 16),
+    ("ani1x", [3, 1], 4),              # four distance shifts x eight angles
+])
+def test_fp32_row_tangents(orc, hp, model, elements, chunk):
+    """Parameter gradients of a force term alone, which reach the parameters
+    through the rows' tangents only; the bound is that of the other FP32
+    parameter gradients."""
+    torch = torch_cuda()
+    hp = synth.ani1x_hparams() if model == "ani1x" else hp
+    b = synth.random_batch(13, [3, 64, 5], ratio=[1.0] * hp["n_species"])
+    b.coords[3:67], b.species[3:67] = _packed(64, 5, 6, elements)
+    w = synth.xavier_weights(1, hp.get("species_widths") or hp["widths"], hp["n_species"], seed=9)
+    h = make_handle(hp, w, 1, "fp32", b)
+    h.set_knob("atom_chunk", chunk)
+    x, s, off = to_device(torch, b, torch.float32)
+    gF = np.random.default_rng(4).normal(size=(int(b.n_atoms), 3)).astype(np.float32) * 1e-2
+    gE = np.zeros(b.n_mols)
+    gp, _ = h.backward(x, s, off, torch.tensor(gE, device="cuda"), torch.tensor(gF, device="cuda"))
+    torch.cuda.synchronize()
+    assert h.device_status() == 0
+    go = orc.param_grad(hp, synth.round_to_fp32(w), 1, b.species, x.double().cpu().numpy(), b.mol_offsets, gE,
+                        gF.astype(np.float64))
+    err = np.linalg.norm(gp.cpu().numpy() - go) / np.linalg.norm(go)
+    assert err < 1e-4
+    h.close()
