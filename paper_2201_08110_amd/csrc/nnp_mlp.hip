@@ -928,9 +928,8 @@ __global__ __launch_bounds__(256 * TW, 2 * TW) void k_tail(TailArgs<P> g) {
     }
 }
 
-template <typename P, int BM, int TW, int H3L = kTailH3>
-static hipError_t run_tail(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, hipStream_t st,
-                           const Timer& tm) {
+template <typename P, int BM>
+static TailArgs<P> tail_args(const Shape& sh, const DevWeights<P>& wt, const Work<P>& w) {
     typedef typename P::TA TA;
     TailArgs<P> a{};
     a.H1 = w.H1; a.DZ1 = w.DZ1; a.ldh = sh.M * sh.H1;
@@ -944,6 +943,13 @@ static hipError_t run_tail(const Shape& sh, const DevWeights<P>& wt, Work<P>& w,
     a.tile_species = w.tile_species; a.row_tile = sh.row_tile;
     a.info = w.info;
     a.nm = sh.Rcap / BM;
+    return a;
+}
+
+template <typename P, int BM, int TW, int H3L = kTailH3>
+static hipError_t run_tail(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, hipStream_t st,
+                           const Timer& tm) {
+    const TailArgs<P> a = tail_args<P, BM>(sh, wt, w);
     const int T = a.nm * sh.M;
     const size_t lds = TailShape<P, BM, kTailH1, kTailH2, kTailH3>::lds_bytes();
     auto kern = k_tail<P, BM, TW, kTailH1, kTailH2, kTailH3, H3L>;
@@ -955,12 +961,224 @@ static hipError_t run_tail(const Shape& sh, const DevWeights<P>& wt, Work<P>& w,
     return hipGetLastError();
 }
 
+// The fused tail of one 16-row BF16 tile, for the buckets of small calls: a
+// tile is a chain of four products whose weights come from HBM, on fewer
+// workgroups than CUs, so it takes NW waves of one 16-column tile each, and
+// every wave requests its weights PD fragments ahead through all four layers
+// (the barriers wait for LDS alone).  The H1 tile stays in LDS for the last
+// epilogue.  The products' K order is k_tail's, so the roundings are too.
+// 64 atoms, 8 models: 9.5 -> 8.4 us (eight waves of two tiles 9.0).  In FP32
+// and FP64 a tile waits for its four SIMDs' matrix products instead, and
+// sixteen waves measured 19.5 against 17.7 us and 34.8 against 30.4: k_tail
+// keeps those.
+template <typename P, int NW, int H1, int H2, int H3, int H3L>
+__global__ __launch_bounds__(64 * NW) void k_tail16(TailArgs<P> g) {
+    typedef typename P::TS TS;
+    typedef typename P::TA TA;
+    typedef MF<TS> mf;
+    typedef typename mf::Acc Acc;
+    typedef Sliced<TS> L;
+    typedef FragGroup<TS> FGp;
+    typedef typename FGp::V FragG;
+    constexpr int ST = mf::kColStride, G = FGp::G, KM = FragK<TS>::KM, KL = FragK<TS>::KL, VE = L::VE, NT = 64 * NW;
+    // per layer: reduction steps, 16-column tiles, tiles a wave, first fragment
+    constexpr int S0 = H1 / KM, S1 = H2 / KM, S2 = H3L / KM, S3 = H2 / KM;
+    constexpr int N0 = H2 / 16, N1 = H3L / 16, N2 = H2 / 16, N3 = H1 / 16;
+    constexpr int T0 = (N0 + NW - 1) / NW, T1 = (N1 + NW - 1) / NW, T2 = (N2 + NW - 1) / NW, T3 = (N3 + NW - 1) / NW;
+    constexpr int B1 = S0 * T0, B2 = B1 + S1 * T1, B3 = B2 + S2 * T2, BE = B3 + S3 * T3;
+    constexpr int PD = NW == 16 ? 18 : 36;
+    extern __shared__ __align__(16) char smem_raw[];
+    TS* A1 = (TS*)smem_raw;            // H1 tile
+    TS* A2 = A1 + 16 * H1;             // H2, later DZ2
+    TS* A3 = A2 + 16 * H2;             // DZ3
+    TA* red = (TA*)(A3 + 16 * H3);     // [16][NW]
+    TA* sb2 = red + 16 * NW;           // b2 [H2], b3 [H3], w4 [H3] of this element and model
+    TA* sb3 = sb2 + H2;
+    TA* sw4 = sb3 + H3;
+
+    const int nm = row_tiles<16>(g.info, g.nm), lin = xcd_tile(nm * g.M);
+    if (lin < 0) return;
+    const int z = lin / nm, row0 = lin % nm * 16;
+    const int tid = threadIdx.x, lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rl = lane & 15, cl = mf::col0(lane), kl = (lane >> 4) * KL;
+    // the H1 tile, requested before the tile's element is known (rows past the
+    // buckets are there, if unused) and ahead of every weight
+    constexpr int NV = 16 * H1 / VE, HV = (NV + NT - 1) / NT;
+    uint4 hv[HV];
+#pragma unroll
+    for (int u = 0; u < HV; ++u) {
+        const int q = min(tid + u * NT, NV - 1);
+        hv[u] = *(const uint4*)(g.H1 + (size_t)(row0 + q / (H1 / VE)) * g.ldh + (size_t)z * H1 + q % (H1 / VE) * VE);
+    }
+    const int rows = g.info->rows, s = g.tile_species[row0 / g.row_tile];
+    asm volatile("" ::: "memory");
+    if (row0 >= rows || s < 0) return;
+    const size_t sz = (size_t)s * g.M + z;
+    constexpr int NPAR = H2 + 2 * H3, HP = (NPAR + NT - 1) / NT;
+    TA pv[HP];
+#pragma unroll
+    for (int u = 0; u < HP; ++u) {
+        const int t = min(tid + u * NT, NPAR - 1);
+        pv[u] = *(t < H2 ? g.b2 + sz * H2 + t : (t < H2 + H3 ? g.b3 + sz * H3 + (t - H2) : g.w4 + sz * H3 + (t - H2 - H3)));
+    }
+    asm volatile("" ::: "memory");
+    // the weight fragments of all four products, one sequence
+    const TS* W0 = g.W2f + sz * H2 * H1 + lane * KL;
+    const TS* W1 = g.W3f + sz * H3 * H2 + lane * KL;
+    const TS* W2 = g.W3Tf + sz * H2 * H3 + lane * KL;
+    const TS* W3 = g.W2Tf + sz * H1 * H2 + lane * KL;
+    FragG ring[PD];
+    auto request = [&](int f) {
+        if (f >= BE) return;
+        const int l = f < B1 ? 0 : f < B2 ? 1 : f < B3 ? 2 : 3;
+        const int o = f - (l == 0 ? 0 : l == 1 ? B1 : l == 2 ? B2 : B3);
+        const int tw = l == 0 ? T0 : l == 1 ? T1 : l == 2 ? T2 : T3, n = l == 0 ? N0 : l == 1 ? N1 : l == 2 ? N2 : N3;
+        const int ks = l == 0 ? S0 : l == 1 ? S1 : l == 2 ? H3 / KM : S3;   // stored steps a tile
+        const TS* W = l == 0 ? W0 : l == 1 ? W1 : l == 2 ? W2 : W3;
+        // (no branch around a load: a wave past the last tile requests it again,
+        // so that every wave's loads are counted alike)
+        const int tile = min(w + NW * (o % tw), n - 1);
+        ring[f % PD] = *(const FragG*)(W + ((size_t)tile * ks + o / tw) * 64 * KL);
+    };
+#pragma unroll
+    for (int f = 0; f < PD; ++f) request(f);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < HV; ++u) {
+        const int q = tid + u * NT;
+        if (q < NV) *(uint4*)(A1 + L::at(16, q / (H1 / VE), q % (H1 / VE) * VE)) = hv[u];
+    }
+#pragma unroll
+    for (int u = 0; u < HP; ++u) {
+        const int t = tid + u * NT;
+        if (t < NPAR) sb2[t] = pv[u];
+    }
+    auto lds_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    lds_barrier();
+
+    // acc of this wave's tiles of one layer, fragments [F0, F0 + steps * tiles)
+    auto product = [&](auto f0_c, auto steps_c, auto tw_c, auto n_c, const TS* As, const TA* bias, auto& acc) {
+        constexpr int F0 = decltype(f0_c)::value, NS = decltype(steps_c)::value, TW = decltype(tw_c)::value,
+                      N = decltype(n_c)::value;
+#pragma unroll
+        for (int j = 0; j < TW; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc[j][r] = bias && w + NW * j < N ? bias[(w + NW * j) * 16 + cl + r * ST] : TA(0);
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+            const FragG af = *(const FragG*)(As + L::at(16, rl, t * KM + kl));
+#pragma unroll
+            for (int j = 0; j < TW; ++j) {
+                const int f = F0 + t * TW + j;
+                if (w + NW * j < N)
+#pragma unroll
+                    for (int u = 0; u < G; ++u) acc[j] = mf::mma(FGp::at(ring[f % PD], u), FGp::at(af, u), acc[j]);
+                request(f + PD);
+            }
+            asm volatile("" ::: "memory");
+        }
+    };
+#define NNP_IC(v) std::integral_constant<int, v>{}
+    // ---- layer 2 forward
+    {
+        Acc acc[T0];
+        product(NNP_IC(0), NNP_IC(S0), NNP_IC(T0), NNP_IC(N0), A1, sb2, acc);
+#pragma unroll
+        for (int j = 0; j < T0; ++j)
+            if (w + NW * j < N0) {
+                TA v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] = celu((TA)acc[j][q], g.alpha, g.inv_alpha);
+                LdsQuad<TS, ST>::st(A2, 16, rl, (w + NW * j) * 16 + cl, v);
+            }
+    }
+    lds_barrier();
+    // ---- layer 3 forward, output layer, dE/dz3
+    {
+        Acc acc[T1];
+        product(NNP_IC(B1), NNP_IC(S1), NNP_IC(T1), NNP_IC(N1), A2, sb3, acc);
+        TA part = 0;
+#pragma unroll
+        for (int j = 0; j < T1; ++j)
+            if (w + NW * j < N1) {
+                const int c = (w + NW * j) * 16 + cl;
+                TA v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const TA ww = sw4[c + q * ST], zz = (TA)acc[j][q];
+                    part += ww * celu(zz, g.alpha, g.inv_alpha);
+                    v[q] = dcelu_z(zz, g.inv_alpha) * (ww * g.gscale);
+                }
+                LdsQuad<TS, ST>::st(A3, 16, rl, c, v);
+            }
+        part += __shfl_xor(part, 16);
+        part += __shfl_xor(part, 32);
+        if (lane < 16) red[lane * NW + w] = part;
+    }
+    lds_barrier();
+    // ---- layer 3 backward: DZ2 = (DZ3 W3) celu'(H2), in place of H2 (which no
+    // product reads any more; each lane overwrites its own elements)
+    {
+        Acc acc[T2];
+        product(NNP_IC(B2), NNP_IC(S2), NNP_IC(T2), NNP_IC(N2), A3, (const TA*)nullptr, acc);
+#pragma unroll
+        for (int j = 0; j < T2; ++j)
+            if (w + NW * j < N2) {
+                const int c = (w + NW * j) * 16 + cl;
+                TA hh[4], v[4];
+                LdsQuad<TS, ST>::ld(A2, 16, rl, c, hh);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] = (TA)acc[j][q] * dcelu_h(hh[q], g.inv_alpha);
+                LdsQuad<TS, ST>::st(A2, 16, rl, c, v);
+            }
+        // the tile's energies, by a wave without columns here
+        if (w == NW - 1 && lane < 16) {
+            TA e = 0;
+#pragma unroll
+            for (int u = 0; u < (N1 < NW ? N1 : NW); ++u) e += red[lane * NW + u];
+            g.epart[(size_t)(row0 + lane) * g.M + z] = e;
+        }
+    }
+    lds_barrier();
+    // ---- layer 2 backward: DZ1 = (DZ2 W2) celu'(H1) -> HBM
+    {
+        Acc acc[T3];
+        product(NNP_IC(B3), NNP_IC(S3), NNP_IC(T3), NNP_IC(N3), A2, (const TA*)nullptr, acc);
+#pragma unroll
+        for (int j = 0; j < T3; ++j)
+            if (w + NW * j < N3) {
+                const int c = (w + NW * j) * 16 + cl;
+                TA hh[4], v[4];
+                LdsQuad<TS, ST>::ld(A1, 16, rl, c, hh);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] = (TA)acc[j][q] * dcelu_h(hh[q], g.inv_alpha);
+                Quad<TS, ST>::st(g.DZ1 + (size_t)(row0 + rl) * g.ldh + (size_t)z * H1 + c, v);
+            }
+    }
+#undef NNP_IC
+}
+
+template <typename P, int H3L>
+static hipError_t run_tail16(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, hipStream_t st, const Timer& tm) {
+    typedef typename P::TA TA;
+    typedef typename P::TS TS;
+    constexpr int NW = 16;
+    const TailArgs<P> a = tail_args<P, 16>(sh, wt, w);
+    const size_t lds = sizeof(TS) * 16 * (kTailH1 + kTailH2 + kTailH3) + sizeof(TA) * (16 * NW + kTailH2 + 2 * kTailH3);
+    auto kern = k_tail16<P, NW, kTailH1, kTailH2, kTailH3, H3L>;
+    hipError_t e = ensure_lds((const void*)kern, lds);
+    if (e != hipSuccess) return e;
+    tm.b("mlp_tail", st);
+    hipLaunchKernelGGL(kern, dim3(a.nm * sh.M), dim3(64 * NW), lds, st, a);
+    tm.e("mlp_tail", st);
+    return hipGetLastError();
+}
+
 bool mlp_fused_supported(int H1, int H2, int H3) {
     return H1 == kTailH1 && H2 == kTailH2 && H3 == kTailH3;
 }
-
-// tail row tile per precision: equal LDS bytes (H1 tile of 32 KiB)
-template <typename P> struct TailBM { static constexpr int v = 128 / (int)sizeof(typename P::TS); };
 
 // the wide layer-1 GEMMs: LDS stages and waves per workgroup from the knobs
 // (8 waves split the 128 x 128 tile 2 x 4, for 128-row buckets only)
@@ -1053,17 +1271,22 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
             if ((e = split_tail(sh, wt, w, st, tm))) return e;
             return mlp_l1_bwd<P, BM>(sh, wt, w, base, st, tm);
         } else {
-        constexpr int TB = TailBM<P>::v, TH = TB / 2 >= 16 ? TB / 2 : 16;
         // layer 3 of at most 160 outputs (ANI-2x): products over the 160 real
         // columns, not the 192 the storage is padded to
         const bool n160 = sh.h3_used <= 160;
-        if (BM == 16) e = n160 ? run_tail<P, 16, 1, 160>(sh, wt, w, st, tm) : run_tail<P, 16, 1>(sh, wt, w, st, tm);
-        else if (sh.tail_tile == 2)
-            e = n160 ? run_tail<P, TH, 1, 160>(sh, wt, w, st, tm) : run_tail<P, TH, 1>(sh, wt, w, st, tm);
-        else if (sh.tail_tile == 3 && TB >= 32)
-            e = n160 ? run_tail<P, TB, TB >= 32 ? 2 : 1, 160>(sh, wt, w, st, tm)
-                     : run_tail<P, TB, TB >= 32 ? 2 : 1>(sh, wt, w, st, tm);
-        else e = n160 ? run_tail<P, TB, 1, 160>(sh, wt, w, st, tm) : run_tail<P, TB, 1>(sh, wt, w, st, tm);
+        // tiles of 32 KiB of H1 rows (half with knob 2, eight waves with knob
+        // 3), or of a 16-row bucket
+        constexpr bool wide = std::is_same<typename P::TS, bf16_t>::value;
+        if constexpr (wide && BM == 16) {
+            e = n160 ? run_tail16<P, 160>(sh, wt, w, st, tm) : run_tail16<P, kTailH3>(sh, wt, w, st, tm);
+        } else if constexpr (!wide) {
+            e = n160 ? run_tail<P, 16, 1, 160>(sh, wt, w, st, tm) : run_tail<P, 16, 1>(sh, wt, w, st, tm);
+        } else {
+            if (sh.tail_tile == 2) e = n160 ? run_tail<P, 32, 1, 160>(sh, wt, w, st, tm) : run_tail<P, 32, 1>(sh, wt, w, st, tm);
+            else if (sh.tail_tile == 3)
+                e = n160 ? run_tail<P, 64, 2, 160>(sh, wt, w, st, tm) : run_tail<P, 64, 2>(sh, wt, w, st, tm);
+            else e = n160 ? run_tail<P, 64, 1, 160>(sh, wt, w, st, tm) : run_tail<P, 64, 1>(sh, wt, w, st, tm);
+        }
         if (e) return e;
         return mlp_l1_bwd<P, BM>(sh, wt, w, base, st, tm);
         }
