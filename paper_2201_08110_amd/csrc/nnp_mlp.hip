@@ -1180,6 +1180,73 @@ bool mlp_fused_supported(int H1, int H2, int H3) {
     return H1 == kTailH1 && H2 == kTailH2 && H3 == kTailH3;
 }
 
+// The layer-1 forward GEMM of the smallest FP64 calls: a 16 x 16 tile a
+// workgroup, its K split over KW waves.  An FP64 matrix instruction holds a
+// SIMD for 64 clocks, so a few 16 x 64 tiles that each run through the whole K
+// leave most of the chip idle.  The operands go from their rows straight into
+// registers, two consecutive K a lane, U steps of 8 K ahead, and the waves'
+// sums meet in LDS.  Those loads touch half a line of sixteen rows at a time,
+// so this pays only while every CU has at most one tile (one model, up to 100
+// atoms: 17.4 -> 12 us; 200 atoms or more 20 -> 23, eight models 28 -> 33; the
+// backward's K of 256 a model 9 -> 12).
+template <int KW, int U, int EPI>
+__global__ __launch_bounds__(64 * KW) void k_gk64(GemmArgs<PrecF64> g) {
+    typedef MF<double> mf;
+    __shared__ mf::Acc part[KW][64];
+    const int nm = row_tiles<16>(g.info, g.nm), lin = xcd_tile(nm * g.nn);
+    if (lin < 0) return;
+    const int tile_n = lin / nm, row0 = lin % nm * 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nk = g.K / 8, rounds = (nk + KW * U - 1) / (KW * U), k0 = wave * rounds * U;
+    const int rows = g.info->rows, s = g.tile_species[row0 / g.row_tile];
+    if (row0 >= rows || s < 0) return;
+    const double* Ap = g.A + (size_t)(row0 + (lane & 15)) * g.lda + 2 * (lane >> 4);
+    const double* Bp = g.B + (size_t)s * g.b_s + (size_t)(tile_n * 16 + (lane & 15)) * g.ldb + 2 * (lane >> 4);
+    f64x2 av[U], bv[U];
+    auto load = [&](int u, int step) {
+        const int st = min(step, nk - 1);
+        bv[u] = *(const f64x2*)(Bp + st * 8);
+        av[u] = *(const f64x2*)(Ap + st * 8);
+    };
+    mf::Acc acc = {0., 0., 0., 0.};
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u, k0 + u);
+    for (int r = 0; r < rounds; ++r) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int step = k0 + r * U + u;
+            f64x2 a = av[u];
+            const f64x2 b = bv[u];
+            if (step >= nk) a = f64x2{0., 0.};
+            load(u, step + U);
+            asm volatile("" ::: "memory");   // the loads stay ahead of the products
+            acc = mf::mma(b[0], a[0], acc);
+            acc = mf::mma(b[1], a[1], acc);
+        }
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave > 0) return;
+    mf::Acc sum[1][1] = {{acc}};
+#pragma unroll
+    for (int w = 1; w < KW; ++w) sum[0][0] += part[w][lane];
+    gemm_epilogue<PrecF64, EPI, 16, 1, 1, 1>(g, sum, lane, row0, 0, tile_n * 16 + mf::col0(lane), s, 0, 0, tile_n, nullptr);
+}
+
+constexpr int kGk64Tiles = 256;   // the CUs
+template <int EPI>
+static hipError_t run_gk64(GemmArgs<PrecF64> a, int R, int N, hipStream_t st, const Timer& tm, const char* name) {
+    constexpr int KW = 8, U = 4;
+    a.nm = R / 16;
+    a.nn = N / 16;
+    a.nz = 1;
+    if (a.K % 8 != 0 || a.K < 8 || N % 16 != 0 || R % 16 != 0 || a.lda % 2 || a.ldb % 2) return hipErrorInvalidValue;
+    tm.b(name, st);
+    hipLaunchKernelGGL((k_gk64<KW, U, EPI>), dim3(a.nm * a.nn), dim3(64 * KW), 0, st, a);
+    tm.e(name, st);
+    return hipGetLastError();
+}
+
 // the wide layer-1 GEMMs: LDS stages and waves per workgroup from the knobs
 // (8 waves split the 128 x 128 tile 2 x 4, for 128-row buckets only)
 template <typename P, int BM, int EPI>
@@ -1190,6 +1257,8 @@ static hipError_t run_l1(GemmArgs<P> a, const typename P::TS* Bf, const bf16_t* 
         return net_gemm<P, BM, EPI>(a, Bf, Bx, R, N, 1, st, tm, name);
     } else {
     typedef Cfg<P, BM> C;
+    if constexpr (std::is_same<P, PrecF64>::value && BM == 16 && EPI == EPI_CELU)
+        if (R / 16 * (N / 16) <= kGk64Tiles) return run_gk64<EPI>(a, R, N, st, tm, name);
     if (N % C::BNW != 0) return net_gemm<P, BM, EPI>(a, nullptr, nullptr, R, N, 1, st, tm, name);
     // 8 waves (2 x 4 of 64 x 32) for the forward GEMM when the knob says so;
     // the backward GEMM measured better on 4
