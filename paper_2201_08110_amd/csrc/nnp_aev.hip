@@ -2364,7 +2364,28 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
           }
           wave_sync();
           // diagonals of this batch: pair q = (d-1) n + a on diagonal d <= D,
-          // q = full + a on the half diagonal d = n/2 of an even n
+          // q = full + a on the half diagonal d = n/2 of an even n.  Neighbour t
+          // is the first of the pair (t, t+d) and the second of (t-d, t); with
+          // one batch every diagonal is in it, and the two places step along
+          if (npair <= 64) {
+            for (int u = lane; u < 3 * nang; u += 64) {
+              const int t = (u * 21846) >> 16, cc = u - 3 * t;   // u / 3
+              const T* fj = pg + 6 * t + cc;
+              const T* fk = pg + 6 * t + 3 + cc;   // (a = t - d, from d = 0)
+              T sum = T(0);
+              int back = t;   // t - d before the turn
+              for (int d = 0; d < D; ++d) {
+                fk += back == 0 ? 6 * (nang - 1) : -6;
+                back = back == 0 ? nang - 1 : back - 1;
+                sum += fj[0] + fk[0];
+                fj += 6 * nang;
+                fk += 6 * nang;
+              }
+              if (!(nang & 1)) sum += pg[6 * full + (t < half ? 6 * t + cc : 6 * (t - half) + 3 + cc)];
+              const int jt = tag_of(nb + kNbStride * t) >> 8;
+              Acc::add(&sF[3 * jt + cc], -sum);
+            }
+          } else {
           const int d0 = P0 < full ? diagonal(P0) : half, d1 = P0 + nbat - 1 < full ? diagonal(P0 + nbat - 1) : half;
           for (int u = lane; u < 3 * nang; u += 64) {
             const int t = (u * 21846) >> 16, cc = u - 3 * t;   // u / 3
@@ -2386,6 +2407,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
             }
             const int jt = tag_of(nb + kNbStride * t) >> 8;
             Acc::add(&sF[3 * jt + cc], -sum);
+          }
           }
           wave_sync();
         }
