@@ -873,8 +873,9 @@ __device__ inline int tag_of(const float* e) { return __float_as_int(e[8]); }
 __device__ inline int tag_of(const double* e) { return (int)e[8]; }
 static_assert(kNbStride >= 9, "record tag slot");
 
-// one neighbour's record from its displacement
-template <typename T>
+// one neighbour's record from its displacement (SLOPE: with the cutoffs'
+// derivatives, which the rows alone do not need)
+template <bool SLOPE, typename T>
 __device__ inline void put_record(const AevConst<T>& c, T* __restrict__ e, T d0, T d1, T d2, bool ang, int j, int sp) {
     const T r = m_sqrt(d0 * d0 + d1 * d1 + d2 * d2);
     e[0] = d0;
@@ -882,14 +883,16 @@ __device__ inline void put_record(const AevConst<T>& c, T* __restrict__ e, T d0,
     e[2] = d2;
     e[3] = r;
     e[4] = T(0.5) * m_cos(c.pi_rcr * r) + T(0.5);
-    e[5] = -T(0.5) * c.pi_rcr * m_sin(c.pi_rcr * r);
     e[6] = ang ? T(0.5) * m_cos(c.pi_rca * r) + T(0.5) : T(0);
-    e[7] = ang ? -T(0.5) * c.pi_rca * m_sin(c.pi_rca * r) : T(0);
+    if constexpr (SLOPE) {
+        e[5] = -T(0.5) * c.pi_rcr * m_sin(c.pi_rcr * r);
+        e[7] = ang ? -T(0.5) * c.pi_rca * m_sin(c.pi_rca * r) : T(0);
+    }
     put_tag(e, (j << 8) | sp);
 }
 
 // load_neighbours with the tag in the record instead of nsp / nid
-template <typename T>
+template <bool SLOPE, typename T>
 __device__ inline void load_records(const AevConst<T>& c, const T* __restrict__ sx,
                                     const int* __restrict__ ssp,
                                     const uint16_t* __restrict__ nb_list, int nang, int nall,
@@ -897,52 +900,74 @@ __device__ inline void load_records(const AevConst<T>& c, const T* __restrict__ 
     const T xi0 = sx[3 * il], xi1 = sx[3 * il + 1], xi2 = sx[3 * il + 2];
     for (int t = lane_id(); t < nall; t += 64) {
         const int j = nb_list[t];
-        put_record(c, nb + kNbStride * t, sx[3 * j] - xi0, sx[3 * j + 1] - xi1, sx[3 * j + 2] - xi2, t < nang, j, ssp[j]);
+        put_record<SLOPE>(c, nb + kNbStride * t, sx[3 * j] - xi0, sx[3 * j + 1] - xi1, sx[3 * j + 2] - xi2, t < nang, j, ssp[j]);
     }
 }
 
-// atom_neighbours and load_records in one step for molecules of at most 128
-// atoms: each lane holds two candidates of the staged order, and a hit writes
-// its record itself.  The list goes to out.
+// atom_neighbours, load_records and the first half of atom_lists in one step,
+// for molecules of at most 128 atoms: each lane holds two candidates and each
+// run's hits are counted element by element (ballots), which gives a hit its
+// place in the list and lane s where element s starts in the runs (ao, ro;
+// lane S: their ends).  A hit writes its record itself, and the list goes to
+// out.  No order of the molecule's atoms is staged and no barrier taken.
 constexpr int kDirectAtoms = 128;
 template <typename T>
-__device__ inline int find_records(const AevConst<T>& c, const T* sx4, const int* sid, const int* ssp, int n, int il,
-                                   T xi0, T xi1, T xi2, T rca2, T rcr2, int cap, T* __restrict__ nb,
-                                   uint16_t* out, int32_t* __restrict__ flag) {
-    const int lane = lane_id();
-    const unsigned long long lt = below(lane);
+__device__ inline int find_records(const AevConst<T>& c, const T* sx, const int* ssp, int n, int il, T rca2, T rcr2, int cap,
+                                   T* __restrict__ nb, uint16_t* out, int32_t* __restrict__ flag, int& ao, int& ro) {
+    const int lane = lane_id(), S = c.S;
+    const T xi0 = sx[3 * il], xi1 = sx[3 * il + 1], xi2 = sx[3 * il + 2];
     T d[2][3];
-    int j[2] = {0, 0};
-    bool ha[2] = {false, false}, hb[2] = {false, false};
+    int key[2][2], sp[2], at[2] = {0, 0};   // key: [slice][run], element of a hit
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int k = 64 * u + lane;
-        if (64 * u < n && k < n) {
-            j[u] = sid[k];
-            d[u][0] = sx4[4 * k] - xi0;
-            d[u][1] = sx4[4 * k + 1] - xi1;
-            d[u][2] = sx4[4 * k + 2] - xi2;
+        const int j = 64 * u + lane;
+        key[u][0] = key[u][1] = sp[u] = -1;
+        if (64 * u < n && j < n) {
+            d[u][0] = sx[3 * j] - xi0;
+            d[u][1] = sx[3 * j + 1] - xi1;
+            d[u][2] = sx[3 * j + 2] - xi2;
+            sp[u] = ssp[j];
             const T r2 = d[u][0] * d[u][0] + d[u][1] * d[u][1] + d[u][2] * d[u][2];
-            ha[u] = j[u] != il && r2 < rca2;
-            hb[u] = j[u] != il && r2 >= rca2 && r2 < rcr2;
+            if (j != il && r2 < rca2) key[u][0] = sp[u];
+            if (j != il && r2 >= rca2 && r2 < rcr2) key[u][1] = sp[u];
         }
     }
-    const unsigned long long a0 = __ballot(ha[0]), a1 = __ballot(ha[1]), b0 = __ballot(hb[0]), b1 = __ballot(hb[1]);
-    int nang = __popcll(a0) + __popcll(a1), nall = nang + __popcll(b0) + __popcll(b1);
+    int base = 0, nang = 0;
+    ao = ro = 0;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-        if (ha[u] || hb[u]) {
-            const int t = ha[u] ? (u ? __popcll(a0) : 0) + __popcll((u ? a1 : a0) & lt)
-                                : nang + (u ? __popcll(b0) : 0) + __popcll((u ? b1 : b0) & lt);
-            if (t < cap) {
-                put_record(c, nb + kNbStride * t, d[u][0], d[u][1], d[u][2], ha[u], j[u], ssp[j[u]]);
-                out[t] = (uint16_t)j[u];
+    for (int run = 0; run < 2; ++run) {
+        int first = 0;
+        for (int q = 0; q < S; ++q) {
+            first = lane == q ? base : first;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (64 * u >= n) continue;
+                const unsigned long long m = __ballot(key[u][run] == q);
+                const int t = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, base));
+                at[u] = key[u][run] == q ? t : at[u];
+                base += __popcll(m);
             }
         }
+        first = lane == S ? base : first;
+        if (run == 0) nang = base, ao = first;
+        else ro = first;
+    }
+    int nall = base;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const bool ang = key[u][0] >= 0;
+        if (64 * u < n && (ang || key[u][1] >= 0) && at[u] < cap) {
+            const int j = 64 * u + lane;
+            put_record<false>(c, nb + kNbStride * at[u], d[u][0], d[u][1], d[u][2], ang, j, sp[u]);
+            out[at[u]] = (uint16_t)j;
+        }
+    }
     if (nall > cap) {
         if (lane == 0) atomicOr(flag, FLAG_CAPACITY);
         nall = cap;
         nang = nang > cap ? cap : nang;
+        ao = min(ao, cap);
+        ro = min(ro, cap);
     }
     return nang | (nall << 16);
 }
@@ -981,16 +1006,34 @@ __device__ inline void block_elements(int L, int S, int& a, int& b) {
     b = a + (L - base);
 }
 
-// The lists of one atom (wave-wide); sp_of(t) = element of neighbour t, (ba,
-// bb) = this lane's block's elements.  Both runs (angular [0, nang),
+// The lists of one atom (wave-wide) from where each element starts in the two
+// runs: lane s <= S, ao in the angular and ro in the radial-only one; (ba, bb)
+// = this lane's block's elements.
+__device__ inline AtomLists atom_lists(int ao, int ro, int S, int ba, int bb) {
+    const int lane = lane_id();
+    AtomLists al;
+    const int ae = next_lane(ao);
+    al.range = ao | (ae << 8) | (ro << 16) | (next_lane(ro) << 24);
+    // angular block sizes and their prefix
+    const int NB = S * (S + 1) / 2, run = ao | ((ae - ao) << 8);
+    const int ra = __shfl(run, ba), rb = __shfl(run, bb), na = ra >> 8, nb = rb >> 8;
+    const int cnt = lane < NB ? (ba < bb ? __mul24(na, nb) : __mul24(na, na - 1) >> 1) : 0;
+    al.bhi = wave_scan(cnt);
+    al.blo = al.bhi - cnt;
+    al.desc = (ra & 0xff) | ((rb & 0xff) << 8) | (nb << 16) | (ba == bb ? 1 << 24 : 0);
+    al.npair = __builtin_amdgcn_readlane(al.bhi, 63);
+    return al;
+}
+
+// The same from the records of a list: both runs (angular [0, nang),
 // radial-only [nang, nall)) are sorted by element, so an element starts after
 // the neighbours of smaller ones.
-template <typename SpOf>
-__device__ inline AtomLists atom_lists(SpOf sp_of, int nang, int nall, int S, int ba, int bb) {
+template <typename T>
+__device__ inline AtomLists record_lists(const T* nb, int nang, int nall, int S, int ba, int bb) {
     const int lane = lane_id();
     int before = 0;   // lane s <= S: smaller elements' neighbours, angular | radial-only << 16
     for (int t0 = 0; t0 < nall; t0 += 64) {
-        const int sp = t0 + lane < nall ? sp_of(t0 + lane) : kMaxSpecies;
+        const int sp = t0 + lane < nall ? tag_of(nb + kNbStride * (t0 + lane)) & 0xff : kMaxSpecies;
         const int na = min(max(nang - t0, 0), 64);
         const unsigned long long ang = na == 64 ? ~0ull : (1ull << na) - 1;
         for (int s = 1; s <= S; ++s) {
@@ -999,19 +1042,7 @@ __device__ inline AtomLists atom_lists(SpOf sp_of, int nang, int nall, int S, in
             before += lane == s ? both : 0;
         }
     }
-    AtomLists al;
-    const int ao = before & 0xffff, ro = nang + (before >> 16);
-    const int ae = next_lane(ao);
-    al.range = ao | (ae << 8) | (ro << 16) | (next_lane(ro) << 24);
-    // angular block sizes and their prefix
-    const int NB = S * (S + 1) / 2, run = ao | ((ae - ao) << 8);
-    const int ra = __shfl(run, ba), rb = __shfl(run, bb), na = ra >> 8, nb = rb >> 8;
-    const int cnt = lane < NB ? (ba < bb ? na * nb : na * (na - 1) / 2) : 0;
-    al.bhi = wave_scan(cnt);
-    al.blo = al.bhi - cnt;
-    al.desc = (ra & 0xff) | ((rb & 0xff) << 8) | (nb << 16) | (ba == bb ? 1 << 24 : 0);
-    al.npair = __builtin_amdgcn_readlane(al.bhi, 63);
-    return al;
+    return atom_lists(before & 0xffff, nang + (before >> 16), S, ba, bb);
 }
 
 // Neighbour indices (j, k) of this lane's pair p0 + lane (block-ordered
@@ -1231,6 +1262,7 @@ __device__ inline void angular_rows(const AtomLists& al, int p0, int nbat, const
 // the molecules' writes the bucket table, the row tiles' elements, the padding
 // rows and the capacity flags (in a molecule's own workgroup those were 3,600
 // of its 33,600 clocks).
+static_assert(kMaxSpecies <= 8 && kPrepBlock <= 64 * 255, "a byte an element and lane");
 struct WaveBuckets {
     int A0, A1;
     bool ok;          // the call's atom range is valid
@@ -1246,30 +1278,59 @@ __device__ inline WaveBuckets wave_buckets(const BucketFuse& bk, int S, int A, c
     w.ok = atom_range(A, bk.B, bk.dA, mol_off, bk.sub, w.A0, w.A1);
     w.tot = w.pre = 0;
     w.bad = false;
-    constexpr int U = 4;   // segments of 64 atoms whose labels load together
-    for (int a4 = w.A0; a4 < w.A1; a4 += 64 * U) {
-        int sv[U];
+    auto element = [&](int a1, int label, bool& bad) {   // of atom a1 + lane, -1 past the end
+        if (bk.zlut) label = (label >= 0 && label < kZLut) ? (int)bk.zlut[label] : -1;
+        bad = a1 + lane < w.A1 && (label < 0 || label >= S);
+        return a1 + lane < w.A1 ? (bad ? 0 : label) : -1;
+    };
+    if (w.A1 - w.A0 <= 64) {
+        bool bad = false;
+        const int s = w.A1 > w.A0 ? element(w.A0, species[min(w.A0 + lane, w.A1 - 1)], bad) : -1;
+        const int before = min(max(a - w.A0, 0), 64);
+        const unsigned long long lt = before == 64 ? ~0ull : (1ull << before) - 1;
+        w.bad = __ballot(bad && w.A0 + lane == a) != 0;
+        for (int q = 0; q < S; ++q) {
+            const unsigned long long m = __ballot(s == q);
+            const int ct = __popcll(m), cb = __popcll(m & lt);
+            w.tot = lane == q ? ct : w.tot;
+            w.pre = lane == q ? cb : w.pre;
+        }
+    } else {
+        // every lane counts its atoms, a byte an element (16 at most), and the
+        // counts are added over the lanes in 16 bits: ballots for every 64
+        // atoms took 12,900 of 34,600 clocks at 16 x 40 atoms
+        constexpr int U = 8;   // labels loaded together
+        unsigned long long nt = 0, np = 0;
+        for (int a8 = w.A0; a8 < w.A1; a8 += 64 * U) {
+            int label[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) sv[u] = species[min(a4 + 64 * u + lane, w.A1 - 1)];
-        if (bk.zlut)
+            for (int u = 0; u < U; ++u) label[u] = species[min(a8 + 64 * u + lane, w.A1 - 1)];
 #pragma unroll
-            for (int u = 0; u < U; ++u) sv[u] = (sv[u] >= 0 && sv[u] < kZLut) ? (int)bk.zlut[sv[u]] : -1;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int a1 = a4 + 64 * u;
-            if (a1 >= w.A1) break;
-            const bool bad = sv[u] < 0 || sv[u] >= S;
-            const int s = a1 + lane < w.A1 ? (bad ? 0 : sv[u]) : -1;
-            const int before = min(max(a - a1, 0), 64);
-            const unsigned long long lt = before == 64 ? ~0ull : (1ull << before) - 1;
-            w.bad |= __ballot(bad && a1 + lane == a && s >= 0) != 0;
-            for (int q = 0; q < S; ++q) {
-                const unsigned long long m = __ballot(s == q);
-                const int ct = __popcll(m), cb = __popcll(m & lt);
-                w.tot += lane == q ? ct : 0;
-                w.pre += lane == q ? cb : 0;
+            for (int u = 0; u < U; ++u) {
+                const int a1 = a8 + 64 * u;
+                if (a1 >= w.A1) break;
+                bool bad;
+                const int s = element(a1, label[u], bad);
+                w.bad |= __ballot(bad && a1 + lane == a) != 0;
+                const unsigned long long one = s < 0 ? 0ull : 1ull << (8 * s);
+                nt += one;
+                np += a1 + lane < a ? one : 0ull;
             }
         }
+        // lane q: the sum over the lanes of byte q
+        auto total = [&](unsigned long long v) {
+            int even[2], odd[2];   // elements 0, 2 | 4, 6 and 1, 3 | 5, 7
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const unsigned x = (unsigned)(v >> (32 * h));
+                even[h] = __builtin_amdgcn_readlane(wave_scan((int)(x & 0x00ff00ffu)), 63);
+                odd[h] = __builtin_amdgcn_readlane(wave_scan((int)(x >> 8 & 0x00ff00ffu)), 63);
+            }
+            const int x = lane & 4 ? (lane & 1 ? odd[1] : even[1]) : (lane & 1 ? odd[0] : even[0]);
+            return lane < 8 ? (int)((unsigned)x >> (lane & 2 ? 16 : 0) & 0xffffu) : 0;
+        };
+        w.tot = total(nt);
+        w.pre = total(np);
     }
     const int pc = (w.tot + bk.row_tile - 1) / bk.row_tile * bk.row_tile;
     w.base = row_scan(pc) - pc;
@@ -1343,7 +1404,10 @@ __device__ inline void bucket_table(const BucketFuse& bk, int S, int A, int max_
 // 18.0 us; 600 atoms: 23.4 -> 20.1; 1,024 x 48 atoms, BF16: 110 -> 106), and
 // from the sums on the matrix cores, where a term costs one instruction and
 // two LDS reads for all its slots (18.0 -> 15.2 us; 106 -> 100; 512 molecules
-// of 10 to 120 atoms 111 -> 97).  Large batches are bound by the lanes'
+// of 10 to 120 atoms 111 -> 97).  The neighbour search that counts its hits by
+// element and the counting of labels by lanes took 16 x 40 atoms from 21.9 to
+// 15.0 us, and 24 atoms in FP64 (with the cutoffs' slopes left out) from 21.6
+// to 19.4.  Large batches are bound by the lanes'
 // instructions, 900 an atom.
 // blocks without pairs: zeros in 16-byte pieces, a few lanes per block
 template <typename TS, typename T>
@@ -1405,15 +1469,17 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     T* nb = lb.take<T>((size_t)nw * cap * kNbStride) + (size_t)wave * cap * kNbStride;
     T* pf = lb.take<T>((size_t)nw * (64 + kPairRoom) * PF) + (size_t)wave * (64 + kPairRoom) * PF;
     int* mark = lb.take<int>((size_t)nw * 64) + (size_t)wave * 64;
-    T* sx4 = fuse ? lb.take<T>(4 * (size_t)max_apm) : nullptr;
-    int* sid = fuse ? lb.take<int>(max_apm) : nullptr;
-    uint16_t* wl = fuse && max_apm > kDirectAtoms ? lb.take<uint16_t>((size_t)nw * cap) + (size_t)wave * cap : nullptr;
+    // (molecules beyond the direct search: their order by element, and a list)
+    const bool staged = fuse && max_apm > kDirectAtoms;
+    T* sx4 = staged ? lb.take<T>(4 * (size_t)max_apm) : nullptr;
+    int* sid = staged ? lb.take<int>(max_apm) : nullptr;
+    uint16_t* wl = staged ? lb.take<uint16_t>((size_t)nw * cap) + (size_t)wave * cap : nullptr;
     cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, MODE == kBuckets ? nullptr : row_of_atom,
             MODE == kBuckets ? nf.bk.zlut : nullptr);
     WaveBuckets wb;
     if constexpr (MODE == kBuckets) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + i0 + wave);
     __syncthreads();
-    if constexpr (fuse) {
+    if (fuse && !direct) {
         if (wave == 0) stage_element_order(cs.sx, cs.ssp, n, S, sx4, sid);
         __syncthreads();
     }
@@ -1426,7 +1492,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     const int qa1 = ql / NZ, qa2 = (ql + 16) / NZ, qzl = ql % NZ;
     for (int ic = wave; ic < nc; ic += nw) {
         const int il = i0 + ic;
-        int cnt, row;
+        int cnt, row, ao = 0, ro = 0;
         const uint16_t* lst;
         if constexpr (MODE == kBuckets) {
             if (ic != wave) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + il);
@@ -1440,10 +1506,11 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             // kernel clears them
             if (nf.F && lane < 3) nf.F[3 * ((size_t)a0 + il) + lane] = T(0);
             if (nf.Fq && lane < 3) nf.Fq[3 * ((size_t)a0 + il) + lane] = 0ull;
-            const T xi0 = cs.sx[3 * il], xi1 = cs.sx[3 * il + 1], xi2 = cs.sx[3 * il + 2];
             uint16_t* out = nf.nbr + ((size_t)a0 + il) * cap;
-            cnt = direct ? find_records(c, sx4, sid, cs.ssp, n, il, xi0, xi1, xi2, nf.rca2, nf.rcr2, cap, nb, out, nf.flag)
-                         : atom_neighbours(sx4, sid, n, il, xi0, xi1, xi2, nf.rca2, nf.rcr2, cap, wl, out, nf.flag);
+            if (direct) cnt = find_records(c, cs.sx, cs.ssp, n, il, nf.rca2, nf.rcr2, cap, nb, out, nf.flag, ao, ro);
+            else
+                cnt = atom_neighbours(sx4, sid, n, il, cs.sx[3 * il], cs.sx[3 * il + 1], cs.sx[3 * il + 2], nf.rca2, nf.rcr2,
+                                      cap, wl, out, nf.flag);
             if (lane == 0) nf.cnt[(size_t)a0 + il] = cnt;
             wave_sync();
             lst = wl;
@@ -1452,11 +1519,14 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             lst = cs.clst + (size_t)ic * cap;
         }
         const int nang = cnt & 0xffff, nall = cnt >> 16;
-        if (!(fuse && direct)) {
-            load_records(c, cs.sx, cs.ssp, lst, nang, nall, il, nb);
+        AtomLists al;
+        if (fuse && direct) {
+            al = atom_lists(ao, ro, S, ba, bb);
+        } else {
+            load_records<false>(c, cs.sx, cs.ssp, lst, nang, nall, il, nb);
             wave_sync();
+            al = record_lists(nb, nang, nall, S, ba, bb);
         }
-        const AtomLists al = atom_lists([&](int t) { return tag_of(nb + kNbStride * t) & 0xff; }, nang, nall, S, ba, bb);
         const int npair = al.npair;
         // every slot is stored once, straight from the lane that owns it
         TS* grow = G + (size_t)row * c.Dp;
@@ -1623,8 +1693,9 @@ static size_t aev_lds(int max_apm, int cap, int NZ, int nw, bool fuse = false) {
     const int PF = kNAZ / NZ + NZ;
     return ChunkStage<T>::bytes(max_apm, cap, !fuse) + lds_bytes<T>((size_t)nw * cap * kNbStride) +
            lds_bytes<T>((size_t)nw * (64 + kPairRoom) * PF) + lds_bytes<int>((size_t)nw * 64) +
-           (fuse ? lds_bytes<T>(4 * (size_t)max_apm) + lds_bytes<int>(max_apm) : 0) +
-           (fuse && max_apm > kDirectAtoms ? lds_bytes<uint16_t>((size_t)nw * cap) : 0);
+           (fuse && max_apm > kDirectAtoms
+                ? lds_bytes<T>(4 * (size_t)max_apm) + lds_bytes<int>(max_apm) + lds_bytes<uint16_t>((size_t)nw * cap)
+                : 0);
 }
 
 template <typename P>
@@ -1925,7 +1996,7 @@ __global__ __launch_bounds__(256) void k_aev_tangent(AevConst<float> c, int A, i
         const int il = i0 + ic;
         const int cnt = uniform(cs.ccnt[ic]), nang = cnt & 0xffff, nall = cnt >> 16;
         TS* grow = Gd + (size_t)uniform(cs.crow[ic]) * c.Dp;
-        load_records(c, cs.sx, cs.ssp, cs.clst + (size_t)ic * cap, nang, nall, il, nb);
+        load_records<true>(c, cs.sx, cs.ssp, cs.clst + (size_t)ic * cap, nang, nall, il, nb);
         wave_sync();
         const float v0 = sv[3 * il], v1 = sv[3 * il + 1], v2 = sv[3 * il + 2];
         for (int t = lane; t < nall; t += 64) {
@@ -1939,7 +2010,7 @@ __global__ __launch_bounds__(256) void k_aev_tangent(AevConst<float> c, int A, i
             o[3] = (e[0] * w0 + e[1] * w1 + e[2] * w2) * m_rcp(e[3]);   // dr/dt
         }
         wave_sync();
-        const AtomLists al = atom_lists([&](int t) { return tag_of(nb + kNbStride * t) & 0xff; }, nang, nall, S, ba, bb);
+        const AtomLists al = record_lists(nb, nang, nall, S, ba, bb);
         for (int e = c.D + lane; e < c.Dp; e += 64) grow[e] = Store<TS>::st(0.f);
         radial_rows<true>(c, al, nb, nt, nang, nall, (f32x4*)pf, grow, nullptr);
         f32x4 carry = {0.f, 0.f, 0.f, 0.f};
@@ -2213,7 +2284,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
                 }
             }
         }
-        load_records(c, cs.sx, cs.ssp, cs.clst + (size_t)ic * cap, nang, nall, il, nb);
+        load_records<true>(c, cs.sx, cs.ssp, cs.clst + (size_t)ic * cap, nang, nall, il, nb);
         wave_sync();
         T fi0 = 0, fi1 = 0, fi2 = 0;   // force on the central atom, per lane
         // radial: lane per (neighbour, group of 4 shifts)
