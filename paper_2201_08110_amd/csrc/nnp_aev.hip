@@ -119,6 +119,17 @@ template <typename T> __device__ inline T row_sum(T v) {
 }
 __device__ inline unsigned long long below(int lane) { return lane == 0 ? 0ull : ~0ull >> (64 - lane); }
 
+// The molecule of a workgroup of a (molecules, chunks) grid.  Workgroups go to
+// the eight XCDs in turn, so with a multiple of eight molecules all chunks of
+// one would land on one XCD and the XCDs' shares differ as the molecules do (48
+// molecules of 10 to 120 atoms: 52 to 156 workgroups, the fullest taking two
+// rounds, 32 us instead of 20).  Row y shifts the molecules within every whole
+// eight by y where the grid's width does not already do so.
+__device__ inline int block_molecule(int y) {
+    const int x = blockIdx.x, w = gridDim.x;
+    return (w & 1) || (x | 7) >= w ? x : (x & ~7) | ((x + y) & 7);
+}
+
 // Starts the load of every line of the kernel's arguments at once: the
 // compiler loads an argument where it is first used, and each line that is
 // not yet in the scalar cache costs about a thousand clocks there (2,300 of
@@ -712,7 +723,7 @@ __global__ __launch_bounds__(256) void k_nbr_pairs(int A, int S, int max_apm, in
                                                    int32_t* __restrict__ nbr_cnt,
                                                    int32_t* __restrict__ flag) {
     extern __shared__ __align__(16) char smem[];
-    const int b = blockIdx.x;
+    const int b = block_molecule(blockIdx.y);
     const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     const int i0 = blockIdx.y * chunk;
@@ -1442,7 +1453,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     constexpr int PF = NA + NZ;
     extern __shared__ __align__(16) char smem[];
     touch_kernargs<sizeof(AevConst<T>) + sizeof(NbrFuse<T>) + 80>();
-    const int b = blockIdx.x;
+    const int b = block_molecule(blockIdx.y);
     // with the bucketing fused in, the last row of workgroups is one
     // workgroup that writes the batch's bucket table
     if constexpr (MODE == kBuckets) {
@@ -1817,7 +1828,7 @@ __global__ __launch_bounds__(256) void k_aev_jvp(AevConst<typename P::T> c, int 
     constexpr int PF = 2 * NA + 2 * NZ;       // P[NA] Q[NA] fz[NZ] dfz[NZ]
     constexpr int TS_ = 4;                     // per neighbour: v_j - v_i (3), rdot
     extern __shared__ __align__(16) char smem[];
-    const int b = blockIdx.x;
+    const int b = block_molecule(blockIdx.y);
     const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     const int i0 = blockIdx.y * chunk;
@@ -1969,7 +1980,7 @@ __global__ __launch_bounds__(256) void k_aev_tangent(AevConst<float> c, int A, i
     typedef typename P::TS TS;
     constexpr int NA = kNAZ / NZ, PT = NA + NZ, PF = 2 * PT;
     extern __shared__ __align__(16) char smem[];
-    const int b = blockIdx.x;
+    const int b = block_molecule(blockIdx.y);
     const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     const int i0 = blockIdx.y * chunk;
@@ -2214,13 +2225,13 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
     extern __shared__ __align__(16) char smem[];
     touch_kernargs<sizeof(AevConst<T>) + sizeof(EnergyArgs<P>) + 88>();
     const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
-    int b = blockIdx.x, by = blockIdx.y;
+    int b = block_molecule(blockIdx.y), by = blockIdx.y;
     // The energies (as k_energy computes them), a molecule per wave, by the
     // first row of workgroups: their chain of loads is as long as half the
     // forces' of an atom, and in the force workgroups one wave waited for it
     // before it began (8,300 of 22,000 clocks on 64 atoms).
     if (ea.E && --by < 0) {
-        b = b * nw + wave;
+        b = blockIdx.x * nw + wave;
         if (b < ea.B && !(ea.dcnt && b >= ea.dcnt[0])) {
             const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
             const bool ok = !(a0 < 0 || n < 0 || a0 + n > A);
@@ -2592,7 +2603,7 @@ __global__ __launch_bounds__(256) void k_forces_tan(AevConst<typename P::T> c, i
     typedef Du<T> D;
     constexpr int NA = kNAZ / NZ;
     extern __shared__ __align__(16) char smem[];
-    const int b = blockIdx.x;
+    const int b = block_molecule(blockIdx.y);
     const int a0 = mol_off[b], n = mol_off[b + 1] - a0;
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     const int i0 = blockIdx.y * chunk;
