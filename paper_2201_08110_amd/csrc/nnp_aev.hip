@@ -793,14 +793,16 @@ hipError_t launch_neighbours(const Shape& sh, const AevConst<typename P::T>& c,
 
 // ==========================================================================
 // Shared set-up of the AEV and force kernels: the molecule's coordinates and
-// elements, and the chunk's neighbour counts, bucket rows and neighbour lists,
-// all staged in LDS once per workgroup.
+// elements, and the chunk's neighbour counts and bucket rows, staged in LDS
+// once per workgroup.  The tangent kernels stage the neighbour lists too; the
+// row and force kernels read an atom's list where they need it, once: 3.8 KB
+// less LDS at 120 atoms, and with the records below five row and six force
+// workgroups a CU instead of four and five (512 molecules of 10 to 120 atoms
+// 92 -> 84 us and 85 -> 77; a list in flight one atom ahead measured 87 and 78).
 // Per-neighbour LDS record: dx dy dz r fc_r dfc_r fc_a dfc_a, padded to an
 // odd number of words so that lanes reading the same field of consecutive
 // records hit distinct banks (a stride of 8 words put every fourth record on
-// the same bank).  The featuriser's LDS stays within a quarter of the CU's
-// 160 KB on the headline shape (four workgroups per CU): odd strides for its
-// pair-factor records too would cross that line.
+// the same bank).
 constexpr int kNbStride = 9;
 
 template <typename T> struct ChunkStage {
@@ -878,11 +880,17 @@ __device__ inline void load_neighbours(const AevConst<T>& c, const T* __restrict
 // The record's ninth word (padding otherwise) carries its tag: neighbour
 // index j << 8 | element of j, so the featuriser and force kernels keep no
 // per-neighbour index arrays beside the records.
-__device__ inline void put_tag(float* e, int v) { e[8] = __int_as_float(v); }
-__device__ inline void put_tag(double* e, int v) { e[8] = (double)v; }
-__device__ inline int tag_of(const float* e) { return __float_as_int(e[8]); }
-__device__ inline int tag_of(const double* e) { return (int)e[8]; }
+// The row kernel's records leave the cutoffs' derivatives out (SLOPE false):
+// with molecules of 120 atoms that makes five of its workgroups fit a CU
+// instead of four.
+template <bool SLOPE> struct Rec {
+    static constexpr int stride = SLOPE ? kNbStride : 7, fca = SLOPE ? 6 : 5, tag = SLOPE ? 8 : 6;
+};
 static_assert(kNbStride >= 9, "record tag slot");
+template <bool SLOPE = true> __device__ inline void put_tag(float* e, int v) { e[Rec<SLOPE>::tag] = __int_as_float(v); }
+template <bool SLOPE = true> __device__ inline void put_tag(double* e, int v) { e[Rec<SLOPE>::tag] = (double)v; }
+template <bool SLOPE = true> __device__ inline int tag_of(const float* e) { return __float_as_int(e[Rec<SLOPE>::tag]); }
+template <bool SLOPE = true> __device__ inline int tag_of(const double* e) { return (int)e[Rec<SLOPE>::tag]; }
 
 // one neighbour's record from its displacement (SLOPE: with the cutoffs'
 // derivatives, which the rows alone do not need)
@@ -894,12 +902,12 @@ __device__ inline void put_record(const AevConst<T>& c, T* __restrict__ e, T d0,
     e[2] = d2;
     e[3] = r;
     e[4] = T(0.5) * m_cos(c.pi_rcr * r) + T(0.5);
-    e[6] = ang ? T(0.5) * m_cos(c.pi_rca * r) + T(0.5) : T(0);
+    e[Rec<SLOPE>::fca] = ang ? T(0.5) * m_cos(c.pi_rca * r) + T(0.5) : T(0);
     if constexpr (SLOPE) {
         e[5] = -T(0.5) * c.pi_rcr * m_sin(c.pi_rcr * r);
         e[7] = ang ? -T(0.5) * c.pi_rca * m_sin(c.pi_rca * r) : T(0);
     }
-    put_tag(e, (j << 8) | sp);
+    put_tag<SLOPE>(e, (j << 8) | sp);
 }
 
 // load_neighbours with the tag in the record instead of nsp / nid
@@ -911,7 +919,7 @@ __device__ inline void load_records(const AevConst<T>& c, const T* __restrict__ 
     const T xi0 = sx[3 * il], xi1 = sx[3 * il + 1], xi2 = sx[3 * il + 2];
     for (int t = lane_id(); t < nall; t += 64) {
         const int j = nb_list[t];
-        put_record<SLOPE>(c, nb + kNbStride * t, sx[3 * j] - xi0, sx[3 * j + 1] - xi1, sx[3 * j + 2] - xi2, t < nang, j, ssp[j]);
+        put_record<SLOPE>(c, nb + Rec<SLOPE>::stride * t, sx[3 * j] - xi0, sx[3 * j + 1] - xi1, sx[3 * j + 2] - xi2, t < nang, j, ssp[j]);
     }
 }
 
@@ -969,7 +977,7 @@ __device__ inline int find_records(const AevConst<T>& c, const T* sx, const int*
         const bool ang = key[u][0] >= 0;
         if (64 * u < n && (ang || key[u][1] >= 0) && at[u] < cap) {
             const int j = 64 * u + lane;
-            put_record<false>(c, nb + kNbStride * at[u], d[u][0], d[u][1], d[u][2], ang, j, sp[u]);
+            put_record<false>(c, nb + Rec<false>::stride * at[u], d[u][0], d[u][1], d[u][2], ang, j, sp[u]);
             out[at[u]] = (uint16_t)j;
         }
     }
@@ -1039,12 +1047,12 @@ __device__ inline AtomLists atom_lists(int ao, int ro, int S, int ba, int bb) {
 // The same from the records of a list: both runs (angular [0, nang),
 // radial-only [nang, nall)) are sorted by element, so an element starts after
 // the neighbours of smaller ones.
-template <typename T>
+template <bool SLOPE, typename T>
 __device__ inline AtomLists record_lists(const T* nb, int nang, int nall, int S, int ba, int bb) {
     const int lane = lane_id();
     int before = 0;   // lane s <= S: smaller elements' neighbours, angular | radial-only << 16
     for (int t0 = 0; t0 < nall; t0 += 64) {
-        const int sp = t0 + lane < nall ? tag_of(nb + kNbStride * (t0 + lane)) & 0xff : kMaxSpecies;
+        const int sp = t0 + lane < nall ? tag_of<SLOPE>(nb + Rec<SLOPE>::stride * (t0 + lane)) & 0xff : kMaxSpecies;
         const int na = min(max(nang - t0, 0), 64);
         const unsigned long long ang = na == 64 ? ~0ull : (1ull << na) - 1;
         for (int s = 1; s <= S; ++s) {
@@ -1140,8 +1148,8 @@ __device__ inline void radial_rows(const AevConst<float>& c, const AtomLists& al
     for (int t0 = 0; t0 < nall; t0 += kRadSlice) {
         const int t = t0 + lane;
         const bool act = lane < kRadSlice && t < nall;
-        const float* e = nb + kNbStride * (act ? t : 0);
-        const int sp = tag_of(e) & 0xff, rng = __shfl(al.range, sp) >> (t < nang ? 0 : 16);
+        const float* e = nb + Rec<TANGENT>::stride * (act ? t : 0);
+        const int sp = tag_of<TANGENT>(e) & 0xff, rng = __shfl(al.range, sp) >> (t < nang ? 0 : 16);
         const int p = t - (rng & 0xff), n = (rng >> 8 & 0xff) - (rng & 0xff);
         const bool second = p < (n & ~3) && (p & 1);
         const unsigned long long ma = __ballot(act), ms = __ballot(second), mo = __ballot(sp & 1);
@@ -1449,6 +1457,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
                                              NbrFuse<typename P::T> nf) {
     typedef typename P::T T;
     typedef typename P::TS TS;
+    typedef Rec<false> R;
     constexpr int NA = kNAZ / NZ;
     constexpr int PF = NA + NZ;
     extern __shared__ __align__(16) char smem[];
@@ -1476,8 +1485,9 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     const bool direct = n <= kDirectAtoms;
     LdsBump lb(smem);
     ChunkStage<T> cs;
-    cs.take(lb, max_apm, cap, !fuse);
-    T* nb = lb.take<T>((size_t)nw * cap * kNbStride) + (size_t)wave * cap * kNbStride;
+    cs.take(lb, max_apm, cap, false);
+    int* ccnt = fuse ? nullptr : lb.take<int>(kChunk);
+    T* nb = lb.take<T>((size_t)nw * cap * R::stride) + (size_t)wave * cap * R::stride;
     T* pf = lb.take<T>((size_t)nw * (64 + kPairRoom) * PF) + (size_t)wave * (64 + kPairRoom) * PF;
     int* mark = lb.take<int>((size_t)nw * 64) + (size_t)wave * 64;
     // (molecules beyond the direct search: their order by element, and a list)
@@ -1485,6 +1495,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     T* sx4 = staged ? lb.take<T>(4 * (size_t)max_apm) : nullptr;
     int* sid = staged ? lb.take<int>(max_apm) : nullptr;
     uint16_t* wl = staged ? lb.take<uint16_t>((size_t)nw * cap) + (size_t)wave * cap : nullptr;
+    if (!fuse && tid < nc) ccnt[tid] = nbr_cnt[(size_t)a0 + i0 + tid];
     cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, MODE == kBuckets ? nullptr : row_of_atom,
             MODE == kBuckets ? nf.bk.zlut : nullptr);
     WaveBuckets wb;
@@ -1526,8 +1537,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             wave_sync();
             lst = wl;
         } else {
-            cnt = uniform(cs.ccnt[ic]);
-            lst = cs.clst + (size_t)ic * cap;
+            cnt = uniform(ccnt[ic]);
+            lst = nbr + ((size_t)a0 + il) * cap;
         }
         const int nang = cnt & 0xffff, nall = cnt >> 16;
         AtomLists al;
@@ -1536,7 +1547,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         } else {
             load_records<false>(c, cs.sx, cs.ssp, lst, nang, nall, il, nb);
             wave_sync();
-            al = record_lists(nb, nang, nall, S, ba, bb);
+            al = record_lists<false>(nb, nang, nall, S, ba, bb);
         }
         const int npair = al.npair;
         // every slot is stored once, straight from the lane that owns it
@@ -1567,8 +1578,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
                         T r[4], f[4];
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
-                            r[u] = nb[kNbStride * (t + u) + 3];
-                            f[u] = nb[kNbStride * (t + u) + 4];
+                            r[u] = nb[R::stride * (t + u) + 3];
+                            f[u] = nb[R::stride * (t + u) + 4];
                         }
 #pragma unroll
                         for (int u = 0; u < 4; u += 2) {
@@ -1578,8 +1589,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
                         }
                     }
                     for (; t < t1; ++t) {
-                        const T d = nb[kNbStride * t + 3] - sk;
-                        acc0 += m_exp(-c.eta_r * d * d) * nb[kNbStride * t + 4];
+                        const T d = nb[R::stride * t + 3] - sk;
+                        acc0 += m_exp(-c.eta_r * d * d) * nb[R::stride * t + 4];
                     }
                 }
                 put(kNR * s + k, c.radial_pref * (acc0 + acc1));
@@ -1600,14 +1611,14 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
             int j, k;
             batch_pairs(al, p0, mark, j, k);
             if (lane < nbat) {
-                const T* ej = nb + kNbStride * j;
-                const T* ek = nb + kNbStride * k;
+                const T* ej = nb + R::stride * j;
+                const T* ek = nb + R::stride * k;
                 const T rj = ej[3], rk = ek[3];
                 T cs_ = (ej[0] * ek[0] + ej[1] * ek[1] + ej[2] * ek[2]) * m_rcp(rj * rk);
                 cs_ = cs_ > T(1) ? T(1) : (cs_ < T(-1) ? T(-1) : cs_);
                 const T cp = c.angle_scale * cs_;
                 const T sn = m_sqrt(T(1) - cp * cp);
-                const T fcc = ej[6] * ek[6];
+                const T fcc = ej[R::fca] * ek[R::fca];
                 const T rm = T(0.5) * (rj + rk);
                 T f[PF];
 #pragma unroll
@@ -1702,8 +1713,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
 template <typename T>
 static size_t aev_lds(int max_apm, int cap, int NZ, int nw, bool fuse = false) {
     const int PF = kNAZ / NZ + NZ;
-    return ChunkStage<T>::bytes(max_apm, cap, !fuse) + lds_bytes<T>((size_t)nw * cap * kNbStride) +
-           lds_bytes<T>((size_t)nw * (64 + kPairRoom) * PF) + lds_bytes<int>((size_t)nw * 64) +
+    return ChunkStage<T>::bytes(max_apm, cap, false) + (fuse ? 0 : lds_bytes<int>(kChunk)) +
+           lds_bytes<T>((size_t)nw * cap * Rec<false>::stride) + lds_bytes<T>((size_t)nw * (64 + kPairRoom) * PF) + lds_bytes<int>((size_t)nw * 64) +
            (fuse && max_apm > kDirectAtoms
                 ? lds_bytes<T>(4 * (size_t)max_apm) + lds_bytes<int>(max_apm) + lds_bytes<uint16_t>((size_t)nw * cap)
                 : 0);
@@ -2021,7 +2032,7 @@ __global__ __launch_bounds__(256) void k_aev_tangent(AevConst<float> c, int A, i
             o[3] = (e[0] * w0 + e[1] * w1 + e[2] * w2) * m_rcp(e[3]);   // dr/dt
         }
         wave_sync();
-        const AtomLists al = record_lists(nb, nang, nall, S, ba, bb);
+        const AtomLists al = record_lists<true>(nb, nang, nall, S, ba, bb);
         for (int e = c.D + lane; e < c.Dp; e += 64) grow[e] = Store<TS>::st(0.f);
         radial_rows<true>(c, al, nb, nt, nang, nall, (f32x4*)pf, grow, nullptr);
         f32x4 carry = {0.f, 0.f, 0.f, 0.f};
@@ -2251,7 +2262,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
 
     LdsBump lb(smem);
     ChunkStage<T> cs;
-    cs.take(lb, max_apm, cap);
+    cs.take(lb, max_apm, cap, false);
+    int* ccnt = lb.take<int>(kChunk);
     V* sF = lb.take<V>(3 * (size_t)max_apm);
     T* nb = lb.take<T>((size_t)nw * cap * kNbStride) + (size_t)wave * cap * kNbStride;
     T* pg = lb.take<T>((size_t)nw * 64 * 6) + (size_t)wave * 64 * 6;   // a batch's pair forces
@@ -2261,13 +2273,14 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
     T* g = GD ? nullptr : lb.take<T>((size_t)nw * GL) + (size_t)wave * GL;
     constexpr int BS = GD ? kNAZ : kBlkPad;
 
+    if (tid < nc) ccnt[tid] = nbr_cnt[(size_t)a0 + i0 + tid];
     cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, row_of_atom);
     for (int t = tid; t < 3 * n; t += blockDim.x) sF[t] = V(0);
     __syncthreads();
     const T nr = -c.eta_r * log2_scale<T>(), na = -c.eta_a * log2_scale<T>();
     for (int ic = wave; ic < nc; ic += nw) {
         const int il = i0 + ic;
-        const int cnt = uniform(cs.ccnt[ic]);
+        const int cnt = uniform(ccnt[ic]);
         const int nang = cnt & 0xffff, nall = cnt >> 16;
         const TG* gsrc = dG + (size_t)uniform(cs.crow[ic]) * c.Dp;
         // the atom's dE/dAEV row: 16 values per lane and load, all in flight
@@ -2295,7 +2308,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
                 }
             }
         }
-        load_records<true>(c, cs.sx, cs.ssp, cs.clst + (size_t)ic * cap, nang, nall, il, nb);
+        load_records<true>(c, cs.sx, cs.ssp, nbr + ((size_t)a0 + il) * cap, nang, nall, il, nb);
         wave_sync();
         T fi0 = 0, fi1 = 0, fi2 = 0;   // force on the central atom, per lane
         // radial: lane per (neighbour, group of 4 shifts)
@@ -2510,7 +2523,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
 template <typename T>
 static size_t forces_lds(int max_apm, int cap, int S, int nw, bool fixed = false, bool gd = false) {
     const int GL = kNR * S + kBlkPad * S * (S + 1) / 2;
-    return ChunkStage<T>::bytes(max_apm, cap) +
+    return ChunkStage<T>::bytes(max_apm, cap, false) + lds_bytes<int>(kChunk) +
            (fixed ? lds_bytes<unsigned long long>(3 * (size_t)max_apm) : lds_bytes<T>(3 * (size_t)max_apm)) +
            lds_bytes<T>((size_t)nw * cap * kNbStride) + lds_bytes<T>((size_t)nw * 64 * 6) +
            (gd ? 0 : lds_bytes<T>((size_t)nw * GL));
