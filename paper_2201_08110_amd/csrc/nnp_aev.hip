@@ -1274,109 +1274,104 @@ __device__ inline void angular_rows(const AtomLists& al, int p0, int nbat, const
     wave_sync();
 }
 
-// Bucketing inside the featuriser, for batches of at most kPrepBlock atoms and
-// molecules: the steps and results of k_bucket_one without its launch.  Every
-// wave counts the elements of the batch's atoms for itself (ballots; no LDS
-// and no barrier) and places the central atoms it takes; one workgroup beside
-// the molecules' writes the bucket table, the row tiles' elements, the padding
+// Bucketing inside the featuriser, for batches of at most kBucketAtoms atoms and
+// molecules: the results of the bucketing kernels without their launches.
+// Every workgroup counts the elements of the batch's atoms and of those before
+// its chunk (64 atoms a wave in turn; every lane counts its own, a byte an
+// element, and the counts are added over the lanes once), which gives the
+// padded bucket starts and its central atoms' rows.  One workgroup beside the
+// molecules' writes the bucket table, the row tiles' elements, the padding
 // rows and the capacity flags (in a molecule's own workgroup those were 3,600
 // of its 33,600 clocks).
-static_assert(kMaxSpecies <= 8 && kPrepBlock <= 64 * 255, "a byte an element and lane");
-struct WaveBuckets {
+constexpr int kBucketAtoms = 4096;
+struct GroupBuckets {
+    int tot, base, pre;   // lane q: atoms of element q, its padded start (lane S: all rows), those before the chunk
     int A0, A1;
-    bool ok;          // the call's atom range is valid
-    int tot, base;    // lane q: atoms of element q and its padded start (lane S: all rows)
-    int pre;          // lane q: atoms of element q before atom a
-    bool bad;         // atom a's label names no element
+    bool ok;              // the call's atom range is valid
 };
-// (a label that names no element counts as element 0, as in the bucketing kernel)
-__device__ inline WaveBuckets wave_buckets(const BucketFuse& bk, int S, int A, const int32_t* __restrict__ mol_off,
-                                           const int32_t* __restrict__ species, int a) {
+static_assert(kMaxSpecies <= 8 && kBucketAtoms / 64 <= 255, "a byte an element and lane");
+// element of an atom's label as the bucketing kernels count it (a label that
+// names none as element 0)
+__device__ inline int bucket_element(const BucketFuse& bk, int label, int S, bool& bad) {
+    if (bk.zlut) label = (label >= 0 && label < kZLut) ? (int)bk.zlut[label] : -1;
+    bad = label < 0 || label >= S;
+    return bad ? 0 : label;
+}
+// this wave's share of the counts -> red [wave][16], atoms of the batch and
+// before c0
+__device__ inline void count_elements(const BucketFuse& bk, GroupBuckets& w, int S, int A, const int32_t* __restrict__ mol_off,
+                                      const int32_t* __restrict__ species, int c0, int wave, int nw, int* red) {
     const int lane = lane_id();
-    WaveBuckets w;
     w.ok = atom_range(A, bk.B, bk.dA, mol_off, bk.sub, w.A0, w.A1);
-    w.tot = w.pre = 0;
-    w.bad = false;
-    auto element = [&](int a1, int label, bool& bad) {   // of atom a1 + lane, -1 past the end
-        if (bk.zlut) label = (label >= 0 && label < kZLut) ? (int)bk.zlut[label] : -1;
-        bad = a1 + lane < w.A1 && (label < 0 || label >= S);
-        return a1 + lane < w.A1 ? (bad ? 0 : label) : -1;
-    };
-    if (w.A1 - w.A0 <= 64) {
-        bool bad = false;
-        const int s = w.A1 > w.A0 ? element(w.A0, species[min(w.A0 + lane, w.A1 - 1)], bad) : -1;
-        const int before = min(max(a - w.A0, 0), 64);
-        const unsigned long long lt = before == 64 ? ~0ull : (1ull << before) - 1;
-        w.bad = __ballot(bad && w.A0 + lane == a) != 0;
-        for (int q = 0; q < S; ++q) {
-            const unsigned long long m = __ballot(s == q);
-            const int ct = __popcll(m), cb = __popcll(m & lt);
-            w.tot = lane == q ? ct : w.tot;
-            w.pre = lane == q ? cb : w.pre;
+    constexpr int U = 4;   // labels loaded together
+    unsigned long long nt = 0, np = 0;
+    for (int a4 = w.A0 + 64 * wave; a4 < w.A1; a4 += 64 * U * nw) {
+        int label[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) label[u] = species[min(a4 + 64 * u * nw + lane, w.A1 - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int a = a4 + 64 * u * nw + lane;
+            bool bad;
+            const int s = bucket_element(bk, label[u], S, bad);
+            const unsigned long long one = a < w.A1 ? 1ull << (8 * s) : 0ull;
+            nt += one;
+            np += a < c0 ? one : 0ull;
         }
-    } else {
-        // every lane counts its atoms, a byte an element (16 at most), and the
-        // counts are added over the lanes in 16 bits: ballots for every 64
-        // atoms took 12,900 of 34,600 clocks at 16 x 40 atoms
-        constexpr int U = 8;   // labels loaded together
-        unsigned long long nt = 0, np = 0;
-        for (int a8 = w.A0; a8 < w.A1; a8 += 64 * U) {
-            int label[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) label[u] = species[min(a8 + 64 * u + lane, w.A1 - 1)];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int a1 = a8 + 64 * u;
-                if (a1 >= w.A1) break;
-                bool bad;
-                const int s = element(a1, label[u], bad);
-                w.bad |= __ballot(bad && a1 + lane == a) != 0;
-                const unsigned long long one = s < 0 ? 0ull : 1ull << (8 * s);
-                nt += one;
-                np += a1 + lane < a ? one : 0ull;
-            }
-        }
-        // lane q: the sum over the lanes of byte q
-        auto total = [&](unsigned long long v) {
-            int even[2], odd[2];   // elements 0, 2 | 4, 6 and 1, 3 | 5, 7
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const unsigned x = (unsigned)(v >> (32 * h));
-                even[h] = __builtin_amdgcn_readlane(wave_scan((int)(x & 0x00ff00ffu)), 63);
-                odd[h] = __builtin_amdgcn_readlane(wave_scan((int)(x >> 8 & 0x00ff00ffu)), 63);
-            }
-            const int x = lane & 4 ? (lane & 1 ? odd[1] : even[1]) : (lane & 1 ? odd[0] : even[0]);
-            return lane < 8 ? (int)((unsigned)x >> (lane & 2 ? 16 : 0) & 0xffffu) : 0;
-        };
-        w.tot = total(nt);
-        w.pre = total(np);
     }
+    // lane q: the sum over the lanes of byte q
+    auto total = [&](unsigned long long v) {
+        int even[2], odd[2];   // elements 0, 2 | 4, 6 and 1, 3 | 5, 7
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const unsigned x = (unsigned)(v >> (32 * h));
+            even[h] = __builtin_amdgcn_readlane(wave_scan((int)(x & 0x00ff00ffu)), 63);
+            odd[h] = __builtin_amdgcn_readlane(wave_scan((int)(x >> 8 & 0x00ff00ffu)), 63);
+        }
+        const int x = lane & 4 ? (lane & 1 ? odd[1] : even[1]) : (lane & 1 ? odd[0] : even[0]);
+        return (int)((unsigned)x >> (lane & 2 ? 16 : 0) & 0xffffu);
+    };
+    const int t = total(nt), p = total(np);
+    if (lane < 16) red[16 * wave + lane] = lane < 8 ? t : p;
+}
+// the waves' counts together (after a barrier)
+__device__ inline void group_buckets(const BucketFuse& bk, GroupBuckets& w, int nw, const int* red) {
+    const int lane = lane_id();
+    w.tot = w.pre = 0;
+    if (lane < 8)
+        for (int v = 0; v < nw; ++v) {
+            w.tot += red[16 * v + lane];
+            w.pre += red[16 * v + 8 + lane];
+        }
     const int pc = (w.tot + bk.row_tile - 1) / bk.row_tile * bk.row_tile;
     w.base = row_scan(pc) - pc;
-    return w;
 }
-// row of the atom a of element s that w was formed for, or -1 when the rows
-// exceed the capacity or the atom lies outside the call's range; writes the
-// atom's outputs
-__device__ inline int bucket_atom(const BucketFuse& bk, const WaveBuckets& w, int S, int s, int a, int b,
-                                  int32_t* __restrict__ flag) {
+// row of the chunk's atom ic, or -1 when the rows exceed the capacity or the
+// atom lies outside the call's range; writes the atom's outputs.  sp: lane l,
+// element of chunk atom l; bad: the chunk's atoms whose labels name none
+__device__ inline int bucket_atom(const BucketFuse& bk, const GroupBuckets& w, int S, int sp, unsigned long long bad, int ic,
+                                  int a, int b, int32_t* __restrict__ flag) {
     if (__builtin_amdgcn_readlane(w.base, S) > bk.Rcap || a < w.A0 || a >= w.A1) return -1;
-    s = __builtin_amdgcn_readfirstlane(s);
-    const int row = __builtin_amdgcn_readlane(w.base, s) + __builtin_amdgcn_readlane(w.pre, s);
+    const int s = __builtin_amdgcn_readlane(sp, ic);
+    const int row = __builtin_amdgcn_readlane(w.base, s) + __builtin_amdgcn_readlane(w.pre, s) +
+                    __popcll(__ballot(sp == s) & ((1ull << ic) - 1));
     if (lane_id() == 0) {
         bk.row_of_atom[a] = row;
         bk.atom_of_row[row] = a;
         bk.mol_of_atom[a] = b;
         if (bk.zlut) bk.sp_out[a] = s;
-        if (w.bad) atomicOr(flag, FLAG_SPECIES);
+        if (bad >> ic & 1) atomicOr(flag, FLAG_SPECIES);
     }
     return row;
 }
 // one workgroup: the bucket table, tile elements, padding rows, capacity flags
 __device__ inline void bucket_table(const BucketFuse& bk, int S, int A, int max_apm, const int32_t* __restrict__ mol_off,
-                                    const int32_t* __restrict__ species, int32_t* __restrict__ flag) {
-    const int tid = threadIdx.x, lane = lane_id();
-    const WaveBuckets w = wave_buckets(bk, S, A, mol_off, species, 0);
+                                    const int32_t* __restrict__ species, int* red, int32_t* __restrict__ flag) {
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
+    GroupBuckets w;
+    count_elements(bk, w, S, A, mol_off, species, 0, wave, nw, red);
+    __syncthreads();
+    group_buckets(bk, w, nw, red);
     if (!w.ok && tid == 0) atomicOr(flag, FLAG_CAPACITY);
     for (int m = tid; m < bk.B; m += blockDim.x) {
         const int m0 = mol_off[m], m1 = mol_off[m + 1];
@@ -1467,7 +1462,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     // workgroup that writes the batch's bucket table
     if constexpr (MODE == kBuckets) {
         if (blockIdx.y == gridDim.y - 1) {
-            if (b == 0) bucket_table(nf.bk, c.S, A, max_apm, mol_off, species, nf.flag);
+            if (b == 0) bucket_table(nf.bk, c.S, A, max_apm, mol_off, species, (int*)smem, nf.flag);
             return;
         }
     }
@@ -1489,6 +1484,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     int* ccnt = fuse ? nullptr : lb.take<int>(kChunk);
     T* nb = lb.take<T>((size_t)nw * cap * R::stride) + (size_t)wave * cap * R::stride;
     T* pf = lb.take<T>((size_t)nw * (64 + kPairRoom) * PF) + (size_t)wave * (64 + kPairRoom) * PF;
+    int* red = MODE == kBuckets ? lb.take<int>(16 * (size_t)nw) : nullptr;
     int* mark = lb.take<int>((size_t)nw * 64) + (size_t)wave * 64;
     // (molecules beyond the direct search: their order by element, and a list)
     const bool staged = fuse && max_apm > kDirectAtoms;
@@ -1498,9 +1494,17 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     if (!fuse && tid < nc) ccnt[tid] = nbr_cnt[(size_t)a0 + i0 + tid];
     cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, MODE == kBuckets ? nullptr : row_of_atom,
             MODE == kBuckets ? nf.bk.zlut : nullptr);
-    WaveBuckets wb;
-    if constexpr (MODE == kBuckets) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + i0 + wave);
+    GroupBuckets gb;
+    int csp = -1;   // lane l: element of chunk atom l
+    unsigned long long cbad = 0;
+    if constexpr (MODE == kBuckets) {
+        bool bad = false;
+        if (lane < nc) csp = bucket_element(nf.bk, species[a0 + i0 + lane], S, bad);
+        cbad = __ballot(bad);
+        count_elements(nf.bk, gb, S, A, mol_off, species, a0 + i0, wave, nw, red);
+    }
     __syncthreads();
+    if constexpr (MODE == kBuckets) group_buckets(nf.bk, gb, nw, red);
     if (fuse && !direct) {
         if (wave == 0) stage_element_order(cs.sx, cs.ssp, n, S, sx4, sid);
         __syncthreads();
@@ -1517,8 +1521,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         int cnt, row, ao = 0, ro = 0;
         const uint16_t* lst;
         if constexpr (MODE == kBuckets) {
-            if (ic != wave) wb = wave_buckets(nf.bk, S, A, mol_off, species, a0 + il);
-            row = bucket_atom(nf.bk, wb, S, cs.ssp[il], a0 + il, b, nf.flag);
+            row = bucket_atom(nf.bk, gb, S, csp, cbad, ic, a0 + il, b, nf.flag);
             if (row < 0) continue;
         } else {
             row = uniform(cs.crow[ic]);
@@ -1715,6 +1718,7 @@ static size_t aev_lds(int max_apm, int cap, int NZ, int nw, bool fuse = false) {
     const int PF = kNAZ / NZ + NZ;
     return ChunkStage<T>::bytes(max_apm, cap, false) + (fuse ? 0 : lds_bytes<int>(kChunk)) +
            lds_bytes<T>((size_t)nw * cap * Rec<false>::stride) + lds_bytes<T>((size_t)nw * (64 + kPairRoom) * PF) + lds_bytes<int>((size_t)nw * 64) +
+           (fuse ? lds_bytes<int>(16 * (size_t)nw) : 0) +
            (fuse && max_apm > kDirectAtoms
                 ? lds_bytes<T>(4 * (size_t)max_apm) + lds_bytes<int>(max_apm) + lds_bytes<uint16_t>((size_t)nw * cap)
                 : 0);
@@ -1772,18 +1776,18 @@ hipError_t launch_features(const Shape& sh, const AevConst<typename P::T>& c, co
     return launch_aev<P>(sh, c, mol_off, species, x, w, aev_out, st, tm, nf);
 }
 
-// Bucketing and featurisation.  A batch that fits one bucketing workgroup and
-// takes the fused neighbour search is bucketed inside the featuriser (one
-// launch for all three steps: on a single small molecule each dependent
-// launch is a visible part of the latency); otherwise the bucketing kernels
-// run first.
+// Bucketing and featurisation.  A batch that takes the fused neighbour search
+// is bucketed inside the featuriser too (one launch for all three steps: each
+// dependent launch is a visible part of the latency); otherwise the bucketing
+// kernels run first.  Every workgroup then counts the whole batch's labels: at
+// 2,403 atoms 25.3 -> 29.6 us for two launches of 4.7 and 6.2 less, at 3,520
+// 20.9 -> 26.5 for 11.4, and the gain ends near kBucketAtoms.
 template <typename P>
 hipError_t launch_prep_features(const Shape& sh, const AevConst<typename P::T>& c, const int32_t* mol_off,
                                 const int32_t* species, const typename P::T* x, typename P::T* F,
                                 bool accumulate, Work<P>& w, typename P::T* aev_out, hipStream_t st,
                                 const Timer& tm) {
-    const bool small = sh.A > 0 && std::max(sh.A, sh.B) <= kPrepBlock && sh.max_apm <= sh.cell_min &&
-                       sh.A <= kFuseAtoms;
+    const bool small = sh.A > 0 && std::max(sh.A, sh.B) <= kBucketAtoms && sh.max_apm <= sh.cell_min;
     if (!small) {
         hipError_t e = launch_prep<P>(sh, mol_off, species, w, st, tm);
         if (e != hipSuccess) return e;

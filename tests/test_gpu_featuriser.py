@@ -1,6 +1,6 @@
 """Neighbour records and bucket rows formed inside the featuriser: molecules at
 the edges of a wave's one and two candidates a lane and of the step beyond
-them, with the bucketing fused in and (more than 1,024 atoms) beside it,
+them, with the bucketing fused in and (more than 4,096 atoms) beside it,
 against the FP64 oracle.  The FP64 tolerance is that of the other FP64 tests;
 FP32 forces are within 1e-4 of the largest."""
 import numpy as np
@@ -18,8 +18,9 @@ pytestmark = pytest.mark.gpu
     [65, 1, 63],
     [127, 2, 128],
     [129, 64, 1, 130],                 # above the records' step, smaller molecules beside
-    [128] * 8,                         # 1,024 atoms: the last batch with fused bucketing
-    [128] * 8 + [3],                   # the first without
+    [128] * 8 + [3],                   # more than one bucketing block
+    [128] * 32,                        # 4,096 atoms: the last batch with fused bucketing
+    [128] * 32 + [3],                  # the first without
 ])
 @pytest.mark.parametrize("prec,chunk", [("fp64", 0), ("fp32", 4), ("fp32", 16)])
 def test_records_and_rows_match_oracle(orc, hp, sizes, prec, chunk):
