@@ -285,8 +285,8 @@ def cpu_leg(hp, w, M, b5, jobs, synth):
 # flops of one coupling pair as counted here: distance (8), reciprocal and
 # reciprocal square root (2), Coulomb (2), Lennard-Jones powers and energy
 # (9), dV/dr (6), force components (6).  One evaluation per pair is the
-# algorithmic count (Newton's third law serves both sides); the kernels
-# evaluate every pair once per side, twice that
+# algorithmic count (Newton's third law serves both sides), which is what the
+# kernels execute
 COUPLING_FLOPS_PER_PAIR = 33
 
 
@@ -322,7 +322,7 @@ def coupling_form(torch, nnp, synth, args):
                      "roofline": {"bound": "alu", "achieved": fl / (us * 1e-6) / 1e12,
                                   "peak": peak / 1e12, "unit": "TFLOP/s",
                                   "frac": fl / (us * 1e-6) / peak,
-                                  "flops_per_launch": fl, "executed_flops": 2 * fl}}
+                                  "flops_per_launch": fl, "executed_flops": fl}}
         c.close()
     if not args.no_cpu:
         import oracle

@@ -303,23 +303,23 @@ int32_t nnp_kernel_times(nnp_handle* h, int32_t cap, const char** names, int64_t
  *                             256-192-{160..192} only),
  *                         2 = one GEMM per layer and direction.
  *                         auto: 1 when supported, else 2.
- *   NNP_KNOB_GEMM_STAGES  LDS pipeline depth of the layer-1 GEMMs on handles
- *                         with 128-row buckets: 2 or 3 (auto 2: two
+ *   NNP_KNOB_GEMM_STAGES  LDS pipeline depth of the layer-1 GEMMs on BF16
+ *                         handles with 128-row buckets: 2 or 3 (auto 2: two
  *                         workgroups fit a compute unit); 16-row buckets
- *                         (small batches, FP64) always take 6.
+ *                         (small batches, FP64) and FP32 handles have their
+ *                         own pipelines.
  *   NNP_KNOB_CELL_MIN     molecules with more atoms than this build their
  *                         neighbour lists through cutoff cells, smaller ones
  *                         scan all atoms: 16..1024 (auto 128).
  *   NNP_KNOB_GEMM_WAVES   waves per workgroup of the layer-1 forward GEMM
- *                         of layer-1 path 1 on handles with 128-row buckets:
+ *                         of layer-1 path 1 on BF16 handles with 128-row buckets:
  *                         4 (2 x 2 waves of 64 x 64) or 8 (2 x 4 waves of
  *                         64 x 32) (auto 8; the backward GEMM always runs 4;
  *                         path 2 always runs 4 waves of 128 x 64).
- *   NNP_KNOB_TAIL_TILE    row tile of the fused layers 2-3 kernel (handles
- *                         with 128-row buckets): 1 = 128 / (operand bytes)
- *                         rows on 4 waves, 2 = half that (at least 16) on 4
- *                         waves, 3 = the full tile on 8 waves (2 x 4); 3 is
- *                         taken as 1 for FP64 (auto 1).
+ *   NNP_KNOB_TAIL_TILE    row tile of the fused layers 2-3 kernel (BF16
+ *                         handles with 128-row buckets; others have one
+ *                         tile): 1 = 64 rows on 4 waves, 2 = 32 rows on 4
+ *                         waves, 3 = 64 rows on 8 waves (2 x 4) (auto 1).
  *   NNP_KNOB_L1_PATH      layer-1 GEMMs of BF16 handles with 128-row
  *                         buckets: 1 = both operands staged through LDS
  *                         (the GEMM_STAGES / GEMM_WAVES knobs apply),
@@ -332,8 +332,8 @@ int32_t nnp_kernel_times(nnp_handle* h, int32_t cap, const char** names, int64_t
  *                         force kernels (4 waves): 4, 8 or 16.  Fewer atoms
  *                         per workgroup spread a small batch over more
  *                         compute units; more share the staging of their
- *                         molecule.  auto: 16 when the capacity gives at
- *                         least 1024 workgroups at 16, else 4.
+ *                         molecule.  auto, by the call's atoms: 4 below
+ *                         16,384, 8 below 48,000, else 16.
  *   NNP_KNOB_FORCE_SUM    1 = forces summed with floating-point atomic adds
  *                         (the last bits vary from run to run), 2 = every
  *                         contribution rounded to a 64-bit fixed-point

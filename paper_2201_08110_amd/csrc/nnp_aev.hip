@@ -1419,7 +1419,7 @@ __device__ inline void bucket_table(const BucketFuse& bk, int S, int A, int max_
 // from the sums on the matrix cores, where a term costs one instruction and
 // two LDS reads for all its slots (18.0 -> 15.2 us; 106 -> 100; 512 molecules
 // of 10 to 120 atoms 111 -> 97).  The neighbour search that counts its hits by
-// element and the counting of labels by lanes took 16 x 40 atoms from 21.9 to
+// element and the counting of labels by lanes took 570 atoms in 16 molecules from 21.9 to
 // 15.0 us, and 24 atoms in FP64 (with the cutoffs' slopes left out) from 21.6
 // to 19.4.  Large batches are bound by the lanes'
 // instructions, 900 an atom.
@@ -1780,7 +1780,7 @@ hipError_t launch_features(const Shape& sh, const AevConst<typename P::T>& c, co
 // is bucketed inside the featuriser too (one launch for all three steps: each
 // dependent launch is a visible part of the latency); otherwise the bucketing
 // kernels run first.  Every workgroup then counts the whole batch's labels: at
-// 2,403 atoms 25.3 -> 29.6 us for two launches of 4.7 and 6.2 less, at 3,520
+// 3,134 atoms 25.3 -> 29.6 us for two launches of 4.7 and 6.2 less, at 3,520
 // 20.9 -> 26.5 for 11.4, and the gain ends near kBucketAtoms.
 template <typename P>
 hipError_t launch_prep_features(const Shape& sh, const AevConst<typename P::T>& c, const int32_t* mol_off,
