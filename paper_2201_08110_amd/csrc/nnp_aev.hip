@@ -1422,7 +1422,7 @@ __device__ inline void bucket_table(const BucketFuse& bk, int S, int A, int max_
 // element and the counting of labels by lanes took 570 atoms in 16 molecules from 21.9 to
 // 15.0 us, and 24 atoms in FP64 (with the cutoffs' slopes left out) from 21.6
 // to 19.4.  Large batches are bound by the lanes'
-// instructions, 900 an atom.
+// instructions, 770 an atom.
 // blocks without pairs: zeros in 16-byte pieces, a few lanes per block
 template <typename TS, typename T>
 __device__ inline void zero_blocks(TS* gang, T* aang, int NB, unsigned long long filled) {
