@@ -130,21 +130,6 @@ __device__ inline int block_molecule(int y) {
     return (w & 1) || (x | 7) >= w ? x : (x & ~7) | ((x + y) & 7);
 }
 
-// Starts the load of every line of the kernel's arguments at once: the
-// compiler loads an argument where it is first used, and each line that is
-// not yet in the scalar cache costs about a thousand clocks there (2,300 of
-// the featuriser's 33,600 on 64 atoms, net of 840 for this).
-template <int BYTES> __device__ inline void touch_kernargs() {
-    typedef const volatile int __attribute__((address_space(4))) * Args;
-    Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
-    int v[BYTES / 64 + 1], all = 0;
-#pragma unroll
-    for (int i = 0; i <= BYTES / 64; ++i) v[i] = p[i * 16 < BYTES / 4 ? i * 16 : BYTES / 4 - 1];
-#pragma unroll
-    for (int i = 0; i <= BYTES / 64; ++i) all |= v[i];
-    asm volatile("" ::"s"(all));
-}
-
 // upper-triangle index of the unordered element pair (b, c)
 __device__ inline int pair_index(int b, int c, int S) {
     const int lo = b < c ? b : c, hi = b < c ? c : b;

@@ -135,6 +135,7 @@ template <int N> __device__ inline void vm_wait() {
 // and writes 8- or 16-byte vectors.
 template <typename P, int BM, int BN, int WM, int WN, int S, int EPI>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs<P> g) {
+    if constexpr (BM == 16) touch_kernargs<sizeof(GemmArgs<P>)>();
     typedef typename P::TS TS;
     typedef typename P::TA TA;
     typedef MF<TS> mf;
@@ -721,6 +722,7 @@ struct TailShape {
 // computes only H3L outputs and its backward reduces over H3L
 template <typename P, int BM, int TW, int H1, int H2, int H3, int H3L = H3>
 __global__ __launch_bounds__(256 * TW, 2 * TW) void k_tail(TailArgs<P> g) {
+    if constexpr (BM == 16) touch_kernargs<sizeof(TailArgs<P>)>();
     typedef typename P::TS TS;
     typedef typename P::TA TA;
     typedef MF<TS> mf;
@@ -1191,6 +1193,7 @@ bool mlp_fused_supported(int H1, int H2, int H3) {
 // backward's K of 256 a model 9 -> 12).
 template <int KW, int U, int EPI>
 __global__ __launch_bounds__(64 * KW) void k_gk64(GemmArgs<PrecF64> g) {
+    touch_kernargs<sizeof(GemmArgs<PrecF64>)>();
     typedef MF<double> mf;
     __shared__ mf::Acc part[KW][64];
     const int nm = row_tiles<16>(g.info, g.nm), lin = xcd_tile(nm * g.nn);

@@ -133,6 +133,7 @@ template <int FM, int FN, int KW> struct KSplit {
 
 template <int FM, int FN, int KW, int U, int EPI>
 __global__ __launch_bounds__(64 * KW, 2) void k_gxk(SplitArgs a) {
+    touch_kernargs<sizeof(SplitArgs)>();
     typedef KSplit<FM, FN, KW> Ks;
     constexpr int TN = Ks::TN, TW = Ks::TW, BM = 16 * FM, BN = 16 * FN;
     extern __shared__ __align__(16) char smem[];
