@@ -412,7 +412,7 @@ template <typename T> hipError_t launch_sub(size_t n, const T* xv, T* y, hipStre
 template <typename TA>
 hipError_t launch_gather(int64_t n, const int32_t* map, const TA* src, TA* dst, hipStream_t st);
 template <typename P>
-hipError_t launch_grad_coords(int A, const int32_t* mol_of_atom, const double* grad_E,
+hipError_t launch_grad_coords(int A, int B, const int32_t* mol_off, const double* grad_E,
                               const typename P::T* F, typename P::T* gx, hipStream_t st);
 template <typename P>
 hipError_t launch_energy(const Shape& sh, const DevWeights<P>& wt, const int32_t* mol_off,

@@ -757,7 +757,7 @@ nnp_status run_backward(nnp_handle* h, const nnp_batch* bin, const typename P::T
         // dL/dx of an energy-only loss: -gE_b F_i from one forward evaluation
         rc = run_forward<P>(h, b, x, h->train_E, (T*)h->train_F, nullptr);
         if (rc) return rc;
-        HIP_TRY(launch_grad_coords<P>(sh.A, w.mol_of_atom, gE, (const T*)h->train_F, gx, st));
+        HIP_TRY(launch_grad_coords<P>(sh.A, sh.B, b->mol_offsets, gE, (const T*)h->train_F, gx, st));
     }
     if (gx && has_gF) {
         // dL/dx = -gE F - H gF.  With K(r) = -sum_i (dG_i/dx)^T r_i the force

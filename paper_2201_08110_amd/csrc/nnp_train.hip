@@ -474,23 +474,35 @@ hipError_t launch_fill(typename P::TS* p, size_t n, hipStream_t st) {
     return hipGetLastError();
 }
 
-// dL/dx of an energy-only loss: sum_b gE_b dE_b/dx_i = -gE_b(i) F_i
+// dL/dx of an energy-only loss: sum_b gE_b dE_b/dx_i = -gE_b(i) F_i.  The
+// molecule comes from the offsets (their last b with mol_off[b] <= i, always
+// one of the B): an evaluation leaves no molecule for the atoms it refuses (a
+// molecule above the capacity, offsets that do not end at the atom count).
 template <typename T>
-__global__ void k_grad_coords(int A, const int32_t* __restrict__ mol_of_atom,
+__global__ void k_grad_coords(int A, int B, const int32_t* __restrict__ mol_off,
                               const double* __restrict__ grad_E, const T* __restrict__ F,
                               T* __restrict__ gx) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 3 * A) return;
-    const double g = grad_E ? grad_E[mol_of_atom[i / 3]] : 0.0;
+    double g = 0.0;
+    if (grad_E) {
+        int lo = 0, hi = B;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (mol_off[mid] <= i / 3) lo = mid;
+            else hi = mid;
+        }
+        g = grad_E[lo];
+    }
     gx[i] = (T)(-g * (double)F[i]);
 }
 
 template <typename P>
-hipError_t launch_grad_coords(int A, const int32_t* mol_of_atom, const double* grad_E,
+hipError_t launch_grad_coords(int A, int B, const int32_t* mol_off, const double* grad_E,
                               const typename P::T* F, typename P::T* gx, hipStream_t st) {
     if (A == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_grad_coords<typename P::T>, dim3((3 * A + 255) / 256), dim3(256), 0, st, A,
-                       mol_of_atom, grad_E, F, gx);
+    hipLaunchKernelGGL(k_grad_coords<typename P::T>, dim3((3 * A + 255) / 256), dim3(256), 0, st, A, B,
+                       mol_off, grad_E, F, gx);
     return hipGetLastError();
 }
 
@@ -520,12 +532,12 @@ template hipError_t launch_gather<double>(int64_t, const int32_t*, const double*
                                               TrainWork<P>&, const int32_t*, const double*,    \
                                               bool, P::TA*, hipStream_t, const Timer&);        \
     template hipError_t launch_fill<P>(P::TS*, size_t, hipStream_t);                           \
-    template hipError_t launch_grad_coords<P>(int, const int32_t*, const double*, const P::T*, \
+    template hipError_t launch_grad_coords<P>(int, int, const int32_t*, const double*, const P::T*, \
                                               P::T*, hipStream_t);
 NNP_TRAIN_INST(PrecF64)
 NNP_TRAIN_INST(PrecF32)
 template hipError_t launch_fill<PrecBF16>(bf16_t*, size_t, hipStream_t);
-template hipError_t launch_grad_coords<PrecBF16>(int, const int32_t*, const double*, const float*,
+template hipError_t launch_grad_coords<PrecBF16>(int, int, const int32_t*, const double*, const float*,
                                                  float*, hipStream_t);
 
 }  // namespace nnp
