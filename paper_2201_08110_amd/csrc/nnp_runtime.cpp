@@ -608,11 +608,13 @@ nnp_status run_forward_split(nnp_handle* h, const nnp_batch* b, const typename P
     return NNP_OK;
 }
 
+// whole: never in two parts (the training backward reads the rows and buckets
+// of the whole batch afterwards)
 template <typename P>
 nnp_status run_forward(nnp_handle* h, const nnp_batch* b, const typename P::T* x, double* E,
-                       typename P::T* F, typename P::T* aev_out) {
+                       typename P::T* F, typename P::T* aev_out, bool whole = false) {
     typedef typename P::T T;
-    if (h->shape.pipeline == 2 && h->pipe_ready && !aev_out && b->n_mols >= 2 &&
+    if (h->shape.pipeline == 2 && h->pipe_ready && !aev_out && !whole && b->n_mols >= 2 &&
         !(b->flags & NNP_FLAG_DEVICE_COUNTS))
         return run_forward_split<P>(h, b, x, E, F);
     int A, B;
@@ -755,7 +757,7 @@ nnp_status run_backward(nnp_handle* h, const nnp_batch* bin, const typename P::T
     const bool has_gF = gF != nullptr;
     if (gx && !has_gF) {
         // dL/dx of an energy-only loss: -gE_b F_i from one forward evaluation
-        rc = run_forward<P>(h, b, x, h->train_E, (T*)h->train_F, nullptr);
+        rc = run_forward<P>(h, b, x, h->train_E, (T*)h->train_F, nullptr, true);
         if (rc) return rc;
         HIP_TRY(launch_grad_coords<P>(sh.A, sh.B, b->mol_offsets, gE, (const T*)h->train_F, gx, st));
     }
@@ -764,7 +766,7 @@ nnp_status run_backward(nnp_handle* h, const nnp_batch* bin, const typename P::T
         // contraction of AEV-row cotangents r: H gF = -K(rows' tangent) -
         // (tangent of K(g) along gF at fixed rows g).  Here gx starts as that
         // second tangent, from the forward pass's rows g = dE/dG ...
-        rc = run_forward<P>(h, b, x, h->train_E, (T*)h->train_F, nullptr);
+        rc = run_forward<P>(h, b, x, h->train_E, (T*)h->train_F, nullptr, true);
         if (rc) return rc;
         HIP_TRY(launch_fill<P>(gx, 3 * (size_t)sh.A, st));
         if (sh.A > 0)

@@ -93,3 +93,28 @@ def test_pipeline_with_element_table(hp):
     h2.energy_forces(x, bad, off)
     from paper_2201_08110_amd.nnp import NNP_E_SPECIES
     assert h2.device_status() == NNP_E_SPECIES
+
+
+@pytest.mark.parametrize("force_loss", [False, True])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_training_backward_of_a_pipelined_handle(hp, prec, force_loss):
+    """The gradients do not depend on the knob: the backward's own evaluation
+    leaves rows and buckets of the whole batch, not of its second half alone.
+    FP64 1e-10, FP32 1e-5 of the largest (atomic force sums in another order)."""
+    torch = torch_cuda()
+    b = synth.random_batch(104, [20, 9, 33, 14, 1])
+    w = synth.xavier_weights(2, hp["widths"], seed=103)
+    dt = torch.float32 if prec == "fp32" else torch.float64
+    x, sp, off = to_device(torch, b, dt)
+    rng = np.random.default_rng(2)
+    gE = torch.tensor(rng.normal(size=b.n_mols), device="cuda")
+    gF = torch.tensor(rng.normal(size=(b.n_atoms, 3)), dtype=dt, device="cuda") if force_loss else None
+    got = []
+    for h in _pair(hp, w, 2, prec, b, 33):
+        gp, gx = h.backward(x, sp, off, gE, gF, want_coords=True)
+        assert h.device_status() == 0
+        got.append((gp.double().cpu().numpy(), gx.double().cpu().numpy()))
+        h.close()
+    tol = 1e-5 if prec == "fp32" else 1e-10
+    for one, two in zip(*got):
+        assert np.abs(one - two).max() <= tol * np.abs(one).max()
