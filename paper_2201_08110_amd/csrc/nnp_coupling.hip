@@ -83,13 +83,22 @@ __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, cons
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15;
     const int ngroups = (n_mm + 15) / 16, nw = gridDim.x * kCoupleWaves;
     const int g0 = wave * gridDim.x + blockIdx.x;      // consecutive groups go to different workgroups
+    if (n_nnp == 0) {
+        for (int i = blockIdx.x * kCoupleThreads + tid; !accumulate && i < 3 * n_mm; i += gridDim.x * kCoupleThreads)
+            F_mm[i] = T(0);
+        if (tid == 0) e_part[blockIdx.x] = 0.0;
+        return;
+    }
     T b[kCoupleVals] = {0, 0, 0, 0, 0, 0};
     if (g0 < ngroups) load_atom(x_mm, par_mm, min(g0 * 16 + c, n_mm - 1), b);   // in flight while the NNP atoms are staged
-    const int nblk = n_nnp > 0 ? (n_nnp + 63) / 64 : 1, np = nblk * 64;
-    T* s = (T*)smem;                                   // [6][np], past n_nnp far away and inert
+    // [6][np], past n_nnp the last atom again without charge, size and well
+    // depth: its pairs are finite wherever that atom's are
+    const int nblk = (n_nnp + 63) / 64, np = nblk * 64;
+    T* s = (T*)smem;
     for (int i = tid; i < np; i += kCoupleThreads) {
-        T a[kCoupleVals] = {T(1e15), T(1e15), T(1e15), T(0), T(0), T(0)};
-        if (i < n_nnp) load_atom(x_nnp, par_nnp, i, a);
+        T a[kCoupleVals];
+        load_atom(x_nnp, par_nnp, min(i, n_nnp - 1), a);
+        if (i >= n_nnp) a[3] = a[4] = a[5] = T(0);
 #pragma unroll
         for (int v = 0; v < kCoupleVals; ++v) s[v * np + i] = a[v];
     }
@@ -109,17 +118,22 @@ __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, cons
                 const T* q = sb + ((c + t) & 15);
                 const T d0 = b[0] - q[0], d1 = b[1] - q[np], d2 = b[2] - q[2 * np];
                 const T r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                T v, dvr;
-                couple_pair(k, r2, q[3 * np] * b[3], q[4 * np] + b[4], q[5 * np] * b[5], v, dvr);
-                if (CUT && r2 >= rc2) v = dvr = T(0);
-                e += (double)v;
-                // F_i = -dV/dx_i = (dV/dr) d / r, F_j = -F_i
-                fj[0] -= dvr * d0;
-                fj[1] -= dvr * d1;
-                fj[2] -= dvr * d2;
-                fr[0] = row_next(fr[0] + dvr * d0);
-                fr[1] = row_next(fr[1] + dvr * d1);
-                fr[2] = row_next(fr[2] + dvr * d2);
+                // a pair beyond the cutoff takes no part: with an atom at
+                // infinity, zero times its distance would not be zero
+                if (!CUT || !(r2 >= rc2)) {
+                    T v, dvr;
+                    couple_pair(k, r2, q[3 * np] * b[3], q[4 * np] + b[4], q[5 * np] * b[5], v, dvr);
+                    e += (double)v;
+                    // F_i = -dV/dx_i = (dV/dr) d / r, F_j = -F_i
+                    fj[0] -= dvr * d0;
+                    fj[1] -= dvr * d1;
+                    fj[2] -= dvr * d2;
+                    fr[0] += dvr * d0;
+                    fr[1] += dvr * d1;
+                    fr[2] += dvr * d2;
+                }
+#pragma unroll
+                for (int d = 0; d < 3; ++d) fr[d] = row_next(fr[d]);
             }
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
