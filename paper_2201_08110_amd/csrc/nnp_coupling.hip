@@ -20,6 +20,8 @@
 // the latency of one trip through memory.  Summing in the same launch (the last
 // workgroup of 16 sums theirs, the last of those the rest) took 18.2: each of
 // the two hand-overs waits for memory three times.
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 
 #include "nnp_internal.h"
@@ -68,9 +70,19 @@ __device__ inline double row_next(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Sums: an MM atom's force in T over 64 NNP atoms (four partial sums of 16), an
-// NNP atom's in T over 16 MM atoms and in FP64 beyond, the energy in FP64.
-template <typename T, bool CUT>
+// Sums: an MM atom's force in T over 64 NNP atoms (four partial sums of 16), the
+// 64s in order, and once onto the caller's; an NNP atom's in T over 16 MM atoms
+// and in FP64 beyond, the energy in FP64.
+// A wave goes through kCoupleRounds of its groups block by block of 64 NNP
+// atoms, so the sums of a block leave the waves once for them all; between
+// blocks the groups' MM forces wait in LDS.  MANY: more than 64 NNP atoms.
+constexpr int kCoupleRounds = 8;
+template <typename T> size_t couple_lds(int n_nnp) {
+    const size_t np = (size_t)(std::max(n_nnp, 1) + 63) / 64 * 64;
+    return sizeof(T) * kCoupleVals * np +
+           (np > 64 ? sizeof(double) * 3 * np + sizeof(T) * 48 * kCoupleWaves * kCoupleRounds : 0);
+}
+template <typename T, bool CUT, bool MANY>
 __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, const T* __restrict__ x_nnp,
                                                                  const T* __restrict__ par_nnp, int n_mm,
                                                                  const T* __restrict__ x_mm,
@@ -93,8 +105,10 @@ __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, cons
     if (g0 < ngroups) load_atom(x_mm, par_mm, min(g0 * 16 + c, n_mm - 1), b);   // in flight while the NNP atoms are staged
     // [6][np], past n_nnp the last atom again without charge, size and well
     // depth: its pairs are finite wherever that atom's are
-    const int nblk = (n_nnp + 63) / 64, np = nblk * 64;
+    const int nblk = MANY ? (n_nnp + 63) / 64 : 1, np = nblk * 64;
     T* s = (T*)smem;
+    double* tot = (double*)(s + kCoupleVals * np);     // [3][np] this workgroup's NNP forces
+    T* keep = (T*)(tot + 3 * np) + wave * 48 * kCoupleRounds;   // [round][3][16]
     for (int i = tid; i < np; i += kCoupleThreads) {
         T a[kCoupleVals];
         load_atom(x_nnp, par_nnp, min(i, n_nnp - 1), a);
@@ -102,63 +116,79 @@ __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, cons
 #pragma unroll
         for (int v = 0; v < kCoupleVals; ++v) s[v * np + i] = a[v];
     }
+    for (int i = tid; MANY && i < 3 * np; i += kCoupleThreads) tot[i] = 0.0;
     __syncthreads();
     double e = 0.0;
-    for (int blk = 0; blk < nblk; ++blk) {
-        const T* sb = s + blk * 64 + (lane & 48);
-        double fi[3] = {0.0, 0.0, 0.0};
-        for (int g = g0; g < ngroups; g += nw) {
-            const int j = g * 16 + c;
-            const bool act = j < n_mm;
-            if (g != g0 || blk > 0) load_atom(x_mm, par_mm, act ? j : n_mm - 1, b);
-            if (!act) b[3] = b[5] = T(0);              // no charge, no well depth: no force, no energy
-            T fj[3] = {0, 0, 0}, fr[3] = {0, 0, 0};
+    const int step = MANY ? kCoupleRounds * nw : ngroups;
+    for (int gs = 0; gs < ngroups; gs += step) {
+        const int ge = min(gs + step, ngroups);
+        for (int blk = 0; blk < nblk; ++blk) {
+            const T* sb = s + blk * 64 + (lane & 48);
+            double fi[3] = {0.0, 0.0, 0.0};
+            T* kp = keep;
+            for (int g = gs + g0; g < ge; g += nw, kp += 48) {
+                const int j = g * 16 + c;
+                const bool act = j < n_mm;
+                if (g != g0 || blk > 0) load_atom(x_mm, par_mm, act ? j : n_mm - 1, b);
+                if (!act) b[3] = b[5] = T(0);          // no charge, no well depth: no force, no energy
+                T fj[3] = {0, 0, 0}, fr[3] = {0, 0, 0};
 #pragma unroll 4
-            for (int t = 0; t < 16; ++t) {
-                const T* q = sb + ((c + t) & 15);
-                const T d0 = b[0] - q[0], d1 = b[1] - q[np], d2 = b[2] - q[2 * np];
-                const T r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                // a pair beyond the cutoff takes no part: with an atom at
-                // infinity, zero times its distance would not be zero
-                if (!CUT || !(r2 >= rc2)) {
-                    T v, dvr;
-                    couple_pair(k, r2, q[3 * np] * b[3], q[4 * np] + b[4], q[5 * np] * b[5], v, dvr);
-                    e += (double)v;
-                    // F_i = -dV/dx_i = (dV/dr) d / r, F_j = -F_i
-                    fj[0] -= dvr * d0;
-                    fj[1] -= dvr * d1;
-                    fj[2] -= dvr * d2;
-                    fr[0] += dvr * d0;
-                    fr[1] += dvr * d1;
-                    fr[2] += dvr * d2;
+                for (int t = 0; t < 16; ++t) {
+                    const T* q = sb + ((c + t) & 15);
+                    const T d0 = b[0] - q[0], d1 = b[1] - q[np], d2 = b[2] - q[2 * np];
+                    const T r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                    // a pair beyond the cutoff takes no part: with an atom at
+                    // infinity, zero times its distance would not be zero
+                    if (!CUT || !(r2 >= rc2)) {
+                        T v, dvr;
+                        couple_pair(k, r2, q[3 * np] * b[3], q[4 * np] + b[4], q[5 * np] * b[5], v, dvr);
+                        e += (double)v;
+                        // F_i = -dV/dx_i = (dV/dr) d / r, F_j = -F_i
+                        fj[0] -= dvr * d0;
+                        fj[1] -= dvr * d1;
+                        fj[2] -= dvr * d2;
+                        fr[0] += dvr * d0;
+                        fr[1] += dvr * d1;
+                        fr[2] += dvr * d2;
+                    }
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) fr[d] = row_next(fr[d]);
                 }
 #pragma unroll
-                for (int d = 0; d < 3; ++d) fr[d] = row_next(fr[d]);
+                for (int d = 0; d < 3; ++d) {
+                    fi[d] += (double)fr[d];
+                    fj[d] += __shfl_xor(fj[d], 16);
+                    fj[d] += __shfl_xor(fj[d], 32);
+                }
+                if (MANY && lane < 16) {
+                    if (blk > 0)
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) fj[d] = kp[16 * d + c] + fj[d];
+                    if (blk + 1 < nblk)
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) kp[16 * d + c] = fj[d];
+                }
+                if (act && lane < 16 && blk + 1 == nblk) {
+                    T* F = F_mm + 3 * (size_t)j;
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) F[d] = (accumulate ? F[d] : T(0)) + fj[d];
+                }
             }
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                fi[d] += (double)fr[d];
-                fj[d] += __shfl_xor(fj[d], 16);
-                fj[d] += __shfl_xor(fj[d], 32);
+            for (int d = 0; d < 3; ++d) red[wave][d][lane] = fi[d];
+            __syncthreads();
+            if (tid < 192) {
+                const int d = tid >> 6;
+                double v = 0.0;
+                for (int w = 0; w < kCoupleWaves; ++w) v += red[w][d][lane];
+                if (MANY) tot[d * np + blk * 64 + lane] += v;
+                else if (lane < n_nnp) f_part[(size_t)(3 * lane + d) * gridDim.x + blockIdx.x] = (T)v;
             }
-            if (act && lane < 16) {
-                T* F = F_mm + 3 * (size_t)j;
-                const bool add = accumulate || blk > 0;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) F[d] = (add ? F[d] : T(0)) + fj[d];
-            }
+            __syncthreads();
         }
-#pragma unroll
-        for (int d = 0; d < 3; ++d) red[wave][d][lane] = fi[d];
-        __syncthreads();
-        if (tid < 192) {
-            const int d = tid >> 6, i = blk * 64 + lane;
-            double v = 0.0;
-            for (int w = 0; w < kCoupleWaves; ++w) v += red[w][d][lane];
-            if (i < n_nnp) f_part[(size_t)(3 * i + d) * gridDim.x + blockIdx.x] = (T)v;
-        }
-        __syncthreads();
     }
+    for (int i = tid; MANY && i < 3 * n_nnp; i += kCoupleThreads)
+        f_part[(size_t)i * gridDim.x + blockIdx.x] = (T)tot[i % 3 * np + i / 3];
     for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
     if (lane == 0) red[wave][0][0] = e;
     __syncthreads();
@@ -205,8 +235,10 @@ hipError_t launch_coupling(const CouplingShape& cs, int n_nnp, const T* x_nnp, c
     // at least: few groups spread over many CUs
     const int ng = (n_mm + 15) / 16, nwg = std::min(kCoupleMaxWg, (ng + 3) / 4);
     if (nwg > 0) {
-        const size_t lds = sizeof(T) * kCoupleVals * ((size_t)(std::max(n_nnp, 1) + 63) / 64 * 64);
-        auto kern = rc2 > T(0) ? k_couple_pairs<T, true> : k_couple_pairs<T, false>;
+        const size_t lds = couple_lds<T>(n_nnp);
+        const bool many = n_nnp > 64;
+        auto kern = rc2 > T(0) ? (many ? k_couple_pairs<T, true, true> : k_couple_pairs<T, true, false>)
+                               : (many ? k_couple_pairs<T, false, true> : k_couple_pairs<T, false, false>);
         hipError_t e = ensure_lds((const void*)kern, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3(nwg), dim3(kCoupleThreads), lds, st, n_nnp, x_nnp, par_nnp, n_mm, x_mm, par_mm,
@@ -241,11 +273,15 @@ hipError_t coupling_scratch(void** ptr) {
         if (!p) return hipErrorInvalidSymbol;
         // raise the pair kernel's dynamic-LDS limit now (its largest size),
         // so later calls do no host-side set-up
-        const size_t lds = kCoupleVals * 1024;
-        for (const void* kern : {(const void*)k_couple_pairs<float, false>, (const void*)k_couple_pairs<float, true>})
-            if (e == hipSuccess) e = ensure_lds(kern, sizeof(float) * lds);
-        for (const void* kern : {(const void*)k_couple_pairs<double, false>, (const void*)k_couple_pairs<double, true>})
-            if (e == hipSuccess) e = ensure_lds(kern, sizeof(double) * lds);
+        const auto raise = [&](auto zero) {
+            typedef decltype(zero) T;
+            for (const void* kern : {(const void*)k_couple_pairs<T, false, false>, (const void*)k_couple_pairs<T, true, false>})
+                if (e == hipSuccess) e = ensure_lds(kern, couple_lds<T>(64));
+            for (const void* kern : {(const void*)k_couple_pairs<T, false, true>, (const void*)k_couple_pairs<T, true, true>})
+                if (e == hipSuccess) e = ensure_lds(kern, couple_lds<T>(1024));
+        };
+        raise(float());
+        raise(double());
         if (e != hipSuccess) return e;
         addr[dev] = p;
     }

@@ -44,3 +44,23 @@ def test_tile_edges(orc, prec, n_nnp, n_mm, cutoff):
     assert abs(float(E) - 2.5 - Eo) <= e_tol * max(A, 2.5)
     again = c(*t)
     assert all(torch.equal(a, b) for a, b in zip(again, (E2, Fn2, Fm2)))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_nnp,n_mm", [(65, 300), (130, 5000), (1024, 33), (70, 16 * 4096 + 5), (70, 8 * 16 * 4096 + 21)])
+def test_accumulated_mm_forces_are_rounded_once(prec, n_nnp, n_mm):
+    """An MM force is summed over all NNP atoms before it meets the caller's:
+    bitwise the caller's force plus the force alone, where adding a block of
+    NNP atoms at a time rounds at the caller's size once a block."""
+    torch = torch_cuda()
+    from paper_2201_08110_amd.nnp import Coupling
+    rng = np.random.default_rng(n_nnp + n_mm)
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    sides = (*_side(rng, n_nnp, 0.0, 12.0), *_side(rng, n_mm, 14.0, 60.0))
+    t = [torch.tensor(a, dtype=dt, device="cuda") for a in sides]
+    base = torch.tensor(100.0 * rng.normal(size=(n_mm, 3)), dtype=dt, device="cuda")
+    c = Coupling(n_nnp, n_mm, K, 0.0, prec)
+    _, _, Fm = c(*t)
+    out = (torch.zeros(1, dtype=torch.float64, device="cuda"), torch.zeros_like(t[0]), base.clone())
+    c(*t, out=out, accumulate=True)
+    assert torch.equal(out[2], base + Fm)
