@@ -75,26 +75,34 @@ __device__ inline double row_next(double v) {
 // and in FP64 beyond, the energy in FP64.
 // A wave goes through kCoupleRounds of its groups block by block of 64 NNP
 // atoms, so the sums of a block leave the waves once for them all; between
-// blocks the groups' MM forces wait in LDS.  MANY: more than 64 NNP atoms.
+// blocks the groups' MM forces wait in LDS.
+// With few groups, `share` waves (a power of two) deal a group's blocks out among
+// themselves and meet in LDS: a wave's chain is one block instead of all (1,024
+// x 100 pairs 55.5 -> 13.6 us in FP32, 65 x 3,000 in FP64 13.4 -> 10.3).
+// KIND: at most 64 NNP atoms (one block), more of them, or more of them shared.
 constexpr int kCoupleRounds = 8;
+enum { COUPLE_ONE = 0, COUPLE_MANY = 1, COUPLE_SHARED = 2 };
 template <typename T> size_t couple_lds(int n_nnp) {
     const size_t np = (size_t)(std::max(n_nnp, 1) + 63) / 64 * 64;
     return sizeof(T) * kCoupleVals * np +
            (np > 64 ? sizeof(double) * 3 * np + sizeof(T) * 48 * kCoupleWaves * kCoupleRounds : 0);
 }
-template <typename T, bool CUT, bool MANY>
+template <typename T, bool CUT, int KIND>
 __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, const T* __restrict__ x_nnp,
                                                                  const T* __restrict__ par_nnp, int n_mm,
                                                                  const T* __restrict__ x_mm,
                                                                  const T* __restrict__ par_mm, T k, T rc2,
-                                                                 T* __restrict__ F_mm, int accumulate,
+                                                                 T* __restrict__ F_mm, int accumulate, int share,
                                                                  double* __restrict__ e_part,
                                                                  T* __restrict__ f_part) {
+    constexpr bool MANY = KIND != COUPLE_ONE;
     extern __shared__ __align__(16) char smem[];
     __shared__ double red[kCoupleWaves][3][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15;
-    const int ngroups = (n_mm + 15) / 16, nw = gridDim.x * kCoupleWaves;
-    const int g0 = wave * gridDim.x + blockIdx.x;      // consecutive groups go to different workgroups
+    const int P = KIND == COUPLE_SHARED ? share : 1, slots = kCoupleWaves / P;
+    const int slot = wave / P, first = wave % P;   // this wave's place among the groups and blocks
+    const int ngroups = (n_mm + 15) / 16, nw = gridDim.x * slots;
+    const int g0 = slot * gridDim.x + blockIdx.x;      // consecutive groups go to different workgroups
     if (n_nnp == 0) {
         for (int i = blockIdx.x * kCoupleThreads + tid; !accumulate && i < 3 * n_mm; i += gridDim.x * kCoupleThreads)
             F_mm[i] = T(0);
@@ -122,14 +130,15 @@ __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, cons
     const int step = MANY ? kCoupleRounds * nw : ngroups;
     for (int gs = 0; gs < ngroups; gs += step) {
         const int ge = min(gs + step, ngroups);
-        for (int blk = 0; blk < nblk; ++blk) {
+        for (int b0 = 0; b0 < nblk; b0 += P) {
+            const int blk = b0 + first;
             const T* sb = s + blk * 64 + (lane & 48);
             double fi[3] = {0.0, 0.0, 0.0};
             T* kp = keep;
-            for (int g = gs + g0; g < ge; g += nw, kp += 48) {
+            for (int g = gs + g0; blk < nblk && g < ge; g += nw, kp += 48) {
                 const int j = g * 16 + c;
                 const bool act = j < n_mm;
-                if (g != g0 || blk > 0) load_atom(x_mm, par_mm, act ? j : n_mm - 1, b);
+                if (g != g0 || b0 > 0) load_atom(x_mm, par_mm, act ? j : n_mm - 1, b);
                 if (!act) b[3] = b[5] = T(0);          // no charge, no well depth: no force, no energy
                 T fj[3] = {0, 0, 0}, fr[3] = {0, 0, 0};
 #pragma unroll 4
@@ -161,14 +170,14 @@ __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, cons
                     fj[d] += __shfl_xor(fj[d], 32);
                 }
                 if (MANY && lane < 16) {
-                    if (blk > 0)
+                    if (b0 > 0)
 #pragma unroll
                         for (int d = 0; d < 3; ++d) fj[d] = kp[16 * d + c] + fj[d];
-                    if (blk + 1 < nblk)
+                    if (P > 1 || blk + 1 < nblk)
 #pragma unroll
                         for (int d = 0; d < 3; ++d) kp[16 * d + c] = fj[d];
                 }
-                if (act && lane < 16 && blk + 1 == nblk) {
+                if (act && lane < 16 && P == 1 && blk + 1 == nblk) {
                     T* F = F_mm + 3 * (size_t)j;
 #pragma unroll
                     for (int d = 0; d < 3; ++d) F[d] = (accumulate ? F[d] : T(0)) + fj[d];
@@ -177,14 +186,29 @@ __global__ __launch_bounds__(kCoupleThreads) void k_couple_pairs(int n_nnp, cons
 #pragma unroll
             for (int d = 0; d < 3; ++d) red[wave][d][lane] = fi[d];
             __syncthreads();
-            if (tid < 192) {
-                const int d = tid >> 6;
+            for (int q = wave / 3; q < P && q < nblk - b0; q += kCoupleWaves / 3) {   // block b0 + q
+                if (wave >= kCoupleWaves / 3 * 3) break;
+                const int d = wave % 3;
                 double v = 0.0;
-                for (int w = 0; w < kCoupleWaves; ++w) v += red[w][d][lane];
-                if (MANY) tot[d * np + blk * 64 + lane] += v;
+                for (int w = 0; w < slots; ++w) v += red[w * P + q][d][lane];
+                if (MANY) tot[d * np + (b0 + q) * 64 + lane] += v;
                 else if (lane < n_nnp) f_part[(size_t)(3 * lane + d) * gridDim.x + blockIdx.x] = (T)v;
             }
             __syncthreads();
+        }
+        if (MANY && P > 1 && first == 0 && lane < 16) {
+            // (the waves' sums are behind the last barrier; one round: share
+            // > 1 comes with a slot a group)
+            const int g = gs + g0, j = g * 16 + c;
+            if (g < ge && j < n_mm) {
+                T* F = F_mm + 3 * (size_t)j;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    T v = keep[16 * d + c];
+                    for (int q = 1; q < P && q < nblk; ++q) v += keep[q * 48 * kCoupleRounds + 16 * d + c];
+                    F[d] = (accumulate ? F[d] : T(0)) + v;
+                }
+            }
         }
     }
     for (int i = tid; MANY && i < 3 * n_nnp; i += kCoupleThreads)
@@ -219,6 +243,12 @@ __global__ __launch_bounds__(kCoupleMaxWg) void k_couple_sum(int n_nnp, int n, c
     else F_nnp[t] = accumulate ? F_nnp[t] + (T)v : (T)v;
 }
 
+template <typename T, bool CUT> auto couple_kernel(int n_nnp, int share) {
+    return n_nnp <= 64 ? k_couple_pairs<T, CUT, COUPLE_ONE>
+           : share > 1 ? k_couple_pairs<T, CUT, COUPLE_SHARED>
+                       : k_couple_pairs<T, CUT, COUPLE_MANY>;
+}
+
 // bytes of the partials of a call with n_nnp NNP atoms
 size_t coupling_scratch_bytes(int n_nnp, size_t tsz) {
     return kCoupleMaxWg * (sizeof(double) + tsz * 3 * (size_t)n_nnp);
@@ -231,18 +261,20 @@ hipError_t launch_coupling(const CouplingShape& cs, int n_nnp, const T* x_nnp, c
     const T k = (T)cs.coulomb_k, rc2 = (T)(cs.cutoff > 0 ? cs.cutoff * cs.cutoff : 0.0);
     double* e_part = (double*)scratch;
     T* f_part = (T*)(e_part + kCoupleMaxWg);
-    // one workgroup per CU at most, and four groups of 16 MM atoms a workgroup
-    // at least: few groups spread over many CUs
-    const int ng = (n_mm + 15) / 16, nwg = std::min(kCoupleMaxWg, (ng + 3) / 4);
+    // one workgroup per CU at most, and four busy waves a workgroup at least:
+    // few groups of 16 MM atoms spread over many CUs.  A group's blocks of 64
+    // NNP atoms are shared while every group has its waves at the same time
+    const int ng = (n_mm + 15) / 16, nblk = (n_nnp + 63) / 64;
+    int share = 1;
+    while (share < kCoupleWaves && share < nblk && ng * 2 * share <= kCoupleMaxWg * kCoupleWaves) share *= 2;
+    const int per = std::max(4 / share, 1), nwg = std::min(kCoupleMaxWg, (ng + per - 1) / per);
     if (nwg > 0) {
         const size_t lds = couple_lds<T>(n_nnp);
-        const bool many = n_nnp > 64;
-        auto kern = rc2 > T(0) ? (many ? k_couple_pairs<T, true, true> : k_couple_pairs<T, true, false>)
-                               : (many ? k_couple_pairs<T, false, true> : k_couple_pairs<T, false, false>);
+        auto kern = rc2 > T(0) ? couple_kernel<T, true>(n_nnp, share) : couple_kernel<T, false>(n_nnp, share);
         hipError_t e = ensure_lds((const void*)kern, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3(nwg), dim3(kCoupleThreads), lds, st, n_nnp, x_nnp, par_nnp, n_mm, x_mm, par_mm,
-                           k, rc2, F_mm, accumulate ? 1 : 0, e_part, f_part);
+                           k, rc2, F_mm, accumulate ? 1 : 0, share, e_part, f_part);
     }
     hipLaunchKernelGGL(k_couple_sum<T>, dim3(3 * n_nnp + 1), dim3(kCoupleMaxWg), 0, st, n_nnp, nwg, f_part,
                        e_part, F_nnp, E, accumulate ? 1 : 0);
@@ -275,10 +307,11 @@ hipError_t coupling_scratch(void** ptr) {
         // so later calls do no host-side set-up
         const auto raise = [&](auto zero) {
             typedef decltype(zero) T;
-            for (const void* kern : {(const void*)k_couple_pairs<T, false, false>, (const void*)k_couple_pairs<T, true, false>})
-                if (e == hipSuccess) e = ensure_lds(kern, couple_lds<T>(64));
-            for (const void* kern : {(const void*)k_couple_pairs<T, false, true>, (const void*)k_couple_pairs<T, true, true>})
-                if (e == hipSuccess) e = ensure_lds(kern, couple_lds<T>(1024));
+            for (const auto& kern : {couple_kernel<T, false>(64, 1), couple_kernel<T, true>(64, 1)})
+                if (e == hipSuccess) e = ensure_lds((const void*)kern, couple_lds<T>(64));
+            for (int share : {1, 2})
+                for (const auto& kern : {couple_kernel<T, false>(1024, share), couple_kernel<T, true>(1024, share)})
+                    if (e == hipSuccess) e = ensure_lds((const void*)kern, couple_lds<T>(1024));
         };
         raise(float());
         raise(double());

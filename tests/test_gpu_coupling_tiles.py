@@ -64,3 +64,16 @@ def test_accumulated_mm_forces_are_rounded_once(prec, n_nnp, n_mm):
     out = (torch.zeros(1, dtype=torch.float64, device="cuda"), torch.zeros_like(t[0]), base.clone())
     c(*t, out=out, accumulate=True)
     assert torch.equal(out[2], base + Fm)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_nnp,n_mm,cutoff", [
+    (65, 40, 0.0),                     # two waves a group
+    (300, 3000, 30.0),                 # eight, three of them without a block
+    (600, 10000, 0.0),                 # four, each several blocks
+    (600, 16 * 1024, 30.0), (600, 16 * 1024 + 1, 0.0),   # the last sizes with four, the first with two
+    (129, 16 * 2048 + 1, 0.0),         # the first without
+])
+def test_blocks_shared_by_waves(orc, prec, n_nnp, n_mm, cutoff):
+    """Few groups: the blocks of 64 NNP atoms are dealt out among several waves."""
+    test_tile_edges(orc, prec, n_nnp, n_mm, cutoff)
