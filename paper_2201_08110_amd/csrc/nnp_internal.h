@@ -235,7 +235,8 @@ hipError_t launch_set_nets(const TSRC* src, const ParamPack& pk, const DevWeight
 struct Shape {
     int S, M, D, Dp, H1, H2, H3;       // H* padded to multiples of 64
     int A, B;                          // atoms, molecules of this call
-    int Rcap;                          // capacity rows
+    int Rcap;                          // rows that launches cover
+    int cap_rows;                      // rows of the handle's capacity: what a choice that changes roundings goes by
     int row_tile;                      // bucket padding = GEMM row tile
     int cap_nbr;
     int max_apm;

@@ -1190,7 +1190,8 @@ bool mlp_fused_supported(int H1, int H2, int H3) {
 // sums meet in LDS.  Those loads touch half a line of sixteen rows at a time,
 // so this pays only while every CU has at most one tile (one model, up to 100
 // atoms: 17.4 -> 12 us; 200 atoms or more 20 -> 23, eight models 28 -> 33; the
-// backward's K of 256 a model 9 -> 12).
+// backward's K of 256 a model 9 -> 12).  Its roundings are not k_gemm's, so the
+// handle's capacity decides, not the call.
 template <int KW, int U, int EPI>
 __global__ __launch_bounds__(64 * KW) void k_gk64(GemmArgs<PrecF64> g) {
     touch_kernargs<sizeof(GemmArgs<PrecF64>)>();
@@ -1261,7 +1262,7 @@ static hipError_t run_l1(GemmArgs<P> a, const typename P::TS* Bf, const bf16_t* 
     } else {
     typedef Cfg<P, BM> C;
     if constexpr (std::is_same<P, PrecF64>::value && BM == 16 && EPI == EPI_CELU)
-        if (R / 16 * (N / 16) <= kGk64Tiles) return run_gk64<EPI>(a, R, N, st, tm, name);
+        if (sh.cap_rows / 16 * (N / 16) <= kGk64Tiles) return run_gk64<EPI>(a, R, N, st, tm, name);
     if (N % C::BNW != 0) return net_gemm<P, BM, EPI>(a, nullptr, nullptr, R, N, 1, st, tm, name);
     // 8 waves (2 x 4 of 64 x 32) for the forward GEMM when the knob says so;
     // the backward GEMM measured better on 4
@@ -1310,6 +1311,7 @@ static hipError_t mlp_all(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, 
     GemmArgs<P> base{};
     base.tile_species = w.tile_species;
     base.row_tile = sh.row_tile;
+    base.cap_rows = sh.cap_rows;
     base.info = w.info;
     base.alpha = (TA)sh.celu_alpha;
     base.inv_alpha = (TA)(1.0 / sh.celu_alpha);
@@ -1420,6 +1422,7 @@ static hipError_t train_mlp(const Shape& sh, const DevWeights<P>& wt, Work<P>& w
     GemmArgs<P> base{};
     base.tile_species = w.tile_species;
     base.row_tile = sh.row_tile;
+    base.cap_rows = sh.cap_rows;
     base.info = w.info;
     base.alpha = (TA)sh.celu_alpha;
     base.inv_alpha = (TA)(1.0 / sh.celu_alpha);
@@ -1479,6 +1482,7 @@ static hipError_t train_mlp_rev(const Shape& sh, const DevWeights<P>& wt, Work<P
     GemmArgs<P> base{};
     base.tile_species = w.tile_species;
     base.row_tile = sh.row_tile;
+    base.cap_rows = sh.cap_rows;
     base.info = w.info;
     base.alpha = (TA)sh.celu_alpha;
     base.inv_alpha = (TA)(1.0 / sh.celu_alpha);
@@ -1545,6 +1549,7 @@ hipError_t launch_l1_bwd(const Shape& sh, const DevWeights<P>& wt, Work<P>& w, h
     GemmArgs<P> base{};
     base.tile_species = w.tile_species;
     base.row_tile = sh.row_tile;
+    base.cap_rows = sh.cap_rows;
     base.info = w.info;
     base.n_models = sh.M;
     if constexpr (std::is_same<P, PrecF32>::value) {

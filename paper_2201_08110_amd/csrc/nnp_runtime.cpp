@@ -1116,7 +1116,7 @@ nnp_status nnp_create(const nnp_model_params* p, nnp_handle** out) {
     sh.row_tile = (p->max_atoms <= 256 || p->precision == NNP_PREC_FP64) ? 16 : 128;
     sh.split = p->precision == NNP_PREC_FP32 && sh.row_tile == 128;
     if (sh.split) sh.row_tile = 64;
-    sh.Rcap = pad_to(p->max_atoms + S * (sh.row_tile - 1), sh.row_tile);
+    sh.Rcap = sh.cap_rows = pad_to(p->max_atoms + S * (sh.row_tile - 1), sh.row_tile);
     sh.cap_nbr = std::max(1, std::min(h->max_apm - 1, kMaxNeighbours));
     sh.max_apm = h->max_apm;
     sh.energy_scale = p->energy_scale;
