@@ -13,7 +13,7 @@ namespace nnp {
 
 // a parameter as three bf16 parts at p[0], p[512], p[1024] (nnp_split.h)
 __device__ inline void put_parts(bf16_t* p, float v) {
-    const bf16_t h = Store<bf16_t>::st(v);
+    const bf16_t h = (bf16_t)(__float_as_uint(v) >> 16);
     const float r = v - bf2f(h);
     const bf16_t m = Store<bf16_t>::st(r);
     p[0] = h;

@@ -1,14 +1,17 @@
 // nnp_split.h -- FP32 operands as three bf16 parts for the bf16 matrix cores.
 //
-// x = h + m + l with h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), all
-// rounded to nearest: |m| <= 2^-8 |x|, |l| <= 2^-16 |x|, and the three hold
-// every bit of the FP32 significand (short of underflow below 2^-110).  A
-// product x y is formed as the six parts of weight >= 2^-16,
+// x = h + m + l with h the bf16 of x's leading bits, m = bf16(x - h) and l =
+// bf16(x - h - m) rounded to nearest: |m| <= 2^-7 |x|, |l| <= 2^-16 |x|, and the
+// three hold every bit of the FP32 significand (short of underflow below
+// 2^-110).  A product x y is formed as the six parts of weight >= 2^-16,
 //   l h' + h l' + m m' + m h' + h m' + h h',
-// each exact in FP32; the three dropped ones are at most 2^-23 of |x y|, and
-// below 2^-26 on average.  gfx950 runs bf16 MFMAs 16 times as fast as FP32
-// ones, so six of them take 0.375 of the FP32 MFMA's time.
-// A non-finite x gives non-finite parts, so a non-finite product.
+// each exact in FP32; the three dropped ones are at most 2^-22 of |x y|, 2^-25
+// on average over the products of a sum (a sum of 1,024 with its FP32 additions:
+// 2.5e-7 of its size, 3.2 to 5.7e-7 in a chain of fused multiply-adds).  gfx950
+// runs bf16 MFMAs 16 times as fast as FP32 ones, so six of them take 0.375 of
+// the FP32 MFMA's time.
+// h is cut, not rounded: the nearest bf16 of a finite x above 3.39e38 is
+// infinite.  An infinite or NaN x gives a part that is NaN, so a product that is.
 #pragma once
 
 #include "nnp_gemm.h"
@@ -20,8 +23,9 @@ constexpr int kSplitRows = 64;   // bucket row tile of the handles that split th
 
 // parts of two values, packed (low half = first)
 __device__ inline void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
-    h = pack_bf16x2(a, b);
-    const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
+    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);   // upper halves of both
+    const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
     m = pack_bf16x2(ra, rb);
     const float sa = ra - __uint_as_float(m << 16), sb = rb - __uint_as_float(m & 0xffff0000u);
     l = pack_bf16x2(sa, sb);

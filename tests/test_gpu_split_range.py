@@ -1,0 +1,42 @@
+"""FP32 weights at the upper end of the range: the largest bf16 is 3.3895e38, so a
+finite FP32 value above it must not become infinite as the first of its three
+bf16 parts.  One weight of 3.4e38 in layer 1, 2 or 3, in the buckets of both
+row sizes, by creation and from device memory, against the FP64 oracle: the
+energy is that weight's term and relative 1e-5 of it."""
+import numpy as np
+import pytest
+
+from paper_2201_08110_amd import synth
+from tests.gpu_util import make_handle, oracle_inputs, to_device, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("path", [1, 2])
+@pytest.mark.parametrize("cap", [64, 512])
+@pytest.mark.parametrize("layer", [0, 1, 2])
+def test_weight_above_the_largest_bf16(orc, hp, layer, cap, path):
+    torch = torch_cuda()
+    b = synth.random_batch(31, [40])
+    w = np.array(synth.xavier_weights(1, hp["widths"], seed=8))
+    widths, at, W = hp["widths"], 0, []
+    for k, n in zip(widths, widths[1:]):             # element 0's network
+        W.append((w[at:at + n * k].reshape(n, k), w[at + n * k:at + n * k + n]))
+        at += n * k + n
+    if layer > 0:                                    # its input to the weight: CELU(0.01) for every atom
+        W[layer - 1][0][0] = 0.0
+        W[layer - 1][1][0] = 0.01
+    W[layer][0][0, 5 if layer == 0 else 0] = 3.4e38
+    x, sp, off = to_device(torch, b, torch.float32)
+    xo, wo = oracle_inputs(b, w, "fp32")
+    Eo, _ = orc.energy_forces(hp, wo, 1, b.species, xo, b.mol_offsets)
+    assert abs(Eo[0]) > 1e30
+    h = make_handle(hp, w, 1, "fp32", b, max_atoms=cap)
+    h.set_knob("mlp_path", path)
+    E, _ = h.energy_forces(x, sp, off)
+    h.set_params(torch.tensor(w, device="cuda"))
+    E2, _ = h.energy_forces(x, sp, off)
+    print(layer, cap, path, Eo[0], float(E), float(E2))
+    assert abs(float(E) - Eo[0]) <= 1e-5 * abs(Eo[0])
+    assert float(E2) == float(E)
+    h.close()
