@@ -1219,9 +1219,8 @@ __global__ __launch_bounds__(64 * KW) void k_gk64(GemmArgs<PrecF64> g) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int step = k0 + r * U + u;
-            f64x2 a = av[u];
-            const f64x2 b = bv[u];
-            if (step >= nk) a = f64x2{0., 0.};
+            f64x2 a = av[u], b = bv[u];
+            if (step >= nk) a = b = f64x2{0., 0.};   // (both: a weight may be infinite)
             load(u, step + U);
             asm volatile("" ::: "memory");   // the loads stay ahead of the products
             acc = mf::mma(b[0], a[0], acc);

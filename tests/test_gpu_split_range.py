@@ -40,3 +40,27 @@ def test_weight_above_the_largest_bf16(orc, hp, layer, cap, path):
     assert abs(float(E) - Eo[0]) <= 1e-5 * abs(Eo[0])
     assert float(E2) == float(E)
     h.close()
+
+
+def test_infinite_weight_beside_the_end_of_k(hp):
+    """FP64 layer 1 of the smallest handles splits K over waves, whose shares may
+    end past K: an infinite weight in the last columns multiplies the features
+    alone, as on a handle whose capacity takes the other kernel."""
+    torch = torch_cuda()
+    hp = synth.ani1x_hparams()                       # 384 features: 48 steps of 8 for 64 places
+    b = synth.random_batch(33, [30], ratio=(30, 20, 5, 5))
+    w = np.array(synth.xavier_weights(1, hp["species_widths"], n_species=4, seed=9))
+    x, sp, off = to_device(torch, b, torch.float64)
+    D, at, got = 384, 0, []
+    big = make_handle(hp, w, 1, "fp64", b, max_atoms=1024)
+    G = big.aev(x, sp, off).cpu().numpy()
+    col = 376 + int(np.argmax((G[:, 376:] > 0).sum(0)))
+    assert (G[:, col] > 0).any()
+    for s, ws in enumerate(hp["species_widths"]):    # unit 0 of every element's first layer
+        w[at + col] = -np.inf
+        at += sum(n * (k + 1) for k, n in zip(ws, ws[1:]))
+    for h in (make_handle(hp, w, 1, "fp64", b), make_handle(hp, w, 1, "fp64", b, max_atoms=1024)):
+        E, _ = h.energy_forces(x, sp, off)
+        got.append(float(E))
+        h.close()
+    assert abs(got[0] - got[1]) <= 1e-10 * abs(got[1])
