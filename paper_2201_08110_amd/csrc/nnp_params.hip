@@ -11,6 +11,11 @@
 
 namespace nnp {
 
+// FP32 matrix entries: infinite ones as the largest finite value, for their
+// parts would be NaN against any feature (and zero past CELU); -infinity times
+// a positive feature still ends in CELU's -alpha
+__device__ inline float finite_weight(float v) { return isinf(v) ? copysignf(3.40282347e38f, v) : v; }
+
 // a parameter as three bf16 parts at p[0], p[512], p[1024] (nnp_split.h)
 __device__ inline void put_parts(bf16_t* p, float v) {
     const bf16_t h = (bf16_t)(__float_as_uint(v) >> 16);
@@ -29,9 +34,10 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
     typedef typename P::TA TA;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double v = (double)src[i];   // parameter first + i
-    const TS vs = Store<TS>::st((typename P::TA)v);
+    double v = (double)src[i];   // parameter first + i
     const TA va = (TA)v;
+    if constexpr (std::is_same<P, PrecF32>::value) v = finite_weight(va);   // (va: biases and the output layer as they are)
+    const TS vs = Store<TS>::st((TA)v);
     // position in the uniform (padded) packed layout: [m][s]{W1 b1 W2 b2 W3 b3 w4 b4}
     const int64_t pi = map ? (int64_t)map[first + i] : first + i;
     const int64_t ms = pi / pk.net;
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(256) void k_set_nets(const TSRC* __restrict__ src, 
     const int N = np[l], K = np[l - 1], nkb = K / 64, n0 = blk / nkb * 64, k0 = blk % nkb * 64;
     src += off;
     for (int r = wave; r < 64; r += 4)
-        t[r][lane] = n0 + r < w[l] && k0 + lane < w[l - 1] ? (float)src[(int64_t)(n0 + r) * w[l - 1] + k0 + lane] : 0.f;
+        t[r][lane] = n0 + r < w[l] && k0 + lane < w[l - 1] ? finite_weight((float)src[(int64_t)(n0 + r) * w[l - 1] + k0 + lane]) : 0.f;
     __syncthreads();
     // layer 1 keeps the models side by side, [S][M * H1][Dp] and its
     // transpose; the others one matrix a model

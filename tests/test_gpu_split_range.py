@@ -64,3 +64,26 @@ def test_infinite_weight_beside_the_end_of_k(hp):
         got.append(float(E))
         h.close()
     assert abs(got[0] - got[1]) <= 1e-10 * abs(got[1])
+
+
+@pytest.mark.parametrize("cap", [64, 512])
+@pytest.mark.parametrize("upload", ["create", "set_weights", "set_params"])
+def test_infinite_fp32_weight(hp, upload, cap):
+    """-infinity in layer 1 ends where the largest negative weight does, for atoms
+    with and without the feature."""
+    torch = torch_cuda()
+    b = synth.random_batch(31, [40])
+    w0 = np.array(synth.xavier_weights(1, hp["widths"], seed=8))
+    x, sp, off = to_device(torch, b, torch.float32)
+    E = []
+    for v in (-3.402e38, -np.inf):
+        w = w0.copy()
+        w[5] = v                                     # hydrogen's unit 0, a radial feature of hydrogen neighbours
+        h = make_handle(hp, w if upload == "create" else w0, 1, "fp32", b, max_atoms=cap)
+        if upload == "set_weights":
+            h.set_weights(w)
+        elif upload == "set_params":
+            h.set_params(torch.tensor(w, device="cuda"))
+        E.append(float(h.energy_forces(x, sp, off)[0]))
+        h.close()
+    assert E[0] == E[1]
