@@ -505,20 +505,39 @@ void launch_bounds(const nnp_handle* h, const nnp_batch* b, int& A, int& B) {
     }
 }
 
+// Central atoms per featuriser / force workgroup where the knob leaves them
+// open: the fewest of 4, 8 and 16 that both of these rules allow.
+// By the call's atoms: a workgroup's four waves take its atoms in turn, so
+// calls of few atoms want 4 (1,178 atoms, both kernels and the neighbour lists:
+// 42 us at 4, 58 at 8, 88 at 16; 4,999: 62 / 72 / 100; 12,011: 96 / 101 / 121),
+// while larger ones want each molecule staged less often (23,990: 156 / 146 /
+// 162).  16 pays once its workgroups (at least A / 16) make two rounds of the
+// six that each of the 256 CUs holds, 49,137 atoms: below, the last round is
+// nearly empty (BF16, one network, at 8 / 16: equal molecules of 48 atoms 235 /
+// 242 us at 36,000, 274 / 276 at 46,992, 359 / 355 at 60,000, 455 / 445 at
+// 79,968; ragged ones of 65 on average 260 / 264 at 35,866, 318 / 322 at 46,962,
+// 408 / 404 at 59,918, 518 / 505 at 79,917).
+// By the launch: its grid is every molecule times the chunks of the largest one
+// the handle takes, and where most of them are empty, starting them is the work:
+// at most eight rounds, 12,288 (1,024 molecules of 4 atoms in BF16, one network,
+// up to 128 atoms a molecule: 84 us at 4, 69 at 8, 63 at 16; 512 of 8: 69 / 65 /
+// 65; up to 1,024 atoms: 402 / 239 / 157; 256 of 16 at 8,192 workgroups: 66 / 71
+// / 86; 512 of 48 at 7,680 with 8: 190 / 184 / 195).
+constexpr int64_t kChunkRounds = 2 * 6 * 256, kChunkGroups = 8 * 6 * 256;
+int auto_chunk(int A, int B, int max_apm) {
+    int chunk = A < 16384 ? 4 : (A + 15) / 16 < kChunkRounds ? 8 : 16;
+    while (chunk < 16 && (int64_t)B * ((max_apm + chunk - 1) / chunk) > kChunkGroups) chunk *= 2;
+    return chunk;
+}
+
 // The handle's shape for a call of at most A atoms and B molecules.  Launches
-// cover the rows A atoms can fill, not the capacity's.  Central atoms per
-// featuriser / force workgroup, unless the knob fixes them: a workgroup's four
-// waves take them in turn, so calls of few atoms want 4 (1,178 atoms, both
-// kernels and the neighbour lists: 42 us at 4, 58 at 8, 88 at 16; 4,999: 62 /
-// 72 / 100; 12,011: 96 / 101 / 121), while large ones want each molecule staged
-// less often (23,990: 156 / 146 / 162; 47,999: 272 / 254 / 268; 49,152 of one
-// ligand: 268 / 225 / 219).
+// cover the rows A atoms can fill, not the capacity's.
 Shape call_shape(const nnp_handle* h, int A, int B) {
     Shape sh = h->shape;
     sh.A = A;
     sh.B = B;
     sh.Rcap = std::min<int64_t>(sh.Rcap, pad_to(A + sh.S * (sh.row_tile - 1), sh.row_tile));
-    if (!h->knob[NNP_KNOB_ATOM_CHUNK]) sh.chunk = A < 16384 ? 4 : A < 48000 ? 8 : 16;
+    if (!h->knob[NNP_KNOB_ATOM_CHUNK]) sh.chunk = auto_chunk(A, B, sh.max_apm);
     return sh;
 }
 
