@@ -761,7 +761,13 @@ hipError_t launch_neighbours(const Shape& sh, const AevConst<typename P::T>& c,
     } else if (accumulate) {
         F = nullptr;
     }
-    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk);
+    // the lists do not depend on the chunk: more atoms a workgroup than the
+    // other kernels' where most workgroups would be empty, whose start is dear
+    // here (LDS for the largest molecule; 1,024 molecules of 4 atoms in a handle
+    // for 1,024, the whole call 157 -> 141 us in BF16, 423 -> 401 in FP64)
+    int chunk = sh.chunk;
+    while (chunk < sh.max_apm && (int64_t)sh.B * ((sh.max_apm + chunk - 1) / chunk) > kMaxGroups) chunk *= 2;
+    dim3 grid(sh.B, (sh.max_apm + chunk - 1) / chunk);
     size_t lds = lds_bytes<T>(4 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm) +
                  lds_bytes<T>(3 * (size_t)sh.max_apm) + lds_bytes<int>(sh.max_apm);
     if (sh.max_apm > sh.cell_min) lds += lds_bytes<int>(kCellKeys + 1) + 2 * lds_bytes<int>(sh.max_apm);
@@ -770,7 +776,7 @@ hipError_t launch_neighbours(const Shape& sh, const AevConst<typename P::T>& c,
     if (e != hipSuccess) return e;
     tm.b("neighbours", st);
     hipLaunchKernelGGL(k_nbr_pairs<T>, grid, dim3(256), lds, st, sh.A, sh.S, sh.max_apm, sh.cell_min,
-                       sh.chunk, sh.cap_nbr, c.rcr, c.rca2, c.rcr2, mol_off, species, x, F, Fq, w.nbr,
+                       chunk, sh.cap_nbr, c.rcr, c.rca2, c.rcr2, mol_off, species, x, F, Fq, w.nbr,
                        w.nbr_cnt, w.flag);
     tm.e("neighbours", st);
     return hipGetLastError();

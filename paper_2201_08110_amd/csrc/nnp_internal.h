@@ -258,6 +258,9 @@ struct Shape {
     int sub;                           // 1: one part of a pipelined evaluation (atoms need not start at 0)
     int pipeline;                      // 2: large batches evaluated as two pipelined parts on two streams
 };
+// most workgroups of a launch over every molecule times the chunks of the
+// largest one the handle takes: eight rounds of six a CU
+constexpr int64_t kMaxGroups = 8 * 6 * 256;
 hipError_t launch_stage_batch(int B, int A, const int32_t* counts, const int32_t* mol_off, int32_t* moff,
                               int32_t* dcnt, int32_t* flag, hipStream_t st);
 

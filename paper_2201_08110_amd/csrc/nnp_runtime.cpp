@@ -523,10 +523,10 @@ void launch_bounds(const nnp_handle* h, const nnp_batch* b, int& A, int& B) {
 // up to 128 atoms a molecule: 84 us at 4, 69 at 8, 63 at 16; 512 of 8: 69 / 65 /
 // 65; up to 1,024 atoms: 402 / 239 / 157; 256 of 16 at 8,192 workgroups: 66 / 71
 // / 86; 512 of 48 at 7,680 with 8: 190 / 184 / 195).
-constexpr int64_t kChunkRounds = 2 * 6 * 256, kChunkGroups = 8 * 6 * 256;
+constexpr int64_t kChunkRounds = 2 * 6 * 256;
 int auto_chunk(int A, int B, int max_apm) {
     int chunk = A < 16384 ? 4 : (A + 15) / 16 < kChunkRounds ? 8 : 16;
-    while (chunk < 16 && (int64_t)B * ((max_apm + chunk - 1) / chunk) > kChunkGroups) chunk *= 2;
+    while (chunk < 16 && (int64_t)B * ((max_apm + chunk - 1) / chunk) > kMaxGroups) chunk *= 2;
     return chunk;
 }
 
