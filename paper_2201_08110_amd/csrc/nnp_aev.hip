@@ -1265,8 +1265,8 @@ __device__ inline void angular_rows(const AtomLists& al, int p0, int nbat, const
     wave_sync();
 }
 
-// Bucketing inside the featuriser, for batches of at most kBucketAtoms atoms and
-// molecules: the results of the bucketing kernels without their launches.
+// Bucketing inside the featuriser, for batches of at most kBucketAtoms atoms: the
+// results of the bucketing kernels without their launches.
 // Every workgroup counts the elements of the batch's atoms and of those before
 // its chunk (64 atoms a wave in turn; every lane counts its own, a byte an
 // element, and the counts are added over the lanes once), which gives the
@@ -1428,9 +1428,9 @@ __device__ inline void zero_blocks(TS* gang, T* aang, int NB, unsigned long long
             if (!((filled >> (e / kNAZ)) & 1ull)) aang[e] = T(0);
 }
 
-// neighbour lists given, found here, or found here with the bucketing too
-constexpr int kLists = 0, kSearch = 1, kBuckets = 2;
-template <typename P, int NZ, int MODE>
+// FUSE: the workgroup finds its atoms' neighbour lists itself (and writes them
+// out for the force kernel) instead of reading them, and their bucket rows
+template <typename P, int NZ, bool FUSE>
 __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev(AevConst<typename P::T> c, int A, int max_apm,
                                              int chunk, int cap, const int32_t* __restrict__ mol_off,
                                              const int32_t* __restrict__ species,
@@ -1451,7 +1451,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     const int b = block_molecule(blockIdx.y);
     // with the bucketing fused in, the last row of workgroups is one
     // workgroup that writes the batch's bucket table
-    if constexpr (MODE == kBuckets) {
+    if constexpr (FUSE) {
         if (blockIdx.y == gridDim.y - 1) {
             if (b == 0) bucket_table(nf.bk, c.S, A, max_apm, mol_off, species, (int*)smem, nf.flag);
             return;
@@ -1465,38 +1465,35 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
 
-    // fused: the workgroup finds its atoms' neighbour lists itself (and
-    // writes them out for the force kernel) instead of reading them
-    constexpr bool fuse = MODE != kLists;
     const bool direct = n <= kDirectAtoms;
     LdsBump lb(smem);
     ChunkStage<T> cs;
     cs.take(lb, max_apm, cap, false);
-    int* ccnt = fuse ? nullptr : lb.take<int>(kChunk);
+    int* ccnt = FUSE ? nullptr : lb.take<int>(kChunk);
     T* nb = lb.take<T>((size_t)nw * cap * R::stride) + (size_t)wave * cap * R::stride;
     T* pf = lb.take<T>((size_t)nw * (64 + kPairRoom) * PF) + (size_t)wave * (64 + kPairRoom) * PF;
-    int* red = MODE == kBuckets ? lb.take<int>(16 * (size_t)nw) : nullptr;
+    int* red = FUSE ? lb.take<int>(16 * (size_t)nw) : nullptr;
     int* mark = lb.take<int>((size_t)nw * 64) + (size_t)wave * 64;
     // (molecules beyond the direct search: their order by element, and a list)
-    const bool staged = fuse && max_apm > kDirectAtoms;
+    const bool staged = FUSE && max_apm > kDirectAtoms;
     T* sx4 = staged ? lb.take<T>(4 * (size_t)max_apm) : nullptr;
     int* sid = staged ? lb.take<int>(max_apm) : nullptr;
     uint16_t* wl = staged ? lb.take<uint16_t>((size_t)nw * cap) + (size_t)wave * cap : nullptr;
-    if (!fuse && tid < nc) ccnt[tid] = nbr_cnt[(size_t)a0 + i0 + tid];
-    cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, MODE == kBuckets ? nullptr : row_of_atom,
-            MODE == kBuckets ? nf.bk.zlut : nullptr);
+    if (!FUSE && tid < nc) ccnt[tid] = nbr_cnt[(size_t)a0 + i0 + tid];
+    cs.load(x, species, S, a0, n, i0, nc, cap, nbr, nbr_cnt, FUSE ? nullptr : row_of_atom,
+            FUSE ? nf.bk.zlut : nullptr);
     GroupBuckets gb;
     int csp = -1;   // lane l: element of chunk atom l
     unsigned long long cbad = 0;
-    if constexpr (MODE == kBuckets) {
+    if constexpr (FUSE) {
         bool bad = false;
         if (lane < nc) csp = bucket_element(nf.bk, species[a0 + i0 + lane], S, bad);
         cbad = __ballot(bad);
         count_elements(nf.bk, gb, S, A, mol_off, species, a0 + i0, wave, nw, red);
     }
     __syncthreads();
-    if constexpr (MODE == kBuckets) group_buckets(nf.bk, gb, nw, red);
-    if (fuse && !direct) {
+    if constexpr (FUSE) group_buckets(nf.bk, gb, nw, red);
+    if (FUSE && !direct) {
         if (wave == 0) stage_element_order(cs.sx, cs.ssp, n, S, sx4, sid);
         __syncthreads();
     }
@@ -1511,13 +1508,13 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         const int il = i0 + ic;
         int cnt, row, ao = 0, ro = 0;
         const uint16_t* lst;
-        if constexpr (MODE == kBuckets) {
+        if constexpr (FUSE) {
             row = bucket_atom(nf.bk, gb, S, csp, cbad, ic, a0 + il, b, nf.flag);
             if (row < 0) continue;
         } else {
             row = uniform(cs.crow[ic]);
         }
-        if constexpr (fuse) {
+        if constexpr (FUSE) {
             // this evaluation's force accumulators, cleared as the neighbour
             // kernel clears them
             if (nf.F && lane < 3) nf.F[3 * ((size_t)a0 + il) + lane] = T(0);
@@ -1536,7 +1533,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
         }
         const int nang = cnt & 0xffff, nall = cnt >> 16;
         AtomLists al;
-        if (fuse && direct) {
+        if (FUSE && direct) {
             al = atom_lists(ao, ro, S, ba, bb);
         } else {
             load_records<false>(c, cs.sx, cs.ssp, lst, nang, nall, il, nb);
@@ -1722,14 +1719,13 @@ hipError_t launch_aev(const Shape& sh, const AevConst<typename P::T>& c, const i
                       const NbrFuse<typename P::T>& nf) {
     typedef typename P::T T;
     int nw = kWaves;
-    const bool fuse = nf.nbr != nullptr, bucket = nf.bk.info != nullptr;
-    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk + (bucket ? 1 : 0));
+    const bool fuse = nf.nbr != nullptr;
+    dim3 grid(sh.B, (sh.max_apm + sh.chunk - 1) / sh.chunk + (fuse ? 1 : 0));
     size_t lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.nZ, nw, fuse);
     while (lds > kMaxLds && nw > 1) lds = aev_lds<T>(sh.max_apm, sh.cap_nbr, c.nZ, nw /= 2, fuse);
     if (lds > kMaxLds) return hipErrorInvalidValue;
-    auto kern = bucket ? (c.nZ == 4 ? k_aev<P, 4, kBuckets> : k_aev<P, 8, kBuckets>)
-              : fuse   ? (c.nZ == 4 ? k_aev<P, 4, kSearch> : k_aev<P, 8, kSearch>)
-                       : (c.nZ == 4 ? k_aev<P, 4, kLists> : k_aev<P, 8, kLists>);
+    auto kern = fuse ? (c.nZ == 4 ? k_aev<P, 4, true> : k_aev<P, 8, true>)
+                     : (c.nZ == 4 ? k_aev<P, 4, false> : k_aev<P, 8, false>);
     hipError_t e = ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     tm.b("aev", st);
@@ -1739,51 +1735,27 @@ hipError_t launch_aev(const Shape& sh, const AevConst<typename P::T>& c, const i
     return hipGetLastError();
 }
 
-// Neighbour lists and AEV rows.  Small batches (up to kFuseAtoms atoms, all
-// molecules within the all-pairs neighbour search) take one fused launch:
-// there the launch and the list round trip are a visible part of the
-// latency.  Large batches measured no faster fused (the search is the same
-// work inside the featuriser's waves), so they keep the neighbour kernels.
-// The force accumulators are cleared as launch_neighbours clears them.
-constexpr int kFuseAtoms = 4096;
-template <typename P>
-hipError_t launch_features(const Shape& sh, const AevConst<typename P::T>& c, const int32_t* mol_off,
-                           const int32_t* species, const typename P::T* x, typename P::T* F,
-                           bool accumulate, Work<P>& w, typename P::T* aev_out, hipStream_t st,
-                           const Timer& tm) {
-    if (sh.max_apm > sh.cell_min || sh.A > kFuseAtoms) {
-        hipError_t e = launch_neighbours<P>(sh, c, mol_off, species, x, F, accumulate, w, st, tm);
-        if (e != hipSuccess) return e;
-        return launch_aev<P>(sh, c, mol_off, species, x, w, aev_out, st, tm, NbrFuse<typename P::T>());
-    }
-    NbrFuse<typename P::T> nf;
-    nf.rca2 = c.rca2;
-    nf.rcr2 = c.rcr2;
-    nf.F = (F && !sh.force_fixed && !accumulate) ? F : nullptr;
-    nf.Fq = (F && sh.force_fixed) ? w.Fq : nullptr;
-    nf.nbr = w.nbr;
-    nf.cnt = w.nbr_cnt;
-    nf.flag = w.flag;
-    return launch_aev<P>(sh, c, mol_off, species, x, w, aev_out, st, tm, nf);
-}
-
-// Bucketing and featurisation.  A batch that takes the fused neighbour search
-// is bucketed inside the featuriser too (one launch for all three steps: each
-// dependent launch is a visible part of the latency); otherwise the bucketing
-// kernels run first.  Every workgroup then counts the whole batch's labels: at
-// 3,134 atoms 25.3 -> 29.6 us for two launches of 4.7 and 6.2 less, at 3,520
-// 20.9 -> 26.5 for 11.4, and the gain ends near kBucketAtoms.
+// Bucketing and featurisation.  A small batch takes one launch for bucketing,
+// neighbour search and rows: each dependent launch is a visible part of its
+// latency.  Small: up to kBucketAtoms atoms, every molecule within the all-pairs
+// search, and up to 1,024 molecules.  Every workgroup counts the whole batch's
+// labels: at 3,134 atoms 25.3 -> 29.6 us for two launches of 4.7 and 6.2 less, at
+// 3,520 20.9 -> 26.5 for 11.4, and the gain ends near kBucketAtoms; and every
+// molecule is a workgroup that counts (FP64, one network, 4,096 molecules of one
+// atom in a handle for 128: 306 us in one launch, 279 apart, 2,048 of two 254 /
+// 248; BF16 76 / 82 and 101 / 100).
 template <typename P>
 hipError_t launch_prep_features(const Shape& sh, const AevConst<typename P::T>& c, const int32_t* mol_off,
                                 const int32_t* species, const typename P::T* x, typename P::T* F,
                                 bool accumulate, Work<P>& w, typename P::T* aev_out, hipStream_t st,
                                 const Timer& tm) {
-    const bool small = sh.A > 0 && std::max(sh.A, sh.B) <= kBucketAtoms && sh.max_apm <= sh.cell_min;
+    const bool small = sh.A > 0 && sh.A <= kBucketAtoms && sh.B <= kPrepBlock && sh.max_apm <= sh.cell_min;
     if (!small) {
         hipError_t e = launch_prep<P>(sh, mol_off, species, w, st, tm);
-        if (e != hipSuccess) return e;
-        if (sh.A == 0) return hipSuccess;
-        return launch_features<P>(sh, c, mol_off, w.zlut ? w.sp : species, x, F, accumulate, w, aev_out, st, tm);
+        if (e != hipSuccess || sh.A == 0) return e;
+        const int32_t* sp = w.zlut ? w.sp : species;
+        if ((e = launch_neighbours<P>(sh, c, mol_off, sp, x, F, accumulate, w, st, tm)) != hipSuccess) return e;
+        return launch_aev<P>(sh, c, mol_off, sp, x, w, aev_out, st, tm, NbrFuse<typename P::T>());
     }
     NbrFuse<typename P::T> nf;
     nf.rca2 = c.rca2;
@@ -2911,9 +2883,6 @@ hipError_t launch_energy(const Shape& sh, const DevWeights<P>& wt, const int32_t
                                                 const int32_t*, const int32_t*, const P::T*,     \
                                                 P::T*, bool, Work<P>&, P::T*, hipStream_t,       \
                                                 const Timer&);                                   \
-    template hipError_t launch_features<P>(const Shape&, const AevConst<P::T>&,                \
-                                           const int32_t*, const int32_t*, const P::T*, P::T*, \
-                                           bool, Work<P>&, P::T*, hipStream_t, const Timer&);  \
     template hipError_t launch_forces<P>(const Shape&, const AevConst<P::T>&, const int32_t*,  \
                                          const int32_t*, const P::T*, Work<P>&, P::T*,         \
                                          hipStream_t, const Timer&, const EnergyArgs<P>&);     \

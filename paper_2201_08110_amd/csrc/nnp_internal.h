@@ -318,10 +318,8 @@ hipError_t launch_neighbours(const Shape& sh, const AevConst<typename P::T>& c,
                              const typename P::T* x, typename P::T* F, bool accumulate, Work<P>& w,
                              hipStream_t st, const Timer& tm);
 // The featuriser finding its own neighbour lists (nbr null: it reads them):
-// cutoffs, the force accumulators it clears, and where the lists go
-// (bucketing, for batches of at most kPrepBlock atoms and molecules: the
-// bucketing kernel's outputs, written by the featuriser instead; info null:
-// the bucketing kernel has run)
+// cutoffs, the force accumulators it clears, where the lists go, and the
+// bucketing kernels' outputs, which it then writes too
 struct BucketFuse {
     const int8_t* zlut = nullptr;      // atomic number -> element, or null
     int32_t* sp_out = nullptr;         // element indices (zlut != null)
@@ -354,11 +352,6 @@ hipError_t launch_prep_features(const Shape& sh, const AevConst<typename P::T>& 
                                 const int32_t* species, const typename P::T* x, typename P::T* F,
                                 bool accumulate, Work<P>& w, typename P::T* aev_out, hipStream_t st,
                                 const Timer& tm);
-template <typename P>
-hipError_t launch_features(const Shape& sh, const AevConst<typename P::T>& c, const int32_t* mol_off,
-                           const int32_t* species, const typename P::T* x, typename P::T* F,
-                           bool accumulate, Work<P>& w, typename P::T* aev_out, hipStream_t st,
-                           const Timer& tm);
 // hidden widths (padded) the fused layers 2-3 kernel is compiled for
 bool mlp_fused_supported(int H1, int H2, int H3);
 

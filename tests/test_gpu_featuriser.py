@@ -108,3 +108,14 @@ def test_fp32_row_tangents(orc, hp, model, elements, chunk):
     err = np.linalg.norm(gp.cpu().numpy() - go) / np.linalg.norm(go)
     assert err < 1e-4
     h.close()
+
+
+@pytest.mark.parametrize("sizes", [
+    [3] * 1023 + [2],                  # 1,024 molecules: the last batch with fused bucketing
+    [3] * 1023 + [2, 4],               # the first without
+    [2, 1, 0] * 1000,                  # most of them empty or one atom
+])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_many_small_molecules(orc, hp, sizes, prec):
+    """At most 4,096 atoms in about a thousand molecules and more."""
+    test_records_and_rows_match_oracle(orc, hp, sizes, prec, 0)
