@@ -1447,7 +1447,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     constexpr int NA = kNAZ / NZ;
     constexpr int PF = NA + NZ;
     extern __shared__ __align__(16) char smem[];
-    touch_kernargs<sizeof(AevConst<T>) + sizeof(NbrFuse<T>) + 80>();
+    constexpr bool late = sizeof(T) == 8;
+    if constexpr (!late) touch_kernargs<sizeof(AevConst<T>) + sizeof(NbrFuse<T>) + 80>();
     const int b = block_molecule(blockIdx.y);
     // with the bucketing fused in, the last row of workgroups is one
     // workgroup that writes the batch's bucket table
@@ -1461,6 +1462,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_aev
     const int i0 = blockIdx.y * chunk;
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     if (i0 >= n) return;
+    if constexpr (late) touch_kernargs<sizeof(AevConst<T>) + sizeof(NbrFuse<T>) + 80>();
     const int nc = min(chunk, n - i0);
     const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
@@ -2201,7 +2203,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
     typedef typename Acc::V V;
     constexpr int NA = kNAZ / NZ;
     extern __shared__ __align__(16) char smem[];
-    touch_kernargs<sizeof(AevConst<T>) + sizeof(EnergyArgs<P>) + 88>();
+    constexpr bool late = sizeof(T) == 8;
+    if constexpr (!late) touch_kernargs<sizeof(AevConst<T>) + sizeof(EnergyArgs<P>) + 88>();
     const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), nw = blockDim.x >> 6;
     int b = block_molecule(blockIdx.y), by = blockIdx.y;
     // The energies (as k_energy computes them), a molecule per wave, by the
@@ -2223,6 +2226,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::T) == 8 ? 1 : 6) void k_for
     if (n <= 0 || n > max_apm || a0 < 0 || a0 + n > A) return;
     const int i0 = by * chunk;
     if (i0 >= n) return;
+    if constexpr (late) touch_kernargs<sizeof(AevConst<T>) + sizeof(EnergyArgs<P>) + 88>();
     const int nc = min(chunk, n - i0);
     const int S = c.S, RL = kNR * S, NB = S * (S + 1) / 2;
     const int GL = RL + kBlkPad * NB;

@@ -156,6 +156,10 @@ struct NetLayout {
 // layer-1 GEMMs 16.7 -> 16.3 and 14.9 -> 14.3 us, FP64 tail 30.9 -> 30.7).
 // For kernels of few workgroups: the large-batch layer-1 GEMM measured 197 ->
 // 202 us with it.
+// In FP64 the row and force kernels start it behind the exit of the workgroups
+// without atoms: their LDS leaves one or two on a CU, so every empty one counts
+// (1,024 molecules of 4 atoms in a handle for 1,024: 401 -> 359 us; the 24-atom
+// molecule the same).  In FP32 that costs the smallest calls 0.4 us.
 template <int BYTES> __device__ inline void touch_kernargs() {
     typedef const volatile int __attribute__((address_space(4))) * Args;
     Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
