@@ -32,11 +32,12 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
                                                     DevWeights<P> dw) {
     typedef typename P::TS TS;
     typedef typename P::TA TA;
+    constexpr bool f32 = std::is_same<P, PrecF32>::value;   // parts, no row-major matrices
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double v = (double)src[i];   // parameter first + i
     const TA va = (TA)v;
-    if constexpr (std::is_same<P, PrecF32>::value) v = finite_weight(va);   // (va: biases and the output layer as they are)
+    if constexpr (f32) v = finite_weight(va);   // (va: biases and the output layer as they are)
     const TS vs = Store<TS>::st((TA)v);
     // position in the uniform (padded) packed layout: [m][s]{W1 b1 W2 b2 W3 b3 w4 b4}
     const int64_t pi = map ? (int64_t)map[first + i] : first + i;
@@ -48,15 +49,15 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
     if (r < pk.offb1) {                       // W1 [o1][D]
         const int nn = (int)(r / pk.D), k = (int)(r % pk.D);
         const int col = m * H1 + nn, N1 = M * H1;
-        if (dw.W1x) {
+        if (f32 && dw.W1x) {
             put_parts(dw.W1x + (size_t)s * N1 * Dp * 3 + split_index(col, k, Dp), (float)v);
             put_parts(dw.W1Tx + (size_t)s * N1 * Dp * 3 + split_index(k, col, N1), (float)v);
         }
-        if (dw.W1) {
+        if (!f32) {
             dw.W1[((size_t)s * N1 + col) * Dp + k] = vs;
             dw.W1T[((size_t)s * Dp + k) * N1 + col] = vs;
         }
-        if (dw.W1f) {
+        if (sizeof(TS) < 8) {
             dw.W1f[(size_t)s * N1 * Dp + frag_index<TS>(col, k, Dp)] = vs;
             dw.W1Tf[(size_t)s * N1 * Dp + frag_index<TS>(k, col, N1)] = vs;
         }
@@ -65,11 +66,11 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
     } else if (r < pk.offb2) {                // W2 [o2][o1]
         const int64_t q = r - pk.offW2;
         const int nn = (int)(q / pk.o1), k = (int)(q % pk.o1);
-        if (dw.W2x) {
+        if (f32 && dw.W2x) {
             put_parts(dw.W2x + sm * H2 * H1 * 3 + split_index(nn, k, H1), (float)v);
             put_parts(dw.W2Tx + sm * H1 * H2 * 3 + split_index(k, nn, H2), (float)v);
         }
-        if (dw.W2) {
+        if (!f32) {
             dw.W2[(sm * H2 + nn) * H1 + k] = vs;
             dw.W2T[(sm * H1 + k) * H2 + nn] = vs;
         }
@@ -80,11 +81,11 @@ __global__ __launch_bounds__(256) void k_set_params(int64_t first, int64_t n, co
     } else if (r < pk.offb3) {                // W3 [o3][o2]
         const int64_t q = r - pk.offW3;
         const int nn = (int)(q / pk.o2), k = (int)(q % pk.o2);
-        if (dw.W3x) {
+        if (f32 && dw.W3x) {
             put_parts(dw.W3x + sm * H3 * H2 * 3 + split_index(nn, k, H2), (float)v);
             put_parts(dw.W3Tx + sm * H2 * H3 * 3 + split_index(k, nn, H3), (float)v);
         }
-        if (dw.W3) {
+        if (!f32) {
             dw.W3[(sm * H3 + nn) * H2 + k] = vs;
             dw.W3T[(sm * H2 + k) * H3 + nn] = vs;
         }
