@@ -341,7 +341,7 @@ int32_t nnp_kernel_times(nnp_handle* h, int32_t cap, const char** names, int64_t
  *                         adds, converted to the force type once: bitwise
  *                         identical forces on every run, stream and launch
  *                         shape (the rest of an evaluation already is).
- *                         auto: 1.  The autotuner leaves this knob alone.
+ *                         auto: 1.
  *   NNP_KNOB_FORCE_PATH   force kernel: 1 = each atom's dE/dAEV row staged in
  *                         LDS, 2 = read from global memory (cache hits),
  *                         leaving the LDS to the force sums.  auto: 2.
@@ -376,12 +376,14 @@ enum {
 nnp_status nnp_set_knob(nnp_handle* h, int32_t knob, int32_t value);
 nnp_status nnp_get_knob(nnp_handle* h, int32_t knob, int32_t* value);
 
-/* Autotuner: times the candidates of every knob on this batch (one warm-up
- * and `reps` evaluations each, HIP events on the batch's stream), knob by
- * knob, and keeps the fastest on the handle.  coords are float (double for
+/* Autotuner: times the candidates of the knobs that have an effect on this
+ * handle (one warm-up and `reps` evaluations each, HIP events on the batch's
+ * stream), knob by knob, and keeps the fastest on the handle.
+ * NNP_KNOB_FORCE_SUM and NNP_KNOB_ATOM_CHUNK stay as they are (the latter's
+ * automatic choice goes by each call).  coords are float (double for
  * FP64 handles).  If cache_path is non-NULL the choice is looked up first in
  * that file (JSON lines, one object per key: device architecture, precision,
- * model shape and capacity) and, when tuned afresh, appended to it.  If
+ * model shape, capacity and the kernels' revision) and, when tuned afresh, appended to it.  If
  * report is non-NULL a JSON object with the key, the chosen values and the
  * timings of every candidate (microseconds per evaluation) is written into it
  * (truncated to report_cap bytes).  Allocates temporary outputs; synchronises

@@ -846,14 +846,22 @@ const char* knob_name(int k) {
          : k == NNP_KNOB_FORCE_PATH ? "force_path" : "pipeline";
 }
 
+// raised when the kernels change, so that choices among older ones are not
+// taken from a cache
+constexpr int kTuneRevision = 2;
+// knobs the tuner and its cache leave alone: reproducible sums are the caller's
+// choice, and a chunk fixed for the tuned batch would serve calls of other sizes
+// worse than the automatic one, which goes by the call
+bool tuned_knob(int k) { return k != NNP_KNOB_FORCE_SUM && k != NNP_KNOB_ATOM_CHUNK; }
+
 std::string tune_key(const nnp_handle* h) {
     hipDeviceProp_t prop;
     std::string arch = "unknown";
     if (hipGetDeviceProperties(&prop, h->device) == hipSuccess) arch = prop.gcnArchName;
     char buf[256];
-    std::snprintf(buf, sizeof(buf), "%s|%s|S%d M%d w%d-%d-%d-%d|atoms%d mols%d apm%d", arch.c_str(),
+    std::snprintf(buf, sizeof(buf), "%s|%s|S%d M%d w%d-%d-%d-%d|atoms%d mols%d apm%d|r%d", arch.c_str(),
                   prec_name(h->precision), h->S, h->M, h->widths[0], h->widths[1], h->widths[2],
-                  h->widths[3], h->max_atoms, h->max_mols, h->max_apm);
+                  h->widths[3], h->max_atoms, h->max_mols, h->max_apm, kTuneRevision);
     return buf;
 }
 
@@ -878,10 +886,10 @@ bool cache_lookup(const char* path, const std::string& key, int32_t knobs[NNP_N_
         int32_t v[NNP_N_KNOBS];
         bool ok = true;
         for (int k = 0; k < NNP_N_KNOBS; ++k)
-            if (k != NNP_KNOB_FORCE_SUM) ok = ok && json_int(line, knob_name(k), v[k]);
+            if (tuned_knob(k)) ok = ok && json_int(line, knob_name(k), v[k]);
         if (ok) {
             for (int k = 0; k < NNP_N_KNOBS; ++k)
-                if (k != NNP_KNOB_FORCE_SUM) knobs[k] = v[k];
+                if (tuned_knob(k)) knobs[k] = v[k];
             hit = true;
         }
     }
@@ -930,21 +938,18 @@ nnp_status autotune(nnp_handle* h, const nnp_batch* b, const typename P::T* x, i
     double idle = 0;
     if (rc == NNP_OK) rc = time_eval<P>(h, b, x, E, F, reps, idle);
     for (int k = 0; k < NNP_N_KNOBS && rc == NNP_OK; ++k) {
+        if (!tuned_knob(k)) continue;
         std::vector<int32_t> cand;
         if (k == NNP_KNOB_MLP_PATH) {
             if (mlp_fused_supported(h->shape.H1, h->shape.H2, h->shape.H3)) cand = {1, 2};
         } else if (k == NNP_KNOB_GEMM_STAGES) {
-            cand = {2, 3};
+            if (h->shape.row_tile == 128) cand = {2, 3};   // (BF16 handles: no other reads it)
         } else if (k == NNP_KNOB_TAIL_TILE) {
             if (knob_value(h, NNP_KNOB_MLP_PATH) == 1 && h->shape.row_tile == 128) cand = {1, 2, 3};
         } else if (k == NNP_KNOB_GEMM_WAVES) {
-            if (h->shape.row_tile == 128 && h->precision != NNP_PREC_FP64) cand = {4, 8};
-        } else if (k == NNP_KNOB_ATOM_CHUNK) {
-            cand = {4, 8, 16};
+            if (h->shape.row_tile == 128) cand = {4, 8};
         } else if (k == NNP_KNOB_L1_PATH) {
             if (l1_regs_supported(h)) cand = {1, 2};
-        } else if (k == NNP_KNOB_FORCE_SUM) {
-            // reproducibility is the caller's choice: never tuned
         } else if (k == NNP_KNOB_FORCE_PATH) {
             cand = {1, 2};
         } else if (k == NNP_KNOB_PIPELINE) {
@@ -1435,7 +1440,7 @@ nnp_status nnp_autotune(nnp_handle* h, const nnp_batch* b, const void* coords, i
     if (hit) {
         if (!h->graphs.empty()) (void)hipDeviceSynchronize();
         for (int k = 0; k < NNP_N_KNOBS; ++k)
-            if (k != NNP_KNOB_FORCE_SUM) h->knob[k] = cached[k];
+            if (tuned_knob(k)) h->knob[k] = cached[k];
         apply_knobs(h);
         if ((rc = ensure_pipeline(h))) return rc;
     } else {
