@@ -308,9 +308,12 @@ int32_t nnp_kernel_times(nnp_handle* h, int32_t cap, const char** names, int64_t
  *                         workgroups fit a compute unit); 16-row buckets
  *                         (small batches, FP64) and FP32 handles have their
  *                         own pipelines.
- *   NNP_KNOB_CELL_MIN     molecules with more atoms than this build their
- *                         neighbour lists through cutoff cells, smaller ones
- *                         scan all atoms: 16..1024 (auto 128).
+ *   NNP_KNOB_CELL_MIN     molecules with more atoms than this list their
+ *                         neighbours in the order of cutoff cells, smaller
+ *                         ones in input order (within an element; every atom
+ *                         is tested either way).  Handles whose largest
+ *                         molecule is no larger find them inside the
+ *                         featuriser in small calls: 16..1024 (auto 128).
  *   NNP_KNOB_GEMM_WAVES   waves per workgroup of the layer-1 forward GEMM
  *                         of layer-1 path 1 on BF16 handles with 128-row buckets:
  *                         4 (2 x 2 waves of 64 x 64) or 8 (2 x 4 waves of
@@ -332,8 +335,10 @@ int32_t nnp_kernel_times(nnp_handle* h, int32_t cap, const char** names, int64_t
  *                         force kernels (4 waves): 4, 8 or 16.  Fewer atoms
  *                         per workgroup spread a small batch over more
  *                         compute units; more share the staging of their
- *                         molecule.  auto, by the call's atoms: 4 below
- *                         16,384, 8 below 48,000, else 16.
+ *                         molecule.  auto, by the call: 4 below 16,384
+ *                         atoms, 8 below 49,137, else 16, and more where
+ *                         molecules times chunks of the handle's largest
+ *                         would exceed 12,288 workgroups.
  *   NNP_KNOB_FORCE_SUM    1 = forces summed with floating-point atomic adds
  *                         (the last bits vary from run to run), 2 = every
  *                         contribution rounded to a 64-bit fixed-point

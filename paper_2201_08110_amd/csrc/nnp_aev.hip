@@ -11,16 +11,16 @@
 //     distances, cutoff values) is cached in the wave's LDS slice;
 //   * neighbour lists are sorted by element (angular neighbours first), so
 //     radial terms of one element and angular terms of one element pair come
-//     in runs: lanes accumulate a run in registers and flush it once into an
-//     LDS row slice they own -- no atomics, bitwise reproducible;
-//   * angular pairs {j<k} are enumerated in-wave from the angular list by a
-//     triangular decode (no triple list is materialised): a lane per pair
-//     computes the 8 distance and 4 angle factors, then lanes per output slot
-//     expand the 32 products;
+//     in runs, and a slot of the row is complete, and stored, when its run is
+//     -- no atomics, bitwise reproducible;
+//   * angular pairs {j<k} are enumerated in-wave, element pair by element pair
+//     (no triple list is materialised): a lane per pair computes the distance
+//     and angle factors, 64 pairs at a time, and the products are summed into
+//     the slots on the matrix cores (FP32) or by the lanes that own them (FP64);
 //   * the backward recomputes the terms, contracts them with the atom's
-//     dE/dAEV row (LDS, element-pair blocks padded to 33 words against bank
-//     conflicts), accumulates the molecule's forces in LDS and adds them to
-//     global memory once per workgroup.
+//     dE/dAEV row (read from global memory, or staged in LDS), accumulates the
+//     molecule's forces in LDS and adds them to global memory once per
+//     workgroup.
 #include <algorithm>
 
 #include "nnp_internal.h"

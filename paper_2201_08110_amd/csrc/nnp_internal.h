@@ -251,7 +251,7 @@ struct Shape {
     int gemm_stages;                   // LDS stages of the layer-1 GEMMs (2 or 3)
     int gemm_waves;                    // waves per workgroup of the layer-1 forward GEMM (4 or 8)
     int l1_path;                       // layer-1 GEMMs: 1 = both operands through LDS, 2 = weights in registers
-    int cell_min;                      // molecules above this many atoms use cutoff cells
+    int cell_min;                      // molecules above this many atoms list neighbours in cutoff-cell order
     int tail_tile;                     // fused kernel tile variant (1, 2 or 3)
     int chunk;                         // central atoms per featuriser / force workgroup (4, 8, 16)
     int force_fixed;                   // 1: forces summed in 64-bit fixed point (bitwise reproducible)

@@ -18,15 +18,14 @@
 //   L1b  dG  = DZ1cat W1cat                       [R x Dp]  (= dE/dAEV)
 //
 // Operands are K-contiguous in memory (weights as [out][in] for the forward
-// and pre-transposed [in][out] copies for the backward).  Each workgroup of 4
-// waves owns a BM x BN output tile; K is streamed in BK slices through a
-// double-buffered LDS tile (the next slice is fetched into registers while the
-// current one feeds the MFMAs); bf16 slices are 128-byte rows whose 16-byte
-// chunks are XOR-swizzled by row so fragment reads and tile writes hit
-// distinct banks.  MFMA: f64 16x16x4, f32 16x16x4, bf16 16x16x32 (FP32
-// accumulation).  Tiles are scheduled N-fastest and remapped so each XCD
-// works through a contiguous range (its L2 keeps the row block and the
-// weights it shares).
+// and pre-transposed [in][out] copies for the backward).  This file holds the
+// GEMMs of BF16 and FP64 handles (k_gemm; k_l1rb for the layer-1 GEMMs of large
+// BF16 batches, k_gk64 for the smallest FP64 calls) and the fused layers 2-3
+// kernels of BF16, FP64 and of FP32 handles with 16-row buckets (k_tail,
+// k_tail16); all other FP32 products are in nnp_split.hip.  MFMA: f64 16x16x4,
+// f32 16x16x4, bf16 16x16x32 (FP32 accumulation).  Every XCD works through a
+// contiguous range of tiles (its L2 keeps the row block and the weights it
+// shares).
 #include "nnp_split.h"
 
 namespace nnp {
@@ -213,12 +212,11 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs<P> g) {
     // and the loop body has no branches (a join would make the compiler wait
     // for every LDS read).  Scheduling barriers keep the compiler from
     // moving the MFMAs of a step above the reads issued for the next one.
-    // FP32 / FP64 fragments hold one element per lane and k-step, so a
-    // plain read would fetch 4 or 8 bytes per lane.  Those are read FG
-    // k-steps at a time instead, one 16-byte chunk per lane: within a group,
-    // lane group g holds k = kk + g FG + j for step j, which still covers
-    // kk .. kk + 4 FG - 1 once each, identically for A and B (only the order
-    // of the K sum changes).
+    // FP64 fragments hold one element per lane and k-step, so a plain read
+    // would fetch 8 bytes per lane.  They are read FG = 2 k-steps at a time
+    // instead, one 16-byte chunk per lane: within a group, lane group g holds
+    // k = kk + g FG + j for step j, which still covers kk .. kk + 4 FG - 1 once
+    // each, identically for A and B (only the order of the K sum changes).
     typedef typename FragGroup<TS>::V FragG;
     constexpr int FG = FragGroup<TS>::G, KG = mf::KM * FG;   // k-steps, K per group
     constexpr int NSTEP = BK / KG;
@@ -1271,8 +1269,8 @@ static hipError_t run_l1(GemmArgs<P> a, const typename P::TS* Bf, const bf16_t* 
                                        : run_gemm<P, BM, C::BNW, 2, 4, 3, EPI>(a, R, N, 1, st, tm, name);
     }
     // 16-row tiles (small batches) stream the weights through a deeper pipeline:
-    // few workgroups, so each keeps more loads in flight (BF16 6 stages; FP32
-    // and FP64, whose slices hold half or a quarter of the K, measured best at 4)
+    // few workgroups, so each keeps more loads in flight (BF16 6 stages; FP64,
+    // whose slices hold a quarter of the K, measured best at 4)
     if constexpr (BM == 16) {
         constexpr int S16 = sizeof(typename P::TS) == 2 ? 6 : 4;
         return run_gemm<P, BM, C::BNW, C::WM, C::WN, S16, EPI>(a, R, N, 1, st, tm, name);
