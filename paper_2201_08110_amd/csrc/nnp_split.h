@@ -23,9 +23,8 @@ constexpr int kSplitRows = 64;   // bucket row tile of the handles that split th
 
 // parts of two values, packed (low half = first)
 __device__ inline void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
-    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);   // upper halves of both
-    const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
+    h = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);   // upper halves of both
+    const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
     m = pack_bf16x2(ra, rb);
     const float sa = ra - __uint_as_float(m << 16), sb = rb - __uint_as_float(m & 0xffff0000u);
     l = pack_bf16x2(sa, sb);
