@@ -95,7 +95,7 @@ template <typename P> struct GemmArgs {
     const int32_t* tile_species; int row_tile;
     const BucketInfo* info;
     int nm, nn, nz;                          // tiles along M (launch bound), N and models
-    int cap_rows;                            // rows of the handle's capacity
+    int pick_rows;                           // rows that the choice of a K split goes by
 };
 
 // Four output elements of one row held by one lane: columns c, c+ST, c+2ST,

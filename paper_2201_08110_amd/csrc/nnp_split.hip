@@ -547,9 +547,9 @@ hipError_t split_gemm(SplitArgs a, int R, int N, int nz, hipStream_t st, const T
     // long K and at most one workgroup per CU: K split over eight waves (the
     // layer-1 backward of 569 atoms 34 us, 40 on the tile below, 55 on 128
     // columns; at two rounds, 848 atoms, 58 against 51).  The split changes the
-    // roundings, so the handle's capacity decides, not the call: the results of
-    // a molecule do not depend on what else, or which bounds, a call has
-    if (a.g.K >= 1024 && a.g.cap_rows / 64 * nz * (N / 64) <= 256) return run_gxk<4, 4, 8, 2, EPI>(a, R, N, st, tm, name);
+    // roundings, so the handle's capacity decides where results must not depend
+    // on what else, or which bounds, a call has (pick_rows)
+    if (a.g.K >= 1024 && a.g.pick_rows / 64 * nz * (N / 64) <= 256) return run_gxk<4, 4, 8, 2, EPI>(a, R, N, st, tm, name);
     // 128 columns where they give about three workgroups per two CUs (3,445
     // atoms, forward / backward: 93 / 97 us, 256 columns 93 / 106; 12,011:
     // 235 / 267 against 252 / 292; 47,999: 817 / 891 against 880 / 900), 64
