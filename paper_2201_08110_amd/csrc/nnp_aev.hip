@@ -1740,18 +1740,20 @@ hipError_t launch_aev(const Shape& sh, const AevConst<typename P::T>& c, const i
 // Bucketing and featurisation.  A small batch takes one launch for bucketing,
 // neighbour search and rows: each dependent launch is a visible part of its
 // latency.  Small: up to kBucketAtoms atoms, every molecule within the all-pairs
-// search, and up to 1,024 molecules.  Every workgroup counts the whole batch's
-// labels: at 3,134 atoms 25.3 -> 29.6 us for two launches of 4.7 and 6.2 less, at
-// 3,520 20.9 -> 26.5 for 11.4, and the gain ends near kBucketAtoms; and every
-// molecule is a workgroup that counts (FP64, one network, 4,096 molecules of one
-// atom in a handle for 128: 306 us in one launch, 279 apart, 2,048 of two 254 /
-// 248; BF16 76 / 82 and 101 / 100).
+// search.  Every workgroup counts the whole batch's labels: at 3,134 atoms 25.3
+// -> 29.6 us for two launches of 4.7 and 6.2 less, at 3,520 20.9 -> 26.5 for
+// 11.4, and the gain ends near kBucketAtoms.  And every molecule is a workgroup
+// that counts: in FP64, where one or two fit a CU, only up to 1,024 molecules
+// (one network, 4,096 of one atom in a handle for 128: 306 us in one launch, 279
+// apart, 2,048 of two 254 / 248; in BF16 101 / 100, 76 / 82, and 2,000 of two in
+// a handle for two, eight networks, 112 / 119).
 template <typename P>
 hipError_t launch_prep_features(const Shape& sh, const AevConst<typename P::T>& c, const int32_t* mol_off,
                                 const int32_t* species, const typename P::T* x, typename P::T* F,
                                 bool accumulate, Work<P>& w, typename P::T* aev_out, hipStream_t st,
                                 const Timer& tm) {
-    const bool small = sh.A > 0 && sh.A <= kBucketAtoms && sh.B <= kPrepBlock && sh.max_apm <= sh.cell_min;
+    constexpr int most = sizeof(typename P::T) == 8 ? 1024 : 2 * kBucketAtoms;
+    const bool small = sh.A > 0 && sh.A <= kBucketAtoms && sh.B <= most && sh.max_apm <= sh.cell_min;
     if (!small) {
         hipError_t e = launch_prep<P>(sh, mol_off, species, w, st, tm);
         if (e != hipSuccess || sh.A == 0) return e;

@@ -111,9 +111,10 @@ def test_fp32_row_tangents(orc, hp, model, elements, chunk):
 
 
 @pytest.mark.parametrize("sizes", [
-    [3] * 1023 + [2],                  # 1,024 molecules: the last batch with fused bucketing
+    [3] * 1023 + [2],                  # 1,024 molecules: the last FP64 batch with fused bucketing
     [3] * 1023 + [2, 4],               # the first without
     [2, 1, 0] * 1000,                  # most of them empty or one atom
+    [0, 1] * 4096, [0, 1] * 4096 + [0],   # the last FP32 batch with it and the first without
 ])
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_many_small_molecules(orc, hp, sizes, prec):
